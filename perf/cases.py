@@ -277,9 +277,9 @@ def work(case):
 
 
 def tolerance(case):
-    # sums of up to a hundred thousand 32-bit terms; the worst seen against 64 bits is 4.3e-7 in the 2-norm (two layers) and
-    # 1e-4 of the root mean square (the bare sum of the largest row of a power-law graph, hundreds of times the mean row)
-    return {"rel": 2e-6, "max": 4e-4}
+    # sums of up to a hundred thousand 32-bit terms: four times the worst seen against 64 bits, 4.3e-7 in the 2-norm (two layers)
+    # and 4e-5 at one value (the bare sum of a power-law graph's largest row, against the root mean square of all rows)
+    return {"rel": 2e-6, "max": 1.6e-4}
 
 
 # --------------------------------------------------------------------------- the same in 64 bits, in plain torch
