@@ -51,9 +51,10 @@ FP32_MFMA_PEAK_TFLOPS = 157.3  # MI355X published dense fp32 matrix rate
 L2_PEAK_GBS = 8 * 16 * 128 * 2.4
 COUNTER_GROUPS = (("fetch", ["FETCH_SIZE"]), ("write", ["WRITE_SIZE"]), ("l2", ["TCC_REQ_sum", "TCC_HIT_sum", "TCC_MISS_sum"]))
 # every kernel a product call can launch (the counter children match dispatches to the library's launch records by order)
-PRODUCT_KERNELS = ("cbm_level_kernel", "cbm_bundle_kernel", "cbm_combine_kernel", "cbm_finish_kernel", "cbm_block_sum_kernel")
+PRODUCT_KERNELS = ("cbm_level_kernel", "cbm_bundle_kernel", "cbm_combine_kernel", "cbm_finish_kernel", "cbm_block_sum_kernel",
+                   "cbm_block_kernel")
 KIND_NAMES = {0: "rounds of paths", 1: "segments of split rows", 2: "combine of split rows", 3: "deferred finish",
-              4: "sum of column blocks"}
+              4: "sum of column blocks", 5: "row blocks"}
 
 DEFAULTS = {  # workload -> k of the timed product, alpha, GCN shape or None
     "tiny": dict(k=16, alpha=0, gcn=(16, 8, 4)),

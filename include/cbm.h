@@ -86,7 +86,11 @@ typedef enum {
  *                matrix of 65536 rows or more the candidate search first looks
  *                at every 64th row: if their best candidates would save under
  *                2 % of their entries, the search stops there and every row is
- *                stored in full.  The
+ *                stored in full.  On a
+ *                square matrix of 512 rows or more whose neighbouring rows share most of
+ *                their columns the same model may let the products run in row blocks:
+ *                one walk over the columns of 128 alike rows, on the matrix cores, in
+ *                one launch; the tree and all counters stay what they are.  The
  *                tree is cut into vertical paths, one work item each;
  *                dependent kernel launches per product = rounds of paths
  *                (cbm_stats), at most the depth.  Any value yields a valid CBM
@@ -306,7 +310,9 @@ typedef struct {
     int32_t kind;           /* 0 = gather/update round, 1 = segments of split rows,
                                2 = split-row combine, 3 = deferred finish of rows that
                                other work items read (row weight, self term, ReLU),
-                               4 = sum of the partial rows of a column-blocked handle    */
+                               4 = sum of the partial rows of a column-blocked handle,
+                               5 = the whole product in row blocks (tasks = blocks, deltas =
+                               columns gathered, each once per block)                    */
     int32_t level;          /* round for kinds 0 and 2, else 0                         */
     int64_t tasks;          /* work items in the launch                               */
     int64_t deltas;         /* delta entries gathered by the launch                   */

@@ -1,0 +1,352 @@
+// Row blocks: products of matrices whose neighbouring rows share most of their columns, on the matrix cores (gfx950, wave64).
+//
+// The paths of cbm_kernels.hip gather a row of X per delta.  Where 128 alike rows together need few distinct columns, one walk
+// over those columns serves all of them: every column's row of X is read once per block and added to the sums of the rows that
+// hold it -- a product of a 0/1 matrix (the block's bits) and the gathered rows of X, which is matrix-core work
+// (protein recipe: 17.8 columns a row against 77 deltas of the tree and 322 entries; no rounds, no dependent launches).
+// X stays 32-bit: a value is split into three bf16 values that add up to it exactly, a bit is exactly 1 in bf16, so the products
+// are exact and the sums are 32-bit ones, of the whole row instead of along a path (protein: error against 64 bits 1.2e-7
+// in the 2-norm, the paths' 3.7e-7).
+//
+// One workgroup of four waves has a block and a slab of 32 columns of X (slabs are the slow grid dimension: while one is
+// walked, an XCD's share of X is its rows times 128 bytes).  The waves take the block's groups of 64 columns in turn, all of its
+// four tiles of 32 rows each, and add their sums through LDS at the end.  A lane loads one column of eight rows of X (one
+// 32-bit load a row: two rows of 128 bytes an instruction, 5.7 cycles; 128-bit loads take 16 and bring a lane four columns of
+// one row, which is not what a matrix-core operand is) and splits them in registers: they are the B operand of
+// v_mfma_f32_32x32x16_bf16 as they stand.  The A operand is a byte of bits through a table in LDS.  Tiles that hold none of a
+// step's 16 columns are left out.
+//
+// What bounds it (protein recipe, k = 256; before: 0.80 ms on the paths, now 0.39): matrix cores 39 % and vector ALU 46 % of the
+// cycles at a clock that the two bring down to 1.9 GHz; rows of X from L1 instead of L2 change 5 %, no weights or table 3 %.
+// Measured on the way: 64 columns a slab with scalar loads of the column numbers 0.52 ms (two waves per SIMD, waits for
+// scalar loads), blocks of 64 rows 0.46 ms, all tiles without a test 0.51 ms, rows not sorted into tiles 0.41 ms.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdlib>
+
+#include "cbm_internal.h"
+
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+
+constexpr int WAVES = 4;  // waves per workgroup: they share a block's groups of columns
+constexpr int T = CBM_BLOCK_TILES;
+static_assert(T == WAVES, "wave s finishes tile s");
+
+struct BlockMap {
+    int64_t begin[CBM_XCD];
+    int64_t count[CBM_XCD];
+};
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// x minus the low (high) half of a pair of bf16 values: one instruction, and exact where the half is x's leading bits.
+// `minus_low` = (-1, 0) comes from a register: as an inline constant -1.0 would stand for (0, -1).
+__device__ __forceinline__ float less(float x, uint32_t pair, uint32_t which) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, which), x, false);
+}
+__device__ __forceinline__ uint32_t high_halves(float x0, float x1) {
+    return __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), 0x07060302u);
+}
+// The 24 significant bits of a value as three bf16 values (8 + 8 + 8 bits, by truncation, so nothing is rounded and nothing
+// overflows): x = h + m + l exactly.  Two values at a time, packed as an operand wants them.
+__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t minus_low, uint32_t& h, uint32_t& m, uint32_t& l) {
+    const uint32_t minus_high = 0xbf800000u;
+    h = high_halves(x0, x1);
+    x0 = less(x0, h, minus_low);
+    x1 = less(x1, h, minus_high);
+    m = high_halves(x0, x1);
+    x0 = less(x0, m, minus_low);
+    x1 = less(x1, m, minus_high);
+    l = high_halves(x0, x1);
+}
+
+template <int MODE, bool BIG>
+__global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(const CbmBlock* __restrict__ blocks, const BlockMap map,
+                                                                  const uint32_t* __restrict__ rows,
+                                                                  const uint32_t* __restrict__ cols,
+                                                                  const float* __restrict__ wcols,
+                                                                  const uintx4* __restrict__ masks,
+                                                                  const float* __restrict__ X, uint32_t ldxb, float* __restrict__ Y,
+                                                                  int64_t ldy, const float* __restrict__ rw, float self_w, int k) {
+    constexpr bool WCOL = MODE == 1 || MODE == 2, WROW = WCOL || MODE == 3, RELU = MODE == 2, SELF = MODE == 4;
+    __shared__ uintx4 lut[256];
+    __shared__ uintx4 ids[WAVES][2][16];
+    __shared__ floatx4 wts[WAVES][2][16];
+    __shared__ float red[2][WAVES - 1][16][64];
+
+    const int xcd = blockIdx.x % CBM_XCD;
+    const int64_t nth = blockIdx.x / CBM_XCD;
+    if (nth >= map.count[xcd]) return;
+    const CbmBlock blk = blocks[map.begin[xcd] + nth];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int half = lane >> 5;
+    {
+        const uint32_t b = threadIdx.x;
+        uintx4 e;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[i] = ((b >> (2 * i)) & 1u) * 0x3f80u + ((b >> (2 * i + 1)) & 1u) * 0x3f800000u;
+        lut[b] = e;
+    }
+    __syncthreads();
+
+    const int lcol = blockIdx.y * 32 + (lane & 31);
+    const int ccol = min(lcol, k - 1);  // loads stay inside the row; what they bring is never stored
+    auto x_at = [&](uint32_t row) -> float {
+        const char* base = reinterpret_cast<const char*>(X);
+        if (BIG) return *reinterpret_cast<const float*>(base + ((uint64_t)row * ldxb + (uint32_t)ccol * 4u));
+        return *reinterpret_cast<const float*>(base + (uint32_t)(__umul24(row, ldxb) + (uint32_t)ccol * 4u));
+    };
+
+    floatx16 acc[T];
+#pragma unroll
+    for (int s = 0; s < T; ++s)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[s][v] = 0.0f;
+    uint32_t minus_low = 0xbf80u;
+    asm("" : "+s"(minus_low));
+
+    struct Ids {
+        uintx4 v[2];
+    };
+    struct Weights {
+        floatx4 v[2];
+    };
+    // step `st` of the group in buffer `buf`: the eight columns of this half-wave, their weights, their rows of X
+    auto read_ids = [&](Ids& i, int buf, int st) {
+        i.v[0] = ids[wave][buf][4 * st + 2 * half];
+        i.v[1] = ids[wave][buf][4 * st + 2 * half + 1];
+    };
+    auto read_weights = [&](Weights& w, int buf, int st) {
+        if (!WCOL) return;
+        w.v[0] = wts[wave][buf][4 * st + 2 * half];
+        w.v[1] = wts[wave][buf][4 * st + 2 * half + 1];
+    };
+    auto load_x = [&](float (&x)[8], const Ids& i) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = x_at(i.v[j / 4][j % 4]);
+    };
+    auto consume = [&](float (&x)[8], const Weights& w, uint32_t mask) {
+        uintx4 a[T];
+#pragma unroll
+        for (int s = 0; s < T; ++s) a[s] = lut[(mask >> (8 * s)) & 255u];
+        __builtin_amdgcn_sched_barrier(0);
+        if (WCOL) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] *= w.v[j / 4][j % 4];
+        }
+        uintx4 P[3];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            uint32_t h, m, l;
+            split_pair(x[2 * p], x[2 * p + 1], minus_low, h, m, l);
+            P[0][p] = h;
+            P[1][p] = m;
+            P[2][p] = l;
+        }
+#pragma unroll
+        for (int s = 0; s < T; ++s)
+            if (__ballot(((mask >> (8 * s)) & 255u) != 0)) {
+#pragma unroll
+                for (int q = 2; q >= 0; --q)
+                    acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[s]), __builtin_bit_cast(bf16x8, P[q]), acc[s], 0, 0, 0);
+            }
+    };
+    if ((uint32_t)wave < blk.ngroups) {
+        // every load is made, with the group held to this wave's last: a load that may not happen would turn the wait for an
+        // older one into a wait for all of them
+        const uint32_t last = blk.ngroups - 1 - (blk.ngroups - 1 - wave) % WAVES;
+        const uint32_t* gc = cols + (size_t)blk.group0 * 64 + lane;
+        const float* gw = wcols + (size_t)blk.group0 * 64 + lane;
+        const uintx4* gm = masks + (size_t)blk.group0 * 64 + lane;
+        auto put = [&](int buf, uint32_t id, float w) {
+            reinterpret_cast<uint32_t*>(ids[wave][buf])[lane] = id;
+            if (WCOL) reinterpret_cast<float*>(wts[wave][buf])[lane] = w;
+        };
+        // (three buffers of rows in flight besides the one in use would cost a wave per SIMD; four names, three alive)
+        float x[4][8];
+        Ids i;
+        Weights w0, w1;
+        uint32_t g = wave;
+        size_t at = (size_t)g * 64, next = (size_t)min(g + WAVES, last) * 64;
+        uintx4 mask = gm[at];
+        put(0, gc[at], WCOL ? gw[at] : 0.0f);
+        uint32_t nid = gc[next];
+        float nw = WCOL ? gw[next] : 0.0f;
+        uintx4 nmask = gm[next];
+        read_ids(i, 0, 0);
+        load_x(x[0], i);
+        read_ids(i, 0, 1);
+        load_x(x[1], i);
+        read_ids(i, 0, 2);
+        read_weights(w0, 0, 0);
+        int buf = 0;
+        for (;;) {
+            // a step: rows of X two steps ahead, columns three, weights one
+            load_x(x[2], i);
+            read_ids(i, buf, 3);
+            read_weights(w1, buf, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(x[0], w0, mask[0]);
+
+            load_x(x[3], i);
+            put(buf ^ 1, nid, nw);
+            next = (size_t)min(g + 2 * WAVES, last) * 64;
+            nid = gc[next];
+            if (WCOL) nw = gw[next];
+            read_ids(i, buf ^ 1, 0);
+            read_weights(w0, buf, 2);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(x[1], w1, mask[1]);
+
+            load_x(x[0], i);
+            read_ids(i, buf ^ 1, 1);
+            read_weights(w1, buf, 3);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(x[2], w0, mask[2]);
+
+            load_x(x[1], i);
+            read_ids(i, buf ^ 1, 2);
+            read_weights(w0, buf ^ 1, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(x[3], w1, mask[3]);
+
+            if (g == last) break;
+            g += WAVES;
+            buf ^= 1;
+            mask = nmask;
+            nmask = gm[next];
+        }
+    }
+
+    // The waves' shares of a tile, added by the wave that will store it (wave s has tile s), two tiles at a time.
+    const uintx4* rr = reinterpret_cast<const uintx4*>(rows + (size_t)blk.row0 + 32 * wave);
+    uintx4 row4[4];  // rows 8 q + 4 half .. + 3 of the wave's tile
+#pragma unroll
+    for (int q = 0; q < 4; ++q) row4[q] = rr[2 * q + half];
+    floatx16 fin;
+#pragma unroll
+    for (int pair = 0; pair < 2; ++pair) {
+        if (pair) __syncthreads();
+#pragma unroll
+        for (int s = 2 * pair; s < 2 * pair + 2; ++s)
+            if (wave != s) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) red[s & 1][wave < s ? wave : wave - 1][v][lane] = acc[s][v];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int s = 2 * pair; s < 2 * pair + 2; ++s)
+            if (wave == s) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) fin[v] = acc[s][v] + red[s & 1][0][v][lane] + red[s & 1][1][v][lane] + red[s & 1][2][v][lane];
+            }
+    }
+    auto store = [&](uint32_t row, float v) {
+        if (SELF) v = fmaf(self_w, x_at(row), v);
+        if (WROW) v *= rw[row];
+        if (RELU) v = fmaxf(v, 0.0f);
+        __builtin_nontemporal_store(v, Y + (int64_t)row * ldy + lcol);
+    };
+    // Two kinds of sums do not come out of the matrix cores.  0 x infinity: a value that is not finite anywhere among the
+    // block's rows of X turns every sum of its column in this tile into NaN.  And the smaller parts of values below 2^-110 are
+    // subnormal in bf16, where the matrix cores take them for zero.  A tile with a sum that is not finite, or not zero and below
+    // 2^-96, is summed again by selection instead of multiplication (protein recipe,
+    // k = 256: 0.38 ms; with one infinity in X 0.63, all of X NaN 5.1).
+    bool plain = true;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) plain = plain && (fin[v] == 0.0f || (fabsf(fin[v]) < INFINITY && fabsf(fin[v]) >= 0x1p-96f));
+    if (__ballot(!plain)) {
+        float sum[16];  // lane l: rows 16 (l / 32) .. + 15 of the tile, column l % 32
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[r] = 0.0f;
+        for (uint32_t i = 0; i < 8 * blk.ngroups; ++i) {  // eight columns at a time
+            const size_t at = (size_t)blk.group0 * 64 + 8 * i;
+            float x[8], w[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = x_at(cols[at + j]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) w[j] = WCOL ? wcols[at + j] : 1.0f;
+            // byte of row r (in lanes r of one half): the columns that the row holds
+            const uint32_t held = (masks[(size_t)(blk.group0 + i / 8) * 64 + 32 * (i & 1) + (lane & 31)][i / 2 % 4] >> (8 * wave)) & 255u;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t bits = (uint32_t)__ballot((held >> j) & 1u) >> (16 * half);  // bit r: this half's row r
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float xs = __uint_as_float(__float_as_uint(x[j]) & (0u - ((bits >> r) & 1u)));
+                    sum[r] = WCOL ? fmaf(w[j], xs, sum[r]) : sum[r] + xs;
+                }
+            }
+        }
+        if (lcol < k) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const uint32_t row = rows[(size_t)blk.row0 + 32 * wave + 16 * half + r];
+                if (row != CBM_BLOCK_NO_ROW) store(row, sum[r]);
+            }
+        }
+        return;
+    }
+    // register v of lane l of a 32 x 32 tile: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
+    if (lcol < k) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const uint32_t row = row4[v / 4][v % 4];
+            if (row != CBM_BLOCK_NO_ROW) store(row, fin[v]);
+        }
+    }
+}
+
+struct Args {
+    const cbm_handle* h;
+    const float* X;
+    int64_t ldx;
+    int k;
+    float* Y;
+    int64_t ldy;
+    const float* rw;
+    float self_w;
+    hipStream_t stream;
+};
+
+template <int MODE, bool BIG>
+void launch(const Args& a) {
+    BlockMap map;
+    int64_t most = 0;
+    for (int j = 0; j < CBM_XCD; ++j) {
+        map.begin[j] = a.h->blk_begin[j];
+        map.count[j] = a.h->blk_count[j];
+        most = std::max(most, map.count[j]);
+    }
+    const dim3 grid((unsigned)(CBM_XCD * most), (unsigned)((a.k + 31) / 32));
+    hipLaunchKernelGGL((cbm_block_kernel<MODE, BIG>), grid, dim3(64 * WAVES), 0, a.stream, a.h->d_blocks, map, a.h->d_block_rows,
+                       a.h->d_block_cols, a.h->d_block_w, reinterpret_cast<const uintx4*>(a.h->d_block_masks), a.X, (uint32_t)(a.ldx * 4),
+                       a.Y, a.ldy, a.rw, a.self_w, a.k);
+}
+template <bool BIG>
+void launch_mode(const Args& a, int mode) {
+    switch (mode) {
+        case 0: return launch<0, BIG>(a);
+        case 1: return launch<1, BIG>(a);
+        case 2: return launch<2, BIG>(a);
+        case 3: return launch<3, BIG>(a);
+        default: return launch<4, BIG>(a);
+    }
+}
+
+}  // namespace
+
+void cbm_launch_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
+                       float self_w, void* stream) {
+    const Args a{h, X, ldx, k, Y, ldy, rw, self_w, (hipStream_t)stream};
+    // 24-bit indices and 32-bit offsets where they reach: one instruction per address
+    const int64_t n = std::max(h->n, h->m);
+    const bool big = n >= (1 << 24) || ldx >= (1 << 22) || n * ldx * 4 >= (int64_t)UINT32_MAX;
+    big ? launch_mode<true>(a, mode) : launch_mode<false>(a, mode);
+}

@@ -20,6 +20,7 @@
 #include <queue>
 #include <thread>
 
+#include "cbm_block_plan.h"
 #include "cbm_internal.h"
 
 namespace {
@@ -49,6 +50,17 @@ constexpr double kLaunchUs = 7.0;
 constexpr double kEntryUs = 0.2;
 constexpr double kBytesPerUs = 6.0e6;
 constexpr double kRefRowBytes = 512.0;
+// Row blocks (Builder::row_block_cost and where it is used)
+constexpr double kBlockGroupUs = 0.0012;    // per group of 64 columns and slab of 32 columns of X, the chip full
+constexpr double kBlockLongestUs = 0.44;    // per group of the longest block: four waves share it
+constexpr double kBlockSampleMargin = 1.1;  // blocks made last find their best rows taken
+constexpr double kBlockMargin = 0.7;        // the paths' model is up to 1.5 times too high where one long row decides
+constexpr double kBlockLongest = 64;        // groups of the longest block: hub rows' blocks are walked by four waves while the
+                                            // rest of the chip is done (R-MAT scale 14, blocks of up to 150 groups, k = 64:
+                                            // 60 us against 56 on the paths)
+constexpr int64_t kBlockMinRows = 512;      // four blocks
+constexpr int64_t kBlockMinDegree = 16;     // mean entries of a row
+constexpr int64_t kBlockColumnGroup = 256;  // blocks whose rows' columns are taken together when a block sorts its columns
 constexpr int64_t kPathChoices[] = {16, 32, 64, 128, 256};
 
 long env_or(const char* name, long dflt) {
@@ -224,6 +236,9 @@ struct Builder {
     bool prune_last_round(int64_t path_max);
     double csr_cost() const;
     cbm_status emit(int32_t nrounds);
+    double row_block_cost(double groups, double longest) const;
+    double sampled_row_block_cost() const;
+    void row_blocks();
 };
 
 cbm_status Builder::validate(const int64_t* in_rowptr, const int32_t* in_colidx) {
@@ -1181,6 +1196,156 @@ cbm_status Builder::emit(int32_t nrounds) {
     return CBM_OK;
 }
 
+// Modelled time of the row-block launch over `groups` groups of 64 columns (k = 128: four column slabs).  Measured: 1.2 ns a
+// group and slab with the chip full (protein recipe, 36,900 groups: 0.18 ms at k = 128, 0.39 ms at k = 256); with few blocks
+// the launch lasts as long as its longest block (6,000 nodes, 60 neighbours: blocks of 13 groups, 11.4 us a product against
+// 18.3 us on the paths; 300 neighbours: 26 groups, 18 against 29 us).
+double Builder::row_block_cost(double groups, double longest) const {
+    if (longest > kBlockLongest) return 1e300;
+    return kLaunchUs + std::max(groups * 4 * kBlockGroupUs, longest * kBlockLongestUs);
+}
+
+// What row blocks would cost, from the blocks that a few evenly spread rows and the rows nearest to them would make: the
+// number of columns a block needs decides, and a matrix whose neighbouring rows have little in common shows it at once.
+double Builder::sampled_row_block_cost() const {
+    std::vector<int32_t> mark((size_t)n, -1), members;
+    std::vector<uint8_t> in((size_t)m, 0);
+    constexpr int kSeeds = 32;
+    double columns = 0, most = 0;
+    int seen = 0;
+    for (int q = 0; q < kSeeds; ++q) {
+        const int32_t s = (int32_t)(m * q / kSeeds);
+        if (rlen(s) == 0) continue;
+        members.assign(1, s);
+        in[s] = 1;
+        nearest_rows(s, rowptr, colidx, [&](int32_t y) { return y < m && !in[y]; }, mark, [&](int32_t y) {
+            if ((int64_t)members.size() < CBM_BLOCK_ROWS) {
+                in[y] = 1;
+                members.push_back(y);
+            }
+        });
+        for (size_t i = 1; i < members.size() && (int64_t)members.size() < CBM_BLOCK_ROWS; ++i)  // too few neighbours: theirs
+            for (int64_t p = rowptr[members[i]]; p < rowptr[members[i] + 1] && (int64_t)members.size() < CBM_BLOCK_ROWS; ++p)
+                if (colidx[p] < m && !in[colidx[p]]) {
+                    in[colidx[p]] = 1;
+                    members.push_back(colidx[p]);
+                }
+        int64_t distinct = 0;
+        for (int32_t x : members)
+            for (int64_t p = rowptr[x]; p < rowptr[x + 1]; ++p)
+                if (mark[colidx[p]] != (int32_t)m + q) {
+                    mark[colidx[p]] = (int32_t)m + q;
+                    ++distinct;
+                }
+        for (int32_t x : members) in[x] = 0;
+        columns += (double)distinct / (double)members.size();
+        most = std::max(most, (double)distinct);
+        ++seen;
+    }
+    if (!seen) return 1e300;
+    return row_block_cost(kBlockSampleMargin * columns / seen * (double)m / 64.0, most / 64.0);
+}
+
+// Row blocks (cbm_blocks.hip): rows in an order of much the same columns, cut every CBM_BLOCK_ROWS rows; a block's columns
+// sorted by where their own rows lie in that order, coarsely, so that blocks that run side by side ask for the same rows of X
+// at about the same time (L2 misses 59 -> 34 % of requests on the protein recipe), and then by which of the block's tiles hold
+// them, so that a step of 16 columns touches as few tiles as it can (2.6 -> 2.25 of 4 with the rows sorted into tiles).
+void Builder::row_blocks() {
+    constexpr int64_t per = CBM_BLOCK_ROWS;
+    constexpr int T = CBM_BLOCK_TILES;
+    const std::vector<int32_t> rows = block_order(m, rowptr, colidx, per);
+    const int64_t nb = (m + per - 1) / per;
+    std::vector<int32_t> pos((size_t)m);
+    for (int64_t i = 0; i < m; ++i) pos[rows[i]] = (int32_t)i;
+    struct Built {
+        std::vector<uint32_t> cols, masks;
+    };
+    std::vector<Built> built((size_t)nb);
+    h->block_rows.assign((size_t)nb * per, CBM_BLOCK_NO_ROW);
+    std::vector<std::vector<int32_t>> local((size_t)nthreads);
+    parallel_chunks(nthreads, nb, 4, [&](int64_t b0, int64_t b1, int th) {
+        std::vector<int32_t>& place = local[th];  // column -> its place among the block's columns
+        if (place.empty()) place.assign((size_t)n, -1);
+        std::vector<int32_t> cols, by;
+        std::vector<uint32_t> bits;  // T words per column: the rows of each tile that hold it
+        std::vector<uint64_t> keys, alike;
+        for (int64_t b = b0; b < b1; ++b) {
+            cols.clear();
+            bits.clear();
+            uint32_t* mine = h->block_rows.data() + (size_t)(b * per);
+            const int count = (int)(std::min(m, (b + 1) * per) - b * per);
+            for (int i = 0; i < count; ++i) mine[i] = (uint32_t)rows[b * per + i];
+            tiles_of_alike_rows(mine, count, 32, rowptr, colidx, place, alike);
+            for (int i = 0; i < count; ++i)
+                for (int64_t p = rowptr[mine[i]]; p < rowptr[mine[i] + 1]; ++p) {
+                    int32_t& at = place[colidx[p]];
+                    if (at < 0) {
+                        at = (int32_t)cols.size();
+                        cols.push_back(colidx[p]);
+                        bits.insert(bits.end(), T, 0u);
+                    }
+                    bits[(size_t)at * T + i / 32] |= 1u << (i % 32);
+                }
+            keys.resize(cols.size());
+            by.resize(cols.size());
+            for (size_t i = 0; i < cols.size(); ++i) {
+                place[cols[i]] = -1;
+                by[i] = (int32_t)i;
+                uint64_t none = 0;  // the tiles without this column
+                for (int s = 0; s < T; ++s) none |= (uint64_t)(bits[i * T + s] == 0) << s;
+                keys[i] = (uint64_t)(pos[cols[i]] / (per * kBlockColumnGroup)) << 36 | none << 32 | (uint32_t)pos[cols[i]];
+            }
+            std::sort(by.begin(), by.end(), [&](int32_t i, int32_t j) { return keys[i] < keys[j]; });
+            const size_t groups = (by.size() + 63) / 64;
+            Built& out = built[b];
+            out.cols.resize(groups * 64);
+            out.masks.assign(groups * 256, 0u);
+            for (size_t i = 0; i < groups * 64; ++i) {
+                const int32_t j = by[std::min(i, by.size() - 1)];
+                out.cols[i] = (uint32_t)cols[j];  // (places past the last column repeat it, with no bits)
+                if (i >= by.size()) continue;
+                uint32_t* words = out.masks.data() + i / 64 * 256 + (i % 16 / 8) * 128 + i % 64 / 16;
+                for (int s = 0; s < T; ++s)
+                    for (uint32_t w = bits[(size_t)j * T + s]; w; w &= w - 1) words[4 * __builtin_ctz(w)] |= 1u << (8 * s + i % 8);
+            }
+        }
+    });
+    h->row_blocks.resize((size_t)nb);
+    size_t at = 0;
+    for (int64_t b = 0; b < nb; ++b) {
+        h->row_blocks[b] = {(uint32_t)(b * per), (uint32_t)at, (uint32_t)(built[b].cols.size() / 64)};
+        at += built[b].cols.size() / 64;
+    }
+    h->block_cols.resize(at * 64);
+    h->block_masks.resize(at * 256);
+    parallel_chunks(nthreads, nb, 4, [&](int64_t b0, int64_t b1, int) {
+        for (int64_t b = b0; b < b1; ++b) {
+            std::copy(built[b].cols.begin(), built[b].cols.end(), h->block_cols.begin() + (size_t)h->row_blocks[b].group0 * 64);
+            std::copy(built[b].masks.begin(), built[b].masks.end(), h->block_masks.begin() + (size_t)h->row_blocks[b].group0 * 256);
+        }
+    });
+    // One contiguous share of equal work per XCD, in the order of the rows (neighbours run side by side and share rows of X
+    // in that XCD's L2) except that the smallest quarter comes last: the launch then ends on short blocks (k = 32: 58 -> 54 us,
+    // nothing lost at k = 256, where longest-first throughout costs 2 %).
+    size_t i = 0;
+    for (int j = 0; j < CBM_XCD; ++j) {
+        h->blk_begin[j] = (int64_t)i;
+        const size_t want = at * (j + 1) / CBM_XCD;
+        while (i < (size_t)nb && (j == CBM_XCD - 1 || h->row_blocks[i].group0 + h->row_blocks[i].ngroups / 2 < want)) ++i;
+        h->blk_count[j] = (int64_t)i - h->blk_begin[j];
+        const auto first = h->row_blocks.begin() + h->blk_begin[j], end = h->row_blocks.begin() + i;
+        std::vector<uint32_t> sizes;
+        for (auto it = first; it != end; ++it) sizes.push_back(it->ngroups);
+        if (sizes.empty()) continue;
+        std::nth_element(sizes.begin(), sizes.begin() + sizes.size() / 4, sizes.end());
+        const uint32_t few = sizes[sizes.size() / 4];
+        std::stable_partition(first, end, [&](const CbmBlock& c) { return c.ngroups > few; });
+    }
+    if (verbose)
+        std::fprintf(stderr, "[cbm_build] row blocks: %ld of %ld rows, %zu groups of 64 columns (%.1f columns a row)\n", (long)nb, (long)per,
+                     at, 64.0 * at / m);
+}
+
 }  // namespace
 
 // Column-blocked CBM: the columns are cut into B equal ranges and the part of every row inside a range becomes a row
@@ -1344,6 +1509,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     // model may also find that no tree pays for its extra launches (small graphs): then every row is
     // stored in full.  A depth cap of 1 means exactly that and needs no candidate search.
     int32_t nrounds = 0;
+    double chosen_us = 1e300;  // modelled time of the plan that is kept
     int64_t best_len = kPathChoices[0], best_split = B.split_min;
     // rows longer than the split threshold are cut into per-XCD segments: worth a launch or two of their own on
     // graphs with many long rows, a loss where only a handful exist
@@ -1458,6 +1624,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
                 }
             }
         }
+        chosen_us = best_us;
         B.lap("tree + path model");
     } else if (!tree) {
         B.all_roots();
@@ -1470,7 +1637,9 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
                 best_split = split;
             }
         }
+        chosen_us = best_us;
     }
+    const double product_us = chosen_us;
     B.split_min = best_split;
     if (tree && exact_tree) {
         // keep the arborescence as found
@@ -1507,6 +1676,31 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     st = B.emit(nrounds);
     if (st != CBM_OK) return st;
     B.lap("paths + work lists");
+    // ---- row blocks ------------------------------------------------------------------------------
+    // Part of the automatic policy: the tree and its counters are what they are, but where one walk over the columns of 128
+    // alike rows on the matrix cores is modelled cheaper than the rounds of paths, the products run that way.
+    // (CBM_ROW_BLOCKS: 0 = never, 1 = whenever the matrix is square and the policy automatic.)
+    const long want_blocks = env_clamped("CBM_ROW_BLOCKS", -1, -1, 1);
+    if (B.auto_depth && !exact_tree && want_blocks != 0 && m == n && m > 0 && (want_blocks == 1 || !(o.flags & CBM_FLAG_HOST_ONLY))) {
+        const double limit = kBlockMargin * product_us;
+        const int32_t most = *std::max_element(h->rownnz.begin(), h->rownnz.end());  // a block needs its longest row's columns
+        const bool worth = want_blocks == 1 || (m >= kBlockMinRows && B.nnz >= kBlockMinDegree * m && most <= 64 * kBlockLongest &&
+                                                B.sampled_row_block_cost() < limit);
+        if (worth) {
+            B.row_blocks();
+            double longest = 0;
+            for (const CbmBlock& b : h->row_blocks) longest = std::max(longest, (double)b.ngroups);
+            const double us = B.row_block_cost((double)h->block_cols.size() / 64.0, longest);
+            if (B.verbose) std::fprintf(stderr, "[cbm_build] row blocks: model %.1f us (paths: %.1f us)\n", us, product_us);
+            if (want_blocks != 1 && us >= limit) {
+                std::vector<CbmBlock>().swap(h->row_blocks);
+                std::vector<uint32_t>().swap(h->block_rows);
+                std::vector<uint32_t>().swap(h->block_cols);
+                std::vector<uint32_t>().swap(h->block_masks);
+            }
+        }
+        B.lap("row blocks");
+    }
 
     // ---- counters (Properties 1 and 2) -----------------------------------------------------------
     s.m = m;

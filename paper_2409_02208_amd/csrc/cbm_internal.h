@@ -53,6 +53,16 @@ struct CbmLevel {
     int64_t xcd_begin[CBM_XCD] = {}, xcd_count[CBM_XCD] = {};
 };
 
+// A row block: up to CBM_BLOCK_ROWS rows whose sums come from one walk over the columns that any of them holds.
+constexpr int CBM_BLOCK_TILES = 4;                       // tiles of 32 rows
+constexpr int CBM_BLOCK_ROWS = 32 * CBM_BLOCK_TILES;
+struct CbmBlock {
+    uint32_t row0;     // first of its CBM_BLOCK_ROWS places in block_rows
+    uint32_t group0;   // first of its groups
+    uint32_t ngroups;  // groups of 64 columns: four steps of 16
+};
+constexpr uint32_t CBM_BLOCK_NO_ROW = 0xffffffffu;  // an empty place
+
 struct cbm_handle {
     int64_t m = 0, n = 0;
     cbm_build_opts opts{};
@@ -79,6 +89,14 @@ struct cbm_handle {
     bool bundled = false;          // some round's paths are emitted as bundles: delta columns are 26-bit in this handle
     cbm_stats_t stats{};
 
+    // ---- row blocks: where they pay, the products run on these instead of the work items above ----
+    std::vector<CbmBlock> row_blocks;    // empty: none
+    std::vector<uint32_t> block_rows;    // CBM_BLOCK_ROWS matrix rows per block
+    std::vector<uint32_t> block_cols;    // 64 columns per group
+    std::vector<uint32_t> block_masks;   // 64 x 4 words per group: byte s of word (l, i) = columns 8 (l / 32) .. + 7 of step i
+                                         // in row 32 s + l % 32
+    int64_t blk_begin[CBM_XCD] = {}, blk_count[CBM_XCD] = {};  // each XCD's run of blocks
+
     // ---- device arrays (owned) ---------------------------------------------------
     int device = -1;
     bool on_device = false;
@@ -89,6 +107,11 @@ struct cbm_handle {
     float* d_rinv = nullptr;
     float* d_wstream = nullptr;  // weight of every stream entry (normalised product), computed on the device at upload
     int32_t* d_internal = nullptr;
+    CbmBlock* d_blocks = nullptr;
+    uint32_t* d_block_rows = nullptr;
+    uint32_t* d_block_cols = nullptr;
+    float* d_block_w = nullptr;  // column weight (d^-1/2) beside each of block_cols (handles built with self-loops)
+    uint32_t* d_block_masks = nullptr;
     mutable float* d_scratch = nullptr;  // num_slots x scratch_k floats, sized on first use
     mutable int64_t scratch_k = 0;
 
@@ -130,6 +153,9 @@ cbm_status cbm_device_deltas(int device, int64_t m, const int64_t* rowptr, const
                              std::vector<uint32_t>* dcol);
 cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
                               CbmEpilogue epi, float self_weight, void* stream, bool static_scratch = false);
+// the product's one launch on a handle with row blocks (cbm_blocks.hip)
+void cbm_launch_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
+                       float self_w, void* stream);
 size_t cbm_static_scratch_bytes();
 // dense fp32 MFMA matmul (cbm_gemm.hip)
 cbm_status cbm_launch_gemm(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb,

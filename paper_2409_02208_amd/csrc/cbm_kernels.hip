@@ -16,6 +16,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <mutex>
+#include <vector>
 
 #include "cbm_internal.h"
 
@@ -741,11 +742,24 @@ cbm_status cbm_upload(cbm_handle* h) {
             HIP_TRY(hipMemcpy(*dptr, vec.data(), vec.size() * sizeof(T), hipMemcpyHostToDevice), CBM_ERR_HIP);
         return CBM_OK;
     };
+    auto up_blocks = [&]() -> cbm_status {
+        if (h->row_blocks.empty()) return CBM_OK;
+        cbm_status bs = CBM_OK;
+        if ((bs = up(&h->d_blocks, h->row_blocks)) != CBM_OK || (bs = up(&h->d_block_rows, h->block_rows)) != CBM_OK ||
+            (bs = up(&h->d_block_cols, h->block_cols)) != CBM_OK || (bs = up(&h->d_block_masks, h->block_masks)) != CBM_OK)
+            return bs;
+        if (h->square_self_loops) {
+            std::vector<float> w(h->block_cols.size());
+            for (size_t i = 0; i < w.size(); ++i) w[i] = h->dinv[h->block_cols[i]];
+            if ((bs = up(&h->d_block_w, w)) != CBM_OK) return bs;
+        }
+        return CBM_OK;
+    };
     cbm_status st = CBM_OK;
     if ((st = up(&h->d_tasks, h->tasks)) != CBM_OK || (st = up(&h->d_comb, h->comb)) != CBM_OK ||
         (st = up(&h->d_stream, h->stream)) != CBM_OK || (st = up(&h->d_dinv, h->dinv)) != CBM_OK ||
         (st = up(&h->d_rinv, h->rinv)) != CBM_OK ||
-        (st = up(&h->d_internal, h->internal_rows)) != CBM_OK) {
+        (st = up(&h->d_internal, h->internal_rows)) != CBM_OK || (st = up_blocks()) != CBM_OK) {
         cbm_release_device(h);
         if (cur != dev) hipSetDevice(cur);
         return st;
@@ -793,6 +807,14 @@ void cbm_release_device(cbm_handle* h) {
     if (h->d_wstream) hipFree(h->d_wstream);
     if (h->d_internal) hipFree(h->d_internal);
     if (h->d_scratch) hipFree(h->d_scratch);
+    if (h->d_blocks) hipFree(h->d_blocks);
+    if (h->d_block_rows) hipFree(h->d_block_rows);
+    if (h->d_block_cols) hipFree(h->d_block_cols);
+    if (h->d_block_w) hipFree(h->d_block_w);
+    if (h->d_block_masks) hipFree(h->d_block_masks);
+    h->d_blocks = nullptr;
+    h->d_block_rows = h->d_block_cols = h->d_block_masks = nullptr;
+    h->d_block_w = nullptr;
     h->d_tasks = h->d_comb = nullptr;
     h->d_stream = nullptr;
     h->d_dinv = nullptr;
@@ -925,6 +947,8 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         return launch_blocked(h, X, ldx, k, Y, ldy, epi, self_weight, stream);
     }
 
+    // row blocks need no scratch; the limits of the static one are those of the paths all the same
+    const bool in_blocks = !h->row_blocks.empty() && ldx < (1 << 30);  // (a row's bytes are a 32-bit number there)
     const int64_t ld_scratch = ((int64_t)k + 3) & ~(int64_t)3;
     float* scratch = nullptr;
     if (static_scratch) {
@@ -942,7 +966,7 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
             }
             if (const cbm_status st = static_scratch_address(cur, &scratch); st != CBM_OK) return st;
         }
-    } else {
+    } else if (!in_blocks) {
         // scratch rows for split rows: sized by cbm_reserve, else for this k on first use
         if (const cbm_status st = cbm_reserve_scratch(h, k); st != CBM_OK) return st;
         scratch = h->d_scratch;
@@ -978,6 +1002,18 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
     const int64_t rowb = 4 * (int64_t)k;
     const int64_t per_delta = rowb + 4 + (wcol ? 4 : 0);
     const int64_t per_row = rowb + 4 + (wrow ? 4 : 0) + (mode == 4 ? rowb : 0);  // Y write, marker, weight, own X row
+    if (in_blocks) {
+        cbm_launch_record rec{};
+        rec.kind = 5;
+        rec.per_xcd = 1;
+        rec.tasks = (int64_t)h->row_blocks.size();
+        rec.deltas = (int64_t)h->block_cols.size();
+        rec.algorithmic_bytes = rec.deltas * per_delta + h->m * per_row;
+        ProfScope ps(h, stream, rec);
+        cbm_launch_blocks(h, X, ldx, k, Y, ldy, mode, ctx.rw, self_weight, stream_);
+        HIP_TRY(hipGetLastError(), CBM_ERR_HIP);
+        return CBM_OK;
+    }
     if (h->num_slots > 0) {
         cbm_launch_record rec{};
         rec.kind = 1;

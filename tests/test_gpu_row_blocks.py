@@ -1,0 +1,159 @@
+"""Products in row blocks against the oracle: every epilogue, widths around the 32-column slab, strided and misaligned operands,
+blocks that are not full, empty rows, directed graphs and their transpose, values that are not finite."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import cbm_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5  # of a row's largest value, as for the paths: the products of the split are exact and the sums 32-bit ones
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    import paper_2409_02208_amd as cbm
+
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    return torch, cbm
+
+
+@pytest.fixture(autouse=True)
+def force(monkeypatch):
+    monkeypatch.setenv("CBM_ROW_BLOCKS", "1")
+
+
+def _err(got, ref, scale_from=None):
+    d = np.abs(got.astype(np.float64) - ref).max(axis=1)
+    s = np.abs(ref if scale_from is None else scale_from).max(axis=1)
+    assert np.all(d[s == 0] == 0)
+    return float((d[s > 0] / s[s > 0]).max()) if np.any(s > 0) else 0.0
+
+
+def _in_blocks(torch, cbm, h, X, Y):
+    cbm.cbm_profile_enable(h, True)
+    cbm.cbm_spmm(h, X, Y)
+    torch.cuda.synchronize()
+    kinds = [r["kind"] for r in cbm.cbm_profile_read(h)]
+    cbm.cbm_profile_enable(h, False)
+    return kinds == [5]
+
+
+def _directed(n, seed):
+    rng = np.random.default_rng(seed)
+    rows = [np.unique(rng.integers(0, n, size=int(rng.integers(0, 40)))) if i % 7 else np.zeros(0, np.int64) for i in range(n)]
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    rowptr[1:] = np.cumsum([len(r) for r in rows])
+    return rowptr, np.concatenate(rows).astype(np.int32)
+
+
+@pytest.mark.parametrize("n", [1, 33, 128, 129, 1000, 4099])
+@pytest.mark.parametrize("k", [1, 31, 32, 33, 64, 100])
+def test_sums_of_whole_numbers_are_exact(env, n, k):
+    torch, cbm = env
+    rowptr, colidx = _directed(n, n)
+    h = cbm.cbm_build(n, n, rowptr, colidx)
+    X = wl.integer_features(n, k, 3)
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    Xd = torch.from_numpy(X).cuda()
+    assert _in_blocks(torch, cbm, h, Xd, Y)
+    ref = orc.spmm_csr(rowptr, colidx, X)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref)
+    cbm.cbm_spmm_noalloc(h, Xd, Y.fill_(float("nan")))
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("layout", ["dense", "strided", "misaligned"])
+@pytest.mark.parametrize("k", [16, 47, 128])
+def test_every_epilogue(env, k, layout):
+    torch, cbm = env
+    g = wl.make_graph("protein", n=3000, knn=50)
+    hn = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=True)
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx)
+    X = wl.gaussian_features(g.n, k, 5)
+    pad, off = {"dense": (0, 0), "strided": (5, 0), "misaligned": (4, 1)}[layout]
+    Xd = torch.zeros((g.n, k + pad), device="cuda")[:, off:off + k]
+    Xd.copy_(torch.from_numpy(X))
+    room = torch.full((g.n, k + pad), float("nan"), device="cuda")
+    Y = room[:, off:off + k]
+
+    def run(fn, *args):
+        room.fill_(float("nan"))
+        fn(*args, Xd, Y)
+        torch.cuda.synchronize()
+        got = room.cpu().numpy()
+        assert np.isnan(np.delete(got, np.arange(off, off + k), axis=1)).all(), "wrote outside the columns"
+        return got[:, off:off + k]
+
+    norm = orc.spmm_csr_normalized(g.rowptr, g.colidx, X)
+    plain = orc.spmm_csr(g.rowptr, g.colidx, X)
+    assert _err(run(cbm.cbm_spmm_normalized, hn), norm) <= TOL
+    assert _err(run(cbm.cbm_spmm_normalized_relu, hn), np.maximum(norm, 0), norm) <= TOL
+    assert _err(run(cbm.cbm_spmm_mean, h), orc.spmm_csr_mean(g.rowptr, g.colidx, X)) <= TOL
+    assert _err(run(cbm.cbm_spmm_gin, h, 0.5), plain + 1.5 * X.astype(np.float64)) <= TOL
+    assert _err(run(cbm.cbm_spmm, h), plain) <= TOL
+
+
+def test_directed_graph_and_its_transpose(env):
+    torch, cbm = env
+    n, k = 2000, 40
+    rowptr, colidx = _directed(n, 9)
+    h = cbm.cbm_build(n, n, rowptr, colidx, add_self_loops=True)
+    ht = cbm.cbm_build(n, n, rowptr, colidx, add_self_loops=True, transpose=True)
+    X, G = (torch.from_numpy(wl.gaussian_features(n, k, s)).cuda() for s in (1, 2))
+    Y, Z = torch.empty_like(X), torch.empty_like(X)
+    cbm.cbm_spmm_normalized(h, X, Y)
+    cbm.cbm_spmm_normalized(ht, G, Z)
+    torch.cuda.synchronize()
+    assert _err(Y.cpu().numpy(), orc.spmm_csr_normalized(rowptr, colidx, X.cpu().numpy())) <= TOL
+    left, right = float((Y.double() * G.double()).sum()), float((X.double() * Z.double()).sum())
+    assert abs(left - right) <= 1e-5 * float((Y.double() * G.double()).abs().sum())
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38])
+def test_values_that_are_not_finite_stay_in_their_rows(env, value):
+    """A row whose columns hold no such value has the sum it has without it (the split multiplies by zero: 0 x inf)."""
+    torch, cbm = env
+    g = wl.make_graph("protein", n=1500, knn=30)
+    k = 50
+    X = wl.gaussian_features(g.n, k, 8)
+    X[[3, 700], [0, 33]] = value
+    with np.errstate(over="ignore", invalid="ignore"):
+        A = np.zeros((g.n, g.n), dtype=bool)
+        A[np.repeat(np.arange(g.n), np.diff(g.rowptr)), g.colidx] = True
+        A[np.arange(g.n), np.arange(g.n)] = True
+    touched = np.zeros((g.n, k), dtype=bool)
+    touched[:, 0], touched[:, 33] = A[:, 3], A[:, 700]
+    clean = X.copy()
+    clean[[3, 700], [0, 33]] = 0.0
+    hn = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=True)
+    got = {}
+    for name, x in (("with", X), ("without", clean)):
+        Y = torch.empty((g.n, k), device="cuda")
+        cbm.cbm_spmm_normalized(hn, torch.from_numpy(x).cuda(), Y)
+        torch.cuda.synchronize()
+        got[name] = Y.cpu().numpy()
+    ref = orc.spmm_csr_normalized(g.rowptr, g.colidx, clean)
+    assert _err(got["without"], ref) <= TOL
+    untouched = np.abs(got["with"] - ref)[~touched] / np.broadcast_to(np.abs(ref).max(axis=1, keepdims=True), ref.shape)[~touched]
+    assert untouched.max() <= TOL
+    hit = got["with"][touched]
+    if np.isfinite(value):
+        assert np.isfinite(hit).all() and (hit > 1e36).all()
+    else:
+        assert np.isnan(hit).all() if np.isnan(value) else np.array_equal(hit, np.full_like(hit, value))
+
+
+@pytest.mark.parametrize("scale", [1e-36, 1e-34, 1e-30, 1e-27, 1e30])
+def test_scale_of_the_values_does_not_matter(env, scale):
+    torch, cbm = env
+    g = wl.make_graph("protein", n=1500, knn=30)
+    X = (wl.gaussian_features(g.n, 33, 8).astype(np.float64) * scale).astype(np.float32)
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx)
+    Y = torch.empty((g.n, 33), device="cuda")
+    cbm.cbm_spmm(h, torch.from_numpy(X).cuda(), Y)
+    torch.cuda.synchronize()
+    assert _err(Y.cpu().numpy(), orc.spmm_csr(g.rowptr, g.colidx, X)) <= TOL
