@@ -379,14 +379,15 @@ cbm_status launch16_nt(int64_t M, int N, int K, const float* A, int64_t lda, con
 // One 16x16x4 MFMA contracts four k: lane (c = l%16, q = l/16) holds A[row c][k0 + 4q .. 4q+3] of a group of 16 k as one
 // 128-bit load and feeds element e to MFMA e, which therefore contracts k0 + 4q + e over q; the B operand of MFMA e is
 // panel[k0 + 4q + e][16t + c].  The panel's row stride (16 NT16 + 4 floats) puts q and q+1 on disjoint halves of the banks.
+// B may have any width and alignment (132534 x 100 . 100 x 47: 31.9 us through the staged kernel, 28.7 here).
 // Loads of A run four groups of 16 k ahead through a ring of registers and are unconditional (addresses clamped into the
 // matrix; what lies beyond K is zeroed when used, rows beyond M are never stored).
 constexpr int WPB = 8;  // waves per block of the panel kernel
 
 template <int NT16>
 __global__ __launch_bounds__(64 * WPB) void cbm_gemm_panel_kernel(int64_t M, int N, int K, int Kp, const float* __restrict__ A, int64_t lda,
-                                                             const float* __restrict__ B, int64_t ldb, float* __restrict__ C,
-                                                             int64_t ldc) {
+                                                             const float* __restrict__ B, int64_t ldb, int vec_b,
+                                                             float* __restrict__ C, int64_t ldc) {
     constexpr int BN = 16 * NT16;
     constexpr int LDB = BN + 4;
     extern __shared__ float smem[];
@@ -510,7 +511,15 @@ __global__ __launch_bounds__(64 * WPB) void cbm_gemm_panel_kernel(int64_t M, int
             for (int u = 0; u < FILL; ++u) {
                 const int idx = min(base + 64 * WPB * u, total - 1);
                 const int k = idx / (BN / 4), col = col0 + (idx % (BN / 4)) * 4;
-                v[u] = *reinterpret_cast<const float4*>(B + (int64_t)min(k, K - 1) * ldb + min(col, N - 4));  // N % 4 == 0
+                const float* row = B + (int64_t)min(k, K - 1) * ldb;
+                if (vec_b) {
+                    v[u] = *reinterpret_cast<const float4*>(row + min(col, N - 4));  // N % 4 == 0
+                } else {  // any width or alignment of B: the panel is read once, element by element costs nothing next to A
+                    v[u] = make_float4(row[min(col, N - 1)], row[min(col + 1, N - 1)], row[min(col + 2, N - 1)], row[min(col + 3, N - 1)]);
+                    if (col + 1 >= N) v[u].y = 0.0f;
+                    if (col + 2 >= N) v[u].z = 0.0f;
+                    if (col + 3 >= N) v[u].w = 0.0f;
+                }
                 if (k >= K || col >= N) v[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }
 #pragma unroll
@@ -562,9 +571,8 @@ __global__ __launch_bounds__(64 * WPB) void cbm_gemm_panel_kernel(int64_t M, int
 }
 
 // LDS bytes of the resident panel, or 0 if this product cannot take the panel kernel.
-inline size_t panel_lds_bytes(int64_t M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb, int* nt16) {
-    const bool vec = K % 4 == 0 && N % 4 == 0 && lda % 4 == 0 && ldb % 4 == 0 && ((uintptr_t)A & 15) == 0 &&
-                     ((uintptr_t)B & 15) == 0 && K >= 4 && N >= 4;
+inline size_t panel_lds_bytes(int N, int K, const float* A, int64_t lda, int* nt16) {
+    const bool vec = K % 4 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0 && K >= 4;
     if (!vec || N < 16) return 0;
     const int tiles = (N + 15) / 16, npanels = (tiles + 7) / 8;
     *nt16 = (tiles + npanels - 1) / npanels;  // panels of equal width, at most 128 columns
@@ -586,7 +594,8 @@ cbm_status launch_panel(int64_t M, int N, int K, const float* A, int64_t lda, co
         lds_opt_in = smem;
     }
     const int Kp = (K + 63) / 64 * 64;
-    hipLaunchKernelGGL((cbm_gemm_panel_kernel<NT16>), dim3(256), dim3(64 * WPB), smem, stream, M, N, K, Kp, A, lda, B, ldb, C, ldc);
+    const int vec_b = N % 4 == 0 && ldb % 4 == 0 && ((uintptr_t)B & 15) == 0;
+    hipLaunchKernelGGL((cbm_gemm_panel_kernel<NT16>), dim3(256), dim3(64 * WPB), smem, stream, M, N, K, Kp, A, lda, B, ldb, vec_b, C, ldc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         cbm_set_error_detail("cbm_gemm_panel_kernel launch", hipGetErrorString(e));
@@ -640,11 +649,16 @@ cbm_status cbm_launch_gemm(int64_t M, int32_t N, int32_t K, const float* A, int6
             return CBM_ERR_HIP;
         return CBM_OK;
     }
+    {   // short and deep, or wide enough to be bound by the matrix cores: their bf16 side
+        bool taken = false;
+        const cbm_status st = cbm_launch_gemm_split(M, N, K, A, lda, B, ldb, C, ldc, stream_, &taken);
+        if (taken || st != CBM_OK) return st;
+    }
     {   // tall A, a weight panel that fits in LDS: the panel-resident kernel
         static const char* env = std::getenv("CBM_GEMM_PANEL_MIN_ROWS");
         const int64_t min_rows = env ? std::atoll(env) : 8192;
         int nt16 = 0;
-        const size_t smem = M >= min_rows ? panel_lds_bytes(M, N, K, A, lda, B, ldb, &nt16) : 0;
+        const size_t smem = M >= min_rows ? panel_lds_bytes(N, K, A, lda, &nt16) : 0;
         if (smem) {
             switch (nt16) {
                 case 1: return launch_panel<1>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);

@@ -1,0 +1,367 @@
+// Dense fp32 matmul C = A.B on the bf16 matrix cores: both operands split into three bf16 parts that add up to the fp32 value
+// exactly (8 + 8 + 8 significant bits, by truncation: x = h + m + l), six products of parts (hh, hm, mh, mm, hl, lh), 32-bit sums.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdlib>
+
+#include "cbm_internal.h"
+#include "cbm_split.h"
+
+// The bf16 matrix cores are 16 times as fast as the fp32 ones, the six products leave 2.7.  Left out are products of parts
+// below 2^-24 of the value's; measured error against 64 bits is smaller than that of the fp32 kernels, whose chain of
+// additions is longer (K = 256: 2.4e-7 against 2.9e-7 in the 2-norm; K = 500 in four parts: 1.8e-7 against 4.0e-7).
+
+namespace {
+
+// Eight fp32 values (consecutive k of one row of A, or of one column of B) as three operands.
+struct Parts {
+    bf16x8 p[3];  // h, m, l
+};
+__device__ __forceinline__ Parts split8(const float (&x)[8], uint32_t minus_low) {
+    uintx4 q[3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t h, m, l;
+        split_pair(x[2 * i], x[2 * i + 1], minus_low, h, m, l);
+        q[0][i] = h;
+        q[1][i] = m;
+        q[2][i] = l;
+    }
+    Parts r;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) r.p[i] = __builtin_bit_cast(bf16x8, q[i]);
+    return r;
+}
+
+// the six products, small ones first; neighbouring instructions write different tiles
+constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+
+template <int NT>
+__device__ __forceinline__ void multiply(floatx16 (&acc)[NT], const Parts& a, const Parts (&b)[NT]) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[PA[i]], b[t].p[PB[i]], acc[t], 0, 0, 0);
+}
+
+// Eight consecutive k of row `row` of A from k0 on, zero beyond K (addresses held inside the matrix).
+template <bool VEC>
+__device__ __forceinline__ void load_a(float (&x)[8], const float* __restrict__ row, int k0, int K) {
+    if (VEC) {  // K and the row's address are multiples of 4
+        const floatx4 lo = *reinterpret_cast<const floatx4*>(row + min(k0, K - 4)), hi = *reinterpret_cast<const floatx4*>(row + min(k0 + 4, K - 4));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            x[j] = lo[j];
+            x[4 + j] = hi[j];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = row[min(k0 + j, K - 1)];
+    }
+}
+__device__ __forceinline__ void cut_a(float (&x)[8], int k0, int K) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = k0 + j < K ? x[j] : 0.0f;
+}
+
+// What the matrix cores cannot be asked: parts of infinities and NaN are NaN, and parts below the smallest normal number count
+// as zero there, an error of up to 2^-126 times the other operand a term.  A sum that is not finite, or not zero and below 2^-90
+// times the largest operand (2^-90 at least), is computed again by fused multiply-adds.
+__device__ __forceinline__ bool doubtful(float v, float largest) {
+    return !(v == 0.0f || (fabsf(v) < INFINITY && fabsf(v) >= 0x1p-90f * largest));
+}
+// rows row0 .. + 31, columns col0 .. + 31 of C
+__device__ __forceinline__ void plain_tile(int64_t M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
+                                        int64_t ldc, int64_t row0, int col0) {
+    const int lane = threadIdx.x & 63;
+    const int c = col0 + (lane & 31);
+    if (c >= N) return;
+    for (int r = lane >> 5; r < 32; r += 2) {
+        if (row0 + r >= M) return;
+        const float* a = A + (row0 + r) * lda;
+        float s = 0.0f;
+        for (int k = 0; k < K; ++k) s = fmaf(a[k], B[(int64_t)k * ldb + c], s);
+        C[(row0 + r) * ldc + c] = s;
+    }
+}
+__device__ __forceinline__ float largest_of(float x) {
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) x = fmaxf(x, __shfl_xor(x, d, 64));
+    return fmaxf(x, 1.0f);
+}
+
+// Narrow C (up to 64 columns), for products that are short and deep: a workgroup has 32 rows of C, its four waves take the
+// steps of 16 k in turn and add their sums through LDS.  Both operands come straight from memory in operand layout (lane l:
+// row, or column, l % 32 and eight k from 8 (l / 32) on): B is small and stays in L2.  Loads run one step ahead (three:
+// 19717 x 500 . 500 x 64 24.9 -> 27.8 us, the loads made past the end cost more than the wait); waves with all of K each: 30 us.
+constexpr int KS = 4, PF = 2;
+
+template <int NT, bool VEC>
+__global__ __launch_bounds__(256) void cbm_gemm_narrow_kernel(int64_t M, int N, int K, const float* __restrict__ A, int64_t lda,
+                                                              const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc) {
+    __shared__ float red[KS - 1][NT * 16][64];
+    __shared__ float high[4];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int64_t row0 = (int64_t)blockIdx.x * 32;
+    const float* arow = A + min(row0 + l32, M - 1) * lda;
+    const float* bcol[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) bcol[t] = B + min(32 * t + l32, N - 1);
+    floatx16 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.0f;
+    uint32_t minus_low = 0xbf80u;
+    asm("" : "+s"(minus_low));
+    float largest = 0.0f;
+
+    const int steps = (K + 15) / 16, first = wave;
+    struct Step {
+        float a[8], b[NT][8];
+    };
+    auto load = [&](Step& s, int i) {
+        const int k0 = 16 * i + 8 * half;
+        load_a<VEC>(s.a, arow, k0, K);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t at = (int64_t)min(k0 + j, K - 1) * ldb;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) s.b[t][j] = bcol[t][at];
+        }
+    };
+    auto use = [&](Step& s, int i) {
+        cut_a(s.a, 16 * i + 8 * half, K);
+#pragma unroll
+        for (int j = 0; j < 8; j += 2) {
+            largest = fmaxf(largest, fmaxf(fabsf(s.a[j]), fabsf(s.a[j + 1])));
+#pragma unroll
+            for (int t = 0; t < NT; ++t) largest = fmaxf(largest, fmaxf(fabsf(s.b[t][j]), fabsf(s.b[t][j + 1])));
+        }
+        const Parts a = split8(s.a, minus_low);
+        Parts b[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) b[t] = split8(s.b[t], minus_low);
+        multiply<NT>(acc, a, b);
+    };
+    if (first < steps) {  // (loads are always made, with the step held to this wave's last)
+        const int last = first + (steps - 1 - first) / KS * KS;
+        Step s[PF];
+#pragma unroll
+        for (int p = 0; p < PF; ++p) {
+            load(s[p], min(first + p * KS, last));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        for (int i = first; i <= last; i += PF * KS) {
+#pragma unroll
+            for (int p = 0; p < PF; ++p) {
+                if (i + p * KS <= last) use(s[p], i + p * KS);
+                load(s[p], min(i + (p + PF) * KS, last));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    largest = largest_of(largest);
+    if (lane == 0) high[wave] = largest;
+    if (wave > 0) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) red[wave - 1][16 * t + v][lane] = acc[t][v];
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    largest = fmaxf(fmaxf(high[0], high[1]), fmaxf(high[2], high[3]));
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+            for (int w = 0; w < KS - 1; ++w) acc[t][v] += red[w][16 * t + v][lane];
+    uint32_t again = 0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        bool bad = false;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) bad = bad || doubtful(acc[t][v], largest);
+        again |= (__ballot(bad) != 0) << t;  // (its stores below are overwritten by the same wave)
+        const int c = 32 * t + l32;
+        if (c < N)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int64_t r = row0 + 8 * (v / 4) + 4 * half + v % 4;
+                if (r < M) C[r * ldc + c] = acc[t][v];
+            }
+    }
+    for (; again; again &= again - 1) plain_tile(M, N, K, A, lda, B, ldb, C, ldc, row0, 32 * __builtin_ctz(again));
+}
+
+// Wider C: a workgroup of four waves has 128 rows by 32 NT columns.  B goes through LDS in chunks of 32 k, split as it is
+// stored (two buffers, one barrier a chunk); A comes straight from memory.
+constexpr int CK = 32;  // k per chunk
+
+template <int NT, bool VEC>
+__global__ __launch_bounds__(256, 2) void cbm_gemm_wide_kernel(int64_t M, int N, int K, const float* __restrict__ A, int64_t lda,
+                                                               const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc) {
+    constexpr int BN = 32 * NT;
+    constexpr int PER = (CK / 8) * BN / 256;  // columns of eight k that a thread stages per chunk
+    static_assert((CK / 8) * BN % 256 == 0, "every thread stages the same number");
+    __shared__ uintx4 stage[2][3][CK / 8][BN];
+    __shared__ float high[4];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int64_t row0 = (int64_t)blockIdx.x * 128 + 32 * wave;
+    const int col0 = blockIdx.y * BN;
+    const float* arow = A + min(row0 + l32, M - 1) * lda;
+    floatx16 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.0f;
+    uint32_t minus_low = 0xbf80u;
+    asm("" : "+s"(minus_low));
+    float largest = 0.0f;
+
+    auto load_b = [&](float (&x)[PER][8], int chunk) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int at = threadIdx.x + 256 * i, k0 = chunk * CK + at / BN * 8;
+            const float* col = B + min(col0 + at % BN, N - 1);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[i][j] = col[(int64_t)min(k0 + j, K - 1) * ldb];
+        }
+    };
+    auto store_b = [&](const float (&x)[PER][8], int buf) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int at = threadIdx.x + 256 * i;
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) largest = fmaxf(largest, fmaxf(fabsf(x[i][j]), fabsf(x[i][j + 1])));
+            const Parts p = split8(x[i], minus_low);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) stage[buf][q][at / BN][at % BN] = __builtin_bit_cast(uintx4, p.p[q]);
+        }
+    };
+    const int chunks = (K + CK - 1) / CK;
+    float xb[PER][8], xa[2][8], na[2][8];
+    load_b(xb, 0);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) load_a<VEC>(xa[s], arow, 16 * s + 8 * half, K);
+    store_b(xb, 0);
+    __syncthreads();
+    for (int c = 0; c < chunks; ++c) {
+        const int next = min(c + 1, chunks - 1);
+        load_b(xb, next);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) load_a<VEC>(na[s], arow, next * CK + 16 * s + 8 * half, K);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            cut_a(xa[s], c * CK + 16 * s + 8 * half, K);
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) largest = fmaxf(largest, fmaxf(fabsf(xa[s][j]), fabsf(xa[s][j + 1])));
+            const Parts a = split8(xa[s], minus_low);
+            Parts b[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) b[t].p[q] = __builtin_bit_cast(bf16x8, stage[c & 1][q][2 * s + half][32 * t + l32]);
+            multiply<NT>(acc, a, b);
+        }
+        store_b(xb, (c + 1) & 1);
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) xa[s][j] = na[s][j];
+    }
+    largest = largest_of(largest);
+    if (lane == 0) high[wave] = largest;
+    __syncthreads();
+    largest = fmaxf(fmaxf(high[0], high[1]), fmaxf(high[2], high[3]));
+    if (row0 >= M) return;
+    uint32_t again = 0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        bool bad = false;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) bad = bad || doubtful(acc[t][v], largest);
+        again |= (__ballot(bad) != 0) << t;
+        const int cc = col0 + 32 * t + l32;
+        if (cc < N)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int64_t r = row0 + 8 * (v / 4) + 4 * half + v % 4;
+                if (r < M) C[r * ldc + cc] = acc[t][v];
+            }
+    }
+    for (; again; again &= again - 1) plain_tile(M, N, K, A, lda, B, ldb, C, ldc, row0, col0 + 32 * __builtin_ctz(again));
+}
+
+struct Shape {
+    int64_t M;
+    int N, K;
+    const float* A;
+    int64_t lda;
+    const float* B;
+    int64_t ldb;
+    float* C;
+    int64_t ldc;
+    hipStream_t stream;
+};
+
+template <int NT, bool VEC>
+void narrow(const Shape& s) {
+    hipLaunchKernelGGL((cbm_gemm_narrow_kernel<NT, VEC>), dim3((unsigned)((s.M + 31) / 32)), dim3(256), 0, s.stream, s.M, s.N, s.K, s.A, s.lda, s.B, s.ldb, s.C, s.ldc);
+}
+template <int NT, bool VEC>
+void wide(const Shape& s) {
+    const dim3 grid((unsigned)((s.M + 127) / 128), (unsigned)((s.N + 32 * NT - 1) / (32 * NT)));
+    hipLaunchKernelGGL((cbm_gemm_wide_kernel<NT, VEC>), grid, dim3(256), 0, s.stream, s.M, s.N, s.K, s.A, s.lda, s.B, s.ldb, s.C, s.ldc);
+}
+template <bool VEC>
+void pick(const Shape& s, int form) {
+    switch (form) {
+        case 1: return narrow<1, VEC>(s);
+        case 2: return narrow<2, VEC>(s);
+        case 3: return wide<2, VEC>(s);
+        default: return wide<4, VEC>(s);
+    }
+}
+
+}  // namespace
+
+// Where the lines lie (microseconds, fp32 kernels of cbm_gemm.hip -> these; M x K . K x N):
+//  up to 64 columns: short and deep products, which leave the chip idle there -- 19717 x 500 . 500 x 64 27.3 -> 24.3,
+//    . 500 x 7 25.7 -> 15.0, 3000 x 512 . 512 x 64 25 -> 11; not 30000 x 200 . 200 x 64 (17.0 -> 17.8) or anything taller, where the
+//    fp32 kernels stream A at the rate of memory;
+//  more columns, few workgroups (tiles of 64 columns): 19717 x 256 . 256 x 256 42 -> 31, 6000 x 300 . 300 x 96 29 -> 16;
+//  more columns, many: 132534 x 256 . 256 x 256 157 -> 137, 132534 x 96 . 96 x 256 92 -> 73, 132534 x 250 . 250 x 250 236 -> 175,
+//    if the last tile of 128 columns is not mostly padding (256 x 160: 107 -> 126; 256 x 112: 75 -> 78) and K is not so short that the
+//    products are bound by memory (132534 x 64 . 64 x 128: 32 -> 38).
+cbm_status cbm_launch_gemm_split(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
+                                 int64_t ldc, void* stream, bool* taken) {
+    int form = 0;
+    if (N <= 64)
+        form = M <= 24576 && K >= 128 ? (N <= 32 ? 1 : 2) : 0;
+    else if ((M + 127) / 128 * ((N + 63) / 64) <= 1024)
+        form = K >= 32 ? 3 : 0;
+    else if (K >= 96 && (N + 127) / 128 * 128 * 10 <= (int64_t)N * 11)
+        form = 4;
+    if (const char* e = std::getenv("CBM_GEMM_SPLIT")) form = std::atoi(e);  // (for tests: 0 = never, 1 to 4 = that kernel)
+    if (form == 1 && N > 32) form = 2;
+    if (form == 2 && N > 64) form = 3;
+    *taken = form != 0;
+    if (!form) return CBM_OK;
+    const Shape s{M, N, K, A, lda, B, ldb, C, ldc, (hipStream_t)stream};
+    const bool vec = K % 4 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0;
+    vec ? pick<true>(s, form) : pick<false>(s, form);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+        cbm_set_error_detail("split matmul launch", hipGetErrorString(e));
+        return CBM_ERR_HIP;
+    }
+    return CBM_OK;
+}

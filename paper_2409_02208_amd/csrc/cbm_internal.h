@@ -157,6 +157,9 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
 void cbm_launch_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
                        float self_w, void* stream);
 size_t cbm_static_scratch_bytes();
+// the same through bf16 parts (cbm_gemm_split.hip) where its own rule says so: *taken
+cbm_status cbm_launch_gemm_split(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
+                                 int64_t ldc, void* stream, bool* taken);
 // dense fp32 MFMA matmul (cbm_gemm.hip)
 cbm_status cbm_launch_gemm(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb,
                            float* C, int64_t ldc, void* stream);
