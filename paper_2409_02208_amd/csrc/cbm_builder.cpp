@@ -976,6 +976,7 @@ cbm_status Builder::emit(int32_t nrounds) {
     h->stream.clear();
     h->num_slots = 0;
     h->seg_deltas = 0;
+    h->seg_longest = 0;
     int64_t split_rows = 0;
     std::vector<std::vector<CbmTask>> rtasks(nrounds + 1), rcomb(nrounds + 1);
     std::vector<std::vector<int32_t>> rrows(nrounds + 1);  // rows of each path, beside rtasks
@@ -1011,6 +1012,7 @@ cbm_status Builder::emit(int32_t nrounds) {
         rtasks[round[x]].push_back({x, y, (uint32_t)start, (uint32_t)(at - start)});
         rrows[round[x]].push_back(path_rows);
         R.parent_reads += y >= 0;
+        R.longest = std::max(R.longest, at - start);
     }
     if (at >= (int64_t)UINT32_MAX) return CBM_ERR_UNSUPPORTED;
     // Which rounds are bundled: those of long work items with more than one row.  (Measured on the protein graph: rounds
@@ -1027,8 +1029,9 @@ cbm_status Builder::emit(int32_t nrounds) {
             most = std::max(most, rrows[r][i]);
         }
         if (verbose)
-            std::fprintf(stderr, "[cbm_build] round %d: %zu work items, %.1f entries each, at most %d rows in a path\n", r, rtasks[r].size(),
-                         rtasks[r].empty() ? 0.0 : (double)ent / (double)rtasks[r].size(), (int)most);
+            std::fprintf(stderr, "[cbm_build] round %d: %zu work items, %.1f entries each (%ld at most), at most %d rows in a path\n", r,
+                         rtasks[r].size(), rtasks[r].empty() ? 0.0 : (double)ent / (double)rtasks[r].size(),
+                         (long)h->levels[r - 1].longest, (int)most);
         // (a round of long single rows has the same entries in either layout: the launch picks the kernel by the width of X)
         h->levels[r - 1].long_single_rows = most == 1 && !rtasks[r].empty() && ent >= kLongSingleRow * (int64_t)rtasks[r].size();
         if (most > 1 && most <= CBM_BUNDLE_ROWS && ent >= bundle_min * (int64_t)rtasks[r].size()) {
@@ -1120,6 +1123,7 @@ cbm_status Builder::emit(int32_t nrounds) {
                 const int64_t e = std::min(end, b + split_len);
                 list.push_back({(int32_t)h->num_slots, -1, (uint32_t)(base + b), (uint32_t)(e - b) | CBM_TASK_SEGMENT});
                 ++h->num_slots;
+                h->seg_longest = std::max(h->seg_longest, e - b);
             }
             pos = end;
         }

@@ -41,6 +41,7 @@ struct CbmLevel {
     int64_t task_begin = 0, task_count = 0;        // into tasks[]: paths headed in this round
     int64_t comb_begin = 0, comb_count = 0;        // into comb[]: split rows of this round
     int64_t deltas = 0;                            // delta entries gathered by the round's main launch
+    int64_t longest = 0;                           // entries of its longest work item
     int64_t parent_reads = 0;                      // tasks in the main launch with a parent
     int64_t rows_written = 0;                      // matrix rows written by the main launch
     int64_t comb_segments = 0;                     // scratch rows read by the combine launch
@@ -86,6 +87,7 @@ struct cbm_handle {
     int64_t num_slots = 0;         // scratch rows needed by split rows
     int64_t seg_begin[CBM_XCD] = {}, seg_count[CBM_XCD] = {};  // segment work items in tasks[], per column range
     int64_t seg_deltas = 0;        // delta entries gathered by the segment launch
+    int64_t seg_longest = 0;       // entries of the longest segment
     bool bundled = false;          // some round's paths are emitted as bundles: delta columns are 26-bit in this handle
     cbm_stats_t stats{};
 

@@ -540,6 +540,9 @@ __global__ __launch_bounds__(256) void cbm_entry_weights_kernel(const uint32_t* 
 
 // 256 CUs x 4 SIMDs x 8 waves = 8192 resident waves at most; from eight times that on, a launch is "many waves"
 constexpr int64_t kManyWavesDefault = 65536;
+constexpr int64_t kManyWavesShort = 16384;
+constexpr double kEntryManyUs = 0.35;      // an entry in batches of 2
+constexpr double kManyBytesPerUs = 6.0e6;  // gathered rows of X
 
 struct LaunchCtx {
     const cbm_handle* h;
@@ -990,13 +993,20 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         h->prof_events.clear();
         h->prof_records.clear();
     }
-    // a launch of this many waves or more hides latency by occupancy: small batches, more waves per SIMD
-    static const int64_t many_waves = [] {
-        const char* e = std::getenv("CBM_MANY_WAVES");
-        return e ? std::atoll(e) : (int64_t)kManyWavesDefault;
-    }();
+    // A launch of 65,536 waves or more hides latency by occupancy: batches of 2 rows, twice the waves per SIMD.  So does one of
+    // 16,384 or more unless its longest work item, which batches of 2 take at about 0.35 us an entry, would then outlast it:
+    // citation recipe, k = 500 (39,000 waves, 25 entries at most) 42 -> 37 us; R-MAT scale 18, k = 47, mean (54,000 and 62,000
+    // waves) 407 -> 326; directed R-MAT scale 17, k = 100, forward and backward (64,000 waves of rows) 256 -> 229; but the roots of the
+    // collaboration recipe's tree, k = 128 (26,500 waves, 81 us) 25 us longer, and below 16,384 waves (segments and roots
+    // of 14,500) 10 to 20 us longer.  (CBM_MANY_WAVES moves the first line and takes the second away.)
+    static const char* many_env = std::getenv("CBM_MANY_WAVES");
+    static const int64_t many_waves = many_env ? std::atoll(many_env) : kManyWavesDefault;
     const int64_t ychunks = ((int64_t)k + lanes * 4 - 1) / (lanes * 4);
-    auto many = [&](int64_t items) { return items / var.group * ychunks >= many_waves; };
+    auto many = [&](int64_t items, int64_t deltas, int64_t longest) {
+        const int64_t waves = items / var.group * ychunks;
+        if (waves >= many_waves) return true;
+        return !many_env && waves >= kManyWavesShort && longest * kEntryManyUs <= 0.8 * (double)deltas * k * 4 / kManyBytesPerUs;
+    };
     const bool wcol = mode == 1 || mode == 2, wrow = wcol || mode == 3;
     const LaunchCtx ctx{h, X, ldx, k, Y, ldy, scratch, ld_scratch, stream, h->d_wstream, mode == 3 ? h->d_rinv : h->d_dinv, self_weight};
     const int64_t rowb = 4 * (int64_t)k;
@@ -1023,7 +1033,7 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         // the method's bytes only: the partial sums of split rows are this implementation's overhead
         rec.algorithmic_bytes = h->seg_deltas * per_delta;
         ProfScope ps(h, stream, rec);
-        (many(h->num_slots) ? var.segments_many : var.segments)(ctx, CbmLevel{});
+        (many(h->num_slots, h->seg_deltas, h->seg_longest) ? var.segments_many : var.segments)(ctx, CbmLevel{});
     }
     for (size_t l = 0; l < h->levels.size(); ++l) {
         const CbmLevel& L = h->levels[l];
@@ -1038,7 +1048,7 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
             // per work item with a parent: the parent's row
             rec.algorithmic_bytes = L.deltas * per_delta + L.rows_written * per_row + L.parent_reads * rowb;
             ProfScope ps(h, stream, rec);
-            (many(L.task_count) ? var.level_many : var.level)(ctx, L);
+            (many(L.task_count, L.deltas, L.longest) ? var.level_many : var.level)(ctx, L);
         }
         if (L.comb_count > 0) {
             cbm_launch_record rec{};
