@@ -46,9 +46,9 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
                                                                   const uint32_t* __restrict__ cols,
                                                                   const float* __restrict__ wcols,
                                                                   const uintx4* __restrict__ masks,
-                                                                  const float* __restrict__ X, uint32_t ldxb, float* __restrict__ Y,
+                                                                  const float* __restrict__ X, int64_t ldxb, float* __restrict__ Y,
                                                                   int64_t ldy, const float* __restrict__ rw, float self_w, int k) {
-    constexpr bool WCOL = MODE == 1 || MODE == 2, WROW = WCOL || MODE == 3, RELU = MODE == 2, SELF = MODE == 4;
+    constexpr bool WCOL = MODE == 1 || MODE == 2 || MODE == 5, WROW = MODE >= 1 && MODE <= 3, RELU = MODE == 2, SELF = MODE == 4;
     __shared__ uintx4 lut[256];
     __shared__ uintx4 ids[WAVES][2][16];
     __shared__ floatx4 wts[WAVES][2][16];
@@ -74,8 +74,8 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
     const int ccol = min(lcol, k - 1);  // loads stay inside the row; what they bring is never stored
     auto x_at = [&](uint32_t row) -> float {
         const char* base = reinterpret_cast<const char*>(X);
-        if (BIG) return *reinterpret_cast<const float*>(base + ((uint64_t)row * ldxb + (uint32_t)ccol * 4u));
-        return *reinterpret_cast<const float*>(base + (uint32_t)(__umul24(row, ldxb) + (uint32_t)ccol * 4u));
+        if (BIG) return *reinterpret_cast<const float*>(base + (int64_t)row * ldxb + (int64_t)ccol * 4);
+        return *reinterpret_cast<const float*>(base + (uint32_t)(__umul24(row, (uint32_t)ldxb) + (uint32_t)ccol * 4u));
     };
 
     floatx16 acc[T];
@@ -301,8 +301,8 @@ void launch(const Args& a) {
     }
     const dim3 grid((unsigned)(CBM_XCD * most), (unsigned)((a.k + 31) / 32));
     hipLaunchKernelGGL((cbm_block_kernel<MODE, BIG>), grid, dim3(64 * WAVES), 0, a.stream, a.h->d_blocks, map, a.h->d_block_rows,
-                       a.h->d_block_cols, a.h->d_block_w, reinterpret_cast<const uintx4*>(a.h->d_block_masks), a.X, (uint32_t)(a.ldx * 4),
-                       a.Y, a.ldy, a.rw, a.self_w, a.k);
+                       a.h->d_block_cols, a.h->d_block_w, reinterpret_cast<const uintx4*>(a.h->d_block_masks), a.X, a.ldx * 4, a.Y,
+                       a.ldy, a.rw, a.self_w, a.k);
 }
 template <bool BIG>
 void launch_mode(const Args& a, int mode) {
@@ -311,17 +311,26 @@ void launch_mode(const Args& a, int mode) {
         case 1: return launch<1, BIG>(a);
         case 2: return launch<2, BIG>(a);
         case 3: return launch<3, BIG>(a);
-        default: return launch<4, BIG>(a);
+        case 4: return launch<4, BIG>(a);
+        default: return launch<5, BIG>(a);
     }
+}
+
+void launch_size(const Args& a, int mode) {
+    // 24-bit indices and 32-bit offsets where they reach: one instruction per address
+    const int64_t n = std::max(a.h->n, a.h->m);
+    const bool big = n >= (1 << 24) || a.ldx >= (1 << 22) || n * a.ldx * 4 >= (int64_t)UINT32_MAX;
+    big ? launch_mode<true>(a, mode) : launch_mode<false>(a, mode);
 }
 
 }  // namespace
 
 void cbm_launch_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
                        float self_w, void* stream) {
-    const Args a{h, X, ldx, k, Y, ldy, rw, self_w, (hipStream_t)stream};
-    // 24-bit indices and 32-bit offsets where they reach: one instruction per address
-    const int64_t n = std::max(h->n, h->m);
-    const bool big = n >= (1 << 24) || ldx >= (1 << 22) || n * ldx * 4 >= (int64_t)UINT32_MAX;
-    big ? launch_mode<true>(a, mode) : launch_mode<false>(a, mode);
+    launch_size({h, X, ldx, k, Y, ldy, rw, self_w, (hipStream_t)stream}, mode);
+}
+
+void cbm_launch_hub_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* scratch, int64_t ld_scratch, bool weighted,
+                           void* stream) {
+    launch_size({h, X, ldx, k, scratch, ld_scratch, nullptr, 0.0f, (hipStream_t)stream}, weighted ? 5 : 0);
 }

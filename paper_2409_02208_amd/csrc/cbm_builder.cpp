@@ -61,6 +61,17 @@ constexpr double kBlockLongest = 64;        // groups of the longest block: hub 
 constexpr int64_t kBlockMinRows = 512;      // four blocks
 constexpr int64_t kBlockMinDegree = 16;     // mean entries of a row
 constexpr int64_t kBlockColumnGroup = 256;  // blocks whose rows' columns are taken together when a block sorts its columns
+// Hub blocks (Builder::hub_blocks)
+constexpr int64_t kHubMinRows = 512;
+// (R-MAT: at least 4 rows 0.233 ms at scale 18 and k = 47, 6 rows 0.258, 10 rows 0.280; at scale 21 and k = 128 anything from 4 to
+// 10 is within 1 %)
+constexpr int64_t kHubLeast = 4;          // rows of a block that hold a column, for the block to take it
+constexpr double kHubEntryUs = 7e-6;      // per slab: an entry of a split row in the gather kernels,
+constexpr double kHubGroupUs = 1.5e-3;    // a group of 64 columns here
+constexpr double kHubMinSavedUs = 2.0;
+constexpr size_t kHubPieceMin = 16, kHubPieceMax = 64;  // groups
+// (R-MAT scale 21, k = 128: up to 48, 64 or 96 entries 3.97 ms, up to 128 4.10; smaller graphs do not care)
+constexpr int64_t kRestWhole = 96;        // entries that hubs leave of a row, up to which they stay one segment
 constexpr int64_t kPathChoices[] = {16, 32, 64, 128, 256};
 
 long env_or(const char* name, long dflt) {
@@ -239,6 +250,18 @@ struct Builder {
     double row_block_cost(double groups, double longest) const;
     double sampled_row_block_cost() const;
     void row_blocks();
+    void hub_blocks(bool force);
+    int64_t count_slots() const;
+    // rows in hub blocks keep only the other entries for the gather kernels
+    struct Rest {
+        int32_t first_block = -1, blocks = 0, place = 0;  // the row's pieces and its place in them
+        std::vector<uint32_t> cols;
+    };
+    std::vector<int32_t> rest_of;  // row -> its Rest, -1 = none; empty: no hub blocks
+    std::vector<Rest> rests;
+    const Rest* rest(int64_t x) const { return rest_of.empty() || rest_of[x] < 0 ? nullptr : &rests[rest_of[x]]; }
+    int64_t elen(int64_t x) const { return rest(x) ? (int64_t)rest(x)->cols.size() : dlen(x); }
+    const uint32_t* entries(int64_t x) const { return rest(x) ? rest(x)->cols.data() : h->dcol.data() + h->dptr[x]; }
 };
 
 cbm_status Builder::validate(const int64_t* in_rowptr, const int32_t* in_colidx) {
@@ -962,6 +985,7 @@ double Builder::csr_cost() const {
 cbm_status Builder::emit(int32_t nrounds) {
     const int phases = (int)env_clamped("CBM_PHASES", kPhasesDefault, 1, 64);
     const int64_t fine_min = env_clamped("CBM_FINE_MIN", kFineMinDefault, 1, (long)CBM_TASK_LEN_MASK);
+    const int64_t rest_whole = env_clamped("CBM_REST_WHOLE", kRestWhole, 0, 1 << 20);
     // rows that a row of ANOTHER work item is compressed against keep their unscaled sum in Y
     std::vector<uint8_t> internal(m, 0);
     h->internal_rows.clear();
@@ -995,7 +1019,7 @@ cbm_status Builder::emit(int32_t nrounds) {
         CbmLevel& R = h->levels[round[x] - 1];
         if (is_split(x)) {
             splits.push_back({x, at});
-            at += dlen(x);
+            at += elen(x);
             continue;
         }
         const int64_t start = at;
@@ -1075,9 +1099,9 @@ cbm_status Builder::emit(int32_t nrounds) {
         for (int64_t i = b; i < e; ++i) {
             const int32_t x = splits[i].x;
             uint32_t* out = h->stream.data() + splits[i].base;
-            std::copy(h->dcol.begin() + h->dptr[x], h->dcol.begin() + h->dptr[x + 1], out);
+            std::copy(entries(x), entries(x) + elen(x), out);
             if (h->nminus[x] > 0)  // Delta+ alone is already in column order
-                std::sort(out, out + dlen(x), [](uint32_t a, uint32_t b2) {
+                std::sort(out, out + elen(x), [](uint32_t a, uint32_t b2) {
                     return (a & CBM_ENTRY_INDEX_MASK) < (b2 & CBM_ENTRY_INDEX_MASK);
                 });
         }
@@ -1094,7 +1118,7 @@ cbm_status Builder::emit(int32_t nrounds) {
         const int P = CBM_XCD * phases;
         std::vector<int64_t> upto((size_t)n + 1, 0);  // entries of split rows in columns < c
         for (const Piece& sp : splits)
-            for (int64_t i = 0; i < dlen(sp.x); ++i) ++upto[(h->stream[sp.base + i] & CBM_ENTRY_INDEX_MASK) + 1];
+            for (int64_t i = 0; i < elen(sp.x); ++i) ++upto[(h->stream[sp.base + i] & CBM_ENTRY_INDEX_MASK) + 1];
         for (int64_t c2 = 0; c2 < n; ++c2) upto[c2 + 1] += upto[c2];
         const int64_t total = upto[n];
         for (int f = 1; f < P; ++f)
@@ -1108,12 +1132,22 @@ cbm_status Builder::emit(int32_t nrounds) {
         const int32_t y = h->parent[x];
         CbmLevel& R = h->levels[round[x] - 1];
         ++split_rows;
-        const int64_t len = dlen(x);
+        const int64_t len = elen(x);
         const int64_t base = sp.base;
         const uint32_t* ent = h->stream.data() + base;
         const int64_t slot0 = h->num_slots;
         const int fine = len >= fine_min ? phases : 1;  // pieces per XCD range
-        const int npieces = CBM_XCD * fine;
+        if (const Rest* r = rest(x)) {
+            for (int32_t b = 0; b < r->blocks; ++b)
+                h->block_rows[(size_t)(r->first_block + b) * CBM_BLOCK_ROWS + r->place] = (uint32_t)h->num_slots++;
+            if (len > 0 && len <= rest_whole) {  // what the hubs leave of a row is seldom worth a piece in every range
+                seg_tasks[(size_t)(sp.x % CBM_XCD) * (phases + 1) + phases].push_back(
+                    {(int32_t)h->num_slots, -1, (uint32_t)base, (uint32_t)len | CBM_TASK_SEGMENT});
+                ++h->num_slots;
+                h->seg_longest = std::max(h->seg_longest, len);
+            }
+        }
+        const int npieces = rest(x) && len <= rest_whole ? 0 : CBM_XCD * fine;
         int64_t pos = 0;
         for (int f = 0; f < npieces; ++f) {
             const uint32_t hi = cut[(size_t)(f + 1) * (phases / fine)];  // columns < hi
@@ -1197,7 +1231,181 @@ cbm_status Builder::emit(int32_t nrounds) {
         h->comb.insert(h->comb.end(), rcomb[r].begin(), rcomb[r].end());
     }
     h->stats.num_split_rows = split_rows;
+    if (!h->hub_blocks) h->noalloc_slots = h->num_slots;
     return CBM_OK;
+}
+
+// Scratch rows that the split rows would take if every one were cut at the column ranges (pass 3 of emit, counted only).
+int64_t Builder::count_slots() const {
+    const int phases = (int)env_clamped("CBM_PHASES", kPhasesDefault, 1, 64);
+    const int64_t fine_min = env_clamped("CBM_FINE_MIN", kFineMinDefault, 1, (long)CBM_TASK_LEN_MASK);
+    const int P = CBM_XCD * phases;
+    std::vector<std::vector<int32_t>> part((size_t)nthreads);
+    parallel_chunks(nthreads, m, 4096, [&](int64_t b, int64_t e, int th) {
+        if (part[th].empty()) part[th].assign((size_t)n, 0);
+        for (int64_t x = b; x < e; ++x)
+            if (is_split(x))
+                for (int64_t i = h->dptr[x]; i < h->dptr[x + 1]; ++i) ++part[th][h->dcol[i] & CBM_ENTRY_INDEX_MASK];
+    });
+    std::vector<int64_t> upto((size_t)n + 1, 0);
+    parallel_chunks(nthreads, n, 16384, [&](int64_t b, int64_t e, int) {
+        for (const auto& p : part)
+            if (!p.empty())
+                for (int64_t c = b; c < e; ++c) upto[c + 1] += p[c];
+    });
+    for (int64_t c = 0; c < n; ++c) upto[c + 1] += upto[c];
+    std::vector<uint32_t> cut((size_t)P + 1, 0);
+    const int64_t total = upto[n];
+    for (int f = 1; f < P; ++f)
+        cut[f] = total > 0 ? (uint32_t)(std::lower_bound(upto.begin(), upto.end(), (total * f + P - 1) / P) - upto.begin()) : (uint32_t)((int64_t)f * n / P);
+    cut[P] = (uint32_t)n;
+    for (int f = 1; f <= P; ++f) cut[f] = std::min<uint32_t>((uint32_t)n, std::max(cut[f], cut[f - 1]));
+    std::atomic<int64_t> slots{0};
+    parallel_chunks(nthreads, m, 4096, [&](int64_t b, int64_t e, int) {
+        int64_t mine = 0;
+        for (int64_t x = b; x < e; ++x) {
+            if (!is_split(x)) continue;
+            const uint32_t *ent = h->dcol.data() + h->dptr[x], *end = ent + dlen(x);
+            const int fine = dlen(x) >= fine_min ? phases : 1;
+            for (int f = 0; f < CBM_XCD * fine; ++f) {
+                const uint32_t* to = std::lower_bound(ent, end, cut[(size_t)(f + 1) * (phases / fine)]);
+                mine += (to - ent + split_len - 1) / split_len;
+                ent = to;
+            }
+        }
+        slots += mine;
+    });
+    return slots;
+}
+
+// Hub blocks: where no tree pays, long rows still share the popular columns.  The split rows, longest first, are cut into blocks
+// of CBM_BLOCK_ROWS; a column that at least `least` of a block's rows hold goes into the block (one row of X gathered for
+// all of them, on the matrix cores), the rest of a row stays with the gather kernels.  A block is walked in pieces of bounded
+// length, each of which writes one partial sum per row into the scratch rows that the combine launch adds up anyway.
+// Measured (with / without): R-MAT scale 21, k = 128 3.97 / 4.42 ms (43 M of the split rows' 104 M entries in 77,000 groups;
+// what is left hits L2 less), scale 20, k = 128 1.69 / 2.02, scale 18, k = 47 0.235 / 0.330, scale 15, k = 64 0.065 / 0.078.
+void Builder::hub_blocks(bool force) {
+    std::vector<int32_t> rows;
+    for (int64_t x = 0; x < m; ++x)
+        if (is_split(x)) rows.push_back((int32_t)x);
+    if (rows.empty() || ((int64_t)rows.size() < kHubMinRows && !force)) return;
+    std::stable_sort(rows.begin(), rows.end(), [&](int32_t a, int32_t c) { return dlen(a) > dlen(c); });
+    constexpr int64_t per = CBM_BLOCK_ROWS;
+    constexpr int T = CBM_BLOCK_TILES;
+    const int least = (int)env_clamped("CBM_HUB_LEAST", kHubLeast, 2, CBM_BLOCK_ROWS);
+    const int64_t nb = ((int64_t)rows.size() + per - 1) / per;
+    // how often each column is held: blocks take their columns most popular first, so that those running at one time are at
+    // the same rows of X
+    std::vector<int32_t> held((size_t)n, 0);
+    {
+        std::vector<std::vector<int32_t>> part((size_t)nthreads);
+        parallel_chunks(nthreads, (int64_t)rows.size(), 256, [&](int64_t b, int64_t e, int th) {
+            if (part[th].empty()) part[th].assign((size_t)n, 0);
+            for (int64_t r = b; r < e; ++r)
+                for (int64_t i = h->dptr[rows[r]]; i < h->dptr[rows[r] + 1]; ++i) ++part[th][h->dcol[i]];
+        });
+        parallel_chunks(nthreads, n, 16384, [&](int64_t b, int64_t e, int) {
+            for (const auto& p : part)
+                if (!p.empty())
+                    for (int64_t c = b; c < e; ++c) held[c] += p[c];
+        });
+    }
+    struct Built {
+        std::vector<uint32_t> cols, masks;
+    };
+    std::vector<Built> built((size_t)nb);
+    rests.resize(rows.size());
+    std::vector<std::vector<int32_t>> local((size_t)nthreads);
+    std::atomic<int64_t> taken{0};
+    parallel_chunks(nthreads, nb, 1, [&](int64_t b0, int64_t b1, int th) {
+        std::vector<int32_t>& count = local[th];  // column -> how many rows of the block hold it, then its place (negative)
+        if (count.empty()) count.assign((size_t)n, 0);
+        std::vector<uint32_t> cols;
+        for (int64_t b = b0; b < b1; ++b) {
+            const int64_t r0 = b * per, r1 = std::min<int64_t>((int64_t)rows.size(), r0 + per);
+            cols.clear();
+            for (int64_t r = r0; r < r1; ++r)
+                for (int64_t i = h->dptr[rows[r]]; i < h->dptr[rows[r] + 1]; ++i)
+                    if (++count[h->dcol[i]] == least) cols.push_back(h->dcol[i]);
+            std::sort(cols.begin(), cols.end(), [&](uint32_t a, uint32_t c) { return held[a] != held[c] ? held[a] > held[c] : a < c; });
+            cols.resize(cols.size() / 64 * 64);  // whole groups
+            for (int64_t r = r0; r < r1; ++r)
+                for (int64_t i = h->dptr[rows[r]]; i < h->dptr[rows[r] + 1]; ++i) count[h->dcol[i]] = 0;
+            for (size_t i = 0; i < cols.size(); ++i) count[cols[i]] = -(int32_t)i - 1;
+            Built& out = built[b];
+            out.cols = cols;
+            out.masks.assign(cols.size() * 4, 0u);
+            int64_t mine = 0;
+            for (int64_t r = r0; r < r1; ++r) {
+                const int32_t x = rows[r], at = (int32_t)(r - r0);
+                std::vector<uint32_t>& left = rests[r].cols;
+                left.reserve((size_t)dlen(x));
+                for (int64_t q = h->dptr[x]; q < h->dptr[x + 1]; ++q) {
+                    const int32_t place = -count[h->dcol[q]] - 1;
+                    if (place < 0) {
+                        left.push_back(h->dcol[q]);
+                        continue;
+                    }
+                    const size_t i = (size_t)place;
+                    out.masks[i / 64 * 256 + 4 * (at % 32 + 32 * (i % 16 / 8)) + i % 64 / 16] |= 1u << (8 * (at / 32) + i % 8);
+                    ++mine;
+                }
+            }
+            for (uint32_t c : cols) count[c] = 0;
+            taken += mine;
+        }
+    });
+    static_assert(T == 4, "a mask word has a byte per tile");
+    size_t groups = 0;
+    for (const Built& x : built) groups += x.cols.size() / 64;
+    // worth it?  per slab of 32 columns of X: 1.5 ns a group, 7 ns a thousand entries gathered from L2
+    const double saved = (double)taken * kHubEntryUs - (double)groups * kHubGroupUs;
+    if (verbose)
+        std::fprintf(stderr, "[cbm_build] hub blocks: %ld rows, %zu groups of 64 columns hold %ld of their entries, saving %.1f us a slab\n",
+                     (long)rows.size(), groups, (long)taken.load(), saved);
+    // pieces: enough to fill the chip, long enough that the partial sums they add are few
+    const long forced_piece = env_or("CBM_HUB_PIECE", 0);
+    const size_t most = forced_piece > 0 ? (size_t)forced_piece : std::min<size_t>(kHubPieceMax, std::max<size_t>(kHubPieceMin, groups / 768));
+    size_t pieces = 0;
+    for (const Built& x : built) pieces += (x.cols.size() / 64 + most - 1) / most;
+    if (groups == 0 || (saved < kHubMinSavedUs && !force)) {
+        rests.clear();
+        return;
+    }
+    const int64_t slots_without = count_slots();
+    rest_of.assign((size_t)m, -1);
+    for (size_t r = 0; r < rows.size(); ++r) rest_of[rows[r]] = (int32_t)r;
+    h->block_cols.clear();
+    h->block_masks.clear();
+    h->block_rows.assign(pieces * per, CBM_BLOCK_NO_ROW);
+    std::vector<CbmBlock> all;
+    for (int64_t b = 0; b < nb; ++b) {
+        const size_t ng = built[b].cols.size() / 64;
+        const int32_t first = (int32_t)all.size();
+        for (size_t g = 0; g < ng; g += most)
+            all.push_back({(uint32_t)(all.size() * per), (uint32_t)(h->block_cols.size() / 64 + g), (uint32_t)std::min(most, ng - g)});
+        for (int64_t r = b * per; r < std::min<int64_t>((int64_t)rows.size(), (b + 1) * per); ++r) {
+            rests[r].first_block = first;
+            rests[r].blocks = (int32_t)all.size() - first;
+            rests[r].place = (int32_t)(r - b * per);
+        }
+        h->block_cols.insert(h->block_cols.end(), built[b].cols.begin(), built[b].cols.end());
+        h->block_masks.insert(h->block_masks.end(), built[b].masks.begin(), built[b].masks.end());
+        built[b] = Built{};
+    }
+    // longest pieces first, dealt over the XCDs
+    std::vector<int32_t> by(all.size());
+    for (size_t i = 0; i < by.size(); ++i) by[i] = (int32_t)i;
+    std::stable_sort(by.begin(), by.end(), [&](int32_t a, int32_t c) { return all[a].ngroups > all[c].ngroups; });
+    h->row_blocks.clear();
+    for (int j = 0; j < CBM_XCD; ++j) {
+        h->blk_begin[j] = (int64_t)h->row_blocks.size();
+        for (size_t i = j; i < by.size(); i += CBM_XCD) h->row_blocks.push_back(all[by[i]]);
+        h->blk_count[j] = (int64_t)h->row_blocks.size() - h->blk_begin[j];
+    }
+    h->hub_blocks = true;
+    h->noalloc_slots = slots_without;
+    lap("hub blocks");
 }
 
 // Modelled time of the row-block launch over `groups` groups of 64 columns (k = 128: four column slabs).  Measured: 1.2 ns a
@@ -1677,7 +1885,21 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     if (tree && B.locality) B.locality_order();
     cbm_stats_t& s = h->stats;
     std::memset(&s, 0, sizeof(s));
+    // (CBM_HUB_BLOCKS: 0 = never, 2 = whatever they save, on host-only handles too)
+    const long want_hubs = env_clamped("CBM_HUB_BLOCKS", 1, 0, 2);
+    if (!tree && B.auto_depth && !exact_tree && (want_hubs == 2 || (want_hubs == 1 && !(o.flags & CBM_FLAG_HOST_ONLY)))) B.hub_blocks(want_hubs == 2);
     st = B.emit(nrounds);
+    // cbm_spmm_noalloc takes a product's columns in as many goes as its scratch needs, at least four columns at a time
+    const int64_t most_slots = (int64_t)(cbm_static_scratch_bytes() / 16);
+    if (st == CBM_OK && h->hub_blocks && h->num_slots > most_slots && h->noalloc_slots <= most_slots) {
+        B.rest_of.clear();
+        h->hub_blocks = false;
+        std::vector<CbmBlock>().swap(h->row_blocks);
+        std::vector<uint32_t>().swap(h->block_rows);
+        std::vector<uint32_t>().swap(h->block_cols);
+        std::vector<uint32_t>().swap(h->block_masks);
+        st = B.emit(nrounds);
+    }
     if (st != CBM_OK) return st;
     B.lap("paths + work lists");
     // ---- row blocks ------------------------------------------------------------------------------
@@ -1685,7 +1907,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     // alike rows on the matrix cores is modelled cheaper than the rounds of paths, the products run that way.
     // (CBM_ROW_BLOCKS: 0 = never, 1 = whenever the matrix is square and the policy automatic.)
     const long want_blocks = env_clamped("CBM_ROW_BLOCKS", -1, -1, 1);
-    if (B.auto_depth && !exact_tree && want_blocks != 0 && m == n && m > 0 && (want_blocks == 1 || !(o.flags & CBM_FLAG_HOST_ONLY))) {
+    if (B.auto_depth && !exact_tree && !h->hub_blocks && want_blocks != 0 && m == n && m > 0 && (want_blocks == 1 || !(o.flags & CBM_FLAG_HOST_ONLY))) {
         const double limit = kBlockMargin * product_us;
         const int32_t most = *std::max_element(h->rownnz.begin(), h->rownnz.end());  // a block needs its longest row's columns
         const bool worth = want_blocks == 1 || (m >= kBlockMinRows && B.nnz >= kBlockMinDegree * m && most <= 64 * kBlockLongest &&
@@ -1727,6 +1949,9 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     s.bytes_csr = 8 * (m + 1) + 4 * in_rowptr[m];
     s.bytes_cbm = 4 * (int64_t)h->stream.size() + (int64_t)sizeof(CbmTask) * (int64_t)(h->tasks.size() + h->comb.size()) +
                   4 * (int64_t)h->internal_rows.size() + 4 * (int64_t)h->dinv.size();
+    if (h->hub_blocks)
+        s.bytes_cbm += 4 * (int64_t)(h->block_rows.size() + h->block_cols.size() + h->block_masks.size()) +
+                       (int64_t)sizeof(CbmBlock) * (int64_t)h->row_blocks.size();
     s.depth = depth;
     s.rounds = nrounds;
     s.alpha = B.alpha;

@@ -93,6 +93,9 @@ struct cbm_handle {
 
     // ---- row blocks: where they pay, the products run on these instead of the work items above ----
     std::vector<CbmBlock> row_blocks;    // empty: none
+    bool hub_blocks = false;             // the blocks hold only what long rows have in common: block_rows are scratch slots, and
+                                         // the sums there are parts of split rows like the segments'
+    int64_t noalloc_slots = 0;           // scratch rows that cbm_spmm_noalloc goes by: those of the handle without row blocks
     std::vector<uint32_t> block_rows;    // CBM_BLOCK_ROWS matrix rows per block
     std::vector<uint32_t> block_cols;    // 64 columns per group
     std::vector<uint32_t> block_masks;   // 64 x 4 words per group: byte s of word (l, i) = columns 8 (l / 32) .. + 7 of step i
@@ -158,7 +161,12 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
 // the product's one launch on a handle with row blocks (cbm_blocks.hip)
 void cbm_launch_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
                        float self_w, void* stream);
-size_t cbm_static_scratch_bytes();
+// the launch before the segments on a handle with hub blocks
+void cbm_launch_hub_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* scratch, int64_t ld_scratch, bool weighted,
+                           void* stream);
+// scratch of cbm_spmm_noalloc: one static array per GPU
+constexpr int64_t CBM_STATIC_SCRATCH_FLOATS = 16 * 1024 * 1024;  // 64 MiB
+inline size_t cbm_static_scratch_bytes() { return (size_t)CBM_STATIC_SCRATCH_FLOATS * sizeof(float); }
 // the same through bf16 parts (cbm_gemm_split.hip) where its own rule says so: *taken
 cbm_status cbm_launch_gemm_split(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                  int64_t ldc, void* stream, bool* taken);

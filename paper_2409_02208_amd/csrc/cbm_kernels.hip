@@ -32,7 +32,6 @@
 // Partial sums of split rows for cbm_spmm_noalloc: the callers of that entry point cannot allocate, so the
 // library brings this array along.  Every GPU the library runs on holds its own copy until the process ends.
 // In host code the name is only a handle for hipGetSymbolAddress -- never a device address.
-#define CBM_STATIC_SCRATCH_FLOATS (16 * 1024 * 1024)  // 64 MiB
 static __device__ __align__(256) float cbm_static_scratch[CBM_STATIC_SCRATCH_FLOATS];
 
 namespace {
@@ -934,8 +933,6 @@ cbm_status launch_blocked(const cbm_handle* h, const float* X, int64_t ldx, int3
 }
 }  // namespace
 
-size_t cbm_static_scratch_bytes() { return (size_t)CBM_STATIC_SCRATCH_FLOATS * sizeof(float); }
-
 cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
                               CbmEpilogue epi, float self_weight, void* stream_, bool static_scratch) {
     hipStream_t stream = (hipStream_t)stream_;
@@ -951,7 +948,7 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
     }
 
     // row blocks need no scratch; the limits of the static one are those of the paths all the same
-    const bool in_blocks = !h->row_blocks.empty() && ldx < (1 << 30);  // (a row's bytes are a 32-bit number there)
+    const bool in_blocks = !h->row_blocks.empty() && !h->hub_blocks;
     const int64_t ld_scratch = ((int64_t)k + 3) & ~(int64_t)3;
     float* scratch = nullptr;
     if (static_scratch) {
@@ -959,15 +956,24 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         // this GPU shares.  Segments overwrite their scratch rows in full before the combine launches read them,
         // so nothing has to be cleared between calls.
         if (h->profiling) return CBM_ERR_STATE;  // per-launch events are created on the fly
-        if (h->num_slots > 0) {
-            if ((uint64_t)h->num_slots * (uint64_t)ld_scratch > (uint64_t)CBM_STATIC_SCRATCH_FLOATS) {
+        if (h->noalloc_slots > 0) {
+            if ((uint64_t)h->noalloc_slots * (uint64_t)ld_scratch > (uint64_t)CBM_STATIC_SCRATCH_FLOATS) {
                 char msg[160];
                 std::snprintf(msg, sizeof(msg), "%lld scratch rows of %lld floats exceed the static scratch of %lld floats",
-                              (long long)h->num_slots, (long long)ld_scratch, (long long)CBM_STATIC_SCRATCH_FLOATS);
+                              (long long)h->noalloc_slots, (long long)ld_scratch, (long long)CBM_STATIC_SCRATCH_FLOATS);
                 cbm_set_error_detail("cbm_spmm_noalloc", msg);
                 return CBM_ERR_UNSUPPORTED;
             }
             if (const cbm_status st = static_scratch_address(cur, &scratch); st != CBM_OK) return st;
+            if (h->num_slots > 0 && h->num_slots * ld_scratch > CBM_STATIC_SCRATCH_FLOATS) {
+                // hub blocks can need a little more scratch than the limit goes by: the columns in as many goes as that takes
+                const int32_t chunk = (int32_t)(CBM_STATIC_SCRATCH_FLOATS / h->num_slots & ~(int64_t)3);
+                for (int32_t c = 0; c < k; c += chunk)
+                    if (const cbm_status st = cbm_launch_product(h, X + c, ldx, std::min(chunk, k - c), Y + c, ldy, epi, self_weight, stream_, true);
+                        st != CBM_OK)
+                        return st;
+                return CBM_OK;
+            }
         }
     } else if (!in_blocks) {
         // scratch rows for split rows: sized by cbm_reserve, else for this k on first use
@@ -1024,7 +1030,17 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         HIP_TRY(hipGetLastError(), CBM_ERR_HIP);
         return CBM_OK;
     }
-    if (h->num_slots > 0) {
+    if (h->hub_blocks) {
+        cbm_launch_record rec{};
+        rec.kind = 5;
+        rec.per_xcd = 1;
+        rec.tasks = (int64_t)h->row_blocks.size();
+        rec.deltas = (int64_t)h->block_cols.size();
+        rec.algorithmic_bytes = rec.deltas * per_delta;
+        ProfScope ps(h, stream, rec);
+        cbm_launch_hub_blocks(h, X, ldx, k, scratch, ld_scratch, wcol, stream_);
+    }
+    if (h->num_slots > 0 && h->seg_deltas > 0) {
         cbm_launch_record rec{};
         rec.kind = 1;
         rec.per_xcd = 1;

@@ -157,3 +157,104 @@ def test_scale_of_the_values_does_not_matter(env, scale):
     cbm.cbm_spmm(h, torch.from_numpy(X).cuda(), Y)
     torch.cuda.synchronize()
     assert _err(Y.cpu().numpy(), orc.spmm_csr(g.rowptr, g.colidx, X)) <= TOL
+
+
+# ---- hub blocks: the popular columns of the split rows of a matrix without a tree ----
+def _popular(m, n, seed):
+    """Rows of 150 to 700 entries among short ones, columns by a steep power law."""
+    rng = np.random.default_rng(seed)
+    rows = [np.unique((n * rng.random(int(rng.integers(150, 700)) if i % 3 == 0 else int(rng.integers(0, 20))) ** 3).astype(np.int64)) for i in range(m)]
+    rowptr = np.zeros(m + 1, dtype=np.int64)
+    rowptr[1:] = np.cumsum([len(r) for r in rows])
+    return rowptr, np.concatenate(rows).astype(np.int32)
+
+
+@pytest.fixture
+def hubs(monkeypatch):
+    monkeypatch.setenv("CBM_ROW_BLOCKS", "0")
+    monkeypatch.setenv("CBM_HUB_BLOCKS", "2")
+    monkeypatch.setenv("CBM_SPLIT_MIN", "128")
+
+
+@pytest.mark.parametrize("m,n", [(700, 700), (1500, 900), (1000, 6000)])
+@pytest.mark.parametrize("k", [1, 32, 47, 128])
+def test_hub_blocks_sums_are_exact(env, hubs, m, n, k):
+    torch, cbm = env
+    rowptr, colidx = _popular(m, n, 4)
+    h = cbm.cbm_build(m, n, rowptr, colidx)
+    X = wl.integer_features(n, k, 3)
+    Xd, Y = torch.from_numpy(X).cuda(), torch.full((m, k), float("nan"), device="cuda")
+    cbm.cbm_profile_enable(h, True)
+    cbm.cbm_spmm(h, Xd, Y)
+    torch.cuda.synchronize()
+    kinds = [r["kind"] for r in cbm.cbm_profile_read(h)]
+    cbm.cbm_profile_enable(h, False)
+    assert kinds[0] == 5 and 2 in kinds
+    ref = orc.spmm_csr(rowptr, colidx, X)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref)
+    cbm.cbm_spmm_noalloc(h, Xd, Y.fill_(float("nan")))
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref)
+    cbm.cbm_spmm_mean(h, Xd, Y)
+    assert _err(Y.cpu().numpy(), orc.spmm_csr_mean(rowptr, colidx, X)) <= TOL
+
+
+@pytest.mark.parametrize("k", [16, 47, 130])
+def test_hub_blocks_normalised_and_transposed(env, hubs, k):
+    torch, cbm = env
+    n = 1200
+    rowptr, colidx = _popular(n, n, 6)
+    h = cbm.cbm_build(n, n, rowptr, colidx, add_self_loops=True)
+    ht = cbm.cbm_build(n, n, rowptr, colidx, add_self_loops=True, transpose=True)
+    X, G = (torch.from_numpy(wl.gaussian_features(n, k, s)).cuda() for s in (1, 2))
+    Y, Z, R = torch.empty_like(X), torch.empty_like(X), torch.empty_like(X)
+    cbm.cbm_spmm_normalized(h, X, Y)
+    cbm.cbm_spmm_normalized_relu(h, X, R)
+    cbm.cbm_spmm_normalized(ht, G, Z)
+    torch.cuda.synchronize()
+    ref = orc.spmm_csr_normalized(rowptr, colidx, X.cpu().numpy())
+    assert _err(Y.cpu().numpy(), ref) <= TOL
+    assert _err(R.cpu().numpy(), np.maximum(ref, 0), ref) <= TOL
+    left, right = float((Y.double() * G.double()).sum()), float((X.double() * Z.double()).sum())
+    assert abs(left - right) <= 1e-5 * float((Y.double() * G.double()).abs().sum())
+    cbm.cbm_spmm_gin(h, 0.5, X, Y)
+    both = orc.spmm_csr(*_with_self(rowptr, colidx), X.cpu().numpy()) + 1.5 * X.cpu().numpy().astype(np.float64)
+    assert _err(Y.cpu().numpy(), both) <= TOL
+
+
+def _with_self(rowptr, colidx):
+    rows = [np.union1d(colidx[rowptr[i]:rowptr[i + 1]], [i]) for i in range(len(rowptr) - 1)]
+    rp = np.zeros(len(rowptr), dtype=np.int64)
+    rp[1:] = np.cumsum([len(r) for r in rows])
+    return rp, np.concatenate(rows).astype(np.int32)
+
+
+def test_hub_blocks_take_noalloc_columns_in_goes(env, hubs, monkeypatch):
+    """Hub blocks can need more scratch than the limit goes by (that of the handle without them): the columns then come in
+    goes; what was refused is refused.  Segments of one entry make the scratch large: 64 MiB at about 250 columns."""
+    torch, cbm = env
+    monkeypatch.setenv("CBM_HUB_PIECE", "1")
+    monkeypatch.setenv("CBM_REST_WHOLE", "0")
+    m, n = 12000, 12000
+    rowptr, colidx = _popular(m, n, 5)
+    h = cbm.cbm_build(m, n, rowptr, colidx)
+    monkeypatch.setenv("CBM_HUB_BLOCKS", "0")
+    plain = cbm.cbm_build(m, n, rowptr, colidx)
+    refused = []
+    for k in range(64, 1600, 64):
+        X = torch.randint(-3, 4, (n, k), device="cuda").float()
+        Y, Z = torch.empty((m, k), device="cuda"), torch.empty((m, k), device="cuda")
+        got = []
+        for handle, out in ((h, Y), (plain, Z)):
+            try:
+                cbm.cbm_spmm_noalloc(handle, X, out)
+                got.append(True)
+            except cbm.CbmError as e:
+                assert e.status == 5
+                got.append(False)
+        assert got[0] == got[1], k
+        if not got[0]:
+            refused.append(k)
+            break
+        torch.cuda.synchronize()
+        assert torch.equal(Y, Z), k
+    assert refused, "widths up to the limit were to be tried"

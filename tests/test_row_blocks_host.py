@@ -23,7 +23,7 @@ def test_blocks_decode_to_the_matrix(tmp_path):
         pytest.skip("sanitizer runtime not available: " + r.stderr[-200:])
     assert r.returncode == 0, r.stderr[-2000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
-    assert r.returncode == 0 and "blocks ok" in r.stdout, (r.stdout[-500:], r.stderr[-3000:])
+    assert r.returncode == 0 and "blocks ok" in r.stdout and "hubs ok" in r.stdout, (r.stdout[-500:], r.stderr[-3000:])
 
 
 def test_blocks_leave_tree_and_counters_alone(monkeypatch):
