@@ -90,7 +90,10 @@ typedef enum {
  *                square matrix of 512 rows or more whose neighbouring rows share most of
  *                their columns the same model may let the products run in row blocks:
  *                one walk over the columns of 128 alike rows, on the matrix cores, in
- *                one launch; the tree and all counters stay what they are.  The
+ *                one launch; the tree and all counters stay what they are.  Where every
+ *                row is stored in full, rows long enough to be split share their popular
+ *                columns in such blocks too (num_tasks and bytes_cbm count what is left
+ *                of them, and the blocks' arrays).  The
  *                tree is cut into vertical paths, one work item each;
  *                dependent kernel launches per product = rounds of paths
  *                (cbm_stats), at most the depth.  Any value yields a valid CBM
@@ -205,10 +208,11 @@ cbm_status cbm_spmm(const cbm_handle* h, const float* X, int64_t ldx, int32_t k,
  * same result as cbm_spmm, but the partial sums of split rows go to a 64 MiB array that is part of the
  * library's device code instead of a scratch the handle allocates; the call makes no hipMalloc / hipFree
  * and no other allocating call.
- *   Limit: (segments the handle's split rows are cut into -- one scratch row each, at most
- *   cbm_stats.num_tasks) x (k rounded up to a multiple of 4) floats must fit 64 MiB = 16,777,216 floats,
+ *   Limit: (segments the handle's split rows are cut into at the column ranges, one scratch row each)
+ *   x (k rounded up to a multiple of 4) floats must fit 64 MiB = 16,777,216 floats,
  *   else CBM_ERR_UNSUPPORTED (cbm_last_error_detail gives the numbers); a handle without split rows
- *   (cbm_stats.num_split_rows == 0) always fits.
+ *   (cbm_stats.num_split_rows == 0) always fits.  Where long rows share their popular columns in blocks
+ *   (see max_depth) and that takes more scratch rows, the columns of X go through in several goes.
  *   CBM_ERR_STATE while per-launch profiling is on (it creates events).
  * Every GPU the library runs on holds one such array until the process ends, and every call on that GPU
  * shares it, whatever the handle: calls that overlap in time on one GPU (two streams, two host threads)
@@ -311,8 +315,9 @@ typedef struct {
                                2 = split-row combine, 3 = deferred finish of rows that
                                other work items read (row weight, self term, ReLU),
                                4 = sum of the partial rows of a column-blocked handle,
-                               5 = the whole product in row blocks (tasks = blocks, deltas =
-                               columns gathered, each once per block)                    */
+                               5 = row blocks: the whole product, or the popular columns of
+                               split rows (tasks = blocks, deltas = columns gathered, each
+                               once per block)                                           */
     int32_t level;          /* round for kinds 0 and 2, else 0                         */
     int64_t tasks;          /* work items in the launch                               */
     int64_t deltas;         /* delta entries gathered by the launch                   */

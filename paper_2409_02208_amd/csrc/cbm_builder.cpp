@@ -1409,7 +1409,7 @@ void Builder::hub_blocks(bool force) {
 }
 
 // Modelled time of the row-block launch over `groups` groups of 64 columns (k = 128: four column slabs).  Measured: 1.2 ns a
-// group and slab with the chip full (protein recipe, 36,900 groups: 0.18 ms at k = 128, 0.39 ms at k = 256); with few blocks
+// group and slab with the chip full (protein recipe, 34,700 groups: 0.18 ms at k = 128, 0.32 to 0.39 ms at k = 256 with the clock); with few blocks
 // the launch lasts as long as its longest block (6,000 nodes, 60 neighbours: blocks of 13 groups, 11.4 us a product against
 // 18.3 us on the paths; 300 neighbours: 26 groups, 18 against 29 us).
 double Builder::row_block_cost(double groups, double longest) const {
@@ -1460,8 +1460,8 @@ double Builder::sampled_row_block_cost() const {
 
 // Row blocks (cbm_blocks.hip): rows in an order of much the same columns, cut every CBM_BLOCK_ROWS rows; a block's columns
 // sorted by where their own rows lie in that order, coarsely, so that blocks that run side by side ask for the same rows of X
-// at about the same time (L2 misses 59 -> 34 % of requests on the protein recipe), and then by which of the block's tiles hold
-// them, so that a step of 16 columns touches as few tiles as it can (2.6 -> 2.25 of 4 with the rows sorted into tiles).
+// at about the same time (L2 misses 59 -> 42 % of requests on the protein recipe), and then by which of the block's tiles hold
+// them, so that a step of 16 columns touches as few tiles as it can (2.6 -> 2.1 of 4 with the rows sorted into tiles).
 void Builder::row_blocks() {
     constexpr int64_t per = CBM_BLOCK_ROWS;
     constexpr int T = CBM_BLOCK_TILES;

@@ -542,6 +542,7 @@ constexpr int64_t kManyWavesDefault = 65536;
 constexpr int64_t kManyWavesShort = 16384;
 constexpr double kEntryManyUs = 0.35;      // an entry in batches of 2
 constexpr double kManyBytesPerUs = 6.0e6;  // gathered rows of X
+constexpr double kManyLongest = 0.75;      // the longest work item's share of the launch
 
 struct LaunchCtx {
     const cbm_handle* h;
@@ -1004,14 +1005,17 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
     // citation recipe, k = 500 (39,000 waves, 25 entries at most) 42 -> 37 us; R-MAT scale 18, k = 47, mean (54,000 and 62,000
     // waves) 407 -> 326; directed R-MAT scale 17, k = 100, forward and backward (64,000 waves of rows) 256 -> 229; but the roots of the
     // collaboration recipe's tree, k = 128 (26,500 waves, 81 us) 25 us longer, and below 16,384 waves (segments and roots
-    // of 14,500) 10 to 20 us longer.  (CBM_MANY_WAVES moves the first line and takes the second away.)
+    // of 14,500) 10 to 20 us longer.  (The share of the launch: directed R-MAT's rows of up to 128 entries gain at 0.73, R-MAT
+    // scale 17, k = 64 lost 9 % at 0.8.  With one work item a wave and 25 entries in it, collaboration recipe of 60,000 nodes,
+    // k = 200, it lost 3 %.)  (CBM_MANY_WAVES moves the first line and takes the second away.)
     static const char* many_env = std::getenv("CBM_MANY_WAVES");
     static const int64_t many_waves = many_env ? std::atoll(many_env) : kManyWavesDefault;
     const int64_t ychunks = ((int64_t)k + lanes * 4 - 1) / (lanes * 4);
     auto many = [&](int64_t items, int64_t deltas, int64_t longest) {
         const int64_t waves = items / var.group * ychunks;
         if (waves >= many_waves) return true;
-        return !many_env && waves >= kManyWavesShort && longest * kEntryManyUs <= 0.8 * (double)deltas * k * 4 / kManyBytesPerUs;
+        if (many_env || waves < kManyWavesShort || (lanes == 64 && deltas >= 16 * items)) return false;
+        return longest * kEntryManyUs <= kManyLongest * (double)deltas * k * 4 / kManyBytesPerUs;
     };
     const bool wcol = mode == 1 || mode == 2, wrow = wcol || mode == 3;
     const LaunchCtx ctx{h, X, ldx, k, Y, ldy, scratch, ld_scratch, stream, h->d_wstream, mode == 3 ? h->d_rinv : h->d_dinv, self_weight};
