@@ -258,7 +258,8 @@ def run_counter_children(args, cache_dir):
         if tag in ("fetch", "write"):
             if not copies:
                 return None, "no calibration copy among the counted dispatches"
-            kib = np.mean([x[counters[0]] for x in copies[-plan["copies"]:]])
+            # the calibration copies are the largest of all (uploads of a handle's arrays are copies too, of any size)
+            kib = np.mean(sorted(x[counters[0]] for x in copies)[-plan["copies"]:])
             calib[tag] = plan["copy_bytes"] / (kib * 1024.0)   # bytes that really moved per byte the counter reports
         at = 0
         for p in plan["plan"]:
