@@ -1,16 +1,22 @@
 // Dense fp32 matmul C = A.B on the bf16 matrix cores: both operands split into three bf16 parts that add up to the fp32 value
-// exactly (8 + 8 + 8 significant bits, by truncation: x = h + m + l), six products of parts (hh, hm, mh, mm, hl, lh), 32-bit sums.
+// exactly (8 + 8 + 8 significant bits, every part rounded to the nearest: x = h + m + l), six products of parts (hh, hm, mh, mm, hl,
+// lh), 32-bit sums.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "cbm_internal.h"
 #include "cbm_split.h"
 
-// The bf16 matrix cores are 16 times as fast as the fp32 ones, the six products leave 2.7.  Left out are products of parts
-// below 2^-24 of the value's; measured error against 64 bits is smaller than that of the fp32 kernels, whose chain of
-// additions is longer (K = 256: 2.4e-7 against 2.9e-7 in the 2-norm; K = 500 in four parts: 1.8e-7 against 4.0e-7).
+// The bf16 matrix cores are 16 times as fast as the fp32 ones, the six products leave 2.7.  Left out are ml, lm and ll: at most
+// 2^-24 of a term (|m| <= 2^-8, |l| <= 2^-17 of the value), of either sign.  (By truncation m and l are twice and four times as large
+// and have the value's sign: up to 7.8 * 2^-24 of a term, all on one side.)  The five small products have sums of their own: added
+// to the large ones at every step, each of them would round a sum of full size.
+// Error against 64 bits, fp32 kernels of cbm_gemm.hip -> these (2-norm, Gaussian values): K = 500 4.0e-7 -> 0.77e-7 up to 64 columns and
+// 1.3e-7 beyond; ten non-zeros a row 5.9e-8 -> 3.0e-8, four 4.0e-8 -> 2.7e-8, one 2.5e-8 -> 2.6e-8 (at most 1.0 -> 1.7 times 2^-24).
+// Time of the wider sums: 132534 x 256 . 256 x 256 133 -> 140 us, 132534 x 250 . 250 x 250 175 -> 191; up to 64 columns nothing.
 
 namespace {
 
@@ -23,7 +29,7 @@ __device__ __forceinline__ Parts split8(const float (&x)[8], uint32_t minus_low)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         uint32_t h, m, l;
-        split_pair(x[2 * i], x[2 * i + 1], minus_low, h, m, l);
+        split_pair_nearest(x[2 * i], x[2 * i + 1], minus_low, h, m, l);
         q[0][i] = h;
         q[1][i] = m;
         q[2][i] = l;
@@ -34,15 +40,19 @@ __device__ __forceinline__ Parts split8(const float (&x)[8], uint32_t minus_low)
     return r;
 }
 
-// the six products, small ones first; neighbouring instructions write different tiles
+// the six products, the one of the large parts last; neighbouring instructions write different tiles
 constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
 
-template <int NT>
-__device__ __forceinline__ void multiply(floatx16 (&acc)[NT], const Parts& a, const Parts (&b)[NT]) {
+// FIRST: the first of b's N tiles
+template <int FIRST, int N, int NT>
+__device__ __forceinline__ void multiply(floatx16 (&acc)[NT], floatx16 (&small)[NT], const Parts& a, const Parts (&b)[N]) {
 #pragma unroll
     for (int i = 0; i < 6; ++i)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[PA[i]], b[t].p[PB[i]], acc[t], 0, 0, 0);
+        for (int t = 0; t < N; ++t) {
+            floatx16& sum = i < 5 ? small[FIRST + t] : acc[FIRST + t];
+            sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[PA[i]], b[t].p[PB[i]], sum, 0, 0, 0);
+        }
 }
 
 // Eight consecutive k of row `row` of A from k0 on, zero beyond K (addresses held inside the matrix).
@@ -98,8 +108,8 @@ __device__ __forceinline__ float largest_of(float x) {
 constexpr int KS = 4, PF = 2;
 
 template <int NT, bool VEC>
-__global__ __launch_bounds__(256) void cbm_gemm_narrow_kernel(int64_t M, int N, int K, const float* __restrict__ A, int64_t lda,
-                                                              const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc) {
+__global__ __launch_bounds__(256, 3) void cbm_gemm_narrow_kernel(int64_t M, int N, int K, const float* __restrict__ A, int64_t lda,
+                                                                 const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc) {
     __shared__ float red[KS - 1][NT * 16][64];
     __shared__ float high[4];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -109,11 +119,11 @@ __global__ __launch_bounds__(256) void cbm_gemm_narrow_kernel(int64_t M, int N, 
     const float* bcol[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) bcol[t] = B + min(32 * t + l32, N - 1);
-    floatx16 acc[NT];
+    floatx16 acc[NT], small[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[t][v] = 0.0f;
+        for (int v = 0; v < 16; ++v) acc[t][v] = small[t][v] = 0.0f;
     uint32_t minus_low = 0xbf80u;
     asm("" : "+s"(minus_low));
     float largest = 0.0f;
@@ -144,7 +154,7 @@ __global__ __launch_bounds__(256) void cbm_gemm_narrow_kernel(int64_t M, int N, 
         Parts b[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) b[t] = split8(s.b[t], minus_low);
-        multiply<NT>(acc, a, b);
+        multiply<0>(acc, small, a, b);
     };
     if (first < steps) {  // (loads are always made, with the step held to this wave's last)
         const int last = first + (steps - 1 - first) / KS * KS;
@@ -165,21 +175,32 @@ __global__ __launch_bounds__(256) void cbm_gemm_narrow_kernel(int64_t M, int N, 
     }
     largest = largest_of(largest);
     if (lane == 0) high[wave] = largest;
-    if (wave > 0) {
+    // the waves' shares, the small sums first and apart: the large ones then lose no bit to them before the last addition
+    auto gather = [&](floatx16 (&x)[NT]) {
+        if (wave > 0) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) red[wave - 1][16 * t + v][lane] = x[t][v];
+        }
+        __syncthreads();
+        if (wave > 0) return;
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) red[wave - 1][16 * t + v][lane] = acc[t][v];
-    }
+            for (int v = 0; v < 16; ++v)
+#pragma unroll
+                for (int w = 0; w < KS - 1; ++w) x[t][v] += red[w][16 * t + v][lane];
+    };
+    gather(small);
     __syncthreads();
+    gather(acc);
     if (wave > 0) return;
     largest = fmaxf(fmaxf(high[0], high[1]), fmaxf(high[2], high[3]));
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-#pragma unroll
-            for (int w = 0; w < KS - 1; ++w) acc[t][v] += red[w][16 * t + v][lane];
+        for (int v = 0; v < 16; ++v) acc[t][v] += small[t][v];
     uint32_t again = 0;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -203,8 +224,9 @@ __global__ __launch_bounds__(256) void cbm_gemm_narrow_kernel(int64_t M, int N, 
 constexpr int CK = 32;  // k per chunk
 
 template <int NT, bool VEC>
-__global__ __launch_bounds__(256, 2) void cbm_gemm_wide_kernel(int64_t M, int N, int K, const float* __restrict__ A, int64_t lda,
-                                                               const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc) {
+__global__ __launch_bounds__(256, NT > 2 ? 2 : 3) void cbm_gemm_wide_kernel(int64_t M, int N, int K, const float* __restrict__ A,
+                                                                            int64_t lda, const float* __restrict__ B, int64_t ldb,
+                                                                            float* __restrict__ C, int64_t ldc) {
     constexpr int BN = 32 * NT;
     constexpr int PER = (CK / 8) * BN / 256;  // columns of eight k that a thread stages per chunk
     static_assert((CK / 8) * BN % 256 == 0, "every thread stages the same number");
@@ -215,11 +237,11 @@ __global__ __launch_bounds__(256, 2) void cbm_gemm_wide_kernel(int64_t M, int N,
     const int64_t row0 = (int64_t)blockIdx.x * 128 + 32 * wave;
     const int col0 = blockIdx.y * BN;
     const float* arow = A + min(row0 + l32, M - 1) * lda;
-    floatx16 acc[NT];
+    floatx16 acc[NT], small[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[t][v] = 0.0f;
+        for (int v = 0; v < 16; ++v) acc[t][v] = small[t][v] = 0.0f;
     uint32_t minus_low = 0xbf80u;
     asm("" : "+s"(minus_low));
     float largest = 0.0f;
@@ -257,18 +279,33 @@ __global__ __launch_bounds__(256, 2) void cbm_gemm_wide_kernel(int64_t M, int N,
 #pragma unroll
         for (int s = 0; s < 2; ++s) load_a<VEC>(na[s], arow, next * CK + 16 * s + 8 * half, K);
         __builtin_amdgcn_sched_barrier(0);
+        // units of work: a step of 16 k, two tiles of B; the next unit's parts of B are read while one is multiplied
+        Parts b[2][2], a;
+        auto read_b = [&](int u) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            cut_a(xa[s], c * CK + 16 * s + 8 * half, K);
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int j = 0; j < 8; j += 2) largest = fmaxf(largest, fmaxf(fabsf(xa[s][j]), fabsf(xa[s][j + 1])));
-            const Parts a = split8(xa[s], minus_low);
-            Parts b[NT];
+                for (int q = 0; q < 3; ++q)
+                    b[u & 1][t].p[q] = __builtin_bit_cast(bf16x8, stage[c & 1][q][2 * (u / (NT / 2)) + half][32 * (u % (NT / 2) * 2 + t) + l32]);
+        };
+        auto unit = [&](auto u) {
+            constexpr int s = u / (NT / 2), first = u % (NT / 2) * 2;
+            if (first == 0) {
+                cut_a(xa[s], c * CK + 16 * s + 8 * half, K);
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int q = 0; q < 3; ++q) b[t].p[q] = __builtin_bit_cast(bf16x8, stage[c & 1][q][2 * s + half][32 * t + l32]);
-            multiply<NT>(acc, a, b);
+                for (int j = 0; j < 8; j += 2) largest = fmaxf(largest, fmaxf(fabsf(xa[s][j]), fabsf(xa[s][j + 1])));
+                a = split8(xa[s], minus_low);
+            }
+            if (u + 1 < NT) read_b(u + 1);
+            multiply<first>(acc, small, a, b[u & 1]);
+            __builtin_amdgcn_sched_barrier(0);  // (one unit's parts at a time: more would not fit the registers)
+        };
+        read_b(0);
+        unit(std::integral_constant<int, 0>{});
+        unit(std::integral_constant<int, 1>{});
+        if constexpr (NT > 2) {
+            unit(std::integral_constant<int, 2>{});
+            unit(std::integral_constant<int, 3>{});
         }
         store_b(xb, (c + 1) & 1);
         __syncthreads();
@@ -282,6 +319,10 @@ __global__ __launch_bounds__(256, 2) void cbm_gemm_wide_kernel(int64_t M, int N,
     __syncthreads();
     largest = fmaxf(fmaxf(high[0], high[1]), fmaxf(high[2], high[3]));
     if (row0 >= M) return;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] += small[t][v];
     uint32_t again = 0;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
