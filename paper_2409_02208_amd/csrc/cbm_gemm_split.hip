@@ -16,7 +16,6 @@
 // to the large ones at every step, each of them would round a sum of full size.
 // Error against 64 bits, fp32 kernels of cbm_gemm.hip -> these (2-norm, Gaussian values): K = 500 4.0e-7 -> 0.77e-7 up to 64 columns and
 // 1.3e-7 beyond; ten non-zeros a row 5.9e-8 -> 3.0e-8, four 4.0e-8 -> 2.7e-8, one 2.5e-8 -> 2.6e-8 (at most 1.0 -> 1.7 times 2^-24).
-// Time of the wider sums: 132534 x 256 . 256 x 256 133 -> 140 us, 132534 x 250 . 250 x 250 175 -> 191; up to 64 columns nothing.
 
 namespace {
 
@@ -70,17 +69,19 @@ __device__ __forceinline__ void load_a(float (&x)[8], const float* __restrict__ 
         for (int j = 0; j < 8; ++j) x[j] = row[min(k0 + j, K - 1)];
     }
 }
+// No bf16 value has bits below 2^-133, and the matrix cores take what is below 2^-126 for zero: operands are split at 2^24 times
+// their size, where the smallest fp32 value is 2^-125, and sums come back by 2^-48 (what is below 2^-126 then is below 2^-174 of
+// the result).  Values and sums that are not finite, or are not any more at that size (from 2^104 and 2^80), give sums that are not
+// finite: those are computed again by fused multiply-adds.  (Cheaper than to look for small values: with the largest operand kept
+// beside the sums and small sums computed again, zeros could not be told from sums that had vanished, and 132534 x 256 . 256 x 256 took
+// 138 us against 128.)
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;
+
 __device__ __forceinline__ void cut_a(float (&x)[8], int k0, int K) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] = k0 + j < K ? x[j] : 0.0f;
+    for (int j = 0; j < 8; ++j) x[j] = k0 + j < K ? x[j] * kUp : 0.0f;
 }
-
-// What the matrix cores cannot be asked: parts of infinities and NaN are NaN, and parts below the smallest normal number count
-// as zero there, an error of up to 2^-126 times the other operand a term.  A sum that is not finite, or not zero and below 2^-90
-// times the largest operand (2^-90 at least), is computed again by fused multiply-adds.
-__device__ __forceinline__ bool doubtful(float v, float largest) {
-    return !(v == 0.0f || (fabsf(v) < INFINITY && fabsf(v) >= 0x1p-90f * largest));
-}
+__device__ __forceinline__ bool doubtful(float v) { return !(fabsf(v) < INFINITY); }
 // rows row0 .. + 31, columns col0 .. + 31 of C
 __device__ __forceinline__ void plain_tile(int64_t M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                         int64_t ldc, int64_t row0, int col0) {
@@ -95,12 +96,6 @@ __device__ __forceinline__ void plain_tile(int64_t M, int N, int K, const float*
         C[(row0 + r) * ldc + c] = s;
     }
 }
-__device__ __forceinline__ float largest_of(float x) {
-#pragma unroll
-    for (int d = 1; d < 64; d *= 2) x = fmaxf(x, __shfl_xor(x, d, 64));
-    return fmaxf(x, 1.0f);
-}
-
 // Narrow C (up to 64 columns), for products that are short and deep: a workgroup has 32 rows of C, its four waves take the
 // steps of 16 k in turn and add their sums through LDS.  Both operands come straight from memory in operand layout (lane l:
 // row, or column, l % 32 and eight k from 8 (l / 32) on): B is small and stays in L2.  Loads run one step ahead (three:
@@ -111,7 +106,6 @@ template <int NT, bool VEC>
 __global__ __launch_bounds__(256, 3) void cbm_gemm_narrow_kernel(int64_t M, int N, int K, const float* __restrict__ A, int64_t lda,
                                                                  const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc) {
     __shared__ float red[KS - 1][NT * 16][64];
-    __shared__ float high[4];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int64_t row0 = (int64_t)blockIdx.x * 32;
@@ -126,7 +120,6 @@ __global__ __launch_bounds__(256, 3) void cbm_gemm_narrow_kernel(int64_t M, int 
         for (int v = 0; v < 16; ++v) acc[t][v] = small[t][v] = 0.0f;
     uint32_t minus_low = 0xbf80u;
     asm("" : "+s"(minus_low));
-    float largest = 0.0f;
 
     const int steps = (K + 15) / 16, first = wave;
     struct Step {
@@ -145,11 +138,9 @@ __global__ __launch_bounds__(256, 3) void cbm_gemm_narrow_kernel(int64_t M, int 
     auto use = [&](Step& s, int i) {
         cut_a(s.a, 16 * i + 8 * half, K);
 #pragma unroll
-        for (int j = 0; j < 8; j += 2) {
-            largest = fmaxf(largest, fmaxf(fabsf(s.a[j]), fabsf(s.a[j + 1])));
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int t = 0; t < NT; ++t) largest = fmaxf(largest, fmaxf(fabsf(s.b[t][j]), fabsf(s.b[t][j + 1])));
-        }
+            for (int j = 0; j < 8; ++j) s.b[t][j] *= kUp;
         const Parts a = split8(s.a, minus_low);
         Parts b[NT];
 #pragma unroll
@@ -173,8 +164,6 @@ __global__ __launch_bounds__(256, 3) void cbm_gemm_narrow_kernel(int64_t M, int 
             }
         }
     }
-    largest = largest_of(largest);
-    if (lane == 0) high[wave] = largest;
     // the waves' shares, the small sums first and apart: the large ones then lose no bit to them before the last addition
     auto gather = [&](floatx16 (&x)[NT]) {
         if (wave > 0) {
@@ -196,17 +185,16 @@ __global__ __launch_bounds__(256, 3) void cbm_gemm_narrow_kernel(int64_t M, int 
     __syncthreads();
     gather(acc);
     if (wave > 0) return;
-    largest = fmaxf(fmaxf(high[0], high[1]), fmaxf(high[2], high[3]));
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[t][v] += small[t][v];
+        for (int v = 0; v < 16; ++v) acc[t][v] = (acc[t][v] + small[t][v]) * kDown;
     uint32_t again = 0;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         bool bad = false;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) bad = bad || doubtful(acc[t][v], largest);
+        for (int v = 0; v < 16; ++v) bad = bad || doubtful(acc[t][v]);
         again |= (__ballot(bad) != 0) << t;  // (its stores below are overwritten by the same wave)
         const int c = 32 * t + l32;
         if (c < N)
@@ -231,7 +219,6 @@ __global__ __launch_bounds__(256, NT > 2 ? 2 : 3) void cbm_gemm_wide_kernel(int6
     constexpr int PER = (CK / 8) * BN / 256;  // columns of eight k that a thread stages per chunk
     static_assert((CK / 8) * BN % 256 == 0, "every thread stages the same number");
     __shared__ uintx4 stage[2][3][CK / 8][BN];
-    __shared__ float high[4];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int64_t row0 = (int64_t)blockIdx.x * 128 + 32 * wave;
@@ -244,7 +231,6 @@ __global__ __launch_bounds__(256, NT > 2 ? 2 : 3) void cbm_gemm_wide_kernel(int6
         for (int v = 0; v < 16; ++v) acc[t][v] = small[t][v] = 0.0f;
     uint32_t minus_low = 0xbf80u;
     asm("" : "+s"(minus_low));
-    float largest = 0.0f;
 
     auto load_b = [&](float (&x)[PER][8], int chunk) {
 #pragma unroll
@@ -259,9 +245,10 @@ __global__ __launch_bounds__(256, NT > 2 ? 2 : 3) void cbm_gemm_wide_kernel(int6
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int at = threadIdx.x + 256 * i;
+            float up[8];
 #pragma unroll
-            for (int j = 0; j < 8; j += 2) largest = fmaxf(largest, fmaxf(fabsf(x[i][j]), fabsf(x[i][j + 1])));
-            const Parts p = split8(x[i], minus_low);
+            for (int j = 0; j < 8; ++j) up[j] = x[i][j] * kUp;
+            const Parts p = split8(up, minus_low);
 #pragma unroll
             for (int q = 0; q < 3; ++q) stage[buf][q][at / BN][at % BN] = __builtin_bit_cast(uintx4, p.p[q]);
         }
@@ -292,8 +279,6 @@ __global__ __launch_bounds__(256, NT > 2 ? 2 : 3) void cbm_gemm_wide_kernel(int6
             constexpr int s = u / (NT / 2), first = u % (NT / 2) * 2;
             if (first == 0) {
                 cut_a(xa[s], c * CK + 16 * s + 8 * half, K);
-#pragma unroll
-                for (int j = 0; j < 8; j += 2) largest = fmaxf(largest, fmaxf(fabsf(xa[s][j]), fabsf(xa[s][j + 1])));
                 a = split8(xa[s], minus_low);
             }
             if (u + 1 < NT) read_b(u + 1);
@@ -314,21 +299,17 @@ __global__ __launch_bounds__(256, NT > 2 ? 2 : 3) void cbm_gemm_wide_kernel(int6
 #pragma unroll
             for (int j = 0; j < 8; ++j) xa[s][j] = na[s][j];
     }
-    largest = largest_of(largest);
-    if (lane == 0) high[wave] = largest;
-    __syncthreads();
-    largest = fmaxf(fmaxf(high[0], high[1]), fmaxf(high[2], high[3]));
     if (row0 >= M) return;
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[t][v] += small[t][v];
+        for (int v = 0; v < 16; ++v) acc[t][v] = (acc[t][v] + small[t][v]) * kDown;
     uint32_t again = 0;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         bool bad = false;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) bad = bad || doubtful(acc[t][v], largest);
+        for (int v = 0; v < 16; ++v) bad = bad || doubtful(acc[t][v]);
         again |= (__ballot(bad) != 0) << t;
         const int cc = col0 + 32 * t + l32;
         if (cc < N)

@@ -112,6 +112,28 @@ def test_values_that_have_no_parts(env, monkeypatch, form):
         assert np.linalg.norm(_product(env, A, B) - ref) <= 1e-6 * np.linalg.norm(ref), (a, b)
 
 
+@pytest.mark.parametrize("form", [1, 2, 3, 4])
+@pytest.mark.parametrize("a,b", [(1e-41, 1e37), (1e-41, 1e30), (1e-39, 1e10), (1e-39, 1.0), (1e10, 1e-40), (1e-22, 1e-22), (2.0 ** -149, 1.0)])
+def test_values_too_small_for_the_parts_are_not_lost(env, monkeypatch, form, a, b):
+    """Operands that are subnormal or nearly so, all of them or some: no sum may vanish.  A result keeps K roundings, and half of the
+    smallest fp32 value where it is subnormal itself."""
+    monkeypatch.setenv("CBM_GEMM_SPLIT", str(form))
+    rng = np.random.default_rng(form)
+    m, k, n = 70, 40, WIDTHS[form][-1]
+    A = (rng.integers(1, 9, (m, k)) * np.float64(a)).astype(np.float32)
+    B = (rng.integers(1, 9, (k, n)) * np.float64(b)).astype(np.float32)
+    A[3], B[:, 1] = 0.0, 0.0
+    A[5, 7:] = 0.0                      # one small value among zeros
+    ref = A.astype(np.float64) @ B.astype(np.float64)
+    got = _product(env, A, B)
+    assert np.all(np.abs(got - ref) <= (k + 6) * 2.0 ** -24 * np.abs(ref) + 2.0 ** -149)
+    assert np.all(got[3] == 0) and np.all(got[:, 1] == 0)
+    A[:, ::2] *= -1.0                   # either sign, beside ordinary rows
+    A[9] = 1e-3
+    ref, size = A.astype(np.float64) @ B.astype(np.float64), np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64)
+    assert np.all(np.abs(_product(env, A, B) - ref) <= (k + 6) * 2.0 ** -24 * size + 2.0 ** -149)
+
+
 @pytest.mark.parametrize("n", [16, 17, 47, 112, 130])
 def test_panel_kernel_on_any_b(env, monkeypatch, n):
     monkeypatch.setenv("CBM_GEMM_SPLIT", "0")
