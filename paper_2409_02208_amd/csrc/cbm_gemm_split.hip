@@ -72,7 +72,7 @@ __device__ __forceinline__ void load_a(float (&x)[8], const float* __restrict__ 
 // No bf16 value has bits below 2^-133, and the matrix cores take what is below 2^-126 for zero: operands are split at 2^24 times
 // their size, where the smallest fp32 value is 2^-125, and sums come back by 2^-48 (what is below 2^-126 then is below 2^-174 of
 // the result).  Values and sums that are not finite, or are not any more at that size (from 2^104 and 2^80), give sums that are not
-// finite: those are computed again by fused multiply-adds.  (Cheaper than to look for small values: with the largest operand kept
+// finite: those are computed again on the fp32 matrix cores.  (Cheaper than to look for small values: with the largest operand kept
 // beside the sums and small sums computed again, zeros could not be told from sums that had vanished, and 132534 x 256 . 256 x 256 took
 // 138 us against 128.)
 constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;
@@ -82,20 +82,43 @@ __device__ __forceinline__ void cut_a(float (&x)[8], int k0, int K) {
     for (int j = 0; j < 8; ++j) x[j] = k0 + j < K ? x[j] * kUp : 0.0f;
 }
 __device__ __forceinline__ bool doubtful(float v) { return !(fabsf(v) < INFINITY); }
-// rows row0 .. + 31, columns col0 .. + 31 of C
+// Rows row0 .. + 31, columns col0 .. + 31 of C on the fp32 matrix cores, for sums that the parts do not give.  Lane l has row, or
+// column, l % 32 and four k from 4 (l / 32) on of every eight.  (132534 x 256 . 256 x 256, 131 us with finite values: one infinity in B
+// 187 us, NaN all over A 444; 4,900 and 8,000 with a chain of multiply-adds per element.)
+template <bool VEC>
 __device__ __forceinline__ void plain_tile(int64_t M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                         int64_t ldc, int64_t row0, int col0) {
-    const int lane = threadIdx.x & 63;
-    const int c = col0 + (lane & 31);
+    const int lane = threadIdx.x & 63, half = lane >> 5, c = col0 + (lane & 31);
+    const float* a = A + min(row0 + (lane & 31), M - 1) * lda;
+    const float* b = B + min(c, N - 1);
+    floatx16 s;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] = 0.0f;
+    for (int k = 0; k < K; k += 8) {
+        const int k0 = k + 4 * half;
+        float x[4], y[4];
+        if constexpr (VEC) {
+            const floatx4 q = *reinterpret_cast<const floatx4*>(a + min(k0, K - 4));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = q[j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = a[min(k0 + j, K - 1)];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = b[(int64_t)min(k0 + j, K - 1) * ldb];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)  // (beyond K both are zero: what stands there may be infinite)
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(k0 + j < K ? x[j] : 0.0f, k0 + j < K ? y[j] : 0.0f, s, 0, 0, 0);
+    }
     if (c >= N) return;
-    for (int r = lane >> 5; r < 32; r += 2) {
-        if (row0 + r >= M) return;
-        const float* a = A + (row0 + r) * lda;
-        float s = 0.0f;
-        for (int k = 0; k < K; ++k) s = fmaf(a[k], B[(int64_t)k * ldb + c], s);
-        C[(row0 + r) * ldc + c] = s;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int64_t r = row0 + 8 * (v / 4) + 4 * half + v % 4;
+        if (r < M) C[r * ldc + c] = s[v];
     }
 }
+
 // Narrow C (up to 64 columns), for products that are short and deep: a workgroup has 32 rows of C, its four waves take the
 // steps of 16 k in turn and add their sums through LDS.  Both operands come straight from memory in operand layout (lane l:
 // row, or column, l % 32 and eight k from 8 (l / 32) on): B is small and stays in L2.  Loads run one step ahead (three:
@@ -195,7 +218,10 @@ __global__ __launch_bounds__(256, 3) void cbm_gemm_narrow_kernel(int64_t M, int 
         bool bad = false;
 #pragma unroll
         for (int v = 0; v < 16; ++v) bad = bad || doubtful(acc[t][v]);
-        again |= (__ballot(bad) != 0) << t;  // (its stores below are overwritten by the same wave)
+        if (__ballot(bad)) {
+            again |= 1u << t;
+            continue;
+        }
         const int c = 32 * t + l32;
         if (c < N)
 #pragma unroll
@@ -204,7 +230,7 @@ __global__ __launch_bounds__(256, 3) void cbm_gemm_narrow_kernel(int64_t M, int 
                 if (r < M) C[r * ldc + c] = acc[t][v];
             }
     }
-    for (; again; again &= again - 1) plain_tile(M, N, K, A, lda, B, ldb, C, ldc, row0, 32 * __builtin_ctz(again));
+    for (; again; again &= again - 1) plain_tile<VEC>(M, N, K, A, lda, B, ldb, C, ldc, row0, 32 * __builtin_ctz(again));
 }
 
 // Wider C: a workgroup of four waves has 128 rows by 32 NT columns.  B goes through LDS in chunks of 32 k, split as it is
@@ -310,7 +336,10 @@ __global__ __launch_bounds__(256, NT > 2 ? 2 : 3) void cbm_gemm_wide_kernel(int6
         bool bad = false;
 #pragma unroll
         for (int v = 0; v < 16; ++v) bad = bad || doubtful(acc[t][v]);
-        again |= (__ballot(bad) != 0) << t;
+        if (__ballot(bad)) {
+            again |= 1u << t;
+            continue;
+        }
         const int cc = col0 + 32 * t + l32;
         if (cc < N)
 #pragma unroll
@@ -319,7 +348,7 @@ __global__ __launch_bounds__(256, NT > 2 ? 2 : 3) void cbm_gemm_wide_kernel(int6
                 if (r < M) C[r * ldc + cc] = acc[t][v];
             }
     }
-    for (; again; again &= again - 1) plain_tile(M, N, K, A, lda, B, ldb, C, ldc, row0, col0 + 32 * __builtin_ctz(again));
+    for (; again; again &= again - 1) plain_tile<VEC>(M, N, K, A, lda, B, ldb, C, ldc, row0, col0 + 32 * __builtin_ctz(again));
 }
 
 struct Shape {

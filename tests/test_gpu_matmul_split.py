@@ -134,6 +134,33 @@ def test_values_too_small_for_the_parts_are_not_lost(env, monkeypatch, form, a, 
     assert np.all(np.abs(_product(env, A, B) - ref) <= (k + 6) * 2.0 ** -24 * size + 2.0 ** -149)
 
 
+@pytest.mark.parametrize("k,n", [(500, 64), (500, 7), (256, 256), (300, 96)])
+def test_values_that_are_not_finite_cost_little(env, k, n):
+    """Tiles computed again take the fp32 matrix cores: at most four times the product's time with NaN everywhere (measured), not the
+    40 to 120 times of a chain per element; the line is at 12 to leave room for noise."""
+    torch, cbm = env
+    A, B, C = torch.randn(20000, k, device="cuda"), torch.randn(k, n, device="cuda"), torch.empty(20000, n, device="cuda")
+
+    def best():
+        us = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                cbm.cbm_dense_matmul(A, B, C)
+            b.record()
+            torch.cuda.synchronize()
+            us.append(a.elapsed_time(b))
+        return min(us)
+
+    best()
+    clean = best()
+    B[3, 2] = float("inf")
+    assert best() <= 12 * clean
+    A.fill_(float("nan"))
+    assert best() <= 12 * clean
+
+
 @pytest.mark.parametrize("n", [16, 17, 47, 112, 130])
 def test_panel_kernel_on_any_b(env, monkeypatch, n):
     monkeypatch.setenv("CBM_GEMM_SPLIT", "0")
