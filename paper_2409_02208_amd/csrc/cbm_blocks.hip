@@ -30,10 +30,10 @@
 
 namespace {
 
-
 constexpr int WAVES = 4;  // waves per workgroup: they share a block's groups of columns
 constexpr int T = CBM_BLOCK_TILES;
 static_assert(T == WAVES, "wave s finishes tile s");
+constexpr float kUp = CBM_BLOCK_UP, kDown = 1.0f / CBM_BLOCK_UP;
 
 struct BlockMap {
     int64_t begin[CBM_XCD];
@@ -111,10 +111,8 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
 #pragma unroll
         for (int s = 0; s < T; ++s) a[s] = lut[(mask >> (8 * s)) & 255u];
         __builtin_amdgcn_sched_barrier(0);
-        if (WCOL) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) x[j] *= w.v[j / 4][j % 4];
-        }
+        for (int j = 0; j < 8; ++j) x[j] *= WCOL ? w.v[j / 4][j % 4] : kUp;  // (the weights come times kUp)
         uintx4 P[3];
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -219,7 +217,8 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
         for (int s = 2 * pair; s < 2 * pair + 2; ++s)
             if (wave == s) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) fin[v] = acc[s][v] + red[s & 1][0][v][lane] + red[s & 1][1][v][lane] + red[s & 1][2][v][lane];
+                for (int v = 0; v < 16; ++v)
+                    fin[v] = (acc[s][v] + red[s & 1][0][v][lane] + red[s & 1][1][v][lane] + red[s & 1][2][v][lane]) * kDown;
             }
     }
     auto store = [&](uint32_t row, float v) {
@@ -228,14 +227,15 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
         if (RELU) v = fmaxf(v, 0.0f);
         __builtin_nontemporal_store(v, Y + (int64_t)row * ldy + lcol);
     };
-    // Two kinds of sums do not come out of the matrix cores.  0 x infinity: a value that is not finite anywhere among the
-    // block's rows of X turns every sum of its column in this tile into NaN.  And the smaller parts of values below 2^-110 are
-    // subnormal in bf16, where the matrix cores take them for zero.  A tile with a sum that is not finite, or not zero and below
-    // 2^-96, is summed again by selection instead of multiplication (protein recipe,
+    // No bf16 value has bits below 2^-133, and the matrix cores take what is below 2^-126 for zero: x (times its weight) is split at
+    // 2^24 times its size, where the smallest 32-bit value is 2^-125, so nothing is lost and a sum of zero is zero.
+    // What does not come out of the matrix cores is 0 x infinity: a value that is not finite (or not any more at that size: from
+    // 2^104) anywhere among the block's rows of X turns every sum of its column in this tile into NaN.  A tile with a sum that is
+    // not finite is summed again by selection instead of multiplication (protein recipe,
     // k = 256: 0.38 ms; with one infinity in X 0.63, all of X NaN 5.1).
     bool plain = true;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) plain = plain && (fin[v] == 0.0f || (fabsf(fin[v]) < INFINITY && fabsf(fin[v]) >= 0x1p-96f));
+    for (int v = 0; v < 16; ++v) plain = plain && fabsf(fin[v]) < INFINITY;
     if (__ballot(!plain)) {
         float sum[16];  // lane l: rows 16 (l / 32) .. + 15 of the tile, column l % 32
 #pragma unroll
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
 #pragma unroll
             for (int j = 0; j < 8; ++j) x[j] = x_at(cols[at + j]);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) w[j] = WCOL ? wcols[at + j] : 1.0f;
+            for (int j = 0; j < 8; ++j) w[j] = WCOL ? wcols[at + j] * kDown : 1.0f;
             // byte of row r (in lanes r of one half): the columns that the row holds
             const uint32_t held = (masks[(size_t)(blk.group0 + i / 8) * 64 + 32 * (i & 1) + (lane & 31)][i / 2 % 4] >> (8 * wave)) & 255u;
 #pragma unroll

@@ -63,6 +63,7 @@ struct CbmBlock {
     uint32_t ngroups;  // groups of 64 columns: four steps of 16
 };
 constexpr uint32_t CBM_BLOCK_NO_ROW = 0xffffffffu;  // an empty place
+constexpr float CBM_BLOCK_UP = 16777216.0f;         // 2^24: rows of X are split at this size (cbm_blocks.hip says why)
 
 struct cbm_handle {
     int64_t m = 0, n = 0;
@@ -115,7 +116,7 @@ struct cbm_handle {
     CbmBlock* d_blocks = nullptr;
     uint32_t* d_block_rows = nullptr;
     uint32_t* d_block_cols = nullptr;
-    float* d_block_w = nullptr;  // column weight (d^-1/2) beside each of block_cols (handles built with self-loops)
+    float* d_block_w = nullptr;  // column weight (d^-1/2) times CBM_BLOCK_UP beside each of block_cols (handles built with self-loops)
     uint32_t* d_block_masks = nullptr;
     mutable float* d_scratch = nullptr;  // num_slots x scratch_k floats, sized on first use
     mutable int64_t scratch_k = 0;

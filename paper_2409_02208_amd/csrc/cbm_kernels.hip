@@ -753,7 +753,7 @@ cbm_status cbm_upload(cbm_handle* h) {
             return bs;
         if (h->square_self_loops) {
             std::vector<float> w(h->block_cols.size());
-            for (size_t i = 0; i < w.size(); ++i) w[i] = h->dinv[h->block_cols[i]];
+            for (size_t i = 0; i < w.size(); ++i) w[i] = h->dinv[h->block_cols[i]] * CBM_BLOCK_UP;
             if ((bs = up(&h->d_block_w, w)) != CBM_OK) return bs;
         }
         return CBM_OK;

@@ -159,6 +159,39 @@ def test_scale_of_the_values_does_not_matter(env, scale):
     assert _err(Y.cpu().numpy(), orc.spmm_csr(g.rowptr, g.colidx, X)) <= TOL
 
 
+@pytest.mark.parametrize("unit", [2.0 ** -149, 2.0 ** -130, 2.0 ** -112])
+def test_sums_of_the_smallest_values_are_exact(env, unit):
+    """Whole multiples of the smallest 32-bit value (and of values whose lower parts are that small): nothing rounds, so every sum is
+    exact, those of few small values and those that cancel to zero among them."""
+    torch, cbm = env
+    g = wl.make_graph("protein", n=1500, knn=30)
+    X = wl.integer_features(g.n, 33, 8) * np.float64(unit)
+    X[:, 5] = 0.0
+    X[::50, 6] *= 4096.0 + 1.0
+    X = X.astype(np.float32)
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx)
+    Y = torch.empty((g.n, 33), device="cuda")
+    Xd = torch.from_numpy(X).cuda()
+    assert _in_blocks(torch, cbm, h, Xd, Y)
+    ref = orc.spmm_csr(g.rowptr, g.colidx, X)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref) and np.any(ref)
+
+
+@pytest.mark.parametrize("scale", [1e-37, 1e-38, 1e-41])
+def test_weights_take_no_value_below_what_the_parts_hold(env, scale):
+    """x d^-1/2 is subnormal where x is not, or loses its last bits: the weighted sum over 300 columns is an ordinary value again."""
+    torch, cbm = env
+    g = wl.make_graph("protein", n=1500, knn=300)
+    X = (np.abs(wl.gaussian_features(g.n, 33, 8)).astype(np.float64) * scale).astype(np.float32)
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=True)
+    Y = torch.empty((g.n, 33), device="cuda")
+    cbm.cbm_spmm_normalized(h, torch.from_numpy(X).cuda(), Y)
+    torch.cuda.synchronize()
+    ref = orc.spmm_csr_normalized(g.rowptr, g.colidx, X)
+    d = np.abs(Y.cpu().numpy().astype(np.float64) - ref)
+    assert np.all(d <= 1e-6 * np.abs(ref) + 2.0 ** -149)  # (half a unit when the row weight makes a sum subnormal; w itself rounds by 2^-24)
+
+
 # ---- hub blocks: the popular columns of the split rows of a matrix without a tree ----
 def _popular(m, n, seed):
     """Rows of 150 to 700 entries among short ones, columns by a steep power law."""
@@ -196,6 +229,23 @@ def test_hub_blocks_sums_are_exact(env, hubs, m, n, k):
     assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref)
     cbm.cbm_spmm_mean(h, Xd, Y)
     assert _err(Y.cpu().numpy(), orc.spmm_csr_mean(rowptr, colidx, X)) <= TOL
+
+
+@pytest.mark.parametrize("unit", [2.0 ** -149, 2.0 ** -130])
+def test_hub_blocks_keep_the_smallest_values(env, hubs, unit):
+    torch, cbm = env
+    rowptr, colidx = _popular(700, 700, 4)
+    X = (wl.integer_features(700, 40, 3) * np.float64(unit)).astype(np.float32)
+    h = cbm.cbm_build(700, 700, rowptr, colidx)
+    Y = torch.empty((700, 40), device="cuda")
+    cbm.cbm_spmm(h, torch.from_numpy(X).cuda(), Y)
+    torch.cuda.synchronize()
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), orc.spmm_csr(rowptr, colidx, X))
+    hn = cbm.cbm_build(700, 700, rowptr, colidx, add_self_loops=True)
+    cbm.cbm_spmm_normalized(hn, torch.from_numpy(np.abs(X)).cuda(), Y)
+    ref = orc.spmm_csr_normalized(rowptr, colidx, np.abs(X))
+    # (a part of a row is rounded to the smallest value on its way through the scratch, as the gather kernels round theirs)
+    assert np.all(np.abs(Y.cpu().numpy().astype(np.float64) - ref) <= 1e-6 * np.abs(ref) + 32 * 2.0 ** -149)
 
 
 @pytest.mark.parametrize("k", [16, 47, 130])
