@@ -278,6 +278,8 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
     }
 }
 
+constexpr int kMostSlabs = 65535;  // a grid's second dimension: wider X (from 2,097,120 columns) takes several launches
+
 struct Args {
     const cbm_handle* h;
     const float* X;
@@ -299,10 +301,13 @@ void launch(const Args& a) {
         map.count[j] = a.h->blk_count[j];
         most = std::max(most, map.count[j]);
     }
-    const dim3 grid((unsigned)(CBM_XCD * most), (unsigned)((a.k + 31) / 32));
-    hipLaunchKernelGGL((cbm_block_kernel<MODE, BIG>), grid, dim3(64 * WAVES), 0, a.stream, a.h->d_blocks, map, a.h->d_block_rows,
-                       a.h->d_block_cols, a.h->d_block_w, reinterpret_cast<const uintx4*>(a.h->d_block_masks), a.X, a.ldx * 4, a.Y,
-                       a.ldy, a.rw, a.self_w, a.k);
+    for (int c = 0; c < a.k; c += kMostSlabs * 32) {
+        const int k = std::min(a.k - c, kMostSlabs * 32);
+        hipLaunchKernelGGL((cbm_block_kernel<MODE, BIG>), dim3((unsigned)(CBM_XCD * most), (unsigned)((k + 31) / 32)), dim3(64 * WAVES), 0, a.stream,
+                           a.h->d_blocks, map, a.h->d_block_rows, a.h->d_block_cols, a.h->d_block_w,
+                           reinterpret_cast<const uintx4*>(a.h->d_block_masks), a.X + c, a.ldx * 4, a.Y + c, a.ldy, a.rw, a.self_w, k);
+        if (a.k - c <= kMostSlabs * 32) break;  // (the next c may not be an int)
+    }
 }
 template <bool BIG>
 void launch_mode(const Args& a, int mode) {

@@ -159,6 +159,21 @@ def test_scale_of_the_values_does_not_matter(env, scale):
     assert _err(Y.cpu().numpy(), orc.spmm_csr(g.rowptr, g.colidx, X)) <= TOL
 
 
+def test_more_columns_than_a_grid_has_slabs(env):
+    """65,535 slabs of 32 columns and a few more: the gather kernels take them in one launch of 128 or 256 columns a block."""
+    torch, cbm = env
+    n, k = 5, 65535 * 32 + 37
+    rowptr, colidx = np.array([0, 2, 2, 5, 6, 8]), np.array([0, 3, 1, 2, 4, 4, 0, 1], dtype=np.int32)
+    X = torch.randint(-8, 9, (n, k), device="cuda").float()
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    h = cbm.cbm_build(n, n, rowptr, colidx)
+    cbm.cbm_spmm(h, X, Y)
+    for i in range(n):
+        assert torch.equal(Y[i], X[torch.from_numpy(colidx[rowptr[i]:rowptr[i + 1]]).cuda().long()].sum(0)), i
+    cbm.cbm_spmm_gin(h, 1.0, X, Y)
+    assert torch.equal(Y[0], X[0] + X[3] + 2 * X[0])
+
+
 @pytest.mark.parametrize("unit", [2.0 ** -149, 2.0 ** -130, 2.0 ** -112])
 def test_sums_of_the_smallest_values_are_exact(env, unit):
     """Whole multiples of the smallest 32-bit value (and of values whose lower parts are that small): nothing rounds, so every sum is
