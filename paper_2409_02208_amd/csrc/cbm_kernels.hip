@@ -1044,16 +1044,18 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         ProfScope ps(h, stream, rec);
         cbm_launch_hub_blocks(h, X, ldx, k, scratch, ld_scratch, wcol, stream_);
     }
-    if (h->num_slots > 0 && h->seg_deltas > 0) {
+    int64_t segments = 0;  // (not num_slots: hub blocks write scratch rows too)
+    for (int64_t c : h->seg_count) segments += c;
+    if (segments > 0) {
         cbm_launch_record rec{};
         rec.kind = 1;
         rec.per_xcd = 1;
-        rec.tasks = h->num_slots;
+        rec.tasks = segments;
         rec.deltas = h->seg_deltas;
         // the method's bytes only: the partial sums of split rows are this implementation's overhead
         rec.algorithmic_bytes = h->seg_deltas * per_delta;
         ProfScope ps(h, stream, rec);
-        (many(h->num_slots, h->seg_deltas, h->seg_longest) ? var.segments_many : var.segments)(ctx, CbmLevel{});
+        (many(segments, h->seg_deltas, h->seg_longest) ? var.segments_many : var.segments)(ctx, CbmLevel{});
     }
     for (size_t l = 0; l < h->levels.size(); ++l) {
         const CbmLevel& L = h->levels[l];

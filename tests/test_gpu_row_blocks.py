@@ -286,6 +286,20 @@ def test_hub_blocks_normalised_and_transposed(env, hubs, k):
     assert _err(Y.cpu().numpy(), both) <= TOL
 
 
+def test_hub_blocks_launch_records_count_work_items(env, hubs):
+    """Scratch rows that the blocks write are no work items of the segment launch (its full-occupancy rule goes by them too)."""
+    torch, cbm = env
+    rowptr, colidx = _popular(1500, 1500, 4)
+    h = cbm.cbm_build(1500, 1500, rowptr, colidx)
+    X, Y = torch.ones((1500, 32), device="cuda"), torch.empty((1500, 32), device="cuda")
+    cbm.cbm_profile_enable(h, True)
+    cbm.cbm_spmm(h, X, Y)
+    torch.cuda.synchronize()
+    records = cbm.cbm_profile_read(h)
+    assert {1, 5} <= {r["kind"] for r in records}
+    assert sum(r["tasks"] for r in records if r["kind"] in (0, 1)) == cbm.cbm_stats(h)["num_tasks"]
+
+
 def _with_self(rowptr, colidx):
     rows = [np.union1d(colidx[rowptr[i]:rowptr[i + 1]], [i]) for i in range(len(rowptr) - 1)]
     rp = np.zeros(len(rowptr), dtype=np.int64)
