@@ -16,7 +16,9 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <functional>
+#include <mutex>
 #include <queue>
 #include <thread>
 
@@ -81,6 +83,38 @@ long env_or(const char* name, long dflt) {
 // a tuning knob from the environment, held to the range the work lists can encode
 long env_clamped(const char* name, long dflt, long lo, long hi) { return std::min(hi, std::max(lo, env_or(name, dflt))); }
 
+// fn(t) for every t < n, each in a thread of its own (n = 1: in the caller's).  What one of them throws is thrown here once all
+// have ended: out of a thread it would end the process.
+template <class F>
+void run_threads(int n, F&& fn) {
+    if (n <= 1) {
+        fn(0);
+        return;
+    }
+    std::exception_ptr error;
+    std::mutex held;
+    auto keep = [&] {
+        std::lock_guard<std::mutex> lock(held);
+        if (!error) error = std::current_exception();
+    };
+    std::vector<std::thread> pool;
+    pool.reserve(n);
+    try {
+        for (int t = 0; t < n; ++t)
+            pool.emplace_back([&, t] {
+                try {
+                    fn(t);
+                } catch (...) {
+                    keep();
+                }
+            });
+    } catch (...) {  // (no more threads to be had)
+        keep();
+    }
+    for (auto& th : pool) th.join();
+    if (error) std::rethrow_exception(error);
+}
+
 template <class F>
 void parallel_chunks(int nthreads, int64_t total, int64_t chunk, F&& fn) {
     if (total <= 0) return;
@@ -92,15 +126,7 @@ void parallel_chunks(int nthreads, int64_t total, int64_t chunk, F&& fn) {
             fn(b, std::min(total, b + chunk), tid);
         }
     };
-    int nt = (int)std::max<int64_t>(1, std::min<int64_t>(nthreads, (total + chunk - 1) / chunk));
-    if (nt == 1) {
-        worker(0);
-        return;
-    }
-    std::vector<std::thread> pool;
-    pool.reserve(nt);
-    for (int t = 0; t < nt; ++t) pool.emplace_back(worker, t);
-    for (auto& th : pool) th.join();
+    run_threads((int)std::max<int64_t>(1, std::min<int64_t>(nthreads, (total + chunk - 1) / chunk)), worker);
 }
 
 // |a n b| for two sorted lists; binary search when one is much longer.
@@ -145,16 +171,7 @@ void transpose_pattern(int nthreads, int64_t m, int64_t n, const int64_t* rowptr
     rb[0] = 0;
     for (int t = 1; t < nt; ++t) rb[t] = std::lower_bound(rowptr, rowptr + m + 1, nz * t / nt) - rowptr;
     std::vector<std::vector<uint32_t>> off(nt);
-    auto run = [&](auto&& fn) {
-        if (nt == 1) {
-            fn(0);
-            return;
-        }
-        std::vector<std::thread> pool;
-        for (int t = 0; t < nt; ++t) pool.emplace_back(fn, t);
-        for (auto& th : pool) th.join();
-    };
-    run([&](int t) {
+    run_threads(nt, [&](int t) {
         off[t].assign(n, 0);
         for (int64_t p = rowptr[rb[t]]; p < rowptr[rb[t + 1]]; ++p) ++off[t][colidx[p]];
     });
@@ -167,7 +184,7 @@ void transpose_pattern(int nthreads, int64_t m, int64_t n, const int64_t* rowptr
         }
         tptr[j + 1] = at;
     }
-    run([&](int t) {
+    run_threads(nt, [&](int t) {
         for (int64_t i = rb[t]; i < rb[t + 1]; ++i)
             for (int64_t p = rowptr[i]; p < rowptr[i + 1]; ++p) trow[off[t][colidx[p]]++] = (int32_t)i;
     });
@@ -1778,15 +1795,11 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
             grown.push_back({forced_seeds >= 0 ? forced_seeds : seeds, {}, {}, {}});
             if (forced_seeds >= 0 || m < 1024) break;
         }
-        {
-            std::vector<std::thread> pool;
-            for (size_t i = 1; i < grown.size() && B.nthreads > 1; ++i)
-                pool.emplace_back([&, i] { B.prim(grown[i].seeds, grown[i].parent, grown[i].level, grown[i].dptr); });
-            B.prim(grown[0].seeds, grown[0].parent, grown[0].level, grown[0].dptr);
-            for (auto& th : pool) th.join();
-            for (size_t i = 1; i < grown.size() && B.nthreads <= 1; ++i)
-                B.prim(grown[i].seeds, grown[i].parent, grown[i].level, grown[i].dptr);
-        }
+        auto grow = [&](size_t i) { B.prim(grown[i].seeds, grown[i].parent, grown[i].level, grown[i].dptr); };
+        if (B.nthreads > 1)
+            run_threads((int)grown.size(), [&](int i) { grow((size_t)i); });
+        else
+            for (size_t i = 0; i < grown.size(); ++i) grow(i);
         size_t best_tree = 0;
         for (size_t gi = 0; gi < grown.size(); ++gi) {
             const int64_t seeds = grown[gi].seeds;

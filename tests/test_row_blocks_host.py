@@ -12,18 +12,33 @@ import workloads as wl
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
-def test_blocks_decode_to_the_matrix(tmp_path):
-    exe = str(tmp_path / "host_blocks")
+def _harness(tmp_path, source, *flags):
+    """The host builder with a main of its own, compiled and run; what it printed."""
+    exe = str(tmp_path / "harness")
     csrc = os.path.join(ROOT, "paper_2409_02208_amd", "csrc")
-    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-I", os.path.join(ROOT, "include"),
-           "-I", csrc, os.path.join(ROOT, "tests", "host_blocks_main.cpp"), os.path.join(csrc, "cbm_builder.cpp"), "-o", exe, "-lpthread"]
+    cmd = ["g++", "-std=c++17", "-O1", "-g", *flags, "-I", os.path.join(ROOT, "include"),
+           "-I", csrc, os.path.join(ROOT, "tests", source), os.path.join(csrc, "cbm_builder.cpp"), "-o", exe, "-lpthread"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0 and "sanitize" in r.stderr:
         pytest.skip("sanitizer runtime not available: " + r.stderr[-200:])
     assert r.returncode == 0, r.stderr[-2000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
-    assert r.returncode == 0 and "blocks ok" in r.stdout and "hubs ok" in r.stdout, (r.stdout[-500:], r.stderr[-3000:])
+    assert r.returncode == 0, (r.returncode, r.stdout[-500:], r.stderr[-3000:])
+    return r.stdout
+
+
+SANITIZED = ("-fsanitize=address,undefined", "-fno-sanitize-recover=all")
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_blocks_decode_to_the_matrix(tmp_path):
+    out = _harness(tmp_path, "host_blocks_main.cpp", *SANITIZED)
+    assert "blocks ok" in out and "hubs ok" in out
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_out_of_memory_in_a_thread_reaches_the_caller(tmp_path):
+    assert "allocations ok" in _harness(tmp_path, "host_alloc_main.cpp")
 
 
 def test_blocks_leave_tree_and_counters_alone(monkeypatch):
