@@ -129,6 +129,11 @@ void parallel_chunks(int nthreads, int64_t total, int64_t chunk, F&& fn) {
     run_threads((int)std::max<int64_t>(1, std::min<int64_t>(nthreads, (total + chunk - 1) / chunk)), worker);
 }
 
+// Threads that may each hold a table of n 32-bit entries: at most 1 GiB of them together.
+int table_threads(int nthreads, int64_t n) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(nthreads, ((int64_t)1 << 28) / std::max<int64_t>(1, n)));
+}
+
 // |a n b| for two sorted lists; binary search when one is much longer.
 int64_t intersect_size(const int32_t* a, int64_t na, const int32_t* b, int64_t nb) {
     if (na > nb) {
@@ -165,8 +170,7 @@ void transpose_pattern(int nthreads, int64_t m, int64_t n, const int64_t* rowptr
     const int64_t nz = rowptr[m];
     tptr.assign(n + 1, 0);
     trow.resize(nz);
-    int nt = nz < (1 << 20) ? 1 : std::max(1, std::min(nthreads, 64));
-    while (nt > 1 && (int64_t)nt * n * 4 > ((int64_t)1 << 30)) --nt;  // at most 1 GiB of per-block offsets
+    const int nt = nz < (1 << 20) ? 1 : table_threads(std::min(nthreads, 64), n);
     std::vector<int64_t> rb(nt + 1, m);
     rb[0] = 0;
     for (int t = 1; t < nt; ++t) rb[t] = std::lower_bound(rowptr, rowptr + m + 1, nz * t / nt) - rowptr;
@@ -1257,8 +1261,8 @@ int64_t Builder::count_slots() const {
     const int phases = (int)env_clamped("CBM_PHASES", kPhasesDefault, 1, 64);
     const int64_t fine_min = env_clamped("CBM_FINE_MIN", kFineMinDefault, 1, (long)CBM_TASK_LEN_MASK);
     const int P = CBM_XCD * phases;
-    std::vector<std::vector<int32_t>> part((size_t)nthreads);
-    parallel_chunks(nthreads, m, 4096, [&](int64_t b, int64_t e, int th) {
+    std::vector<std::vector<int32_t>> part((size_t)table_threads(nthreads, n));
+    parallel_chunks((int)part.size(), m, 4096, [&](int64_t b, int64_t e, int th) {
         if (part[th].empty()) part[th].assign((size_t)n, 0);
         for (int64_t x = b; x < e; ++x)
             if (is_split(x))
@@ -1315,8 +1319,8 @@ void Builder::hub_blocks(bool force) {
     // the same rows of X
     std::vector<int32_t> held((size_t)n, 0);
     {
-        std::vector<std::vector<int32_t>> part((size_t)nthreads);
-        parallel_chunks(nthreads, (int64_t)rows.size(), 256, [&](int64_t b, int64_t e, int th) {
+        std::vector<std::vector<int32_t>> part((size_t)table_threads(nthreads, n));
+        parallel_chunks((int)part.size(), (int64_t)rows.size(), 256, [&](int64_t b, int64_t e, int th) {
             if (part[th].empty()) part[th].assign((size_t)n, 0);
             for (int64_t r = b; r < e; ++r)
                 for (int64_t i = h->dptr[rows[r]]; i < h->dptr[rows[r] + 1]; ++i) ++part[th][h->dcol[i]];
@@ -1332,9 +1336,9 @@ void Builder::hub_blocks(bool force) {
     };
     std::vector<Built> built((size_t)nb);
     rests.resize(rows.size());
-    std::vector<std::vector<int32_t>> local((size_t)nthreads);
+    std::vector<std::vector<int32_t>> local((size_t)table_threads(nthreads, n));
     std::atomic<int64_t> taken{0};
-    parallel_chunks(nthreads, nb, 1, [&](int64_t b0, int64_t b1, int th) {
+    parallel_chunks((int)local.size(), nb, 1, [&](int64_t b0, int64_t b1, int th) {
         std::vector<int32_t>& count = local[th];  // column -> how many rows of the block hold it, then its place (negative)
         if (count.empty()) count.assign((size_t)n, 0);
         std::vector<uint32_t> cols;
@@ -1372,6 +1376,7 @@ void Builder::hub_blocks(bool force) {
             taken += mine;
         }
     });
+    std::vector<std::vector<int32_t>>().swap(local);
     static_assert(T == 4, "a mask word has a byte per tile");
     size_t groups = 0;
     for (const Built& x : built) groups += x.cols.size() / 64;
@@ -1491,8 +1496,8 @@ void Builder::row_blocks() {
     };
     std::vector<Built> built((size_t)nb);
     h->block_rows.assign((size_t)nb * per, CBM_BLOCK_NO_ROW);
-    std::vector<std::vector<int32_t>> local((size_t)nthreads);
-    parallel_chunks(nthreads, nb, 4, [&](int64_t b0, int64_t b1, int th) {
+    std::vector<std::vector<int32_t>> local((size_t)table_threads(nthreads, n));
+    parallel_chunks((int)local.size(), nb, 4, [&](int64_t b0, int64_t b1, int th) {
         std::vector<int32_t>& place = local[th];  // column -> its place among the block's columns
         if (place.empty()) place.assign((size_t)n, -1);
         std::vector<int32_t> cols, by;
