@@ -86,14 +86,16 @@ typedef enum {
  *                matrix of 65536 rows or more the candidate search first looks
  *                at every 64th row: if their best candidates would save under
  *                2 % of their entries, the search stops there and every row is
- *                stored in full.  On a
- *                square matrix of 512 rows or more whose neighbouring rows share most of
- *                their columns the same model may let the products run in row blocks:
- *                one walk over the columns of 128 alike rows, on the matrix cores, in
- *                one launch; the tree and all counters stay what they are.  Where every
- *                row is stored in full, rows long enough to be split share their popular
- *                columns in such blocks too (num_tasks and bytes_cbm count what is left
- *                of them, and the blocks' arrays).  The
+ *                stored in full.  On a square matrix of 512 rows or more whose
+ *                neighbouring rows share most of their columns the same model may
+ *                let the products run in row blocks: one walk over the columns of
+ *                128 alike rows, on the matrix cores, in one launch.  The tree and
+ *                its counters stay what they are; the device then holds the blocks
+ *                only, and bytes_cbm counts them.  Where every row is stored in
+ *                full, rows long enough to be split share their popular columns in
+ *                such blocks too (num_tasks and bytes_cbm count what is left of
+ *                them, bytes_cbm also the blocks).  A host-only handle has no
+ *                blocks: num_tasks and bytes_cbm are those of the paths.  The
  *                tree is cut into vertical paths, one work item each;
  *                dependent kernel launches per product = rounds of paths
  *                (cbm_stats), at most the depth.  Any value yields a valid CBM
@@ -144,7 +146,8 @@ typedef struct {
     int64_t num_tasks;       /* GPU work items (rows, plus segments of split rows)   */
     int64_t num_split_rows;  /* rows whose delta list is cut into several segments   */
     int64_t bytes_csr;       /* int64 row offsets + int32 columns, no values         */
-    int64_t bytes_cbm;       /* packed device arrays of this handle                  */
+    int64_t bytes_cbm;       /* packed device arrays of this handle (host-only: the
+                                arrays that it would upload without blocks)           */
     int32_t depth;           /* number of tree levels                                */
     int32_t alpha;
     int32_t add_self_loops;

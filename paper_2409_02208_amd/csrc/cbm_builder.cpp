@@ -1965,11 +1965,13 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     s.num_internal = (int64_t)h->internal_rows.size();
     s.num_tasks = (int64_t)h->tasks.size();
     s.bytes_csr = 8 * (m + 1) + 4 * in_rowptr[m];
-    s.bytes_cbm = 4 * (int64_t)h->stream.size() + (int64_t)sizeof(CbmTask) * (int64_t)(h->tasks.size() + h->comb.size()) +
-                  4 * (int64_t)h->internal_rows.size() + 4 * (int64_t)h->dinv.size();
-    if (h->hub_blocks)
-        s.bytes_cbm += 4 * (int64_t)(h->block_rows.size() + h->block_cols.size() + h->block_masks.size()) +
-                       (int64_t)sizeof(CbmBlock) * (int64_t)h->row_blocks.size();
+    // (a host-only handle counts its work lists; row blocks are all that a device handle with them uploads)
+    const int64_t block_bytes = 4 * (int64_t)(h->block_rows.size() + h->block_cols.size() + h->block_masks.size()) +
+                                (int64_t)sizeof(CbmBlock) * (int64_t)h->row_blocks.size();
+    const bool blocks_only = h->in_row_blocks() && !(o.flags & CBM_FLAG_HOST_ONLY);
+    s.bytes_cbm = 4 * (int64_t)h->dinv.size() + (blocks_only || h->hub_blocks ? block_bytes : 0);
+    if (!blocks_only)
+        s.bytes_cbm += 4 * (int64_t)(h->stream.size() + h->internal_rows.size()) + (int64_t)sizeof(CbmTask) * (int64_t)(h->tasks.size() + h->comb.size());
     s.depth = depth;
     s.rounds = nrounds;
     s.alpha = B.alpha;

@@ -131,6 +131,9 @@ struct cbm_handle {
     bool profiling = false;
     mutable std::vector<cbm_launch_record> prof_records;
     mutable std::vector<void*> prof_events;  // hipEvent_t pairs
+
+    // every product is one launch over row blocks: the work items above are never launched (and stay on the host)
+    bool in_row_blocks() const { return !row_blocks.empty() && !hub_blocks; }
 };
 
 // Detail text of the most recent failure on this thread (which HIP call, which error).

@@ -758,16 +758,22 @@ cbm_status cbm_upload(cbm_handle* h) {
         }
         return CBM_OK;
     };
+    auto up_paths = [&]() -> cbm_status {
+        if (h->in_row_blocks()) return CBM_OK;
+        cbm_status ps = CBM_OK;
+        if ((ps = up(&h->d_tasks, h->tasks)) != CBM_OK || (ps = up(&h->d_comb, h->comb)) != CBM_OK ||
+            (ps = up(&h->d_stream, h->stream)) != CBM_OK || (ps = up(&h->d_internal, h->internal_rows)) != CBM_OK)
+            return ps;
+        return CBM_OK;
+    };
     cbm_status st = CBM_OK;
-    if ((st = up(&h->d_tasks, h->tasks)) != CBM_OK || (st = up(&h->d_comb, h->comb)) != CBM_OK ||
-        (st = up(&h->d_stream, h->stream)) != CBM_OK || (st = up(&h->d_dinv, h->dinv)) != CBM_OK ||
-        (st = up(&h->d_rinv, h->rinv)) != CBM_OK ||
-        (st = up(&h->d_internal, h->internal_rows)) != CBM_OK || (st = up_blocks()) != CBM_OK) {
+    if ((st = up_paths()) != CBM_OK || (st = up(&h->d_dinv, h->dinv)) != CBM_OK || (st = up(&h->d_rinv, h->rinv)) != CBM_OK ||
+        (st = up_blocks()) != CBM_OK) {
         cbm_release_device(h);
         if (cur != dev) hipSetDevice(cur);
         return st;
     }
-    if (h->square_self_loops && !h->stream.empty()) {
+    if (h->square_self_loops && h->d_stream && !h->stream.empty()) {
         const int64_t nent = (int64_t)h->stream.size();
         hipError_t e = hipMalloc((void**)&h->d_wstream, nent * sizeof(float));
         if (e == hipSuccess) {
@@ -842,7 +848,7 @@ cbm_status cbm_reserve_scratch(const cbm_handle* h, int32_t k) {
         }
         return cbm_reserve_scratch(h->inner, k);
     }
-    if (h->num_slots <= 0 || h->scratch_k >= ld_scratch) return CBM_OK;
+    if (h->num_slots <= 0 || h->in_row_blocks() || h->scratch_k >= ld_scratch) return CBM_OK;
     // hipFree waits for the device: no product enqueued earlier is still reading the old array when it goes
     if (h->d_scratch) hipFree(h->d_scratch);
     h->d_scratch = nullptr;
@@ -949,7 +955,7 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
     }
 
     // row blocks need no scratch; the limits of the static one are those of the paths all the same
-    const bool in_blocks = !h->row_blocks.empty() && !h->hub_blocks;
+    const bool in_blocks = h->in_row_blocks();
     const int64_t ld_scratch = ((int64_t)k + 3) & ~(int64_t)3;
     float* scratch = nullptr;
     if (static_scratch) {
@@ -976,7 +982,7 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
                 return CBM_OK;
             }
         }
-    } else if (!in_blocks) {
+    } else {
         // scratch rows for split rows: sized by cbm_reserve, else for this k on first use
         if (const cbm_status st = cbm_reserve_scratch(h, k); st != CBM_OK) return st;
         scratch = h->d_scratch;

@@ -159,6 +159,34 @@ def test_scale_of_the_values_does_not_matter(env, scale):
     assert _err(Y.cpu().numpy(), orc.spmm_csr(g.rowptr, g.colidx, X)) <= TOL
 
 
+def test_handles_in_row_blocks_hold_and_count_the_blocks_only(env, monkeypatch):
+    """The paths' arrays stay on the host, no scratch is sized for split rows that nothing launches, and bytes_cbm counts the blocks."""
+    torch, cbm = env
+    monkeypatch.setenv("CBM_SPLIT_MIN", "16")
+    g = wl.make_graph("protein", n=6000, knn=80)
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=True)
+    stats = cbm.cbm_stats(h)
+    assert stats["num_split_rows"] > 100
+    X, Y = torch.ones((g.n, 32), device="cuda"), torch.empty((g.n, 32), device="cuda")
+    cbm.cbm_profile_enable(h, True)
+    cbm.cbm_spmm_normalized(h, X, Y)
+    torch.cuda.synchronize()
+    (r,) = cbm.cbm_profile_read(h)
+    cbm.cbm_profile_enable(h, False)
+    assert r["kind"] == 5
+    # a block: its place and 128 rows; a column: its number and a bit for each of 128 rows
+    assert stats["bytes_cbm"] == r["tasks"] * (12 + 4 * 128) + r["deltas"] * (4 + 16) + 4 * g.n
+    free = torch.cuda.mem_get_info()[0]
+    cbm.cbm_reserve(h, 65536)   # 100 split rows in 8 segments each would take 200 MB
+    assert free - torch.cuda.mem_get_info()[0] < 16 << 20
+    W = torch.eye(32, device="cuda")
+    out, ws = torch.empty_like(Y), torch.empty(cbm.cbm_gcn2_workspace_bytes(h, 32, 32, 32), dtype=torch.uint8, device="cuda")
+    cbm.cbm_gcn2_forward(h, X, W, W, out, ws)
+    Xh = X.cpu().numpy()
+    ref = orc.gcn2(g.rowptr, g.colidx, Xh, np.eye(32, dtype=np.float32), np.eye(32, dtype=np.float32))
+    assert _err(out.cpu().numpy(), ref) <= TOL
+
+
 def test_more_columns_than_a_grid_has_slabs(env):
     """65,535 slabs of 32 columns and a few more: the gather kernels take them in one launch of 128 or 256 columns a block."""
     torch, cbm = env
