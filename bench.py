@@ -300,6 +300,19 @@ def compulsory_bytes(stats, k, normalized):
     return 4 * k * (stats["n"] + stats["m"]) + (nd + stats["m"]) * (8 if normalized else 4)
 
 
+def method_figures(stats, k, normalized, agg, nprof):
+    """(bytes the method moves, rows of X it gathers, bytes HBM must move at least) of one product.  Where launches over row or hub
+    blocks do the work, the tree's deltas are not what is gathered: the launch records say what is, and a column of a block is
+    read with its bit in each of 128 rows (16 bytes) beside its number and weight."""
+    if not any(kind == 5 for kind in agg):
+        return (algorithmic_bytes(stats, k, normalized), stats["num_delta_plus"] + stats["num_delta_minus"],
+                compulsory_bytes(stats, k, normalized))
+    entry = 8 if normalized else 4
+    gathered = {kind: a["deltas"] / nprof for kind, a in agg.items()}
+    stream = sum(d * (entry + (16 if kind == 5 else 0)) for kind, d in gathered.items()) + stats["m"] * entry
+    return sum(a["bytes"] for a in agg.values()) / nprof, sum(gathered.values()), 4 * k * (stats["n"] + stats["m"]) + stream
+
+
 def profile_product(torch, cbm, h, fn, steps):
     """Per-launch HIP-event timing inside the library (events on the stream the kernels run on), summed per kind."""
     cbm.cbm_profile_enable(h, True)
@@ -401,23 +414,22 @@ def bench_product(torch, cbm, orc, g, h, hc, Xh, k, steps, warmup, workload, cou
     step = lambda: cbm.cbm_spmm_normalized(h, X, Y)  # noqa: E731
     ms = time_steps(torch, step, steps, warmup)
     ms_median = float(np.median(per_step_ms(torch, step, steps)))
-    b_alg = algorithmic_bytes(st, k, True)
-    b_min = compulsory_bytes(st, k, True)
     nprof = max(1, min(steps, profile_steps))
     agg, ms_prof = profile_product(torch, cbm, h, step, nprof)
+    b_alg, gathered, b_min = method_figures(st, k, True, agg, nprof)
     launches = launch_table(agg, nprof, counted)
     hbm_total = sum(l["hbm_bytes"] for l in launches) if launches and all("hbm_bytes" in l for l in launches) else None
     log(f"{workload} k={k}: cbm_spmm_normalized {ms:.4f} ms/step; algorithmic {b_alg / ms / 1e6:.0f} GB/s"
         + (f", HBM side {hbm_total / ms / 1e6:.0f} GB/s ({hbm_total / 1e9:.2f} GB)" if hbm_total else ""))
 
-    # dominant kernel = cbm_level_kernel; its dominant launch = the kind that takes the most time
-    lv = [l for l in launches if l["kind"] in (0, 1)]
+    # the dominant launch = the kind that takes the most time
+    lv = [l for l in launches if l["kind"] in (0, 1, 5)]
     dom = max(lv, key=lambda l: l["ms"]) if lv else None
     roofline = None
     if dom is not None:
         per = dom["launches_per_product"]
         avg_ms = dom["ms"] / per
-        roofline = dict(bound="hbm", kernel="cbm_level_kernel", launch=dom["launch"], peak=HBM_PEAK_GBS, unit="GB/s",
+        roofline = dict(bound="hbm", kernel="cbm_block_kernel" if dom["kind"] == 5 else "cbm_level_kernel", launch=dom["launch"], peak=HBM_PEAK_GBS, unit="GB/s",
                         avg_launch_ms=avg_ms, launches_per_step=per,
                         algorithmic_bytes_per_launch=dom["algorithmic_bytes"] / per, algorithmic_GBps=dom["algorithmic_GBps"],
                         share_of_step_ms=dom["ms"] / ms_prof if ms_prof > 0 else None)
@@ -461,7 +473,7 @@ def bench_product(torch, cbm, orc, g, h, hc, Xh, k, steps, warmup, workload, cou
                 hbm_over_compulsory=None if hbm_total is None else hbm_total / b_min,
                 launches=launches, roofline=roofline, parity_err=err, rows_checked=len(rows),
                 gpu_csr=gpu_csr, speedup=None if ms_csr is None else ms_csr / ms,
-                edges_k_per_s=st["nnz"] * k / ms * 1e3, deltas_k_per_s=nd * k / ms * 1e3,
+                edges_k_per_s=st["nnz"] * k / ms * 1e3, deltas_k_per_s=gathered * k / ms * 1e3,
                 deltas_over_nnz=nd / max(1, st["nnz"]), depth=st["depth"], rounds=st["rounds"], roots=st["num_roots"],
                 build_seconds=st["build_seconds"], stats=st)
 

@@ -51,3 +51,17 @@ def test_blocks_leave_tree_and_counters_alone(monkeypatch):
     assert {k: v for k, v in a.items() if k != "build_seconds"} == {k: v for k, v in b.items() if k != "build_seconds"}
     for x, y in zip(cbm.cbm_get_tree(handles[0]).values(), cbm.cbm_get_tree(handles[1]).values()):
         assert np.array_equal(x, y)
+
+
+def test_bench_figures_are_of_what_runs():
+    """With launches over blocks the bytes and gathered rows are those of the launch records, not of the tree's deltas."""
+    import bench
+
+    stats = dict(m=100, n=100, num_delta_plus=5000, num_delta_minus=1000, num_roots=20)
+    k = 32
+    paths = {0: dict(deltas=12000, bytes=0), 2: dict(deltas=0, bytes=0)}
+    assert bench.method_figures(stats, k, True, paths, 2) == (bench.algorithmic_bytes(stats, k, True), 6000, bench.compulsory_bytes(stats, k, True))
+    blocks = {5: dict(deltas=1280, bytes=2000000)}   # two products
+    assert bench.method_figures(stats, k, True, blocks, 2) == (1000000, 640, 4 * k * 200 + 640 * 24 + 100 * 8)
+    hubs = {5: dict(deltas=1280, bytes=200000), 1: dict(deltas=400, bytes=300000), 0: dict(deltas=800, bytes=500000)}
+    assert bench.method_figures(stats, k, True, hubs, 2) == (500000, 1240, 4 * k * 200 + 640 * 24 + 600 * 8 + 100 * 8)
