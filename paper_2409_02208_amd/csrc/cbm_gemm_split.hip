@@ -401,7 +401,8 @@ cbm_status cbm_launch_gemm_split(int64_t M, int32_t N, int32_t K, const float* A
         form = K >= 32 ? 3 : 0;
     else if (K >= 96 && (N + 127) / 128 * 128 * 10 <= (int64_t)N * 11)
         form = 4;
-    if (const char* e = std::getenv("CBM_GEMM_SPLIT")) form = std::atoi(e);  // (for tests: 0 = never, 1 to 4 = that kernel)
+    // (for tests, which run several in one process: 0 = never, 1 to 4 = that kernel; anything else is not listened to)
+    if (const char* e = std::getenv("CBM_GEMM_SPLIT"); e && e[0] >= '0' && e[0] <= '4' && !e[1]) form = e[0] - '0';
     if (form == 1 && N > 32) form = 2;
     if (form == 2 && N > 64) form = 3;
     *taken = form != 0;
