@@ -1903,12 +1903,13 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     if (tree && B.locality) B.locality_order();
     cbm_stats_t& s = h->stats;
     std::memset(&s, 0, sizeof(s));
-    // (CBM_HUB_BLOCKS: 0 = never, 2 = whatever they save, on host-only handles too)
-    const long want_hubs = env_clamped("CBM_HUB_BLOCKS", 1, 0, 2);
-    if (!tree && B.auto_depth && !exact_tree && (want_hubs == 2 || (want_hubs == 1 && !(o.flags & CBM_FLAG_HOST_ONLY)))) B.hub_blocks(want_hubs == 2);
+    // (CBM_HUB_BLOCKS: 0 = never, 2 = whatever they save, on host-only handles too, 3 = as by default, on host-only handles too)
+    const long want_hubs = env_clamped("CBM_HUB_BLOCKS", 1, 0, 3);
+    if (!tree && B.auto_depth && !exact_tree && (want_hubs >= 2 || (want_hubs == 1 && !(o.flags & CBM_FLAG_HOST_ONLY)))) B.hub_blocks(want_hubs == 2);
     st = B.emit(nrounds);
     // cbm_spmm_noalloc takes a product's columns in as many goes as its scratch needs, at least four columns at a time
-    const int64_t most_slots = (int64_t)(cbm_static_scratch_bytes() / 16);
+    const int64_t all_slots = (int64_t)(cbm_static_scratch_bytes() / 16);
+    const int64_t most_slots = env_clamped("CBM_MOST_SLOTS", all_slots, 0, all_slots);
     if (st == CBM_OK && h->hub_blocks && h->num_slots > most_slots && h->noalloc_slots <= most_slots) {
         B.rest_of.clear();
         h->hub_blocks = false;
@@ -1923,9 +1924,9 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     // ---- row blocks ------------------------------------------------------------------------------
     // Part of the automatic policy: the tree and its counters are what they are, but where one walk over the columns of 128
     // alike rows on the matrix cores is modelled cheaper than the rounds of paths, the products run that way.
-    // (CBM_ROW_BLOCKS: 0 = never, 1 = whenever the matrix is square and the policy automatic.)
-    const long want_blocks = env_clamped("CBM_ROW_BLOCKS", -1, -1, 1);
-    if (B.auto_depth && !exact_tree && !h->hub_blocks && want_blocks != 0 && m == n && m > 0 && (want_blocks == 1 || !(o.flags & CBM_FLAG_HOST_ONLY))) {
+    // (CBM_ROW_BLOCKS: 0 = never, 1 = whenever the matrix is square and the policy automatic, 2 = as by default, on host-only handles too.)
+    const long want_blocks = env_clamped("CBM_ROW_BLOCKS", -1, -1, 2);
+    if (B.auto_depth && !exact_tree && !h->hub_blocks && want_blocks != 0 && m == n && m > 0 && (want_blocks >= 1 || !(o.flags & CBM_FLAG_HOST_ONLY))) {
         const double limit = kBlockMargin * product_us;
         const int32_t most = *std::max_element(h->rownnz.begin(), h->rownnz.end());  // a block needs its longest row's columns
         const bool worth = want_blocks == 1 || (m >= kBlockMinRows && B.nnz >= kBlockMinDegree * m && most <= 64 * kBlockLongest &&

@@ -187,6 +187,40 @@ def test_handles_in_row_blocks_hold_and_count_the_blocks_only(env, monkeypatch):
     assert _err(out.cpu().numpy(), ref) <= TOL
 
 
+@pytest.mark.parametrize("form", ["rows", "hubs"])
+def test_rows_of_x_beyond_32_bit_offsets(env, monkeypatch, form):
+    """A leading dimension of 2^22: the kernel's large variant, which addresses X in 64 bits.  The last rows start beyond 4 GB."""
+    torch, cbm = env
+    n, k, ld = 700, 40, (1 << 22) + 4
+    if form == "rows":
+        rowptr, colidx = _directed(n, 9)
+    else:
+        for name, value in (("CBM_ROW_BLOCKS", "0"), ("CBM_HUB_BLOCKS", "2"), ("CBM_SPLIT_MIN", "128")):
+            monkeypatch.setenv(name, value)
+        rowptr, colidx = _popular(n, n, 4)
+    h = cbm.cbm_build(n, n, rowptr, colidx)
+    hn = cbm.cbm_build(n, n, rowptr, colidx, add_self_loops=True)
+    room = torch.empty((n, ld), device="cuda")
+    X, Y = room[:, 4:4 + k], torch.empty((n, k), device="cuda")
+    Xi, Xg = wl.integer_features(n, k, 3), wl.gaussian_features(n, k, 5)
+    X.copy_(torch.from_numpy(Xi))
+    cbm.cbm_profile_enable(h, True)
+    cbm.cbm_spmm(h, X, Y)
+    torch.cuda.synchronize()
+    assert cbm.cbm_profile_read(h)[0]["kind"] == 5
+    cbm.cbm_profile_enable(h, False)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), orc.spmm_csr(rowptr, colidx, Xi))
+    X.copy_(torch.from_numpy(Xg))
+    norm, plain = orc.spmm_csr_normalized(rowptr, colidx, Xg), orc.spmm_csr(rowptr, colidx, Xg)
+    for run, ref, scale in ((lambda: cbm.cbm_spmm_normalized(hn, X, Y), norm, None),
+                            (lambda: cbm.cbm_spmm_normalized_relu(hn, X, Y), np.maximum(norm, 0), norm),
+                            (lambda: cbm.cbm_spmm_mean(h, X, Y), orc.spmm_csr_mean(rowptr, colidx, Xg), None),
+                            (lambda: cbm.cbm_spmm_gin(h, 0.5, X, Y), plain + 1.5 * Xg.astype(np.float64), None)):
+        Y.fill_(float("nan"))
+        run()
+        assert _err(Y.cpu().numpy(), ref, scale) <= TOL
+
+
 def test_more_columns_than_a_grid_has_slabs(env):
     """65,535 slabs of 32 columns and a few more: the gather kernels take them in one launch of 128 or 256 columns a block."""
     torch, cbm = env
@@ -337,13 +371,22 @@ def _with_self(rowptr, colidx):
 
 def test_hub_blocks_take_noalloc_columns_in_goes(env, hubs, monkeypatch):
     """Hub blocks can need more scratch than the limit goes by (that of the handle without them): the columns then come in
-    goes; what was refused is refused.  Segments of one entry make the scratch large: 64 MiB at about 250 columns."""
+    goes; what was refused is refused.  Pieces of one group make the scratch large: 64 MiB at about 58 columns, where the limit
+    lies at about 524."""
     torch, cbm = env
     monkeypatch.setenv("CBM_HUB_PIECE", "1")
     monkeypatch.setenv("CBM_REST_WHOLE", "0")
     m, n = 12000, 12000
     rowptr, colidx = _popular(m, n, 5)
     h = cbm.cbm_build(m, n, rowptr, colidx)
+    cbm.cbm_profile_enable(h, True)
+    cbm.cbm_spmm(h, torch.zeros((n, 4), device="cuda"), torch.empty((m, 4), device="cuda"))
+    torch.cuda.synchronize()
+    tasks = {r["kind"]: r["tasks"] for r in cbm.cbm_profile_read(h)}
+    cbm.cbm_profile_enable(h, False)
+    # a scratch row for each segment and for each of a piece's rows (the last block of 128 may be short, and has the fewest pieces)
+    slots = tasks[1] + 128 * (tasks[5] - tasks[5] // (4000 // 128))
+    assert slots * 128 > 16 << 20, "widths from 128 on take several goes"
     monkeypatch.setenv("CBM_HUB_BLOCKS", "0")
     plain = cbm.cbm_build(m, n, rowptr, colidx)
     refused = []
@@ -364,4 +407,58 @@ def test_hub_blocks_take_noalloc_columns_in_goes(env, hubs, monkeypatch):
             break
         torch.cuda.synchronize()
         assert torch.equal(Y, Z), k
+    assert k > 448, "widths with several goes were to be tried"
     assert refused, "widths up to the limit were to be tried"
+
+
+# ---- column-blocked handles: the blocks are those of the inner handle, whose rows are parts of rows ----
+def _kinds(torch, cbm, h, n, k):
+    cbm.cbm_profile_enable(h, True)
+    cbm.cbm_spmm(h, torch.ones((n, k), device="cuda"), torch.empty((cbm.cbm_stats(h)["m"], k), device="cuda"))
+    torch.cuda.synchronize()
+    kinds = {r["kind"] for r in cbm.cbm_profile_read(h)}
+    cbm.cbm_profile_enable(h, False)
+    return kinds
+
+
+@pytest.mark.parametrize("k", [32, 47])
+def test_column_blocked_handle_with_hub_blocks_inside(env, hubs, k):
+    torch, cbm = env
+    n = 1200
+    rowptr, colidx = _popular(n, n, 6)
+    h = cbm.cbm_build(n, n, rowptr, colidx, column_blocks=2)
+    hn = cbm.cbm_build(n, n, rowptr, colidx, column_blocks=2, add_self_loops=True)
+    assert {4, 5} <= _kinds(torch, cbm, h, n, k) and {4, 5} <= _kinds(torch, cbm, hn, n, k)
+    Xi, Xg = wl.integer_features(n, k, 3), wl.gaussian_features(n, k, 5)
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    cbm.cbm_spmm(h, torch.from_numpy(Xi).cuda(), Y)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), orc.spmm_csr(rowptr, colidx, Xi))
+    X = torch.from_numpy(Xg).cuda()
+    norm, plain = orc.spmm_csr_normalized(rowptr, colidx, Xg), orc.spmm_csr(rowptr, colidx, Xg)
+    for run, ref, scale in ((lambda: cbm.cbm_spmm_normalized(hn, X, Y), norm, None),
+                            (lambda: cbm.cbm_spmm_normalized_relu(hn, X, Y), np.maximum(norm, 0), norm),
+                            (lambda: cbm.cbm_spmm_mean(h, X, Y), orc.spmm_csr_mean(rowptr, colidx, Xg), None),
+                            (lambda: cbm.cbm_spmm_gin(h, 0.5, X, Y), plain + 1.5 * Xg.astype(np.float64), None)):
+        Y.fill_(float("nan"))
+        run()
+        assert _err(Y.cpu().numpy(), ref, scale) <= TOL
+
+
+@pytest.mark.parametrize("k", [32, 47])
+def test_column_blocked_handle_with_row_blocks_inside(env, k):
+    """Two part-rows a row and twice as many columns as rows: the inner matrix is square and takes row blocks."""
+    torch, cbm = env
+    m, n = 700, 1400
+    rng = np.random.default_rng(4)
+    rows = [np.unique(rng.integers(0, n, size=int(rng.integers(0, 40)))) for _ in range(m)]
+    rowptr = np.zeros(m + 1, dtype=np.int64)
+    rowptr[1:] = np.cumsum([len(r) for r in rows])
+    colidx = np.concatenate(rows).astype(np.int32)
+    h = cbm.cbm_build(m, n, rowptr, colidx, column_blocks=2)
+    assert _kinds(torch, cbm, h, n, k) == {4, 5}
+    Xi, Xg = wl.integer_features(n, k, 3), wl.gaussian_features(n, k, 5)
+    Y = torch.full((m, k), float("nan"), device="cuda")
+    cbm.cbm_spmm(h, torch.from_numpy(Xi).cuda(), Y)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), orc.spmm_csr(rowptr, colidx, Xi))
+    cbm.cbm_spmm_mean(h, torch.from_numpy(Xg).cuda(), Y)
+    assert _err(Y.cpu().numpy(), orc.spmm_csr_mean(rowptr, colidx, Xg)) <= TOL

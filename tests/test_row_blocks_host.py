@@ -1,4 +1,5 @@
-"""Row blocks on the host: the blocks decode to the matrix, and the automatic policy leaves the tree and its counters alone."""
+"""Row and hub blocks on the host: the blocks decode to the matrix and leave the tree and its counters alone, the automatic rules take them
+where they should, and a build that runs out of memory says so."""
 import os
 import shutil
 import subprocess
@@ -39,6 +40,12 @@ def test_blocks_decode_to_the_matrix(tmp_path):
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_out_of_memory_in_a_thread_reaches_the_caller(tmp_path):
     assert "allocations ok" in _harness(tmp_path, "host_alloc_main.cpp")
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_who_takes_blocks_and_what_is_left_of_a_plan_given_up(tmp_path):
+    """The automatic rules themselves (the other tests force the blocks or leave them out)."""
+    assert "policy ok" in _harness(tmp_path, "host_policy_main.cpp")
 
 
 def test_blocks_leave_tree_and_counters_alone(monkeypatch):
