@@ -1012,8 +1012,11 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
     // waves) 407 -> 326; directed R-MAT scale 17, k = 100, forward and backward (64,000 waves of rows) 256 -> 229; but the roots of the
     // collaboration recipe's tree, k = 128 (26,500 waves, 81 us) 25 us longer, and below 16,384 waves (segments and roots
     // of 14,500) 10 to 20 us longer.  (The share of the launch: directed R-MAT's rows of up to 128 entries gain at 0.73, R-MAT
-    // scale 17, k = 64 lost 9 % at 0.8.  With one work item a wave and 25 entries in it, collaboration recipe of 60,000 nodes,
-    // k = 200, it lost 3 %.)  (CBM_MANY_WAVES moves the first line and takes the second away.)
+    // scale 17, k = 64 lost 9 % at 0.8.  With one work item a wave, rows of different lengths lose first: collaboration recipe of
+    // 60,000 nodes, 25 entries a row, k = 200 lost 3 %.  Rows of one length would gain there too -- 60,000 scattered rows of 24 entries,
+    // k = 200: 172 us in batches of 8, 160 in batches of 2 -- so the line at 16 entries leaves that, and takes what gains either way: 8 entries
+    // k = 140 59 -> 48, k = 250 82 -> 79, 12 entries k = 140 69 -> 65, k = 250 111.5 -> 113.5.)  (CBM_MANY_WAVES moves the first line and
+    // takes the second away.)
     static const char* many_env = std::getenv("CBM_MANY_WAVES");
     static const int64_t many_waves = many_env ? std::atoll(many_env) : kManyWavesDefault;
     const int64_t ychunks = ((int64_t)k + lanes * 4 - 1) / (lanes * 4);
