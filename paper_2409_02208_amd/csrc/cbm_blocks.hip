@@ -229,44 +229,102 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
     };
     // No bf16 value has bits below 2^-133, and the matrix cores take what is below 2^-126 for zero: x (times its weight) is split at
     // 2^24 times its size, where the smallest 32-bit value is 2^-125, so nothing is lost and a sum of zero is zero.
-    // What does not come out of the matrix cores is 0 x infinity: a value that is not finite (or not any more at that size: from
-    // 2^104) anywhere among the block's rows of X turns every sum of its column in this tile into NaN.  A tile with a sum that is
-    // not finite is summed again by selection instead of multiplication (protein recipe,
-    // k = 256: 0.38 ms; with one infinity in X 0.63, all of X NaN 5.1).
+    // What does not come out that way is 0 x infinity: a value that is not finite (or not any more at that size: from 2^104)
+    // anywhere among the block's rows of X turns every sum of its column in this tile into NaN.  A tile with a sum that is not
+    // finite is summed again by its wave, with large values at another size in sums of their own and infinities and NaN counted (protein
+    // recipe, k = 256: 0.33 ms; with one infinity in X 0.34, every 20th row the type's lowest value 2.1, all of X NaN 1.9; a walk that
+    // selects entry by entry took 0.51, 5.1 and 5.2).
     bool plain = true;
 #pragma unroll
     for (int v = 0; v < 16; ++v) plain = plain && fabsf(fin[v]) < INFINITY;
     if (__ballot(!plain)) {
-        float sum[16];  // lane l: rows 16 (l / 32) .. + 15 of the tile, column l % 32
+        constexpr float kLarge = 0x1p88f;  // below it 4,096 values (a block's most) add up to less than 2^100
+        floatx16 sum, large, up, down;     // up: infinities and NaN, down: minus infinities and NaN
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sum[r] = 0.0f;
-        for (uint32_t i = 0; i < 8 * blk.ngroups; ++i) {  // eight columns at a time
-            const size_t at = (size_t)blk.group0 * 64 + 8 * i;
-            float x[8], w[8];
+        for (int v = 0; v < 16; ++v) sum[v] = large[v] = up[v] = down[v] = 0.0f;
+        auto add = [&](floatx16& to, const float (&x)[8], const uintx4& bits) {
+            uintx4 P[3];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) x[j] = x_at(cols[at + j]);
+            for (int p = 0; p < 4; ++p) {
+                uint32_t h, m, l;
+                split_pair(x[2 * p], x[2 * p + 1], minus_low, h, m, l);
+                P[0][p] = h;
+                P[1][p] = m;
+                P[2][p] = l;
+            }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) w[j] = WCOL ? wcols[at + j] * kDown : 1.0f;
-            // byte of row r (in lanes r of one half): the columns that the row holds
-            const uint32_t held = (masks[(size_t)(blk.group0 + i / 8) * 64 + 32 * (i & 1) + (lane & 31)][i / 2 % 4] >> (8 * wave)) & 255u;
+            for (int q = 2; q >= 0; --q)
+                to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bits), __builtin_bit_cast(bf16x8, P[q]), to, 0, 0, 0);
+        };
+        auto count = [&](floatx16& to, const float (&x)[8], float which, const uintx4& bits) {
+            uintx4 ones;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const bool lo = x[2 * p] == which || x[2 * p] != x[2 * p], hi = x[2 * p + 1] == which || x[2 * p + 1] != x[2 * p + 1];
+                ones[p] = (lo ? 0x3f80u : 0u) | (hi ? 0x3f800000u : 0u);
+            }
+            to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bits), __builtin_bit_cast(bf16x8, ones), to, 0, 0, 0);
+        };
+        // 16 columns a step, eight for each half of the wave; rows of X one step ahead, columns, bits and weights two
+        const int last = 4 * (int)blk.ngroups - 1;
+        const uintx4* gc = reinterpret_cast<const uintx4*>(cols + (size_t)blk.group0 * 64 + 8 * half);
+        const floatx4* gw = reinterpret_cast<const floatx4*>(wcols + (size_t)blk.group0 * 64 + 8 * half);
+        const uint32_t* gm = reinterpret_cast<const uint32_t*>(masks + (size_t)blk.group0 * 64 + lane);
+        Ids ci;
+        Weights w, nw;
+        uint32_t held, nheld;
+        float nx[8];
+        auto fetch = [&](int i) {
+            ci.v[0] = gc[4 * i];
+            ci.v[1] = gc[4 * i + 1];
+            if (WCOL) {
+                nw.v[0] = gw[4 * i];
+                nw.v[1] = gw[4 * i + 1];
+            }
+            nheld = gm[(size_t)(i / 4) * 256 + i % 4] >> (8 * wave) & 255u;
+        };
+        fetch(0);
+        load_x(nx, ci);
+        w = nw;
+        held = nheld;
+        fetch(min(1, last));
+        for (int i = 0; i <= last; ++i) {
+            float x[8], y[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = WCOL ? nx[j] * (w.v[j / 4][j % 4] * kDown) : nx[j];
+            const uintx4 bits = lut[held];
+            load_x(nx, ci);
+            w = nw;
+            held = nheld;
+            fetch(min(i + 2, last));
+            bool any_small = false, any_large = false, any_other = false;  // (one kind at a time is the rule: leave out the rest)
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const uint32_t bits = (uint32_t)__ballot((held >> j) & 1u) >> (16 * half);  // bit r: this half's row r
+                any_small = any_small || fabsf(x[j]) < kLarge;
+                any_large = any_large || (fabsf(x[j]) >= kLarge && fabsf(x[j]) < INFINITY);
+                any_other = any_other || !(fabsf(x[j]) < INFINITY);
+            }
+            if (__ballot(any_small)) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float xs = __uint_as_float(__float_as_uint(x[j]) & (0u - ((bits >> r) & 1u)));
-                    sum[r] = WCOL ? fmaf(w[j], xs, sum[r]) : sum[r] + xs;
-                }
+                for (int j = 0; j < 8; ++j) y[j] = fabsf(x[j]) < kLarge ? x[j] * kUp : 0.0f;
+                add(sum, y, bits);
+            }
+            if (__ballot(any_large)) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) y[j] = fabsf(x[j]) >= kLarge && fabsf(x[j]) < INFINITY ? x[j] * kDown : 0.0f;
+                add(large, y, bits);
+            }
+            if (__ballot(any_other)) {
+                count(up, x, INFINITY, bits);
+                count(down, x, -INFINITY, bits);
             }
         }
-        if (lcol < k) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t row = rows[(size_t)blk.row0 + 32 * wave + 16 * half + r];
-                if (row != CBM_BLOCK_NO_ROW) store(row, sum[r]);
-            }
+        for (int v = 0; v < 16; ++v) {
+            fin[v] = fmaf(large[v], kUp, sum[v] * kDown);
+            if (up[v] > 0.0f) fin[v] = INFINITY;
+            if (down[v] > 0.0f) fin[v] = up[v] > 0.0f ? NAN : -INFINITY;
         }
-        return;
     }
     // register v of lane l of a 32 x 32 tile: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
     if (lcol < k) {

@@ -147,6 +147,78 @@ def test_values_that_are_not_finite_stay_in_their_rows(env, value):
         assert np.isnan(hit).all() if np.isnan(value) else np.array_equal(hit, np.full_like(hit, value))
 
 
+@pytest.mark.parametrize("form", ["rows", "hubs"])
+@pytest.mark.parametrize("k", [33, 64])
+def test_infinities_nan_and_large_values_beside_small_ones(env, monkeypatch, form, k):
+    """Every sum is what its own entries make it: infinities of both signs, NaN, values that overflow only together or at 2^24 times
+    their size, and in other rows of the same tile ordinary and the smallest values."""
+    torch, cbm = env
+    n = 1500
+    if form == "rows":
+        g = wl.make_graph("protein", n=n, knn=30)
+        rowptr, colidx = g.rowptr, g.colidx
+    else:
+        for name, value in (("CBM_ROW_BLOCKS", "0"), ("CBM_HUB_BLOCKS", "2"), ("CBM_SPLIT_MIN", "128")):
+            monkeypatch.setenv(name, value)
+        rowptr, colidx = _popular(n, n, 4)
+    rng = np.random.default_rng(k)
+    X = wl.integer_features(n, k, 8).astype(np.float64)
+    small = np.arange(0, k, 3)                       # columns of whole multiples of the smallest value, but for a few entries
+    X[:, small] *= 2.0 ** -149
+    where = rng.integers(0, n, 400), rng.integers(0, k, 400)
+    X[where] = rng.choice([np.inf, -np.inf, np.nan, 3e38, -3e38, 2.0 ** 104, -(2.0 ** 100), 2.0 ** 90, 2.0 ** 87], 400)
+    X = X.astype(np.float32)
+    h = cbm.cbm_build(n, n, rowptr, colidx)
+    Y = torch.empty((n, k), device="cuda")
+    cbm.cbm_spmm(h, torch.from_numpy(X).cuda(), Y)
+    got = Y.cpu().numpy()
+    with np.errstate(all="ignore"):
+        A = np.zeros((n, n))
+        A[np.repeat(np.arange(n), np.diff(rowptr)), colidx] = 1.0
+        finite = np.where(np.isfinite(X), X, 0.0).astype(np.float64)
+        size = A @ np.abs(finite)
+        ref = A @ finite
+        up, down = A @ (np.isnan(X) | (X == np.inf)), A @ (np.isnan(X) | (X == -np.inf))
+        over = np.abs(ref) >= 2.0 ** 128
+        ref = np.where(up > 0, np.inf, np.where(over, np.sign(ref) * np.inf, ref))
+        ref = np.where(down > 0, np.where(up > 0, np.nan, -np.inf), ref)
+        near = np.abs(size) >= 2.0 ** 127   # may overflow on the way, or not
+        same = np.isfinite(ref) & ~near
+        assert np.array_equal(np.isnan(got)[~near], np.isnan(ref)[~near])
+        assert np.array_equal(got[np.isinf(ref) & ~near], ref[np.isinf(ref) & ~near].astype(np.float32))
+        assert np.all(np.abs(got - ref)[same] <= 2.0 ** -18 * size[same])
+        exact = same & (size < 2.0 ** 24 * np.where(np.isin(np.arange(k), small), 2.0 ** -149, 1.0))
+        assert exact.sum() > 0.3 * exact.size and np.array_equal(got[exact].astype(np.float64), ref[exact])
+
+
+def test_values_that_are_not_finite_cost_little(env):
+    """A tile summed again takes the matrix cores: about six times the product's time with NaN everywhere; a walk that selects entry by
+    entry took sixteen times.  The line is at 11 to leave room for noise."""
+    torch, cbm = env
+    g = wl.make_graph("protein", n=20000, knn=150)
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx)
+    X, Y = torch.randn((g.n, 256), device="cuda"), torch.empty((g.n, 256), device="cuda")
+
+    def best():
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                cbm.cbm_spmm(h, X, Y)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    best()
+    clean = best()
+    X.fill_(float("nan"))
+    assert best() <= 11 * clean
+    X.normal_().mul_(1e-35)
+    assert best() <= 2 * clean
+
+
 @pytest.mark.parametrize("scale", [1e-36, 1e-34, 1e-30, 1e-27, 1e30])
 def test_scale_of_the_values_does_not_matter(env, scale):
     torch, cbm = env
