@@ -263,7 +263,9 @@ cbm_status cbm_spmm_gin(const cbm_handle* h, float eps, const float* X, int64_t 
 
 /*
  * cbm_dense_matmul -- C = A . B for dense row-major fp32 device matrices
- * (the X . W products of Eq. (1)); fp32 MFMA, fp32 accumulation.
+ * (the X . W products of Eq. (1)), fp32 accumulation: on the fp32 matrix cores, or, where that is faster, on the bf16 ones
+ * with each operand split into three bf16 parts that add up to it exactly (the products of parts that are left out are
+ * below 2^-24 of a term).  Infinities, NaN and subnormal values are what they are in fp32.
  *   A  M x K (lda >= K),  B  K x N (ldb >= N),  C  M x N (ldc >= N), no overlap.
  */
 cbm_status cbm_dense_matmul(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B,

@@ -16,7 +16,7 @@
 // v_mfma_f32_32x32x16_bf16 as they stand.  The A operand is a byte of bits through a table in LDS.  Tiles that hold none of a
 // step's 16 columns are left out.
 //
-// What bounds it (protein recipe, k = 256; before: 0.79 ms on the paths, now 0.32): matrix cores 35 % and vector ALU 52 % of the
+// What bounds it (protein recipe, k = 256; before: 0.79 ms on the paths, now 0.32): matrix cores 36 % and vector ALU 53 % of the
 // cycles at a clock that the two bring down to 1.9 GHz; rows of X from L1 instead of L2 change 5 %, no weights or table 3 %.
 // Measured on the way: 64 columns a slab with scalar loads of the column numbers 0.52 ms (two waves per SIMD, waits for
 // scalar loads), blocks of 64 rows 0.46 ms, all tiles without a test 0.51 ms, rows not sorted into tiles 0.41 ms.

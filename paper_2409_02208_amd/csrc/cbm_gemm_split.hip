@@ -394,7 +394,7 @@ void pick(const Shape& s, int form) {
 //    gain (12.2, 10.4), at 64 they lose (9.0, 9.9);
 //  more columns, few workgroups (tiles of 64 columns): 19717 x 256 . 256 x 256 42 -> 28, 6000 x 300 . 300 x 96 28 -> 15, 4000 x 96 . 96 x 96
 //    11 -> 8 (K = 32: level);
-//  more columns, many: 132534 x 256 . 256 x 256 156 -> 130, 132534 x 96 . 96 x 256 92 -> 71, 132534 x 250 . 250 x 250 234 -> 182,
+//  more columns, many: 132534 x 256 . 256 x 256 156 -> 130, 132534 x 96 . 96 x 256 89 -> 66, 132534 x 250 . 250 x 250 234 -> 182,
 //    if the last tile of 128 columns is not mostly padding (256 x 160: 105, 134; 256 x 112: 75, 76) and K is not so short that the
 //    products are bound by memory (132534 x 64 . 64 x 128: 32, 33).
 cbm_status cbm_launch_gemm_split(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
