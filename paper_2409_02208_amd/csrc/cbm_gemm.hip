@@ -379,7 +379,7 @@ cbm_status launch16_nt(int64_t M, int N, int K, const float* A, int64_t lda, con
 // One 16x16x4 MFMA contracts four k: lane (c = l%16, q = l/16) holds A[row c][k0 + 4q .. 4q+3] of a group of 16 k as one
 // 128-bit load and feeds element e to MFMA e, which therefore contracts k0 + 4q + e over q; the B operand of MFMA e is
 // panel[k0 + 4q + e][16t + c].  The panel's row stride (16 NT16 + 4 floats) puts q and q+1 on disjoint halves of the banks.
-// B may have any width and alignment (132534 x 100 . 100 x 47: 31.9 us through the staged kernel, 28.7 here).
+// B may have any width and alignment, where cbm_panel_takes_unaligned says that this pays.
 // Loads of A run four groups of 16 k ahead through a ring of registers and are unconditional (addresses clamped into the
 // matrix; what lies beyond K is zeroed when used, rows beyond M are never stored).
 constexpr int WPB = 8;  // waves per block of the panel kernel
@@ -570,6 +570,8 @@ __global__ __launch_bounds__(64 * WPB) void cbm_gemm_panel_kernel(int64_t M, int
     }
 }
 
+inline bool wide_loads_of_b(int N, const float* B, int64_t ldb) { return N % 4 == 0 && ldb % 4 == 0 && ((uintptr_t)B & 15) == 0; }
+
 // LDS bytes of the resident panel, or 0 if this product cannot take the panel kernel.
 inline size_t panel_lds_bytes(int N, int K, const float* A, int64_t lda, int* nt16) {
     const bool vec = K % 4 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0 && K >= 4;
@@ -594,7 +596,7 @@ cbm_status launch_panel(int64_t M, int N, int K, const float* A, int64_t lda, co
         lds_opt_in = smem;
     }
     const int Kp = (K + 63) / 64 * 64;
-    const int vec_b = N % 4 == 0 && ldb % 4 == 0 && ((uintptr_t)B & 15) == 0;
+    const int vec_b = wide_loads_of_b(N, B, ldb);
     hipLaunchKernelGGL((cbm_gemm_panel_kernel<NT16>), dim3(256), dim3(64 * WPB), smem, stream, M, N, K, Kp, A, lda, B, ldb, vec_b, C, ldc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
@@ -658,7 +660,8 @@ cbm_status cbm_launch_gemm(int64_t M, int32_t N, int32_t K, const float* A, int6
         static const char* env = std::getenv("CBM_GEMM_PANEL_MIN_ROWS");
         const int64_t min_rows = env ? std::atoll(env) : 8192;
         int nt16 = 0;
-        const size_t smem = M >= min_rows ? panel_lds_bytes(N, K, A, lda, &nt16) : 0;
+        const bool pays = M >= min_rows && (wide_loads_of_b(N, B, ldb) || cbm_panel_takes_unaligned(M, N, K));
+        const size_t smem = pays ? panel_lds_bytes(N, K, A, lda, &nt16) : 0;
         if (smem) {
             switch (nt16) {
                 case 1: return launch_panel<1>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);

@@ -174,6 +174,20 @@ inline size_t cbm_static_scratch_bytes() { return (size_t)CBM_STATIC_SCRATCH_FLO
 // the same through bf16 parts (cbm_gemm_split.hip) where its own rule says so: *taken
 cbm_status cbm_launch_gemm_split(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                  int64_t ldc, void* stream, bool* taken);
+// Whether the panel-resident fp32 kernel also takes a B that 128-bit loads cannot read (odd width or alignment): filling the panel
+// element by element has to be earned by depth and by rows.  The staged kernel has blocks of 128 rows, so it loses where M / 128 just
+// exceeds the 256 compute units, and tiles of 48 columns, which suit N from 33 to 48 (microseconds, or its share of the staged kernel's time):
+//  N > 64: 132534 x 64 . 64 x 130 0.61, 132534 x 32 . 32 x 65 17.8 -> 24.2, 40000 x 32 . 32 x 250 21.5 -> 25.7;
+//  N <= 64, K >= 100: 34000 x 100 . 100 x 17 0.93, 32768 rows 1.23; N = 33 to 48 40000 x 100 . 100 x 47 13.3 -> 14.9, 50000 rows 0.93, and at
+//    K = 256 from 40000 rows on 0.92; few rows, both kernels short of work: 9000 x 100 . 100 x 17 0.92, 12000 rows 1.08; 8192 x 100 . 100 x 50 0.84,
+//    16000 rows 0.97, 18000 rows 1.15;
+//  shallower: 132534 x 64 . 64 x 47 and 200000 x 48 . 48 x 47 0.90, 100000 x 64 . 64 x 47 1.06, 132534 x 32 . 32 x 47 13.2 -> 18.5.
+inline bool cbm_panel_takes_unaligned(int64_t M, int32_t N, int32_t K) {
+    if (N > 64) return K >= 48;
+    if (K < 100) return K >= 48 && M >= 131072;
+    if (N > 32 && N <= 48) return M >= (K >= 256 ? 32769 : 49152);
+    return M > 32768 || M <= (N <= 32 ? 10240 : 16384);
+}
 // dense fp32 MFMA matmul (cbm_gemm.hip)
 cbm_status cbm_launch_gemm(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb,
                            float* C, int64_t ldc, void* stream);

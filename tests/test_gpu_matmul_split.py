@@ -173,11 +173,12 @@ def test_values_that_are_not_finite_cost_little(env, k, n):
     assert best() <= 12 * clean
 
 
-@pytest.mark.parametrize("n", [16, 17, 47, 112, 130])
-def test_panel_kernel_on_any_b(env, monkeypatch, n):
+# just tall enough for the panel kernel; and just deep or tall enough for it to take a B of any width
+@pytest.mark.parametrize("m,k,n", [(8193, 36, n) for n in (16, 17, 47, 112, 130)] +
+                         [(8193, 48, 65), (8193, 48, 130), (32769, 256, 47), (49153, 100, 33), (131073, 48, 17)])
+def test_panel_kernel_on_any_b(env, monkeypatch, m, k, n):
     monkeypatch.setenv("CBM_GEMM_SPLIT", "0")
     rng = np.random.default_rng(n)
-    m, k = 8193, 36   # just tall enough for the panel kernel
     A, B = (rng.integers(-9, 10, s).astype(np.float32) for s in ((m, k), (k, n)))
     ref = A.astype(np.float64) @ B.astype(np.float64)
     for pad in ((0, 0, 0), (4, 1, 3), (4, 3, 0)):

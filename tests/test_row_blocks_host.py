@@ -72,3 +72,22 @@ def test_bench_figures_are_of_what_runs():
     assert bench.method_figures(stats, k, True, blocks, 2) == (1000000, 640, 4 * k * 200 + 640 * 24 + 100 * 8)
     hubs = {5: dict(deltas=1280, bytes=200000), 1: dict(deltas=400, bytes=300000), 0: dict(deltas=800, bytes=500000)}
     assert bench.method_figures(stats, k, True, hubs, 2) == (500000, 1240, 4 * k * 200 + 640 * 24 + 600 * 8 + 100 * 8)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_panel_kernel_takes_an_unaligned_b_where_that_was_measured_to_pay(tmp_path):
+    """(M, N, K, staged kernel, panel kernel: microseconds, or the panel's time over the staged kernel's) on both sides of the rule's lines."""
+    measured = [(132534, 17, 32, 10.3, 14.8), (132534, 47, 32, 13.2, 18.5), (132534, 65, 32, 17.8, 24.2), (40000, 250, 32, 21.5, 25.7),
+                (20000, 17, 100, 8.3, 10.3), (20000, 50, 64, 8.4, 10.0), (40000, 33, 100, 13.0, 14.7), (28000, 17, 256, 1.0, 1.42),
+                (100000, 47, 64, 1.0, 1.06), (132534, 47, 100, 31.9, 28.7), (132534, 17, 64, 1.0, 0.92), (132534, 130, 64, 1.0, 0.61),
+                (40000, 250, 64, 1.0, 0.84), (200000, 33, 48, 1.0, 0.90), (50000, 47, 100, 1.0, 0.93), (40000, 17, 256, 1.0, 0.73),
+                (34000, 17, 100, 1.0, 0.93), (34000, 50, 128, 1.0, 0.91), (32768, 17, 100, 1.0, 1.23), (32768, 63, 200, 1.0, 1.06), (40000, 47, 256, 1.0, 0.91),
+                (9000, 17, 100, 1.0, 0.92), (12000, 17, 100, 1.0, 1.08), (8192, 50, 100, 1.0, 0.84), (18000, 50, 100, 1.0, 1.15), (8192, 47, 120, 1.0, 1.12)]
+    main = tmp_path / "rule.cpp"
+    main.write_text('#include <cstdio>\n#include "cbm_internal.h"\nint main() {\n' +
+                    "".join(f"    std::printf(\"%d\", cbm_panel_takes_unaligned({m}, {n}, {k}));\n" for m, n, k, _, _ in measured) + "}\n")
+    exe = str(tmp_path / "rule")
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2409_02208_amd", "csrc"), str(main), "-o", exe],
+                   check=True)
+    taken = [c == "1" for c in subprocess.run([exe], capture_output=True, text=True, check=True).stdout]
+    assert taken == [panel < staged for _, _, _, staged, panel in measured]
