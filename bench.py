@@ -52,9 +52,9 @@ L2_PEAK_GBS = 8 * 16 * 128 * 2.4
 COUNTER_GROUPS = (("fetch", ["FETCH_SIZE"]), ("write", ["WRITE_SIZE"]), ("l2", ["TCC_REQ_sum", "TCC_HIT_sum", "TCC_MISS_sum"]))
 # every kernel a product call can launch (the counter children match dispatches to the library's launch records by order)
 PRODUCT_KERNELS = ("cbm_level_kernel", "cbm_bundle_kernel", "cbm_combine_kernel", "cbm_finish_kernel", "cbm_block_sum_kernel",
-                   "cbm_block_kernel")
+                   "cbm_block_kernel", "cbm_sum_sets_kernel", "cbm_sum_rows_kernel")
 KIND_NAMES = {0: "rounds of paths", 1: "segments of split rows", 2: "combine of split rows", 3: "deferred finish",
-              4: "sum of column blocks", 5: "row blocks"}
+              4: "sum of column blocks", 5: "row blocks", 6: "shared sums"}
 
 DEFAULTS = {  # workload -> k of the timed product, alpha, GCN shape or None
     "tiny": dict(k=16, alpha=0, gcn=(16, 8, 4)),
@@ -302,9 +302,9 @@ def compulsory_bytes(stats, k, normalized):
 
 def method_figures(stats, k, normalized, agg, nprof):
     """(bytes the method moves, rows of X it gathers, bytes HBM must move at least) of one product.  Where launches over row or hub
-    blocks do the work, the tree's deltas are not what is gathered: the launch records say what is, and a column of a block is
+    blocks or through shared sums do the work, the tree's deltas are not what is gathered: the launch records say what is, and a column of a block is
     read with its bit in each of 128 rows (16 bytes) beside its number and weight."""
-    if not any(kind == 5 for kind in agg):
+    if not any(kind in (5, 6) for kind in agg):
         return (algorithmic_bytes(stats, k, normalized), stats["num_delta_plus"] + stats["num_delta_minus"],
                 compulsory_bytes(stats, k, normalized))
     entry = 8 if normalized else 4
@@ -423,13 +423,13 @@ def bench_product(torch, cbm, orc, g, h, hc, Xh, k, steps, warmup, workload, cou
         + (f", HBM side {hbm_total / ms / 1e6:.0f} GB/s ({hbm_total / 1e9:.2f} GB)" if hbm_total else ""))
 
     # the dominant launch = the kind that takes the most time
-    lv = [l for l in launches if l["kind"] in (0, 1, 5)]
+    lv = [l for l in launches if l["kind"] in (0, 1, 5, 6)]
     dom = max(lv, key=lambda l: l["ms"]) if lv else None
     roofline = None
     if dom is not None:
         per = dom["launches_per_product"]
         avg_ms = dom["ms"] / per
-        roofline = dict(bound="hbm", kernel="cbm_block_kernel" if dom["kind"] == 5 else "cbm_level_kernel", launch=dom["launch"], peak=HBM_PEAK_GBS, unit="GB/s",
+        roofline = dict(bound="hbm", kernel={5: "cbm_block_kernel", 6: "cbm_sum_rows_kernel"}.get(dom["kind"], "cbm_level_kernel"), launch=dom["launch"], peak=HBM_PEAK_GBS, unit="GB/s",
                         avg_launch_ms=avg_ms, launches_per_step=per,
                         algorithmic_bytes_per_launch=dom["algorithmic_bytes"] / per, algorithmic_GBps=dom["algorithmic_GBps"],
                         share_of_step_ms=dom["ms"] / ms_prof if ms_prof > 0 else None)

@@ -94,8 +94,12 @@ typedef enum {
  *                only, and bytes_cbm counts them.  Where every row is stored in
  *                full, rows long enough to be split share their popular columns in
  *                such blocks too (num_tasks and bytes_cbm count what is left of
- *                them, bytes_cbm also the blocks).  A host-only handle has no
- *                blocks: num_tasks and bytes_cbm are those of the paths.  The
+ *                them, bytes_cbm also the blocks).  On a square matrix whose rows
+ *                share whole column sets (the cliques of a collaboration network)
+ *                the same model may sum each set once and make the rows of those
+ *                sums; bytes_cbm counts these lists too.  A host-only handle has no
+ *                blocks or shared sums: num_tasks and bytes_cbm are those of the
+ *                paths.  The
  *                tree is cut into vertical paths, one work item each;
  *                dependent kernel launches per product = rounds of paths
  *                (cbm_stats), at most the depth.  Any value yields a valid CBM
@@ -147,7 +151,7 @@ typedef struct {
     int64_t num_split_rows;  /* rows whose delta list is cut into several segments   */
     int64_t bytes_csr;       /* int64 row offsets + int32 columns, no values         */
     int64_t bytes_cbm;       /* packed device arrays of this handle (host-only: the
-                                arrays that it would upload without blocks)           */
+                                arrays that it would upload without blocks or sums)   */
     int32_t depth;           /* number of tree levels                                */
     int32_t alpha;
     int32_t add_self_loops;
@@ -200,6 +204,10 @@ cbm_status cbm_build(int64_t m, int64_t n, const int64_t* rowptr, const int32_t*
  *    any before it frees and reallocates it (the free waits for the device), which is
  *    not allowed under HIP-graph capture: call cbm_reserve(h, widest k) once beforehand;
  *    after that, products with k <= that width only launch kernels and can be captured.
+ * A handle whose products take shared sums keeps an array of at most 32 MiB (128 columns of sums where
+ * that is more) for each of up to eight streams and captures, the first from cbm_build on; the others are
+ * allocated when a product first needs them, also under capture, and products for which there is none run
+ * without shared sums.  Such products may overlap freely.
  * Per-launch profiling (cbm_profile_enable) records events and must be off during capture.
  */
 cbm_status cbm_spmm(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
@@ -215,7 +223,8 @@ cbm_status cbm_spmm(const cbm_handle* h, const float* X, int64_t ldx, int32_t k,
  *   x (k rounded up to a multiple of 4) floats must fit 64 MiB = 16,777,216 floats,
  *   else CBM_ERR_UNSUPPORTED (cbm_last_error_detail gives the numbers); a handle without split rows
  *   (cbm_stats.num_split_rows == 0) always fits.  Where long rows share their popular columns in blocks
- *   (see max_depth) and that takes more scratch rows, the columns of X go through in several goes.
+ *   (see max_depth) and that takes more scratch rows, the columns of X go through in several goes; so
+ *   they do where shared sums need more.
  *   CBM_ERR_STATE while per-launch profiling is on (it creates events).
  * Every GPU the library runs on holds one such array until the process ends, and every call on that GPU
  * shares it, whatever the handle: calls that overlap in time on one GPU (two streams, two host threads)
@@ -322,8 +331,10 @@ typedef struct {
                                4 = sum of the partial rows of a column-blocked handle,
                                5 = row blocks: the whole product, or the popular columns of
                                split rows (tasks = blocks, deltas = columns gathered, each
-                               once per block)                                           */
-    int32_t level;          /* round for kinds 0 and 2, else 0                         */
+                               once per block), 6 = shared sums: level 1 the sets, level 2
+                               the rows made of them (tasks = sets or rows, deltas = rows of X
+                               and sums gathered)                                        */
+    int32_t level;          /* round for kinds 0 and 2, launch for kind 6, else 0      */
     int64_t tasks;          /* work items in the launch                               */
     int64_t deltas;         /* delta entries gathered by the launch                   */
     int64_t algorithmic_bytes; /* bytes the method itself must move in this launch    */

@@ -24,6 +24,7 @@
 
 #include "cbm_block_plan.h"
 #include "cbm_internal.h"
+#include "cbm_sum_plan.h"
 
 namespace {
 
@@ -74,6 +75,13 @@ constexpr double kHubMinSavedUs = 2.0;
 constexpr size_t kHubPieceMin = 16, kHubPieceMax = 64;  // groups
 // (R-MAT scale 21, k = 128: up to 48, 64 or 96 entries 3.97 ms, up to 128 4.10; smaller graphs do not care)
 constexpr int64_t kRestWhole = 96;        // entries that hubs leave of a row, up to which they stay one segment
+// Shared sums (Builder::shared_sums)
+constexpr int64_t kSumMinRows = 512;
+constexpr int64_t kSumSample = 256;      // rows looked at first
+constexpr double kSumMargin = 0.8;       // of the paths' modelled time
+constexpr double kSumBlockMargin = 1.1;  // of the row blocks' (collaboration recipe, k = 64: 10,000 nodes, models level, 22.6 -> 14.9 us; 2,500
+                                         // nodes, this one 1.9 times the other, 13.7 -> 15.1)
+constexpr size_t kSumWindow = 256;       // items that are put in order of length among themselves
 constexpr int64_t kPathChoices[] = {16, 32, 64, 128, 256};
 
 long env_or(const char* name, long dflt) {
@@ -272,6 +280,8 @@ struct Builder {
     double sampled_row_block_cost() const;
     void row_blocks();
     void hub_blocks(bool force);
+    double shared_sums_cost(double gathers, double sets, double longest) const;
+    void shared_sums(const std::vector<uint8_t>& holds_own);
     int64_t count_slots() const;
     // rows in hub blocks keep only the other entries for the gather kernels
     struct Rest {
@@ -1580,6 +1590,87 @@ void Builder::row_blocks() {
                      at, 64.0 * at / m);
 }
 
+// Modelled time of one product through shared sums: two dependent launches of gathers.
+double Builder::shared_sums_cost(double gathers, double sets, double longest) const {
+    return 2 * kLaunchUs + std::max(longest * kEntryUs, (gathers + sets + (double)m) * kRefRowBytes / kBytesPerUs);
+}
+
+// Sets and rows as work items.  Rows of the same largest set come one after the other, on one XCD: its sum is then read from that XCD's L2.
+// Inside stretches of kSumWindow items the longest come first, so that the items of a wave are of one length.
+void Builder::shared_sums(const std::vector<uint8_t>& holds_own) {
+    const SharedSums S = SharedSumFinder(m, rowptr, colidx, holds_own.data()).find([&](int64_t total, auto&& fn) {
+        parallel_chunks(nthreads, total, 16, [&](int64_t b, int64_t e, int) { fn(b, e); });
+    });
+    const int64_t ns = S.num_sets();
+    if (ns == 0 || ns > CBM_MOST_SUMS) return;
+    auto set_len = [&](int64_t g) { return S.set_ptr[g + 1] - S.set_ptr[g]; };
+    auto by_window = [&](std::vector<int32_t>& order, auto&& len) {
+        for (size_t b = 0; b < order.size(); b += kSumWindow)
+            std::stable_sort(order.begin() + b, order.begin() + std::min(order.size(), b + kSumWindow), [&](int32_t x, int32_t y) { return len(x) > len(y); });
+    };
+    std::vector<int32_t> sets((size_t)ns), at((size_t)ns), rows((size_t)m), largest((size_t)m, (int32_t)ns);
+    for (int64_t g = 0; g < ns; ++g) sets[g] = (int32_t)g;
+    by_window(sets, set_len);
+    for (int64_t i = 0; i < ns; ++i) at[sets[i]] = (int32_t)i;
+    std::vector<int32_t> len((size_t)m);
+    parallel_chunks(nthreads, m, 1024, [&](int64_t x0, int64_t x1, int) {
+        for (int64_t x = x0; x < x1; ++x) {
+            rows[x] = (int32_t)x;
+            int64_t most = 0;
+            for (int64_t q = S.row_ptr[x]; q < S.row_ptr[x + 1]; ++q)
+                if (set_len(S.row_sets[q]) > most) most = set_len(S.row_sets[q]), largest[x] = S.row_sets[q];
+            int64_t single = -(int64_t)holds_own[x];  // (the own column is never covered)
+            for (int64_t p = rowptr[x]; p < rowptr[x + 1]; ++p) single += !S.covered[p];
+            len[x] = (int32_t)(S.row_ptr[x + 1] - S.row_ptr[x] + single);
+        }
+    });
+    std::stable_sort(rows.begin(), rows.end(), [&](int32_t x, int32_t y) { return largest[x] < largest[y]; });
+    by_window(rows, [&](int32_t x) { return len[x]; });
+    h->num_sums = ns;
+    h->sum_items.resize((size_t)(ns + m));
+    uint32_t end = 0;
+    for (int64_t i = 0; i < ns; ++i) {
+        h->sum_items[i] = {end, (uint32_t)set_len(sets[i]), 0, 0};
+        end += (uint32_t)set_len(sets[i]);
+    }
+    for (int64_t i = 0; i < m; ++i) {
+        const int32_t x = rows[i];
+        h->sum_items[ns + i] = {end, (uint32_t)len[x] | (holds_own[x] ? CBM_SUM_OWN : 0u), x, S.own[x]};
+        end += (uint32_t)len[x];
+    }
+    h->sum_entries.resize(end);
+    parallel_chunks(nthreads, ns + m, 1024, [&](int64_t i0, int64_t i1, int) {
+        for (int64_t i = i0; i < i1; ++i) {
+            uint32_t* e = h->sum_entries.data() + h->sum_items[i].start;
+            if (i < ns) {
+                std::copy(S.set_cols.begin() + S.set_ptr[sets[i]], S.set_cols.begin() + S.set_ptr[sets[i] + 1], e);
+                continue;
+            }
+            const int32_t x = rows[i - ns];
+            for (int64_t q = S.row_ptr[x]; q < S.row_ptr[x + 1]; ++q) *e++ = CBM_SUM_BIT | (uint32_t)at[S.row_sets[q]];
+            for (int64_t p = rowptr[x]; p < rowptr[x + 1]; ++p)
+                if (colidx[p] != x && !S.covered[p]) *e++ = (uint32_t)colidx[p];
+        }
+    });
+    for (int half = 0; half < 2; ++half) {  // equal shares of the entries, and an item costs about as much as two of them
+        const int64_t first = half ? ns : 0, last = half ? ns + m : ns;
+        auto cost = [&](int64_t i) { return (int64_t)(h->sum_items[i].len & ~CBM_SUM_OWN) + 2; };
+        int64_t total = 0, sum = 0, i = first;
+        for (int64_t j = first; j < last; ++j) {
+            total += cost(j);
+            h->sum_longest[half] = std::max(h->sum_longest[half], cost(j) - 2);
+        }
+        for (int j = 0; j < CBM_XCD; ++j) {
+            h->sum_begin[half][j] = i;
+            while (i < last && (j == CBM_XCD - 1 || sum + cost(i) / 2 < total * (j + 1) / CBM_XCD)) sum += cost(i++);
+            h->sum_count[half][j] = i - h->sum_begin[half][j];
+        }
+    }
+    if (verbose)
+        std::fprintf(stderr, "[cbm_build] shared sums: %ld sets of %ld columns, %ld entries in their rows (%ld before)\n", (long)ns, (long)S.set_cols.size(),
+                     (long)(h->sum_entries.size() - S.set_cols.size()), (long)nnz);
+}
+
 }  // namespace
 
 // Column-blocked CBM: the columns are cut into B equal ranges and the part of every row inside a range becomes a row
@@ -1926,6 +2017,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     // alike rows on the matrix cores is modelled cheaper than the rounds of paths, the products run that way.
     // (CBM_ROW_BLOCKS: 0 = never, 1 = whenever the matrix is square and the policy automatic, 2 = as by default, on host-only handles too.)
     const long want_blocks = env_clamped("CBM_ROW_BLOCKS", -1, -1, 2);
+    double blocks_us = 0;
     if (B.auto_depth && !exact_tree && !h->hub_blocks && want_blocks != 0 && m == n && m > 0 && (want_blocks >= 1 || !(o.flags & CBM_FLAG_HOST_ONLY))) {
         const double limit = kBlockMargin * product_us;
         const int32_t most = *std::max_element(h->rownnz.begin(), h->rownnz.end());  // a block needs its longest row's columns
@@ -1936,6 +2028,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
             double longest = 0;
             for (const CbmBlock& b : h->row_blocks) longest = std::max(longest, (double)b.ngroups);
             const double us = B.row_block_cost((double)h->block_cols.size() / 64.0, longest);
+            blocks_us = us;
             if (B.verbose) std::fprintf(stderr, "[cbm_build] row blocks: model %.1f us (paths: %.1f us)\n", us, product_us);
             if (want_blocks != 1 && us >= limit) {
                 std::vector<CbmBlock>().swap(h->row_blocks);
@@ -1945,6 +2038,38 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
             }
         }
         B.lap("row blocks");
+    }
+
+    // ---- shared sums -----------------------------------------------------------------------------
+    // Part of the automatic policy too: column sets that many rows hold in full (the cliques of a collaboration network) are summed
+    // once and the rows made of the sums.  The paths (or row blocks) stay: products run on them where a stream has no scratch.
+    // (CBM_SHARED_SUMS: 0 = never, 1 = whenever there are any, 2 = as by default, on host-only handles too.)
+    const long want_sums = env_clamped("CBM_SHARED_SUMS", -1, -1, 2);
+    if (B.verbose && h->hub_blocks) std::fprintf(stderr, "[cbm_build] shared sums: products do without\n");
+    if (B.auto_depth && !exact_tree && !h->hub_blocks && want_sums != 0 && m == n && m > 0 && (want_sums == 1 || want_blocks != 1) &&
+        (want_sums >= 1 || !(o.flags & CBM_FLAG_HOST_ONLY))) {
+        const double limit = h->row_blocks.empty() ? kSumMargin * product_us : std::min(kSumMargin * product_us, kSumBlockMargin * blocks_us);
+        std::vector<uint8_t> holds_own((size_t)m, 1);
+        if (!h->square_self_loops)
+            parallel_chunks(B.nthreads, m, 4096, [&](int64_t x0, int64_t x1, int) {
+                for (int64_t x = x0; x < x1; ++x) holds_own[x] = std::binary_search(B.row(x), B.row(x) + B.rlen(x), (int32_t)x);
+            });
+        auto sampled = [&] { return SharedSumFinder(m, B.rowptr, B.colidx, holds_own.data()).sample(kSumSample) * (double)B.nnz; };
+        const bool worth = want_sums == 1 || (m >= kSumMinRows && B.shared_sums_cost(sampled(), 0, 0) < limit);
+        if (worth) {
+            B.shared_sums(holds_own);
+            double gathers = (double)h->sum_entries.size();
+            for (const CbmSumItem& it : h->sum_items) gathers += it.own != 0;
+            const double us = B.shared_sums_cost(gathers, (double)h->num_sums, (double)(h->sum_longest[0] + h->sum_longest[1]));
+            if (B.verbose) std::fprintf(stderr, "[cbm_build] shared sums: model %.1f us (paths: %.1f us)\n", us, product_us);
+            if (want_sums != 1 && us >= limit) {
+                h->num_sums = 0;
+                std::vector<CbmSumItem>().swap(h->sum_items);
+                std::vector<uint32_t>().swap(h->sum_entries);
+            }
+        }
+        if (B.verbose) std::fprintf(stderr, "[cbm_build] shared sums: products %s\n", h->num_sums > 0 ? "take them" : "do without");
+        B.lap("shared sums");
     }
 
     // ---- counters (Properties 1 and 2) -----------------------------------------------------------
@@ -1973,6 +2098,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     s.bytes_cbm = 4 * (int64_t)h->dinv.size() + (blocks_only || h->hub_blocks ? block_bytes : 0);
     if (!blocks_only)
         s.bytes_cbm += 4 * (int64_t)(h->stream.size() + h->internal_rows.size()) + (int64_t)sizeof(CbmTask) * (int64_t)(h->tasks.size() + h->comb.size());
+    if (!(o.flags & CBM_FLAG_HOST_ONLY)) s.bytes_cbm += 4 * (int64_t)h->sum_entries.size() + (int64_t)sizeof(CbmSumItem) * (int64_t)h->sum_items.size();
     s.depth = depth;
     s.rounds = nrounds;
     s.alpha = B.alpha;

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <cstdint>
+#include <mutex>
 #include <vector>
 
 #include "cbm.h"
@@ -65,6 +66,25 @@ struct CbmBlock {
 constexpr uint32_t CBM_BLOCK_NO_ROW = 0xffffffffu;  // an empty place
 constexpr float CBM_BLOCK_UP = 16777216.0f;         // 2^24: rows of X are split at this size (cbm_blocks.hip says why)
 
+// Shared sums: a work item is a column set that is summed once, or a row made of such sums and of columns of its own.
+struct CbmSumItem {
+    uint32_t start, len;  // its entries: columns, or CBM_SUM_BIT | set
+    int32_t row;          // the row it stores
+    int32_t own;          // how often the row adds its own column (negative: its sets hold it more often than the row does)
+};
+constexpr uint32_t CBM_SUM_BIT = 0x80000000u;
+constexpr uint32_t CBM_SUM_OWN = 0x80000000u;  // in len of a row: the matrix holds the row's own column
+constexpr int64_t CBM_MOST_SUMS = 1 << 19;     // 32 columns of that many fill the static scratch
+// Columns of X whose sums are in memory at a time: 32 MiB of them, 128 at least and 1024 at most.
+inline int64_t cbm_sum_columns(int64_t num_sums) {
+    const int64_t fit = ((int64_t)8 << 20) / (num_sums > 0 ? num_sums : 1) & ~(int64_t)127;
+    return fit < 128 ? 128 : fit > 1024 ? 1024 : fit;
+}
+struct CbmSumScratch {  // num_sums x cbm_sum_columns floats of the products that one stream, or one capture on it, enqueues
+    uint64_t stream, capture, thread;
+    float* sums;
+};
+
 struct cbm_handle {
     int64_t m = 0, n = 0;
     cbm_build_opts opts{};
@@ -103,6 +123,13 @@ struct cbm_handle {
                                          // in row 32 s + l % 32
     int64_t blk_begin[CBM_XCD] = {}, blk_count[CBM_XCD] = {};  // each XCD's run of blocks
 
+    // ---- shared sums: where they pay, the products run on these; the work items above stand in where there is no scratch to be had ----
+    std::vector<CbmSumItem> sum_items;   // the num_sums sets (set i = item i), then the m rows
+    std::vector<uint32_t> sum_entries;
+    int64_t num_sums = 0;                // 0: none
+    int64_t sum_begin[2][CBM_XCD] = {}, sum_count[2][CBM_XCD] = {};  // each XCD's run of sets and of rows in sum_items
+    int64_t sum_longest[2] = {};         // entries of the longest set and of the longest row
+
     // ---- device arrays (owned) ---------------------------------------------------
     int device = -1;
     bool on_device = false;
@@ -118,6 +145,11 @@ struct cbm_handle {
     uint32_t* d_block_cols = nullptr;
     float* d_block_w = nullptr;  // column weight (d^-1/2) times CBM_BLOCK_UP beside each of block_cols (handles built with self-loops)
     uint32_t* d_block_masks = nullptr;
+    CbmSumItem* d_sum_items = nullptr;
+    uint32_t* d_sum_entries = nullptr;
+    float* d_sum_w = nullptr;            // d_j^-1/2 beside a column, 1 beside a sum (handles built with self-loops)
+    mutable std::mutex sum_mutex;        // held while the two launches of a chunk of columns are enqueued, and for the list below
+    mutable std::vector<CbmSumScratch> sum_scratch;
     mutable float* d_scratch = nullptr;  // num_slots x scratch_k floats, sized on first use
     mutable int64_t scratch_k = 0;
 
@@ -168,6 +200,13 @@ void cbm_launch_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t
 // the launch before the segments on a handle with hub blocks
 void cbm_launch_hub_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* scratch, int64_t ld_scratch, bool weighted,
                            void* stream);
+// Products through shared sums (cbm_sums.hip): one of the two launches over k <= lds columns (sums at S, lds floats apart), and the
+// array for the sums of a stream's products (nullptr: none to be had; the caller holds h->sum_mutex).
+void cbm_launch_sum_chunk(const cbm_handle* h, bool rows, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
+                          float self_w, float* S, int64_t lds, void* stream);
+float* cbm_sum_scratch(const cbm_handle* h, void* stream);
+cbm_status cbm_upload_sums(cbm_handle* h);
+void cbm_release_sums(cbm_handle* h);
 // scratch of cbm_spmm_noalloc: one static array per GPU
 constexpr int64_t CBM_STATIC_SCRATCH_FLOATS = 16 * 1024 * 1024;  // 64 MiB
 inline size_t cbm_static_scratch_bytes() { return (size_t)CBM_STATIC_SCRATCH_FLOATS * sizeof(float); }

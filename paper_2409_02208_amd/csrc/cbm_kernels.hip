@@ -768,7 +768,7 @@ cbm_status cbm_upload(cbm_handle* h) {
     };
     cbm_status st = CBM_OK;
     if ((st = up_paths()) != CBM_OK || (st = up(&h->d_dinv, h->dinv)) != CBM_OK || (st = up(&h->d_rinv, h->rinv)) != CBM_OK ||
-        (st = up_blocks()) != CBM_OK) {
+        (st = up_blocks()) != CBM_OK || (st = cbm_upload_sums(h)) != CBM_OK) {
         cbm_release_device(h);
         if (cur != dev) hipSetDevice(cur);
         return st;
@@ -821,6 +821,7 @@ void cbm_release_device(cbm_handle* h) {
     if (h->d_block_cols) hipFree(h->d_block_cols);
     if (h->d_block_w) hipFree(h->d_block_w);
     if (h->d_block_masks) hipFree(h->d_block_masks);
+    cbm_release_sums(h);
     h->d_blocks = nullptr;
     h->d_block_rows = h->d_block_cols = h->d_block_masks = nullptr;
     h->d_block_w = nullptr;
@@ -940,6 +941,48 @@ cbm_status launch_blocked(const cbm_handle* h, const float* X, int64_t ldx, int3
 }
 }  // namespace
 
+namespace {
+// The product through shared sums: as many columns at a time as the array of sums holds, in goes of about equal width and of whole cache
+// lines.  *taken = false: nothing was enqueued.
+cbm_status launch_sums(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
+                       float self_w, hipStream_t stream, float* static_sums, bool* taken) {
+    *taken = false;
+    if (ldx >= (int64_t)1 << 30 || ldy >= (int64_t)1 << 30) return CBM_OK;  // the kernels hold strides in 32 bits
+    std::lock_guard<std::mutex> lock(h->sum_mutex);  // both launches of a chunk follow each other on their stream
+    float* sums = static_sums ? static_sums : cbm_sum_scratch(h, stream);
+    if (!sums) return CBM_OK;
+    *taken = true;
+    int64_t most = cbm_sum_columns(h->num_sums);
+    if (static_sums) most = std::min<int64_t>(most, CBM_STATIC_SCRATCH_FLOATS / h->num_sums & ~(int64_t)31);
+    const int64_t goes = (k + most - 1) / most;
+    const int32_t width = (int32_t)(((k + goes - 1) / goes + 31) & ~(int64_t)31);
+    if (h->profiling) {
+        for (void* e : h->prof_events) hipEventDestroy((hipEvent_t)e);
+        h->prof_events.clear();
+        h->prof_records.clear();
+    }
+    const bool wcol = mode == 1 || mode == 2;
+    const int64_t set_entries = h->sum_items[(size_t)h->num_sums].start, row_entries = (int64_t)h->sum_entries.size() - set_entries;
+    for (int64_t c = 0; c < k; c += width) {
+        const int32_t kc = (int32_t)std::min<int64_t>(width, k - c);
+        const int64_t rowb = 4 * (int64_t)kc, per_delta = rowb + 4 + (wcol ? 4 : 0);
+        for (int rows = 0; rows < 2; ++rows) {
+            cbm_launch_record rec{};
+            rec.kind = 6;
+            rec.per_xcd = 1;
+            rec.level = rows + 1;
+            rec.tasks = rows ? h->m : h->num_sums;
+            rec.deltas = rows ? row_entries : set_entries;
+            rec.algorithmic_bytes = rec.deltas * per_delta + rec.tasks * rowb;
+            ProfScope ps(h, stream, rec);
+            cbm_launch_sum_chunk(h, rows, X + c, ldx, kc, Y + c, ldy, mode, rw, self_w, sums, width, stream);
+        }
+    }
+    HIP_TRY(hipGetLastError(), CBM_ERR_HIP);
+    return CBM_OK;
+}
+}  // namespace
+
 cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
                               CbmEpilogue epi, float self_weight, void* stream_, bool static_scratch) {
     hipStream_t stream = (hipStream_t)stream_;
@@ -954,6 +997,11 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         return launch_blocked(h, X, ldx, k, Y, ldy, epi, self_weight, stream);
     }
 
+    if (h->num_sums > 0 && !static_scratch) {
+        bool taken = false;
+        const cbm_status st = launch_sums(h, X, ldx, k, Y, ldy, (int)epi, epi == CBM_EPI_MEAN ? h->d_rinv : h->d_dinv, self_weight, stream, nullptr, &taken);
+        if (st != CBM_OK || taken) return st;
+    }
     // row blocks need no scratch; the limits of the static one are those of the paths all the same
     const bool in_blocks = h->in_row_blocks();
     const int64_t ld_scratch = ((int64_t)k + 3) & ~(int64_t)3;
@@ -971,7 +1019,15 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
                 cbm_set_error_detail("cbm_spmm_noalloc", msg);
                 return CBM_ERR_UNSUPPORTED;
             }
+        }
+        if (h->noalloc_slots > 0 || h->num_sums > 0)
             if (const cbm_status st = static_scratch_address(cur, &scratch); st != CBM_OK) return st;
+        if (h->num_sums > 0) {
+            bool taken = false;
+            const cbm_status st = launch_sums(h, X, ldx, k, Y, ldy, (int)epi, epi == CBM_EPI_MEAN ? h->d_rinv : h->d_dinv, self_weight, stream, scratch, &taken);
+            if (st != CBM_OK || taken) return st;
+        }
+        if (h->noalloc_slots > 0) {
             if (h->num_slots > 0 && h->num_slots * ld_scratch > CBM_STATIC_SCRATCH_FLOATS) {
                 // hub blocks can need a little more scratch than the limit goes by: the columns in as many goes as that takes
                 const int32_t chunk = (int32_t)(CBM_STATIC_SCRATCH_FLOATS / h->num_slots & ~(int64_t)3);

@@ -1,0 +1,269 @@
+"""Products through shared sums against the oracle: every epilogue, widths around the lane groups and the chunk of 128 columns, strided and
+misaligned operands, values that are not finite, several streams, threads and captures at a time, and the call that allocates nothing."""
+import threading
+
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import cbm_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5  # of a row's largest value, as for the paths: sums of 32-bit terms, a row's own column less than ten times over
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    import paper_2409_02208_amd as cbm
+
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    return torch, cbm
+
+
+@pytest.fixture(autouse=True)
+def force(monkeypatch):
+    monkeypatch.setenv("CBM_SHARED_SUMS", "1")
+    monkeypatch.setenv("CBM_ROW_BLOCKS", "0")
+
+
+def _err(got, ref, scale_from=None):
+    d = np.abs(got.astype(np.float64) - ref).max(axis=1)
+    s = np.abs(ref if scale_from is None else scale_from).max(axis=1)
+    assert np.all(d[s == 0] == 0)
+    return float((d[s > 0] / s[s > 0]).max()) if np.any(s > 0) else 0.0
+
+
+def _kinds(torch, cbm, h, call):
+    cbm.cbm_profile_enable(h, True)
+    call()
+    torch.cuda.synchronize()
+    kinds = [r["kind"] for r in cbm.cbm_profile_read(h)]
+    cbm.cbm_profile_enable(h, False)
+    return kinds
+
+
+@pytest.fixture(scope="module")
+def graph():
+    return wl.make_graph("collaboration", n=3000)
+
+
+@pytest.mark.parametrize("loops", [False, True])
+@pytest.mark.parametrize("k", [1, 7, 31, 32, 33, 64, 65, 100, 128, 129, 130, 257, 300])
+def test_sums_of_whole_numbers_are_exact(env, graph, k, loops):
+    torch, cbm = env
+    g = graph
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=loops)
+    X = wl.integer_features(g.n, k, 3)
+    Xd, Y = torch.from_numpy(X).cuda(), torch.full((g.n, k), float("nan"), device="cuda")
+    kinds = _kinds(torch, cbm, h, lambda: cbm.cbm_spmm(h, Xd, Y))
+    assert kinds == [6, 6]
+    ref = orc.spmm_csr(g.rowptr, g.colidx, X) + (X if loops else 0)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref)
+    cbm.cbm_spmm_noalloc(h, Xd, Y.fill_(float("nan")))
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("layout", ["dense", "strided", "misaligned"])
+@pytest.mark.parametrize("k", [16, 47, 96, 128, 160])
+def test_every_epilogue(env, graph, k, layout):
+    torch, cbm = env
+    g = graph
+    hn = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=True)
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx)
+    X = wl.gaussian_features(g.n, k, 5)
+    pad, off = {"dense": (0, 0), "strided": (5, 0), "misaligned": (4, 1)}[layout]
+    Xd = torch.zeros((g.n, k + pad), device="cuda")[:, off:off + k]
+    Xd.copy_(torch.from_numpy(X))
+    room = torch.full((g.n, k + pad), float("nan"), device="cuda")
+    Y = room[:, off:off + k]
+
+    def run(fn, *args):
+        room.fill_(float("nan"))
+        fn(*args, Xd, Y)
+        torch.cuda.synchronize()
+        got = room.cpu().numpy()
+        assert np.isnan(np.delete(got, np.arange(off, off + k), axis=1)).all(), "wrote outside the columns"
+        return got[:, off:off + k]
+
+    norm = orc.spmm_csr_normalized(g.rowptr, g.colidx, X)
+    plain = orc.spmm_csr(g.rowptr, g.colidx, X)
+    assert _err(run(cbm.cbm_spmm_normalized, hn), norm) <= TOL
+    assert _err(run(cbm.cbm_spmm_normalized_relu, hn), np.maximum(norm, 0), norm) <= TOL
+    assert _err(run(cbm.cbm_spmm_mean, h), orc.spmm_csr_mean(g.rowptr, g.colidx, X)) <= TOL
+    assert _err(run(cbm.cbm_spmm_gin, h, 0.5), plain + 1.5 * X.astype(np.float64)) <= TOL
+    assert _err(run(cbm.cbm_spmm_gin, hn, 0.5), plain + 2.5 * X.astype(np.float64)) <= TOL
+    assert _err(run(cbm.cbm_spmm, h), plain) <= TOL
+
+
+def test_directed_graph_and_its_transpose(env):
+    """Sets whose rows are not their columns: a directed graph in which groups of nodes point at the same nodes."""
+    torch, cbm = env
+    rng = np.random.default_rng(4)
+    n, k = 1500, 40
+    rows = [set() for _ in range(n)]
+    for _ in range(200):
+        members, also = rng.choice(n, 14, replace=False), rng.choice(n, 3, replace=False)
+        for r in members:
+            rows[r] |= set(members.tolist()) | set(also.tolist())
+    rows = [np.array(sorted(r - {i} if i % 3 else r), dtype=np.int32) for i, r in enumerate(rows)]
+    rowptr = np.concatenate(([0], np.cumsum([len(r) for r in rows]))).astype(np.int64)
+    colidx = np.concatenate(rows).astype(np.int32)
+    X, G = (torch.from_numpy(wl.gaussian_features(n, k, s)).cuda() for s in (1, 2))
+    Y, Z = torch.empty_like(X), torch.empty_like(X)
+    h = cbm.cbm_build(n, n, rowptr, colidx, add_self_loops=True)
+    ht = cbm.cbm_build(n, n, rowptr, colidx, add_self_loops=True, transpose=True)
+    assert set(_kinds(torch, cbm, h, lambda: cbm.cbm_spmm_normalized(h, X, Y))) == {6}
+    assert set(_kinds(torch, cbm, ht, lambda: cbm.cbm_spmm_normalized(ht, G, Z))) == {6}
+    assert _err(Y.cpu().numpy(), orc.spmm_csr_normalized(rowptr, colidx, X.cpu().numpy())) <= TOL
+    left, right = float((Y.double() * G.double()).sum()), float((X.double() * Z.double()).sum())
+    assert abs(left - right) <= 1e-5 * float((Y.double() * G.double()).abs().sum())
+
+
+@pytest.mark.parametrize("op", ["normalized", "gin", "spmm", "mean"])
+def test_values_that_are_not_finite_are_summed_as_they_stand(env, graph, op):
+    """A sum that holds a row's own column more often than the row does is no place for an infinity less itself."""
+    torch, cbm = env
+    g, k = graph, 50
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=op == "normalized")
+    X = wl.gaussian_features(g.n, k, 8)
+    X[3, 0], X[700, 33], X[41, 5], X[42, 5], X[900, 49] = np.inf, -np.inf, np.inf, -np.inf, np.nan
+    with np.errstate(invalid="ignore"):
+        plain = np.add.reduceat(np.vstack([X[g.colidx], np.zeros((1, k))]), np.minimum(g.rowptr[:-1], len(g.colidx)), axis=0).astype(np.float64)
+        plain[np.diff(g.rowptr) == 0] = 0
+        ref = {"normalized": plain + X, "gin": plain + 1.25 * X, "spmm": plain, "mean": plain}[op]
+    Xd, Y = torch.from_numpy(X).cuda(), torch.empty((g.n, k), device="cuda")
+    call = {"normalized": cbm.cbm_spmm_normalized, "gin": lambda *a: cbm.cbm_spmm_gin(a[0], 0.25, *a[1:]), "spmm": cbm.cbm_spmm, "mean": cbm.cbm_spmm_mean}[op]
+    call(h, Xd, Y)
+    torch.cuda.synchronize()
+    got = Y.cpu().numpy()
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref))
+    clean = np.where(np.isfinite(X), X, 0).astype(np.float32)
+    other = torch.empty_like(Y)
+    call(h, torch.from_numpy(clean).cuda(), other)
+    torch.cuda.synchronize()
+    ok = np.isfinite(ref)
+    assert np.allclose(got[ok], other.cpu().numpy()[ok], rtol=1e-5, atol=1e-4)
+
+
+def test_streams_threads_and_captures_at_a_time(env, graph):
+    """Products of one handle overlap freely: each stream and each capture has sums of its own, and what finds none takes the paths."""
+    torch, cbm = env
+    g, k = graph, 64
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=True)
+    Xs = [torch.from_numpy(wl.gaussian_features(g.n, k, s)).cuda() for s in range(12)]
+    want = []
+    for X in Xs:
+        Y = torch.empty_like(X)
+        cbm.cbm_spmm_normalized(h, X, Y)
+        torch.cuda.synchronize()
+        want.append(Y)
+    close = lambda a, b: float((a - b).abs().max()) <= 1e-5 * float(b.abs().max())
+    # more streams than the handle has arrays for: the last ones run on the paths
+    streams = [torch.cuda.Stream() for _ in Xs]
+    Ys = [torch.full_like(X, float("nan")) for X in Xs]
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for s, X, Y in zip(streams, Xs, Ys):
+            with torch.cuda.stream(s):
+                cbm.cbm_spmm_normalized(h, X, Y)
+    torch.cuda.synchronize()
+    assert all(close(a, b) for a, b in zip(Ys, want))
+    assert sum(torch.equal(a, b) for a, b in zip(Ys, want)) >= 7
+    # host threads on one stream: the two launches of a product stay together
+    errors = []
+
+    def work(i):
+        try:
+            for _ in range(20):
+                cbm.cbm_spmm_normalized(h, Xs[i], Ys[i])
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    for Y in Ys:
+        Y.fill_(float("nan"))
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors and all(torch.equal(a, b) for a, b in zip(Ys[:4], want))
+
+
+def test_captured_products_replay_beside_others(env, graph):
+    torch, cbm = env
+    g, k = graph, 64
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=True)
+    Xs = [torch.from_numpy(wl.gaussian_features(g.n, k, s)).cuda() for s in range(3)]
+    Ys = [torch.empty_like(X) for X in Xs]
+    graphs = []
+    for X, Y in zip(Xs[:2], Ys[:2]):     # no product before the first capture
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            cbm.cbm_spmm_normalized(h, X, Y)
+    side = [torch.cuda.Stream() for _ in range(2)]
+    for it in range(4):
+        for i, X in enumerate(Xs):
+            X.copy_(torch.from_numpy(wl.gaussian_features(g.n, k, 10 + 3 * it + i)))
+            Ys[i].fill_(float("nan"))
+        torch.cuda.synchronize()
+        for _ in range(5):
+            for s, gr in zip(side, graphs):
+                with torch.cuda.stream(s):
+                    gr.replay()
+            cbm.cbm_spmm_normalized(h, Xs[2], Ys[2])
+        torch.cuda.synchronize()
+        for X, Y in zip(Xs, Ys):
+            Z = torch.empty_like(X)
+            cbm.cbm_spmm_normalized(h, X, Z)
+            torch.cuda.synchronize()
+            assert torch.equal(Y, Z)
+    assert _err(Ys[0].cpu().numpy(), orc.spmm_csr_normalized(g.rowptr, g.colidx, Xs[0].cpu().numpy())) <= TOL
+
+
+def test_columns_in_goes(env, monkeypatch):
+    """More sets than the arrays of sums have room for beside a wide X: the columns go through in several goes, the same sums."""
+    torch, cbm = env
+    n, k = 150000, 300
+    members = np.random.default_rng(2).permutation(n).reshape(-1, 6)   # 25,000 cliques of six: 32 MiB hold 256 columns of sums
+    src, dst = (np.concatenate([members[:, i] for i in range(6) for j in range(6) if i < j]), np.concatenate([members[:, j] for i in range(6) for j in range(6) if i < j]))
+    rowptr, colidx = wl.graphs.csr_from_edges(n, src, dst)
+    h = cbm.cbm_build(n, n, rowptr, colidx, add_self_loops=True)
+    X = torch.from_numpy(wl.integer_features(n, k, 1)).cuda()
+    Y, Z = torch.empty_like(X), torch.empty_like(X)
+    assert _kinds(torch, cbm, h, lambda: cbm.cbm_spmm(h, X, Y)) == [6] * 4
+    cbm.cbm_spmm_noalloc(h, X, Z)
+    sums = torch.zeros(len(members), k, device="cuda").index_add_(0, torch.from_numpy(np.argsort(members.reshape(-1)) // 6).cuda(), X)
+    want = sums[torch.from_numpy(np.argsort(members.reshape(-1)) // 6).cuda()]
+    assert torch.equal(Y, want) and torch.equal(Z, want)
+
+
+def test_nothing_is_allocated(env, graph):
+    torch, cbm = env
+    g = graph
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx)
+    X = torch.from_numpy(wl.integer_features(g.n, 200, 1)).cuda()
+    Y, Z = torch.empty_like(X), torch.empty_like(X)
+    cbm.cbm_spmm_noalloc(h, X[:, :8], Z[:, :8])  # (the kernels' code is on the GPU before memory is compared)
+    cbm.cbm_spmm(h, X, Y)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    cbm.cbm_spmm_noalloc(h, X, Z)
+    cbm.cbm_spmm(h, X, Y)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] == free and torch.equal(Y, Z)
+
+
+@pytest.mark.parametrize("name,taken", [("collaboration", True), ("citation", False), ("rmat", False)])
+def test_the_rule_takes_what_it_should(env, monkeypatch, name, taken):
+    torch, cbm = env
+    monkeypatch.delenv("CBM_SHARED_SUMS")
+    g = wl.make_graph(name, **{"collaboration": dict(n=20000), "citation": dict(n=5000, p_in=1.6e-3, p_out=8e-5), "rmat": dict(scale=14)}[name])
+    h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=True)
+    X = torch.from_numpy(wl.gaussian_features(g.n, 64, 1)).cuda()
+    Y = torch.empty_like(X)
+    assert (6 in _kinds(torch, cbm, h, lambda: cbm.cbm_spmm_normalized(h, X, Y))) == taken
+    assert _err(Y.cpu().numpy(), orc.spmm_csr_normalized(g.rowptr, g.colidx, X.cpu().numpy())) <= TOL
