@@ -1055,6 +1055,14 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
     // (the chunk index is the slow grid dimension): half the bytes per gathered row, so twice the rows of X stay in
     // L2 (k = 256, 512: 5 % faster).  With a partly filled last chunk, walking the entries again costs more than that.
     if (lanes == 64 && k % 128 == 0) lanes = 32;
+    // So does one whose last chunk of 256 would be at most half full: groups of 64 lanes walk it with the other half idle (k = 320: R-MAT scale
+    // 18 1127 -> 915 us, 60,000 nodes of the citation recipe 80 -> 69; k = 301 1270 -> 1083 and 87 -> 83; k = 500 would lose 8 %).
+    if (lanes == 64 && k > 256 && (k - 1) % 256 < 128) lanes = 32;
+    // Where X is far larger than the caches, slabs of 64 columns keep twice as many of its popular rows in them again, at the price of one
+    // more walk over the entries: at two million rows k = 128 pays (R-MAT scale 21, 32 edges a node 3993 -> 3785 us, 8 edges 1627 -> 1609; citation
+    // recipe of 2.5 million nodes 1154 -> 1112; at scale 20 1681 / 1690) and k = 256 does not (8025 / 7951, 3238 / 3284); an odd multiple
+    // of 64 has a chunk half empty otherwise and pays from a million rows on (k = 192 2853 -> 2530; at scale 16 it would lose 23 %).
+    if (aligned && k > 64 && k % 64 == 0 && ((k == 128 && h->n >= (1 << 21)) || (k % 128 == 64 && h->n >= (1 << 20)))) lanes = 16;
     const int mode = (int)epi;
     const Variant var = aligned ? pick_lanes<false>(lanes, mode) : pick_lanes<true>(lanes, mode);
     if (h->profiling) {
