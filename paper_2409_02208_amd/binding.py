@@ -59,17 +59,19 @@ class cbm_launch_record(C.Structure):
 
 
 _LIB = None
+_F32 = None  # torch.float32, known once the library is loaded
 
 
 def _lib():
-    global _LIB
+    global _LIB, _F32
     if _LIB is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is not built: run `python -m paper_2409_02208_amd.build`")
         # PyTorch ships its own HIP runtime.  It must be in the process before libcbm.so is loaded, so that
         # the library binds to that same runtime: device pointers and streams are only meaningful within one.
-        import torch  # noqa: F401
+        import torch
 
+        _F32 = torch.float32
         lib = C.CDLL(LIB_PATH)
         vp, i64, i32, f32p = C.c_void_p, C.c_int64, C.c_int32, C.c_void_p
         lib.cbm_build.argtypes = [i64, i64, vp, vp, C.POINTER(cbm_build_opts), C.POINTER(vp)]
@@ -101,18 +103,33 @@ def _check(status: int, where: str):
         raise CbmError(status, where)
 
 
-def _stream_ptr(stream):
-    if stream is None:
-        import torch
+def _current_stream():
+    """The raw handle of PyTorch's current stream on the current device, without the stream object that `current_stream()` makes first (1 us of a
+    small product's 9)."""
+    import torch
 
-        return torch.cuda.current_stream().cuda_stream
-    return getattr(stream, "cuda_stream", stream)
+    global _current_stream
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        _current_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+    else:
+        torch.cuda.current_stream()  # (initialises the runtime)
+        _current_stream = lambda: raw(device())  # noqa: E731
+    return _current_stream()
+
+
+def _stream_ptr(stream):
+    return _current_stream() if stream is None else getattr(stream, "cuda_stream", stream)
 
 
 def _dev_f32(t, name):
-    if not (t.is_cuda and t.dtype.is_floating_point and t.element_size() == 4 and t.dim() == 2 and t.stride(1) == 1):
+    """(address, leading dimension, rows, columns) of a matrix, each attribute asked for once: a small product's time is this code."""
+    strides = t.stride()
+    if not (t.is_cuda and t.dtype is _F32 and len(strides) == 2 and strides[1] == 1):
         raise ValueError(f"{name} must be a 2-D fp32 device tensor with unit column stride")
-    return t.data_ptr(), t.stride(0) if t.shape[0] > 1 else max(t.stride(0), t.shape[1])
+    rows, cols = t.shape
+    ld = strides[0]
+    return t.data_ptr(), ld if rows > 1 else max(ld, cols), rows, cols
 
 
 class Handle:
@@ -155,11 +172,14 @@ def cbm_build(m: int, n: int, rowptr: np.ndarray, colidx: np.ndarray, *, alpha: 
 
 
 def _product(fn_name, h: Handle, X, Y, stream):
-    xp, ldx = _dev_f32(X, "X")
-    yp, ldy = _dev_f32(Y, "Y")
-    if X.shape[1] != Y.shape[1]:
+    lib = _LIB or _lib()
+    xp, ldx, _, k = _dev_f32(X, "X")
+    yp, ldy, _, ky = _dev_f32(Y, "Y")
+    if k != ky:
         raise ValueError("X and Y must have the same number of columns")
-    _check(getattr(_lib(), fn_name)(h.ptr, xp, ldx, X.shape[1], yp, ldy, _stream_ptr(stream)), fn_name)
+    status = getattr(lib, fn_name)(h.ptr, xp, ldx, k, yp, ldy, _stream_ptr(stream))
+    if status:
+        raise CbmError(status, fn_name)
     return Y
 
 
@@ -184,11 +204,12 @@ def cbm_spmm_mean(h: Handle, X, Y, stream=None):
 
 
 def cbm_spmm_gin(h: Handle, eps: float, X, Y, stream=None):
-    xp, ldx = _dev_f32(X, "X")
-    yp, ldy = _dev_f32(Y, "Y")
-    if X.shape[1] != Y.shape[1]:
+    lib = _LIB or _lib()
+    xp, ldx, _, k = _dev_f32(X, "X")
+    yp, ldy, _, ky = _dev_f32(Y, "Y")
+    if k != ky:
         raise ValueError("X and Y must have the same number of columns")
-    _check(_lib().cbm_spmm_gin(h.ptr, float(eps), xp, ldx, X.shape[1], yp, ldy, _stream_ptr(stream)), "cbm_spmm_gin")
+    _check(lib.cbm_spmm_gin(h.ptr, float(eps), xp, ldx, k, yp, ldy, _stream_ptr(stream)), "cbm_spmm_gin")
     return Y
 
 
@@ -197,14 +218,13 @@ def cbm_reserve(h: Handle, max_k: int):
 
 
 def cbm_dense_matmul(A, B, Cout, stream=None):
-    ap, lda = _dev_f32(A, "A")
-    bp, ldb = _dev_f32(B, "B")
-    cp, ldc = _dev_f32(Cout, "C")
-    M, K = A.shape
-    if B.shape[0] != K or Cout.shape != (M, B.shape[1]):
+    lib = _LIB or _lib()
+    ap, lda, M, K = _dev_f32(A, "A")
+    bp, ldb, kb, N = _dev_f32(B, "B")
+    cp, ldc, mc, nc = _dev_f32(Cout, "C")
+    if kb != K or mc != M or nc != N:
         raise ValueError("shape mismatch")
-    _check(_lib().cbm_dense_matmul(M, B.shape[1], K, ap, lda, bp, ldb, cp, ldc, _stream_ptr(stream)),
-           "cbm_dense_matmul")
+    _check(lib.cbm_dense_matmul(M, N, K, ap, lda, bp, ldb, cp, ldc, _stream_ptr(stream)), "cbm_dense_matmul")
     return Cout
 
 
@@ -213,16 +233,17 @@ def cbm_gcn2_workspace_bytes(h: Handle, f_in: int, hidden: int, f_out: int) -> i
 
 
 def cbm_gcn2_forward(h: Handle, X, W0, W1, out, workspace, stream=None):
+    lib = _LIB or _lib()
+    operands = []
     for t, name in ((X, "X"), (W0, "W0"), (W1, "W1"), (out, "out")):
-        _dev_f32(t, name)
+        operands.append(_dev_f32(t, name))
         if not t.is_contiguous():
             raise ValueError(f"{name} must be densely packed")
-    f_in, hidden, f_out = X.shape[1], W0.shape[1], W1.shape[1]
-    if W0.shape[0] != f_in or W1.shape[0] != hidden or out.shape != (X.shape[0], f_out):
+    (xp, _, n, f_in), (w0, _, r0, hidden), (w1, _, r1, f_out), (op, _, no, fo) = operands
+    if r0 != f_in or r1 != hidden or no != n or fo != f_out:
         raise ValueError("shape mismatch")
-    _check(_lib().cbm_gcn2_forward(h.ptr, X.data_ptr(), f_in, W0.data_ptr(), hidden, W1.data_ptr(), f_out,
-                                   out.data_ptr(), workspace.data_ptr(), workspace.numel() * workspace.element_size(),
-                                   _stream_ptr(stream)), "cbm_gcn2_forward")
+    _check(lib.cbm_gcn2_forward(h.ptr, xp, f_in, w0, hidden, w1, f_out, op, workspace.data_ptr(), workspace.numel() * workspace.element_size(),
+                                _stream_ptr(stream)), "cbm_gcn2_forward")
     return out
 
 
