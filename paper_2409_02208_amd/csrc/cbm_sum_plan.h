@@ -27,7 +27,8 @@ public:
         : m(m_), rowptr(rowptr_), colidx(colidx_), holds_own(holds_own_) {}
 
     // Gathered rows of X or of a set's sum per entry of the matrix, from `count` evenly spread rows: what whole neighbourhoods
-    // would give, before sets of different rows get in each other's way.
+    // would give, before sets of different rows get in each other's way.  A few million steps of looking at entries have to do: where
+    // neighbourhoods are so large that they are spent early, the rows looked at by then speak for the rest.
     double sample(int64_t count) {
         covered.assign((size_t)rowptr[m], 0);
         sets_of.assign((size_t)m, 0);
@@ -35,6 +36,7 @@ public:
         double gathers = 0, entries = 0;
         const int64_t step = std::max<int64_t>(1, m / count);
         for (int64_t u = 0; u < m; u += step) {
+            if (w.steps > kSampleSteps) break;
             std::vector<Found> found;
             propose(u, true, w, found);
             double left = (double)(rowptr[u + 1] - rowptr[u]);
@@ -113,6 +115,7 @@ public:
 private:
     static constexpr int64_t kLongestRow = 2048;  // entries of a row that takes part
     static constexpr size_t kLeastSet = 4, kMostSet = 512;
+    static constexpr int64_t kSampleSteps = 1 << 22;
     static constexpr int64_t kLeastGain = 2;      // gathered rows that a set has to save
     struct Found {
         std::vector<int32_t> cols, rows;
@@ -160,6 +163,7 @@ private:
         for (int64_t p = ub; p < ue; ++p) {
             const int32_t v = colidx[p];
             if (w.mine[p - ub] || v == u || (!all && v < u)) continue;
+            if (all && w.steps > kSampleSteps) return;
             const int64_t vb = rowptr[v], ve = rowptr[v + 1];
             if (ve - vb > kLongestRow) continue;
             const int64_t back = find_entry(v, (int32_t)u);
