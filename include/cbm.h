@@ -91,7 +91,9 @@ typedef enum {
  *                let the products run in row blocks: one walk over the columns of
  *                128 alike rows, on the matrix cores, in one launch.  The tree and
  *                its counters stay what they are; the device then holds the blocks
- *                only, and bytes_cbm counts them.  Where every row is stored in
+ *                only, and bytes_cbm counts them (a small matrix whose rows are all
+ *                stored in full keeps these beside its blocks or sums, and the width of
+ *                a product decides which it runs on).  Where every row is stored in
  *                full, rows long enough to be split share their popular columns in
  *                such blocks too (num_tasks and bytes_cbm count what is left of
  *                them, bytes_cbm also the blocks).  On a square matrix whose rows

@@ -81,6 +81,10 @@ constexpr int64_t kSumSample = 256;      // rows looked at first
 constexpr double kSumMargin = 0.8;       // of the paths' modelled time
 constexpr double kSumBlockMargin = 1.1;  // of the row blocks' (collaboration recipe, k = 64: 10,000 nodes, models level, 22.6 -> 14.9 us; 2,500
                                          // nodes, this one 1.9 times the other, 13.7 -> 15.1)
+// What row blocks and shared sums of small matrices really take of their modelled time (row blocks of 1,024 nodes 13.2 us and measured 9.1, of
+// 5,000 21 and 18; shared sums of 5,000 nodes 39 and 16, of 10,000 34 and 15): the rows as they stand may take less (cbm_flat.hip)
+constexpr double kFlatBlockMargin = 0.7;
+constexpr double kFlatSumMargin = 0.45;
 constexpr size_t kSumWindow = 256;       // items that are put in order of length among themselves
 constexpr int64_t kPathChoices[] = {16, 32, 64, 128, 256};
 
@@ -1262,6 +1266,20 @@ cbm_status Builder::emit(int32_t nrounds) {
         h->comb.insert(h->comb.end(), rcomb[r].begin(), rcomb[r].end());
     }
     h->stats.num_split_rows = split_rows;
+    h->flat = nrounds == 1 && !h->levels[0].by_xcd && std::all_of(h->parent.begin(), h->parent.end(), [](int32_t y) { return y < 0; });
+    h->flat_long = 0;
+    h->flat_rich = false;
+    if (h->flat) {
+        const CbmLevel& R = h->levels[0];
+        int64_t longs = h->seg_deltas;
+        for (int64_t i = 0; i < R.task_count; ++i) {
+            const int64_t len = (int64_t)(h->tasks[R.task_begin + i].len_flags & CBM_TASK_LEN_MASK) - 1;  // (less the marker)
+            if (len <= CBM_FLAT_SHORT) break;
+            ++h->flat_long;
+            longs += len;
+        }
+        h->flat_rich = longs > 0 && 4 * longs >= h->seg_deltas + R.deltas;
+    }
     if (!h->hub_blocks) h->noalloc_slots = h->num_slots;
     return CBM_OK;
 }
@@ -2017,7 +2035,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     // alike rows on the matrix cores is modelled cheaper than the rounds of paths, the products run that way.
     // (CBM_ROW_BLOCKS: 0 = never, 1 = whenever the matrix is square and the policy automatic, 2 = as by default, on host-only handles too.)
     const long want_blocks = env_clamped("CBM_ROW_BLOCKS", -1, -1, 2);
-    double blocks_us = 0;
+    double blocks_us = 0, sums_us = 0;
     if (B.auto_depth && !exact_tree && !h->hub_blocks && want_blocks != 0 && m == n && m > 0 && (want_blocks >= 1 || !(o.flags & CBM_FLAG_HOST_ONLY))) {
         const double limit = kBlockMargin * product_us;
         const int32_t most = *std::max_element(h->rownnz.begin(), h->rownnz.end());  // a block needs its longest row's columns
@@ -2048,7 +2066,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     if (B.verbose && h->hub_blocks) std::fprintf(stderr, "[cbm_build] shared sums: products do without\n");
     if (B.auto_depth && !exact_tree && !h->hub_blocks && want_sums != 0 && m == n && m > 0 && (want_sums == 1 || want_blocks != 1) &&
         (want_sums >= 1 || !(o.flags & CBM_FLAG_HOST_ONLY))) {
-        const double limit = h->row_blocks.empty() ? kSumMargin * product_us : std::min(kSumMargin * product_us, kSumBlockMargin * blocks_us);
+        const double limit = std::min(kSumMargin * product_us, h->row_blocks.empty() ? 1e300 : kSumBlockMargin * blocks_us);
         std::vector<uint8_t> holds_own((size_t)m, 1);
         if (!h->square_self_loops)
             parallel_chunks(B.nthreads, m, 4096, [&](int64_t x0, int64_t x1, int) {
@@ -2061,6 +2079,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
             double gathers = (double)h->sum_entries.size();
             for (const CbmSumItem& it : h->sum_items) gathers += it.own != 0;
             const double us = B.shared_sums_cost(gathers, (double)h->num_sums, (double)(h->sum_longest[0] + h->sum_longest[1]));
+            sums_us = us;
             if (B.verbose) std::fprintf(stderr, "[cbm_build] shared sums: model %.1f us (paths: %.1f us)\n", us, product_us);
             if (want_sums != 1 && us >= limit) {
                 h->num_sums = 0;
@@ -2072,10 +2091,16 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
         B.lap("shared sums");
     }
 
+    s.nnz = B.nnz;
+    // (the narrowest product is where the rows as they stand do best)
+    if (B.auto_depth && !exact_tree && h->flat_rich && h->num_slots == 0 && want_blocks != 1 && want_sums != 1 && (h->in_row_blocks() || h->num_sums > 0)) {
+        const double us = h->num_sums > 0 ? kFlatSumMargin * sums_us : kFlatBlockMargin * blocks_us;
+        if (cbm_flat_waves(h, 8, 32) <= CBM_FLAT_MOST_WAVES && cbm_flat_us(h, 32, 8) < us) h->other_us = us;
+    }
+
     // ---- counters (Properties 1 and 2) -----------------------------------------------------------
     s.m = m;
     s.n = n;
-    s.nnz = B.nnz;
     int32_t depth = 0;
     for (int64_t x = 0; x < m; ++x) {
         depth = std::max(depth, h->level[x]);
@@ -2094,7 +2119,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     // (a host-only handle counts its work lists; row blocks are all that a device handle with them uploads)
     const int64_t block_bytes = 4 * (int64_t)(h->block_rows.size() + h->block_cols.size() + h->block_masks.size()) +
                                 (int64_t)sizeof(CbmBlock) * (int64_t)h->row_blocks.size();
-    const bool blocks_only = h->in_row_blocks() && !(o.flags & CBM_FLAG_HOST_ONLY);
+    const bool blocks_only = h->in_row_blocks() && h->other_us == 0 && !(o.flags & CBM_FLAG_HOST_ONLY);
     s.bytes_cbm = 4 * (int64_t)h->dinv.size() + (blocks_only || h->hub_blocks ? block_bytes : 0);
     if (!blocks_only)
         s.bytes_cbm += 4 * (int64_t)(h->stream.size() + h->internal_rows.size()) + (int64_t)sizeof(CbmTask) * (int64_t)(h->tasks.size() + h->comb.size());

@@ -35,6 +35,10 @@ constexpr uint32_t CBM_ENTRY_INDEX_MASK = 0x1fffffffu;
 constexpr uint32_t CBM_BUNDLE_SLOT_SHIFT = 26;
 constexpr uint32_t CBM_BUNDLE_INDEX_MASK = 0x03ffffffu;
 constexpr int32_t CBM_BUNDLE_ROWS = 4;  // most rows in a bundled path (a power of two)
+// Small products of flat handles (cbm_flat.hip): rows of up to so many entries have a group of lanes each, longer ones and segments a wave, and a
+// product takes this way up to so many waves.
+constexpr int64_t CBM_FLAT_SHORT = 32;
+constexpr int64_t CBM_FLAT_MOST_WAVES = 40960;
 constexpr int CBM_XCD = 8;  // accelerator complex dies of an MI355X; workgroup (linear id) b runs on XCD b mod 8
 
 struct CbmLevel {
@@ -109,6 +113,11 @@ struct cbm_handle {
     int64_t seg_begin[CBM_XCD] = {}, seg_count[CBM_XCD] = {};  // segment work items in tasks[], per column range
     int64_t seg_deltas = 0;        // delta entries gathered by the segment launch
     int64_t seg_longest = 0;       // entries of the longest segment
+    bool flat = false;             // every row is stored in full: one round of single rows, longest first, and segments
+    int64_t flat_long = 0;         // how many of the rows have more than CBM_FLAT_SHORT entries
+    bool flat_rich = false;        // a quarter of the entries or more are theirs or segments'
+    double other_us = 0;           // > 0: products run in row blocks or through shared sums, in about this time, unless the rows as they stand
+                                   // (none of them split) take less: the device holds both
     bool bundled = false;          // some round's paths are emitted as bundles: delta columns are 26-bit in this handle
     cbm_stats_t stats{};
 
@@ -193,13 +202,28 @@ cbm_status cbm_device_deltas(int device, int64_t m, const int64_t* rowptr, const
                              std::vector<int32_t>* nplus, std::vector<int32_t>* nminus, std::vector<int64_t>* dptr,
                              std::vector<uint32_t>* dcol);
 cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
-                              CbmEpilogue epi, float self_weight, void* stream, bool static_scratch = false);
+                              CbmEpilogue epi, float self_weight, void* stream, bool static_scratch = false, int32_t k_rule = 0);
+// (k_rule: the columns of the whole product where this is one of several goes, so that all of them add in the same order)
 // the product's one launch on a handle with row blocks (cbm_blocks.hip)
 void cbm_launch_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
                        float self_w, void* stream);
 // the launch before the segments on a handle with hub blocks
 void cbm_launch_hub_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* scratch, int64_t ld_scratch, bool weighted,
                            void* stream);
+// Segments and / or rows of a handle whose rows are all stored in full, for products small enough to be bound by latency (cbm_flat.hip):
+// lanes per group and entry, 0 if this product is not for it.
+int cbm_flat_lanes(const cbm_handle* h, int32_t k);
+inline int64_t cbm_flat_waves(const cbm_handle* h, int lanes, int64_t k) {  // of such a launch, chunks of 4 lanes columns each their own
+    const int64_t shorts = h->levels[0].task_count - h->flat_long;
+    return ((int64_t)h->tasks.size() - shorts + (shorts * lanes + 63) / 64) * ((k + 4 * lanes - 1) / (4 * lanes));
+}
+void cbm_launch_flat(const cbm_handle* h, bool segments, bool rows, int lanes, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
+                     float* scratch, int64_t ld_scratch, int mode, const float* rw, float self_w, bool aligned, void* stream);
+// Their modelled time: a launch, the longest row's batches of eight loads in each of its groups, and the gathers at L2's rate, whole cache lines of
+// them (communities of 5,000 nodes, k = 128 8.1 us; 5,000 nodes of the collaboration recipe, k = 128 15.4; 1,200 nodes, k = 200 12.4).
+inline double cbm_flat_us(const cbm_handle* h, int64_t k, int lanes) {
+    return 4.0 + 0.25 * (double)h->levels[0].longest * lanes / 512.0 + (double)h->stats.nnz * 4.0 * (double)(k < 32 ? 32 : k) / 12.0e6;
+}
 // Products through shared sums (cbm_sums.hip): one of the two launches over k <= lds columns (sums at S, lds floats apart), and the
 // array for the sums of a stream's products (nullptr: none to be had; the caller holds h->sum_mutex).
 void cbm_launch_sum_chunk(const cbm_handle* h, bool rows, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,

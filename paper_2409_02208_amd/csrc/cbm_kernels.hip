@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "cbm_internal.h"
+#include "cbm_rows.h"
 
 #define HIP_TRY(call, status)                                      \
     do {                                                          \
@@ -58,84 +59,6 @@ cbm_status static_scratch_address(int device, float** out) {
     return CBM_OK;
 }
 
-// Four columns of a row: what one lane holds.
-struct alignas(16) Vec4 {
-    float v[4];
-};
-typedef float float4a __attribute__((ext_vector_type(4)));
-
-// Which four columns a lane holds, and how it moves them.
-// RAGGED = false: k is a multiple of 4 and every row starts on a 16-byte boundary; lane l of a group holds the
-// consecutive columns 4l .. 4l+3 of the group's column chunk: one aligned 128-bit access.
-// RAGGED = true: any k, leading dimension and base address; lane l holds columns l, l + LANES, l + 2 LANES,
-// l + 3 LANES of the chunk, so every access is a 32-bit one that the group's lanes make to consecutive words.
-template <bool RAGGED, int LANES>
-__device__ __forceinline__ Vec4 ld_row(const float* row, int c0, int k) {
-    Vec4 r;
-    if (!RAGGED) {
-        const float4a t = *reinterpret_cast<const float4a*>(row + c0);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) r.v[c] = t[c];
-    } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) r.v[c] = c0 + c * LANES < k ? row[c0 + c * LANES] : 0.0f;
-    }
-    return r;
-}
-// Streaming store: rows of Y and partial sums are written once and not re-read by the same launch, so
-// they should not displace the gathered rows of X from L2.
-template <bool RAGGED, int LANES>
-__device__ __forceinline__ void st_row(float* row, int c0, int k, const Vec4& x) {
-    if (!RAGGED) {
-        float4a t;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) t[c] = x.v[c];
-        __builtin_nontemporal_store(t, reinterpret_cast<float4a*>(row + c0));
-    } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if (c0 + c * LANES < k) __builtin_nontemporal_store(x.v[c], row + c0 + c * LANES);
-    }
-}
-// first column of lane `sl` in column chunk `chunk` (a chunk = 4 LANES columns either way)
-template <bool RAGGED, int LANES>
-__device__ __forceinline__ int first_column(int chunk, int sl) {
-    return RAGGED ? chunk * 4 * LANES + sl : (chunk * LANES + sl) * 4;
-}
-
-// MODE 0: Y = M X (M = the compressed matrix).
-// MODE 1: Y = D^-1/2 M D^-1/2 X with M = A v I (the normalised adjacency).  MODE 2: MODE 1 then max(., 0).
-// MODE 3: Y = D^-1 M X (mean over each row's entries: the GraphSAGE mean aggregator).
-// MODE 4: Y = M X + s X (s = 1 + eps: the GIN aggregator).
-// Column weights multiply gathered rows, row weights the stored row; the self term of MODE 4 is the
-// row's own X row, fetched by its marker entry like any gathered row.
-// A row that ANOTHER work item is compressed against (INTERNAL) is written as the bare running sum,
-// because that work item continues from it (the row scale belongs to the update step, Section 2.2);
-// cbm_finish_kernel applies the row weight / self term to those rows once every round is done.
-template <int MODE>
-struct Mode {
-    static constexpr bool wcol = MODE == 1 || MODE == 2;
-    static constexpr bool wrow = MODE == 1 || MODE == 2 || MODE == 3;
-    static constexpr bool relu = MODE == 2;
-    static constexpr bool self = MODE == 4;
-    static constexpr bool weights = wcol || wrow;
-};
-
-// out = finish(acc): acc (+ self_w * own X row) (* row weight) (then ReLU)
-template <bool RAGGED, int LANES, int MODE>
-__device__ __forceinline__ void store_row(float* row, int c0, int k, Vec4 acc, bool finish, float w, const Vec4& own,
-                                          float self_w) {
-    if (finish) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if (Mode<MODE>::self) acc.v[c] = fmaf(self_w, own.v[c], acc.v[c]);
-            if (Mode<MODE>::wrow) acc.v[c] *= w;
-            if (Mode<MODE>::relu) acc.v[c] = fmaxf(acc.v[c], 0.0f);
-        }
-    }
-    st_row<RAGGED, LANES>(row, c0, k, acc);
-}
-
 // One work item = one path of the compression tree (or one segment of a split row): start from
 // the parent's row, walk the entry stream; a delta entry gathers a row of X, a marker entry stores
 // the running sum as a finished row of Y and the walk goes on from the same registers.
@@ -150,11 +73,6 @@ __device__ __forceinline__ void store_row(float* row, int c0, int k, Vec4 acc, b
 // Some launches map workgroups to work items per XCD: workgroup b runs on XCD b mod 8 and takes its
 // items from that XCD's block of the task list -- the segments of one column range of X, or one share
 // of a round whose work items were put in graph-locality order.
-struct CbmSegMap {
-    int64_t begin[CBM_XCD];
-    int64_t count[CBM_XCD];
-    int use;
-};
 
 // Waves per SIMD the register allocation is held to: 4 with batches of 8 rows, 8 with batches of 2 --
 // one less for the few variants that would otherwise spill registers.
@@ -759,7 +677,7 @@ cbm_status cbm_upload(cbm_handle* h) {
         return CBM_OK;
     };
     auto up_paths = [&]() -> cbm_status {
-        if (h->in_row_blocks()) return CBM_OK;
+        if (h->in_row_blocks() && h->other_us == 0) return CBM_OK;
         cbm_status ps = CBM_OK;
         if ((ps = up(&h->d_tasks, h->tasks)) != CBM_OK || (ps = up(&h->d_comb, h->comb)) != CBM_OK ||
             (ps = up(&h->d_stream, h->stream)) != CBM_OK || (ps = up(&h->d_internal, h->internal_rows)) != CBM_OK)
@@ -984,7 +902,7 @@ cbm_status launch_sums(const cbm_handle* h, const float* X, int64_t ldx, int32_t
 }  // namespace
 
 cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
-                              CbmEpilogue epi, float self_weight, void* stream_, bool static_scratch) {
+                              CbmEpilogue epi, float self_weight, void* stream_, bool static_scratch, int32_t k_rule) {
     hipStream_t stream = (hipStream_t)stream_;
     int cur = -1;
     HIP_TRY(hipGetDevice(&cur), CBM_ERR_HIP);
@@ -997,13 +915,18 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         return launch_blocked(h, X, ldx, k, Y, ldy, epi, self_weight, stream);
     }
 
-    if (h->num_sums > 0 && !static_scratch) {
+    // every row stored in full, and few of them: segments and rows side by side, each shared by the groups of a wave (cbm_flat.hip)
+    const int32_t k_whole = k_rule > 0 ? k_rule : k;
+    const bool others = h->num_sums > 0 || h->in_row_blocks();  // (these leave the rows as they stand alone unless other_us says which is faster)
+    int flat_lanes = h->flat_rich && (!others || h->other_us > 0) ? cbm_flat_lanes(h, k_whole) : 0;
+    if (flat_lanes && others && cbm_flat_us(h, k_whole, flat_lanes) >= h->other_us) flat_lanes = 0;
+    if (h->num_sums > 0 && !flat_lanes && !static_scratch) {
         bool taken = false;
         const cbm_status st = launch_sums(h, X, ldx, k, Y, ldy, (int)epi, epi == CBM_EPI_MEAN ? h->d_rinv : h->d_dinv, self_weight, stream, nullptr, &taken);
         if (st != CBM_OK || taken) return st;
     }
     // row blocks need no scratch; the limits of the static one are those of the paths all the same
-    const bool in_blocks = h->in_row_blocks();
+    const bool in_blocks = h->in_row_blocks() && !flat_lanes;
     const int64_t ld_scratch = ((int64_t)k + 3) & ~(int64_t)3;
     float* scratch = nullptr;
     if (static_scratch) {
@@ -1020,9 +943,9 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
                 return CBM_ERR_UNSUPPORTED;
             }
         }
-        if (h->noalloc_slots > 0 || h->num_sums > 0)
+        if (h->noalloc_slots > 0 || (h->num_sums > 0 && !flat_lanes))
             if (const cbm_status st = static_scratch_address(cur, &scratch); st != CBM_OK) return st;
-        if (h->num_sums > 0) {
+        if (h->num_sums > 0 && !flat_lanes) {
             bool taken = false;
             const cbm_status st = launch_sums(h, X, ldx, k, Y, ldy, (int)epi, epi == CBM_EPI_MEAN ? h->d_rinv : h->d_dinv, self_weight, stream, scratch, &taken);
             if (st != CBM_OK || taken) return st;
@@ -1032,7 +955,7 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
                 // hub blocks can need a little more scratch than the limit goes by: the columns in as many goes as that takes
                 const int32_t chunk = (int32_t)(CBM_STATIC_SCRATCH_FLOATS / h->num_slots & ~(int64_t)3);
                 for (int32_t c = 0; c < k; c += chunk)
-                    if (const cbm_status st = cbm_launch_product(h, X + c, ldx, std::min(chunk, k - c), Y + c, ldy, epi, self_weight, stream_, true);
+                    if (const cbm_status st = cbm_launch_product(h, X + c, ldx, std::min(chunk, k - c), Y + c, ldy, epi, self_weight, stream_, true, k);
                         st != CBM_OK)
                         return st;
                 return CBM_OK;
@@ -1128,7 +1051,8 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         // the method's bytes only: the partial sums of split rows are this implementation's overhead
         rec.algorithmic_bytes = h->seg_deltas * per_delta;
         ProfScope ps(h, stream, rec);
-        (many(segments, h->seg_deltas, h->seg_longest) ? var.segments_many : var.segments)(ctx, CbmLevel{});
+        if (flat_lanes) cbm_launch_flat(h, true, !h->profiling, flat_lanes, X, ldx, k, Y, ldy, scratch, ld_scratch, mode, ctx.rw, self_weight, aligned, stream_);
+        else (many(segments, h->seg_deltas, h->seg_longest) ? var.segments_many : var.segments)(ctx, CbmLevel{});
     }
     for (size_t l = 0; l < h->levels.size(); ++l) {
         const CbmLevel& L = h->levels[l];
@@ -1143,7 +1067,9 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
             // per work item with a parent: the parent's row
             rec.algorithmic_bytes = L.deltas * per_delta + L.rows_written * per_row + L.parent_reads * rowb;
             ProfScope ps(h, stream, rec);
-            (many(L.task_count, L.deltas, L.longest) ? var.level_many : var.level)(ctx, L);
+            if (!flat_lanes) (many(L.task_count, L.deltas, L.longest) ? var.level_many : var.level)(ctx, L);
+            else if (segments == 0 || h->profiling)
+                cbm_launch_flat(h, false, true, flat_lanes, X, ldx, k, Y, ldy, scratch, ld_scratch, mode, ctx.rw, self_weight, aligned, stream_);
         }
         if (L.comb_count > 0) {
             cbm_launch_record rec{};
