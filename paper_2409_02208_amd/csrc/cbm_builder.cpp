@@ -86,6 +86,9 @@ constexpr double kSumBlockMargin = 1.1;  // of the row blocks' (collaboration re
 constexpr double kFlatBlockMargin = 0.7;
 constexpr double kFlatSumMargin = 0.45;
 constexpr size_t kSumWindow = 256;       // items that are put in order of length among themselves
+constexpr int64_t kIndexShareMinRows = 16384;  // (below, all of X is in L2 anyway)
+constexpr double kIndexShareMost = 0.9;        // R-MAT 1.0, citation recipe 0.7
+constexpr long kIndexShareBucket = 8;          // entries: rows this much alike stay in their order in shares of many rows
 constexpr int64_t kPathChoices[] = {16, 32, 64, 128, 256};
 
 long env_or(const char* name, long dflt) {
@@ -248,6 +251,9 @@ struct Builder {
     void transpose_matrix();
     std::vector<int32_t> loc;  // position of every row in a breadth-first walk of the graph (square matrices)
     void locality_order();
+    bool index_shares = false;  // loc is the rows' own order, for a handle whose rows are all stored in full
+    bool rows_share_by_index() const;
+    void index_order();
     std::vector<int64_t> optr;  // candidate edges bucketed by parent
     std::vector<int32_t> ochild, ow;
     bool device_candidates = false;  // run the candidate search on the GPU
@@ -379,6 +385,46 @@ void Builder::locality_order() {
             }
         }
     }
+}
+
+// Whether rows near each other in the matrix's own order hold the same columns: how many of the eight XCDs would gather a column if each had a
+// contiguous share of the rows, against shares dealt out at random.  (Counted on every few columns, over all rows.)
+// Contiguous shares, an eighth of the entries each, longest rows first inside: citation recipe, 170,000 nodes, k = 128 77 -> 69 us, k = 500 314 -> 292;
+// 60,000 nodes 28 -> 24.6; 19,717 nodes, k = 500 36.4 -> 30.7, k = 64 7.3 -> 6.8.  Where the order of the rows says nothing they change nothing (directed R-MAT scale 17, k = 128 97.3 /
+// 97.9), and small products of long rows do better by another way (cbm_flat.hip).
+bool Builder::rows_share_by_index() const {
+    if (m < kIndexShareMinRows) return false;
+    int64_t longs = 0, long_rows = 0;
+    for (int64_t x = 0; x < m; ++x)
+        if (rlen(x) > CBM_FLAT_SHORT) longs += rlen(x), ++long_rows;
+    if (4 * longs >= nnz && long_rows + (m - long_rows) / 2 <= CBM_FLAT_MOST_WAVES) return false;
+    const uint32_t every = (uint32_t)std::max<int64_t>(1, nnz >> 20);
+    std::vector<std::atomic<uint8_t>> near((size_t)n), far((size_t)n);  // the shares that hold a column
+    parallel_chunks(nthreads, m, 4096, [&](int64_t x0, int64_t x1, int) {
+        for (int64_t x = x0; x < x1; ++x) {
+            if (is_split(x)) continue;
+            const uint8_t here = (uint8_t)(1u << (rowptr[x] * CBM_XCD / std::max<int64_t>(1, nnz)));
+            const uint8_t there = (uint8_t)(1u << ((uint32_t)x * 2654435761u >> 29));
+            for (int64_t p = rowptr[x]; p < rowptr[x + 1]; ++p) {
+                const uint32_t c = (uint32_t)colidx[p];
+                if (every > 1 && c * 0x9e3779b1u % every) continue;
+                near[c].fetch_or(here, std::memory_order_relaxed);
+                far[c].fetch_or(there, std::memory_order_relaxed);
+            }
+        }
+    });
+    int64_t a = 0, b = 0;
+    for (int64_t c = 0; c < n; ++c) {
+        a += __builtin_popcount(near[c].load(std::memory_order_relaxed));
+        b += __builtin_popcount(far[c].load(std::memory_order_relaxed));
+    }
+    if (verbose) std::fprintf(stderr, "[cbm_build] columns on an XCD: %ld with contiguous shares of the rows, %ld with random ones\n", (long)a, (long)b);
+    return a <= kIndexShareMost * b;
+}
+void Builder::index_order() {
+    index_shares = true;
+    loc.resize((size_t)m);
+    for (int64_t x = 0; x < m; ++x) loc[x] = (int32_t)x;
 }
 
 void Builder::all_roots() {
@@ -1226,7 +1272,7 @@ cbm_status Builder::emit(int32_t nrounds) {
         for (auto& t : lt) round_entries += (t.len_flags & CBM_TASK_LEN_MASK);
         // worth it for rounds of long work items (protein: 8 % faster); rounds of short ones lose more to the
         // ragged tail of each XCD's block than they gain (and a graph without a tree has no such order at all)
-        if (by_locality && (int64_t)lt.size() >= 64 * CBM_XCD && round_entries >= locality_min * (int64_t)lt.size()) {
+        if (by_locality && (int64_t)lt.size() >= 64 * CBM_XCD && (index_shares || round_entries >= locality_min * (int64_t)lt.size())) {
             // neighbours in the graph next to each other, one contiguous share of the entries per XCD: what the
             // work items running on an XCD at one time gather overlaps, and stays in that XCD's L2
             std::stable_sort(lt.begin(), lt.end(), [&](const CbmTask& a, const CbmTask& b2) { return loc[a.row] < loc[b2.row]; });
@@ -1249,7 +1295,7 @@ cbm_status Builder::emit(int32_t nrounds) {
             const long share_mode = env_clamped("CBM_SHARE_SORT", -1, -1, 1 << 20);
             for (int j = 0; j < CBM_XCD; ++j) {
                 auto b = lt.begin() + (R.xcd_begin[j] - R.task_begin);
-                const long mode = share_mode >= 0 ? share_mode : (R.xcd_count[j] <= kShareSortItems ? 1 : kShareBucket);
+                const long mode = share_mode >= 0 ? share_mode : (R.xcd_count[j] <= kShareSortItems ? 1 : index_shares ? kIndexShareBucket : kShareBucket);
                 if (mode == 1)
                     std::stable_sort(b, b + R.xcd_count[j], longest_first);
                 else if (mode > 1)
@@ -2010,6 +2056,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
     B.tree_index();
     B.plan(best_len, &nrounds);
     if (tree && B.locality) B.locality_order();
+    else if (!tree && B.locality && B.rows_share_by_index()) B.index_order();
     cbm_stats_t& s = h->stats;
     std::memset(&s, 0, sizeof(s));
     // (CBM_HUB_BLOCKS: 0 = never, 2 = whatever they save, on host-only handles too, 3 = as by default, on host-only handles too)

@@ -47,3 +47,31 @@ def test_slabs_of_64_columns_of_a_large_x(env, n, ks):
         want[0] += X[at].sum(0)
         want[at] += X[0]
         assert torch.equal(Y, want), k
+
+
+@pytest.mark.parametrize("n,shuffled", [(16383, False), (16384, False), (70001, False), (20000, True)])
+def test_rows_shared_out_in_their_own_order(env, capfd, monkeypatch, n, shuffled):
+    """Rows whose neighbours in the matrix hold the same columns go to the XCDs in contiguous shares; every row is written once, whatever their order."""
+    torch, cbm = env
+    monkeypatch.setenv("CBM_VERBOSE", "1")
+    rng = np.random.default_rng(n)
+    src = rng.integers(0, n, 3 * n)
+    dst = np.clip(src + rng.integers(-40, 41, 3 * n), 0, n - 1)
+    if shuffled:
+        label = rng.permutation(n)
+        src, dst = label[src], label[dst]
+    rowptr, colidx = wl.graphs.csr_from_edges(n, src, dst)
+    h = cbm.cbm_build(n, n, rowptr, colidx, max_depth=1)
+    said = [ln.split() for ln in capfd.readouterr().err.splitlines() if "columns on an XCD" in ln]
+    assert len(said) == (n >= 16384) and all((int(s[5]) <= 0.9 * int(s[12])) != shuffled for s in said)
+    for k in (5, 64, 200):
+        X = wl.integer_features(n, k, 3)
+        Y = torch.full((n, k), float("nan"), device="cuda")
+        cbm.cbm_spmm(h, torch.from_numpy(X).cuda(), Y)
+        assert np.array_equal(Y.cpu().numpy().astype(np.float64), orc.spmm_csr(rowptr, colidx, X))
+        if k == 64:
+            cbm.cbm_profile_enable(h, True)
+            cbm.cbm_spmm(h, torch.from_numpy(X).cuda(), Y)
+            torch.cuda.synchronize()
+            assert [r["per_xcd"] for r in cbm.cbm_profile_read(h)] == [int(n >= 16384 and not shuffled)]
+            cbm.cbm_profile_enable(h, False)
