@@ -384,7 +384,8 @@ cbm_status launch16_nt(int64_t M, int N, int K, const float* A, int64_t lda, con
 // matrix; what lies beyond K is zeroed when used, rows beyond M are never stored).
 constexpr int WPB = 8;  // waves per block of the panel kernel
 
-template <int NT16>
+// RINGS: the groups of 16 k that a wave keeps in flight (panel_ring)
+template <int NT16, int RINGS>
 __global__ __launch_bounds__(64 * WPB) void cbm_gemm_panel_kernel(int64_t M, int N, int K, int Kp, const float* __restrict__ A, int64_t lda,
                                                              const float* __restrict__ B, int64_t ldb, int vec_b,
                                                              float* __restrict__ C, int64_t ldc) {
@@ -397,7 +398,7 @@ __global__ __launch_bounds__(64 * WPB) void cbm_gemm_panel_kernel(int64_t M, int
     const int lane = tid & 63;
     const int c = lane & 15;
     const int q = lane >> 4;
-    const int nkg = Kp / 16;  // groups of 16 k; Kp is a multiple of 64
+    const int nkg = Kp / 16;  // groups of 16 k, a multiple of RINGS
     const int64_t G = (M + 31) / 32;
     const int64_t nwaves = (int64_t)gridDim.x * WPB;
     const int64_t gw = (int64_t)blockIdx.x * WPB + wave;
@@ -553,24 +554,40 @@ __global__ __launch_bounds__(64 * WPB) void cbm_gemm_panel_kernel(int64_t M, int
                 else if (nkg % 8 == 0)
                     groups(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{}, g, g + 1, t, col0);
                 else
-                    groups(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{}, g, g + 1, t, col0);
+                    groups(std::integral_constant<int, 1>{}, std::integral_constant<int, RINGS>{}, g, g + 1, t, col0);
             } else if (NT16 > 2 && chunk == 2) {
                 if (nkg % 8 == 0)
                     groups(std::integral_constant<int, (NT16 > 2 ? 2 : 1)>{}, std::integral_constant<int, 8>{}, g, g + 1, t, col0);
                 else
-                    groups(std::integral_constant<int, (NT16 > 2 ? 2 : 1)>{}, std::integral_constant<int, 4>{}, g, g + 1, t, col0);
+                    groups(std::integral_constant<int, (NT16 > 2 ? 2 : 1)>{}, std::integral_constant<int, RINGS>{}, g, g + 1, t, col0);
             } else if (NT16 > 4 && chunk == 4) {
-                groups(std::integral_constant<int, (NT16 > 4 ? 4 : 1)>{}, std::integral_constant<int, 4>{}, g, g + 1, t, col0);
+                groups(std::integral_constant<int, (NT16 > 4 ? 4 : 1)>{}, std::integral_constant<int, RINGS>{}, g, g + 1, t, col0);
             } else {
-                groups(std::integral_constant<int, NT16>{}, std::integral_constant<int, 4>{}, g, g + 1, 0, col0);
+                groups(std::integral_constant<int, NT16>{}, std::integral_constant<int, RINGS>{}, g, g + 1, 0, col0);
             }
         }
         if (each > 0)
-            groups(std::integral_constant<int, NT16>{}, std::integral_constant<int, 4>{}, gwp * each, (gwp + 1) * each, 0, col0);
+            groups(std::integral_constant<int, NT16>{}, std::integral_constant<int, RINGS>{}, gwp * each, (gwp + 1) * each, 0, col0);
     }
 }
 
 inline bool wide_loads_of_b(int N, const float* B, int64_t ldb) { return N % 4 == 0 && ldb % 4 == 0 && ((uintptr_t)B & 15) == 0; }
+
+// Groups of 16 k that a wave of the panel kernel keeps in flight, and that its K loop is a multiple of: whichever of 4, 3, 5 and 7 pads K least
+// (132,534 x K . K x 47, us, with 4 always -> here: K = 48 18.2 -> 16.7, 80 25.4 -> 20.7, 96 26.0 -> 23.0, 100 27.1 -> 25.7, 144 33.3 -> 29.0; x 64: 80 29.9 -> 23.1,
+// 200 47.7 -> 44.7; 7 beside one tile would lose, 100 x 16 17.7 -> 18.4).
+inline int panel_ring(int K, int nt16) {
+    const int nkg = (K + 15) / 16;
+    int best = 4;
+    if (nt16 > 4) return best;  // (registers for no more than that beside so many tiles)
+    for (int r : {3, 5, 7})
+        if ((r < 7 || nt16 > 2) && (nkg + r - 1) / r * r < (nkg + best - 1) / best * best) best = r;
+    return best;
+}
+inline int panel_depth(int K, int nt16) {
+    const int ring = panel_ring(K, nt16);
+    return ((K + 15) / 16 + ring - 1) / ring * ring * 16;
+}
 
 // LDS bytes of the resident panel, or 0 if this product cannot take the panel kernel.
 inline size_t panel_lds_bytes(int N, int K, const float* A, int64_t lda, int* nt16) {
@@ -578,32 +595,46 @@ inline size_t panel_lds_bytes(int N, int K, const float* A, int64_t lda, int* nt
     if (!vec || N < 16) return 0;
     const int tiles = (N + 15) / 16, npanels = (tiles + 7) / 8;
     *nt16 = (tiles + npanels - 1) / npanels;  // panels of equal width, at most 128 columns
-    const int64_t Kp = ((int64_t)K + 63) / 64 * 64;
+    if (K > 4096) return 0;  // (no panel of that depth fits)
+    const int64_t Kp = panel_depth(K, *nt16);
     const size_t bytes = (size_t)Kp * (16 * *nt16 + 4) * sizeof(float);
     return bytes <= 160 * 1024 ? bytes : 0;
 }
 
-template <int NT16>
-cbm_status launch_panel(int64_t M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
+template <int NT16, int RINGS>
+cbm_status launch_panel_as(int64_t M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
                         size_t smem, hipStream_t stream) {
     static size_t lds_opt_in = 0;  // buffers above 64 KiB need the per-kernel opt-in; raised when a larger one comes
     if (smem > 64 * 1024 && smem > lds_opt_in) {
-        hipError_t e = hipFuncSetAttribute((const void*)cbm_gemm_panel_kernel<NT16>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        hipError_t e = hipFuncSetAttribute((const void*)cbm_gemm_panel_kernel<NT16, RINGS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) {
             cbm_set_error_detail("hipFuncSetAttribute(MaxDynamicSharedMemorySize)", hipGetErrorString(e));
             return CBM_ERR_HIP;
         }
         lds_opt_in = smem;
     }
-    const int Kp = (K + 63) / 64 * 64;
+    const int Kp = panel_depth(K, NT16);
     const int vec_b = wide_loads_of_b(N, B, ldb);
-    hipLaunchKernelGGL((cbm_gemm_panel_kernel<NT16>), dim3(256), dim3(64 * WPB), smem, stream, M, N, K, Kp, A, lda, B, ldb, vec_b, C, ldc);
+    hipLaunchKernelGGL((cbm_gemm_panel_kernel<NT16, RINGS>), dim3(256), dim3(64 * WPB), smem, stream, M, N, K, Kp, A, lda, B, ldb, vec_b, C, ldc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         cbm_set_error_detail("cbm_gemm_panel_kernel launch", hipGetErrorString(e));
         return CBM_ERR_HIP;
     }
     return CBM_OK;
+}
+
+template <int NT16>
+cbm_status launch_panel(int64_t M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
+                        size_t smem, hipStream_t stream) {
+    if constexpr (NT16 <= 4) {
+        const int ring = panel_ring(K, NT16);
+        if (ring == 3) return launch_panel_as<NT16, 3>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);
+        if (ring == 5) return launch_panel_as<NT16, 5>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);
+        if constexpr (NT16 > 2)
+            if (ring == 7) return launch_panel_as<NT16, 7>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);
+    }
+    return launch_panel_as<NT16, 4>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);
 }
 
 template <int NT, bool VEC>

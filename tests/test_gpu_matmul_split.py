@@ -192,3 +192,18 @@ def test_panel_kernel_on_any_b(env, monkeypatch, m, k, n):
         cbm.cbm_dense_matmul(Ad, Bd, C)
         torch.cuda.synchronize()
         assert np.array_equal(C.cpu().numpy().astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("k", [4, 16, 32, 36, 48, 64, 68, 80, 84, 96, 100, 112, 116, 128, 132, 144, 160, 176, 200, 240, 320])
+@pytest.mark.parametrize("n", [16, 32, 48, 64, 112])
+def test_depths_of_the_panel_kernel(env, monkeypatch, k, n):
+    """K of every remainder of the groups that a wave keeps in flight, with rows that leave a chunk: whole numbers, bit for bit."""
+    monkeypatch.setenv("CBM_GEMM_SPLIT", "0")
+    torch, cbm = env
+    gen = torch.Generator(device="cuda").manual_seed(k * 1000 + n)
+    for m in (8192, 8209):
+        A = torch.randint(-8, 9, (m, k), device="cuda", generator=gen).float()
+        B = torch.randint(-8, 9, (k, n), device="cuda", generator=gen).float()
+        C = torch.full((m, n), float("nan"), device="cuda")
+        cbm.cbm_dense_matmul(A, B, C)
+        assert torch.equal(C.double(), A.double() @ B.double()), (m, k, n)
