@@ -209,7 +209,8 @@ cbm_status cbm_build(int64_t m, int64_t n, const int64_t* rowptr, const int32_t*
  * A handle whose products take shared sums keeps an array of at most 32 MiB (128 columns of sums where
  * that is more) for each of up to eight streams and captures, the first from cbm_build on; the others are
  * allocated when a product first needs them, also under capture, and products for which there is none run
- * without shared sums.  Such products may overlap freely.
+ * without shared sums.  Such products may overlap freely; a stream may be destroyed once those it was
+ * given are done.
  * Per-launch profiling (cbm_profile_enable) records events and must be off during capture.
  */
 cbm_status cbm_spmm(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
