@@ -4,8 +4,8 @@
 // weights) to scratch memory; the second makes each row of Y from its sets' sums, the columns no set brings and, where the sets hold the
 // row's own column more or less often than the row does, its own row of X as often as that takes.  Both are gathers like those of the
 // paths, bound by the memory behind L2; what they gain is that there are fewer of them (collaboration recipe, 235,868 nodes: 1.8 million
-// rows read or written a product instead of 5.0 million, and no round waits for another but the second for the first: k = 128 333 -> 135 us,
-// 42 for the sets at 7.1 TB/s and 88 for the rows at 6.4; GIN, k = 64 191 -> 73; 20,000 nodes, k = 64 37 -> 18).
+// rows read or written a product instead of 5.0 million, and no round waits for another but the second for the first: k = 128 334 -> 136 us,
+// 48 for the sets at 6.1 TB/s behind L2 and 84 for the rows at 6.5; GIN, k = 64 191 -> 73; 20,000 nodes, k = 64 37 -> 18).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
