@@ -99,7 +99,11 @@ typedef enum {
  *                them, bytes_cbm also the blocks).  On a square matrix whose rows
  *                share whole column sets (the cliques of a collaboration network)
  *                the same model may sum each set once and make the rows of those
- *                sums; bytes_cbm counts these lists too.  A host-only handle has no
+ *                sums; bytes_cbm counts these lists too.  A row that does not hold its
+ *                own column is then its sets' sums less its own row of X as often as
+ *                they hold it, unless that is more than 32 times the largest other value
+ *                of a column: what rounding leaves of it stays below 2e-6 of the row's
+ *                terms, whatever value the row itself has.  A host-only handle has no
  *                blocks or shared sums: num_tasks and bytes_cbm are those of the
  *                paths.  The
  *                tree is cut into vertical paths, one work item each;

@@ -1700,6 +1700,7 @@ void Builder::shared_sums(const std::vector<uint8_t>& holds_own) {
     for (int64_t i = 0; i < m; ++i) {
         const int32_t x = rows[i];
         h->sum_items[ns + i] = {end, (uint32_t)len[x] | (holds_own[x] ? CBM_SUM_OWN : 0u), x, S.own[x]};
+        if (!holds_own[x]) h->sum_most_taken_off = std::max(h->sum_most_taken_off, -S.own[x]);
         end += (uint32_t)len[x];
     }
     h->sum_entries.resize(end);

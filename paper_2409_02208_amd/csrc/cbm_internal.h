@@ -84,7 +84,9 @@ inline int64_t cbm_sum_columns(int64_t num_sums) {
     const int64_t fit = ((int64_t)8 << 20) / (num_sums > 0 ? num_sums : 1) & ~(int64_t)127;
     return fit < 128 ? 128 : fit > 1024 ? 1024 : fit;
 }
-struct CbmSumScratch {  // num_sums x cbm_sum_columns floats of the products that one stream, or one capture on it, enqueues
+// Words beside a set's sums of k columns that hold the sizes of its values (cbm_sums.hip): one for each lane, a quarter of the columns at most.
+inline int64_t cbm_sum_sizes(int64_t k) { return k <= 32 ? 8 : k <= 64 ? 16 : (k + 127) / 128 * 32; }
+struct CbmSumScratch {  // cbm_sum_bytes of the products that one stream, or one capture on it, enqueues
     uint64_t stream, capture, thread;
     float* sums;
 };
@@ -138,6 +140,7 @@ struct cbm_handle {
     int64_t num_sums = 0;                // 0: none
     int64_t sum_begin[2][CBM_XCD] = {}, sum_count[2][CBM_XCD] = {};  // each XCD's run of sets and of rows in sum_items
     int64_t sum_longest[2] = {};         // entries of the longest set and of the longest row
+    int32_t sum_most_taken_off = 0;      // how often a row that does not hold its own column takes it off its sets' sums, at most
 
     // ---- device arrays (owned) ---------------------------------------------------
     int device = -1;
@@ -229,6 +232,10 @@ inline double cbm_flat_us(const cbm_handle* h, int64_t k, int lanes) {
 void cbm_launch_sum_chunk(const cbm_handle* h, bool rows, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
                           float self_w, float* S, int64_t lds, void* stream);
 float* cbm_sum_scratch(const cbm_handle* h, void* stream);
+bool cbm_sum_guarded(const cbm_handle* h, int mode, float self_w);  // whether the product keeps the sets' sizes beside their sums
+inline size_t cbm_sum_bytes(const cbm_handle* h) {
+    return (size_t)h->num_sums * cbm_sum_columns(h->num_sums) * sizeof(float) / 4 * (h->sum_most_taken_off > 0 ? 5 : 4);
+}
 cbm_status cbm_upload_sums(cbm_handle* h);
 void cbm_release_sums(cbm_handle* h);
 // scratch of cbm_spmm_noalloc: one static array per GPU

@@ -871,9 +871,14 @@ cbm_status launch_sums(const cbm_handle* h, const float* X, int64_t ldx, int32_t
     if (!sums) return CBM_OK;
     *taken = true;
     int64_t most = cbm_sum_columns(h->num_sums);
-    if (static_sums) most = std::min<int64_t>(most, CBM_STATIC_SCRATCH_FLOATS / h->num_sums & ~(int64_t)31);
+    if (static_sums) {  // (32 floats a set and more: 16 columns and their sizes always fit)
+        const int64_t room = CBM_STATIC_SCRATCH_FLOATS / h->num_sums;
+        const bool sizes = cbm_sum_guarded(h, mode, self_w);
+        for (most = std::min(most, room) & ~(int64_t)31; most > 0 && most + (sizes ? cbm_sum_sizes(most) : 0) > room;) most -= 32;
+        if (most == 0) most = 16;
+    }
     const int64_t goes = (k + most - 1) / most;
-    const int32_t width = (int32_t)(((k + goes - 1) / goes + 31) & ~(int64_t)31);
+    const int32_t width = (int32_t)std::min(((k + goes - 1) / goes + 31) & ~(int64_t)31, most);
     if (h->profiling) {
         for (void* e : h->prof_events) hipEventDestroy((hipEvent_t)e);
         h->prof_events.clear();

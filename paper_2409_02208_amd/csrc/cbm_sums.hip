@@ -9,14 +9,27 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <functional>
 #include <thread>
+#include <type_traits>
 
 #include "cbm_internal.h"
 
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+
+// Rows that do not hold their own column (A without self-loops) are made of sums that do, and what rounding takes from these is relative to the
+// row's own value, which the row's sum may be far below: own value 1e5, others near 1, 2e-4 of the sum; the type's lowest value, 0 instead of the sum.
+// So the sets' launch also writes the exponent of each set's second largest value in every column (a byte beside four), and a row whose own value, as
+// often as it is taken off, is more than kGuard times the largest of the others (or half as much: the exponent is all that is known of it) is put
+// together without it.  What is let through is off by 32 x 2^-24 = 2e-6 of the row's terms at most.  Rows put together again are waited for, and
+// sets have as few as four columns: with 16 the rows' launch takes 113 us instead of 83 on Gaussian features (235,868 nodes, k = 128), with 32 and 128
+// the same (79 where no row is looked at); of features with every other value zero 89, with 128 86.  Both launches 137 us instead of 127; 30,000 nodes,
+// k = 64 26 instead of 23.  (Rows that hold their own column are off by as much of a sum that it is part of.)
+constexpr float kGuard = 32.0f;
 
 // The four columns of a lane in the block's 4 LANES.  RAGGED = false: 4 sl .. 4 sl + 3, one 128-bit access; true: sl, sl + LANES, ..., 32-bit
 // accesses.
@@ -62,11 +75,53 @@ struct SumMap {
     uint32_t begin[CBM_XCD], count[CBM_XCD];
 };
 
+// What a row's others amount to, for rows that do not hold their own column (kGuard above): in the sets' launch the largest and the second largest value
+// of each column, in the rows' launch the largest of the single ones and, as packed exponents, of the sets' second largest.
+struct Sizes {
+    f4 first = {0.0f, 0.0f, 0.0f, 0.0f}, second = {0.0f, 0.0f, 0.0f, 0.0f};
+    ushort2v even = {0, 0}, odd = {0, 0};
+    __device__ __forceinline__ void add_to_set(const f4& x) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            second[c] = __builtin_amdgcn_fmed3f(first[c], second[c], fabsf(x[c]));
+            first[c] = fmaxf(first[c], fabsf(x[c]));
+        }
+    }
+    // exponents of the second largest ones, a byte for each column: 0 for zero, 1 for all others below 2^-125
+    __device__ __forceinline__ uint32_t packed() const {
+        uint32_t r = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) r |= (second[c] != 0.0f ? max(__float_as_uint(second[c]) >> 23 & 255u, 1u) : 0u) << (8 * c);
+        return r;
+    }
+    __device__ __forceinline__ void add_to_row(const f4& x, bool set, uint32_t exponents) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) first[c] = fmaxf(first[c], fabsf(set ? 0.0f : x[c]));
+        exponents = set ? exponents : 0u;
+        even = __builtin_elementwise_max(even, __builtin_bit_cast(ushort2v, exponents & 0x00ff00ffu));
+        odd = __builtin_elementwise_max(odd, __builtin_bit_cast(ushort2v, exponents >> 8 & 0x00ff00ffu));
+    }
+    __device__ __forceinline__ float others(int c) const {  // no more than the largest of them, no less than half of it
+        const uint32_t exponent = c % 2 ? odd[c / 2] : even[c / 2];
+        return fmaxf(first[c], __uint_as_float(exponent == 1 ? 1u : exponent << 23));
+    }
+};
+
+struct Rows {  // where the rows of X and the sums are
+    const float* X;
+    uint32_t ldx;
+    const float* S;
+    uint32_t lds;
+    const uint32_t* sizes;  // of the sets, this lane's
+    uint32_t ld_sizes;
+};
+
 // acc += sum over the entries of (weight times) the row of X, or the set's sum, that each names.  Entries come LANES at a time, the
-// next ones while these are worked on, and are broadcast inside the group; U rows are in flight at a time.
-template <bool RAGGED, int LANES, bool WEIGHTED, bool SETS, int U>
-__device__ __forceinline__ void walk(f4& acc, const uint32_t* __restrict__ es, const float* __restrict__ ws, uint32_t len, int sl, const float* X,
-                                     uint32_t ldx, const float* S, uint32_t lds, const Columns<RAGGED, LANES>& cols) {
+// next ones while these are worked on, and are broadcast inside the group; U rows are in flight at a time.  SIZED: the entries are a set's, whose
+// sizes are wanted.  SKIP: entry `skip` is left out.
+template <bool RAGGED, int LANES, bool WEIGHTED, bool SETS, bool SIZED, bool SKIP, int U>
+__device__ __forceinline__ void walk(f4& acc, Sizes& sizes, const uint32_t* __restrict__ es, const float* __restrict__ ws, uint32_t len, int sl,
+                                     const Rows& r, uint32_t skip, const Columns<RAGGED, LANES>& cols) {
     uint32_t e = (uint32_t)sl < len ? __builtin_nontemporal_load(es + sl) : 0u;
     float w = WEIGHTED && (uint32_t)sl < len ? __builtin_nontemporal_load(ws + sl) : 0.0f;
     for (uint32_t at = 0; at < len; at += LANES) {
@@ -83,9 +138,9 @@ __device__ __forceinline__ void walk(f4& acc, const uint32_t* __restrict__ es, c
             for (int u = 0; u < U; ++u) {
                 const uint32_t eu = (uint32_t)__shfl((int)e, b + u, LANES);
                 x[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-                if (b + u < n) {
+                if (b + u < n && !(SKIP && eu == skip)) {
                     const bool sum = SETS && (eu & CBM_SUM_BIT);
-                    x[u] = cols.load((sum ? S : X) + (uint64_t)(eu & ~CBM_SUM_BIT) * (sum ? lds : ldx));
+                    x[u] = cols.load((sum ? r.S : r.X) + (uint64_t)(eu & ~CBM_SUM_BIT) * (sum ? r.lds : r.ldx));
                 }
             }
 #pragma unroll
@@ -97,10 +152,51 @@ __device__ __forceinline__ void walk(f4& acc, const uint32_t* __restrict__ es, c
                 } else {
                     acc += x[u];
                 }
+                if (SIZED) sizes.add_to_set(x[u]);
             }
         }
         e = e1;
         w = w1;
+    }
+}
+
+// The same for a row whose others' sizes are wanted too.  These cost a batch of entries twice its instructions where sets are among them (30,000 nodes,
+// k = 64: 6 us more, waiting for the longest rows); sets come first, and batches without any do without.
+template <bool RAGGED, int LANES, int U0>
+__device__ __forceinline__ void walk_sized(f4& acc, Sizes& sizes, const uint32_t* __restrict__ es, uint32_t len, int sl, const Rows& r,
+                                           const Columns<RAGGED, LANES>& cols) {
+    uint32_t e = (uint32_t)sl < len ? __builtin_nontemporal_load(es + sl) : 0u;
+    for (uint32_t at = 0; at < len; at += LANES) {
+        const uint32_t e1 = at + LANES + sl < len ? __builtin_nontemporal_load(es + at + LANES + sl) : 0u;
+        const int n = (int)min((uint32_t)LANES, len - at);
+        const uint64_t group = ((1ull << LANES) - 1) << ((threadIdx.x & 63) / LANES * LANES);
+        const int sets = __popcll(__ballot(e & CBM_SUM_BIT) & group);
+        auto batch = [&](int b, auto mixed) {
+            constexpr bool MIXED = decltype(mixed)::value;
+            constexpr int U = MIXED ? U0 / 2 : U0;
+            f4 x[U];
+            uint32_t size[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t eu = (uint32_t)__shfl((int)e, b + u, LANES);
+                x[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+                size[u] = 0u;
+                if (b + u < n) {
+                    const bool sum = MIXED && (eu & CBM_SUM_BIT);
+                    x[u] = cols.load((sum ? r.S : r.X) + (uint64_t)(eu & ~CBM_SUM_BIT) * (sum ? r.lds : r.ldx));
+                    if (MIXED) size[u] = r.sizes[(uint64_t)(sum ? eu & ~CBM_SUM_BIT : 0u) * r.ld_sizes];  // (a column: any set's)
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                acc += x[u];
+                sizes.add_to_row(x[u], MIXED && b + u < sets, size[u]);
+            }
+        };
+        int b = 0;
+        for (; b < sets; b += U0 / 2) batch(b, std::true_type{});
+        for (; b < n; b += U0) batch(b, std::false_type{});
+        e = e1;
     }
 }
 
@@ -112,31 +208,54 @@ __device__ __forceinline__ int64_t item_of(const SumMap& map) {  // workgroup b 
     return i < map.count[xcd] ? (int64_t)map.begin[xcd] + i : -1;
 }
 
-template <bool RAGGED, int LANES, bool WEIGHTED, int U>
+template <bool RAGGED, int LANES, bool WEIGHTED, bool GUARD, int U>
 __global__ __launch_bounds__(256, 4) void cbm_sum_sets_kernel(const CbmSumItem* __restrict__ items, const SumMap map,
                                                               const uint32_t* __restrict__ entries, const float* __restrict__ ws,
-                                                              const float* __restrict__ X, uint32_t ldx, float* __restrict__ S, uint32_t lds, int k) {
+                                                              const float* __restrict__ X, uint32_t ldx, float* __restrict__ S, uint32_t lds,
+                                                              uint32_t* __restrict__ set_sizes, uint32_t ld_sizes, int k) {
     const int64_t t = item_of<LANES>(map);
     if (t < 0) return;
     const uint32_t start = items[t].start, len = items[t].len;
     const int sl = threadIdx.x % LANES;
     const Columns<RAGGED, LANES> cols(sl, k);
     f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    walk<RAGGED, LANES, WEIGHTED, false, U>(acc, entries + start, WEIGHTED ? ws + start : nullptr, len, sl, X, ldx, nullptr, 0, cols);
+    Sizes sizes;
+    walk<RAGGED, LANES, WEIGHTED, false, GUARD, false, U>(acc, sizes, entries + start, WEIGHTED ? ws + start : nullptr, len, sl,
+                                                          Rows{X, ldx, nullptr, 0, nullptr, 0}, 0, cols);
     cols.template store<true>(S + (uint64_t)t * lds, acc);
+    if (GUARD) set_sizes[(uint64_t)t * ld_sizes + blockIdx.y * LANES + sl] = sizes.packed();
+}
+
+// The sum over a row's entries with its sets' columns one by one, its own left out of them.
+template <bool RAGGED, int LANES, bool WEIGHTED>
+__device__ __forceinline__ f4 apart(const CbmSumItem* __restrict__ items, const uint32_t* __restrict__ entries, const float* __restrict__ ws,
+                                    uint32_t start, uint32_t len, uint32_t row, int sl, const Rows& r, const Columns<RAGGED, LANES>& cols) {
+    f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    Sizes none;
+    uint32_t i = start;
+    for (; i < start + len; ++i) {  // sets come first
+        const uint32_t e = entries[i];
+        if (!(e & CBM_SUM_BIT)) break;
+        const uint32_t first = items[e & ~CBM_SUM_BIT].start, n = items[e & ~CBM_SUM_BIT].len;
+        walk<RAGGED, LANES, WEIGHTED, false, false, true, 4>(acc, none, entries + first, WEIGHTED ? ws + first : nullptr, n, sl, r, row, cols);
+    }
+    walk<RAGGED, LANES, WEIGHTED, false, false, false, 4>(acc, none, entries + i, WEIGHTED ? ws + i : nullptr, start + len - i, sl, r, 0, cols);
+    return acc;
 }
 
 // MODE as for the paths: 0 M X, 1 D^-1/2 M D^-1/2 X, 2 = 1 then max(., 0), 3 D^-1 M X, 4 M X + s X.
-template <bool RAGGED, int LANES, int MODE, int U>
+template <bool RAGGED, int LANES, int MODE, bool GUARD, int U>
 __global__ __launch_bounds__(256, 4) void cbm_sum_rows_kernel(const CbmSumItem* __restrict__ items, const SumMap map,
                                                               const uint32_t* __restrict__ entries, const float* __restrict__ ws,
                                                               const float* __restrict__ X, uint32_t ldx, const float* __restrict__ S, uint32_t lds,
-                                                              float* __restrict__ Y, uint32_t ldy, const float* __restrict__ rw, float self_w, int k) {
+                                                              const uint32_t* __restrict__ set_sizes, uint32_t ld_sizes, float* __restrict__ Y,
+                                                              uint32_t ldy, const float* __restrict__ rw, float self_w, int k) {
     constexpr bool WEIGHTED = MODE == 1 || MODE == 2;
     const int64_t t = item_of<LANES>(map);
     if (t < 0) return;
     const CbmSumItem it = items[t];
     const uint32_t len = it.len & ~CBM_SUM_OWN;
+    const bool holds_own = it.len & CBM_SUM_OWN;
     const int sl = threadIdx.x % LANES;
     const Columns<RAGGED, LANES> cols(sl, k);
     const float w = MODE == 0 || MODE == 4 ? 1.0f : rw[it.row];
@@ -145,43 +264,41 @@ __global__ __launch_bounds__(256, 4) void cbm_sum_rows_kernel(const CbmSumItem* 
     f4 own = {0.0f, 0.0f, 0.0f, 0.0f};
     if (add_own) own = cols.load(mine);
     f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    walk<RAGGED, LANES, WEIGHTED, true, U>(acc, entries + it.start, WEIGHTED ? ws + it.start : nullptr, len, sl, X, ldx, S, lds, cols);
+    Sizes sizes;
+    const Rows from{X, ldx, S, lds, GUARD ? set_sizes + blockIdx.y * LANES + sl : nullptr, ld_sizes};
+    if constexpr (GUARD) walk_sized<RAGGED, LANES, U>(acc, sizes, entries + it.start, len, sl, from, cols);
+    else walk<RAGGED, LANES, WEIGHTED, true, false, false, U>(acc, sizes, entries + it.start, WEIGHTED ? ws + it.start : nullptr, len, sl, from, 0, cols);
     const float times = ((float)it.own + (MODE == 4 ? self_w : 0.0f)) * (WEIGHTED ? w : 1.0f);
     if (add_own)
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[c] = fmaf(times, own[c], acc[c]);
     if (it.own < 0) {
-        // The row's own column was summed more often than the row holds it and taken off again: right for finite sums only (an infinity
-        // less itself is NaN).  Where a sum is not finite the row is put together from its sets' columns, each once.
-        bool bad = false;
+        // The row's own column was summed more often than the row holds it and taken off again.  That is right for finite sums only (an
+        // infinity less itself is NaN), and where the row does not hold its own column at all, what rounding leaves of it has to be small beside
+        // what the row does hold (kGuard).  Otherwise the row is put together from its sets' columns, each once.
+        bool again[4], any = false;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) bad = bad || !(fabsf(acc[c]) < INFINITY);
-        const uint64_t group = (LANES == 64 ? ~0ull : ((1ull << LANES) - 1)) << ((threadIdx.x & 63) / LANES * LANES);
-        if (__ballot(bad) & group) {
-            f4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
-            auto add = [&](uint32_t entry, uint32_t place) {
-                const f4 x = cols.load(X + (uint64_t)entry * ldx);
-                const float v = WEIGHTED ? ws[place] : 1.0f;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) sum[c] = fmaf(v, x[c], sum[c]);
-            };
-            for (uint32_t i = it.start; i < it.start + len; ++i) {
-                const uint32_t e = entries[i];
-                if (e & CBM_SUM_BIT) {
-                    const CbmSumItem set = items[e & ~CBM_SUM_BIT];
-                    for (uint32_t j = set.start; j < set.start + set.len; ++j)
-                        if (entries[j] != (uint32_t)it.row) add(entries[j], j);
-                } else {
-                    add(e, i);
+        for (int c = 0; c < 4; ++c) {
+            again[c] = !(fabsf(acc[c]) < INFINITY);
+            if (GUARD && !holds_own && !again[c]) {
+                const float kept = MODE == 4 ? fabsf(self_w * own[c]) : 0.0f;
+                if (-(float)it.own * fabsf(own[c]) > kGuard * fmaxf(sizes.others(c), kept)) {
+                    if (sizes.others(c) == 0.0f) acc[c] = MODE == 4 ? self_w * own[c] : 0.0f;  // all others are zero
+                    else again[c] = true;
                 }
             }
-            const float once = ((it.len & CBM_SUM_OWN ? 1.0f : 0.0f) + (MODE == 4 ? self_w : 0.0f)) * (WEIGHTED ? w : 1.0f);
+            any = any || again[c];
+        }
+        const uint64_t group = (LANES == 64 ? ~0ull : ((1ull << LANES) - 1)) << ((threadIdx.x & 63) / LANES * LANES);
+        if (__ballot(any) & group) {
+            // (its place among the entries is read once more: two registers less beside the walk, 7 waves a SIMD where there would be 6: 139 -> 136 us at k = 128)
+            const volatile CbmSumItem* me = items + item_of<LANES>(map);
+            const f4 sum = apart<RAGGED, LANES, WEIGHTED>(items, entries, ws, me->start, me->len & ~CBM_SUM_OWN, (uint32_t)it.row, sl, from, cols);
+            const float once = ((holds_own ? 1.0f : 0.0f) + (MODE == 4 ? self_w : 0.0f)) * (WEIGHTED ? w : 1.0f);
             const f4 x = cols.load(mine);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (MODE == 4 || (it.len & CBM_SUM_OWN)) sum[c] = fmaf(once, x[c], sum[c]);
-                if (!(fabsf(acc[c]) < INFINITY)) acc[c] = sum[c];
-            }
+            for (int c = 0; c < 4; ++c)
+                if (again[c]) acc[c] = MODE == 4 || holds_own ? fmaf(once, x[c], sum[c]) : sum[c];
         }
     }
 #pragma unroll
@@ -198,6 +315,7 @@ struct Args {
     uint32_t ldx;
     float* S;
     uint32_t lds;
+    uint32_t* sizes;  // nullptr: no guard
     float* Y;
     uint32_t ldy;
     const float* rw;
@@ -206,7 +324,7 @@ struct Args {
     hipStream_t stream;
 };
 
-template <bool RAGGED, int LANES, int MODE>
+template <bool RAGGED, int LANES, int MODE, bool GUARD>
 void launch(const Args& a, bool rows) {
     constexpr int G = 64 / LANES;
     constexpr int U = 8;  // 4 waves a SIMD; 4 rows at 8 waves: 30,000 nodes, k = 64 26 us instead of 22, 235,868 nodes the same; 2 rows 31
@@ -218,22 +336,24 @@ void launch(const Args& a, bool rows) {
         most = std::max(most, map.count[j]);
     }
     const dim3 grid(CBM_XCD * ((most + 4 * G - 1) / (4 * G)), (a.k + 4 * LANES - 1) / (4 * LANES));
+    const uint32_t ld_sizes = (uint32_t)cbm_sum_sizes(a.k);
     if (rows)
-        hipLaunchKernelGGL((cbm_sum_rows_kernel<RAGGED, LANES, MODE, U>), grid, dim3(256), 0, a.stream, a.h->d_sum_items, map, a.h->d_sum_entries,
-                           a.h->d_sum_w, a.X, a.ldx, a.S, a.lds, a.Y, a.ldy, a.rw, a.self_w, a.k);
+        hipLaunchKernelGGL((cbm_sum_rows_kernel<RAGGED, LANES, MODE, GUARD, U>), grid, dim3(256), 0, a.stream, a.h->d_sum_items, map, a.h->d_sum_entries,
+                           a.h->d_sum_w, a.X, a.ldx, a.S, a.lds, a.sizes, ld_sizes, a.Y, a.ldy, a.rw, a.self_w, a.k);
     else
-        hipLaunchKernelGGL((cbm_sum_sets_kernel<RAGGED, LANES, MODE == 1, U>), grid, dim3(256), 0, a.stream, a.h->d_sum_items, map, a.h->d_sum_entries,
-                           a.h->d_sum_w, a.X, a.ldx, a.S, a.lds, a.k);
+        hipLaunchKernelGGL((cbm_sum_sets_kernel<RAGGED, LANES, MODE == 1, GUARD, U>), grid, dim3(256), 0, a.stream, a.h->d_sum_items, map,
+                           a.h->d_sum_entries, a.h->d_sum_w, a.X, a.ldx, a.S, a.lds, a.sizes, ld_sizes, a.k);
 }
 template <bool RAGGED, int LANES>
 void launch_mode(const Args& a, int mode, bool rows) {
-    if (!rows) return mode == 1 || mode == 2 ? launch<RAGGED, LANES, 1>(a, false) : launch<RAGGED, LANES, 0>(a, false);
+    const bool guard = a.sizes != nullptr;
+    if (!rows) return mode == 1 || mode == 2 ? launch<RAGGED, LANES, 1, false>(a, false) : guard ? launch<RAGGED, LANES, 0, true>(a, false) : launch<RAGGED, LANES, 0, false>(a, false);
     switch (mode) {
-        case 0: return launch<RAGGED, LANES, 0>(a, true);
-        case 1: return launch<RAGGED, LANES, 1>(a, true);
-        case 2: return launch<RAGGED, LANES, 2>(a, true);
-        case 3: return launch<RAGGED, LANES, 3>(a, true);
-        default: return launch<RAGGED, LANES, 4>(a, true);
+        case 0: return guard ? launch<RAGGED, LANES, 0, true>(a, true) : launch<RAGGED, LANES, 0, false>(a, true);
+        case 1: return launch<RAGGED, LANES, 1, false>(a, true);
+        case 2: return launch<RAGGED, LANES, 2, false>(a, true);
+        case 3: return guard ? launch<RAGGED, LANES, 3, true>(a, true) : launch<RAGGED, LANES, 3, false>(a, true);
+        default: return guard ? launch<RAGGED, LANES, 4, true>(a, true) : launch<RAGGED, LANES, 4, false>(a, true);
     }
 }
 template <bool RAGGED>
@@ -250,10 +370,15 @@ constexpr uint64_t kNobody = ~0ull;
 
 void cbm_launch_sum_chunk(const cbm_handle* h, bool rows, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
                           float self_w, float* S, int64_t lds, void* stream) {
-    const Args a{h, X, (uint32_t)ldx, S, (uint32_t)lds, Y, (uint32_t)ldy, rw, self_w, (int)k, (hipStream_t)stream};
+    uint32_t* sizes = cbm_sum_guarded(h, mode, self_w) ? reinterpret_cast<uint32_t*>(S + h->num_sums * lds) : nullptr;
+    const Args a{h, X, (uint32_t)ldx, S, (uint32_t)lds, sizes, Y, (uint32_t)ldy, rw, self_w, (int)k, (hipStream_t)stream};
     const bool aligned = k % 4 == 0 && ldx % 4 == 0 && ldy % 4 == 0 && ((uintptr_t)X & 15) == 0 && ((uintptr_t)Y & 15) == 0;
     if (aligned) launch_lanes<false>(a, mode, rows);
     else launch_lanes<true>(a, mode, rows);
+}
+
+bool cbm_sum_guarded(const cbm_handle* h, int mode, float self_w) {  // (the sum that a GIN layer makes holds 1 + eps times the row's own value)
+    return (mode == 0 || mode == 3 || mode == 4) && (float)h->sum_most_taken_off > (mode == 4 ? kGuard * std::fabs(self_w) : 0.0f);
 }
 
 // The array for the sums of products on this stream; nullptr if there is none and none can be had.  Products of different streams may
@@ -282,7 +407,7 @@ float* cbm_sum_scratch(const cbm_handle* h, void* stream_) {
         (void)hipGetLastError();
         return nullptr;
     }
-    const hipError_t err = hipMalloc((void**)&key.sums, (size_t)h->num_sums * cbm_sum_columns(h->num_sums) * sizeof(float));
+    const hipError_t err = hipMalloc((void**)&key.sums, cbm_sum_bytes(h));
     if (err != hipSuccess) (void)hipGetLastError();
     (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (err != hipSuccess) return nullptr;
@@ -304,7 +429,7 @@ cbm_status cbm_upload_sums(cbm_handle* h) {
         ok = up(&h->d_sum_w, w.data(), w.size() * sizeof(float));
     }
     CbmSumScratch first{kNobody, 0, 0, nullptr};
-    if (ok) ok = hipMalloc((void**)&first.sums, (size_t)h->num_sums * cbm_sum_columns(h->num_sums) * sizeof(float)) == hipSuccess;
+    if (ok) ok = hipMalloc((void**)&first.sums, cbm_sum_bytes(h)) == hipSuccess;
     if (!ok) {  // the paths do without
         (void)hipGetLastError();
         cbm_release_sums(h);

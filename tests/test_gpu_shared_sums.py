@@ -148,6 +148,92 @@ def test_values_that_are_not_finite_are_summed_as_they_stand(env, graph, op):
     assert np.allclose(got[ok], other.cpu().numpy()[ok], rtol=1e-5, atol=1e-4)
 
 
+LOWEST = float(np.finfo(np.float32).min)
+
+
+def _cliques(n, twice=False, size=20, seed=3):
+    """Random cliques without self-loops: node i is in 1 + i % 3 of them, or each node in two."""
+    rng = np.random.default_rng(seed)
+    src, dst = [], []
+    for r in range(2 if twice else 3):
+        who = rng.permutation(n) if twice else rng.permutation(np.flatnonzero(np.arange(n) % 3 >= r))
+        who = who[:len(who) // size * size].reshape(-1, size)
+        for i in range(size):
+            for j in range(i):
+                src.append(who[:, i])
+                dst.append(who[:, j])
+    return wl.graphs.csr_from_edges(n, np.concatenate(src), np.concatenate(dst))
+
+
+@pytest.fixture(scope="module")
+def cliques():
+    return _cliques(3000)
+
+
+@pytest.mark.parametrize("op", ["spmm", "mean", "gin-1", "gin", "noalloc"])
+@pytest.mark.parametrize("k", [16, 50, 128, 160])
+def test_a_value_that_its_neighbours_do_not_see(env, cliques, k, op):
+    """Sums that hold a row's own value, however large beside its neighbours', leave nothing of it in the row: the error is relative to what the row holds.
+    (An own value of up to 32 times the largest other is taken off again: 32 x 2^-24 for each of the few additions that it took part in.)"""
+    torch, cbm = env
+    rowptr, colidx = cliques
+    n = len(rowptr) - 1
+    h = cbm.cbm_build(n, n, rowptr, colidx)
+    X = wl.gaussian_features(n, k, 9)
+    values = (20.0, -40.0, 100.0, 1e3, -1e5, 1e8, -1e20, LOWEST)
+    rng = np.random.default_rng(6)
+    rows = rng.choice(n, 60, replace=False)       # few of them are neighbours
+    for i, r in enumerate(rows):
+        X[r, rng.choice(k, 5, replace=False)] = values[i % len(values)]
+    X[:, 3] = 0.0                                 # a column that one row alone has anything in, and one of very small values
+    X[rows[0], 3] = 0.1
+    X[:, 4] *= 1e-41
+    X[rows[1], 4] = 1e-30
+    s = {"gin-1": 0.0, "gin": 1.25}.get(op)
+    call = {"spmm": cbm.cbm_spmm, "mean": cbm.cbm_spmm_mean, "gin-1": lambda *a: cbm.cbm_spmm_gin(a[0], -1.0, *a[1:]),
+            "gin": lambda *a: cbm.cbm_spmm_gin(a[0], 0.25, *a[1:]), "noalloc": cbm.cbm_spmm_noalloc}[op]
+    Xd, Y = torch.from_numpy(X).cuda(), torch.full((n, k), float("nan"), device="cuda")
+    call(h, Xd, Y)
+    torch.cuda.synchronize()
+
+    def sums(x):
+        out = np.add.reduceat(np.vstack([x[colidx], np.zeros((1, k))]), np.minimum(rowptr[:-1], len(colidx)), axis=0)
+        out[np.diff(rowptr) == 0] = 0
+        return out + (s * x if s else 0)
+
+    X64 = X.astype(np.float64)
+    ref, scale = sums(X64), sums(np.abs(X64))
+    with np.errstate(over="ignore"):
+        fits = np.isfinite(ref.astype(np.float32))   # (two lowest values in a row, or 1.25 times one, do not)
+    if op == "mean":
+        deg = np.maximum(np.diff(rowptr), 1)[:, None]
+        ref, scale = ref / deg, scale / deg
+    got = Y.cpu().numpy()
+    assert np.isneginf(got[~fits]).all() and np.isfinite(got[fits]).all()
+    bad = fits & ~(np.abs(got - ref) <= TOL * scale + 1e-45)
+    assert not bad.any(), [(int(r), int(c), float(X[r, c]), float(ref[r, c]), float(Y[r, c]), int(r % 3 + 1)) for r, c in np.argwhere(bad)[:5]]
+
+
+def test_a_mask_on_a_graph_that_row_blocks_take_too(env, monkeypatch):
+    """As the library chooses by itself: with shared sums and without, a row next to nothing but ordinary values is an ordinary value."""
+    torch, cbm = env
+    rowptr, colidx = _cliques(20000, twice=True)
+    n, k = len(rowptr) - 1, 64
+    X = torch.from_numpy(wl.gaussian_features(n, k, 2)).cuda()
+    masked = torch.arange(0, n, 501, device="cuda")
+    X[masked, 7] = LOWEST
+    X[masked, 9] = -1e8
+    Y, Z = torch.empty_like(X), torch.empty_like(X)
+    for sums, out, kinds in (("2", Y, [6, 6]), ("0", Z, [5])):
+        monkeypatch.setenv("CBM_SHARED_SUMS", sums)
+        monkeypatch.delenv("CBM_ROW_BLOCKS", raising=False)
+        h = cbm.cbm_build(n, n, rowptr, colidx)
+        assert _kinds(torch, cbm, h, lambda: cbm.cbm_spmm(h, X, out)) == kinds
+    ok = Z.abs() < 1e6
+    assert ok[masked].float().mean() > 0.9
+    assert float((Y - Z).abs()[ok].max()) <= 1e-5 * 20 * 3
+
+
 def test_streams_threads_and_captures_at_a_time(env, graph):
     """Products of one handle overlap freely: each stream and each capture has sums of its own, and what finds none takes the paths."""
     torch, cbm = env
