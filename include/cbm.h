@@ -210,11 +210,11 @@ cbm_status cbm_build(int64_t m, int64_t n, const int64_t* rowptr, const int32_t*
  *    any before it frees and reallocates it (the free waits for the device), which is
  *    not allowed under HIP-graph capture: call cbm_reserve(h, widest k) once beforehand;
  *    after that, products with k <= that width only launch kernels and can be captured.
- * A handle whose products take shared sums keeps an array of at most 32 MiB (128 columns of sums where
- * that is more) for each of up to eight streams and captures, the first from cbm_build on; the others are
- * allocated when a product first needs them, also under capture, and products for which there is none run
- * without shared sums.  Such products may overlap freely; a stream may be destroyed once those it was
- * given are done.
+ * A handle whose products take shared sums (launch records of kind 6) keeps an array of at most 32 MiB (128 columns of sums
+ * where that is more; a quarter more without self-loops) for each of up to eight streams and captures, the first from cbm_build on; the others are
+ * allocated when a product first needs them, also under capture.  A product for which there is none sums each row's sets in place: one
+ * launch, the same bits, two to four times the time.  Neither touches the scratch of split rows, so such products may overlap freely,
+ * whatever num_split_rows says; a stream may be destroyed once those it was given are done.
  * Per-launch profiling (cbm_profile_enable) records events and must be off during capture.
  */
 cbm_status cbm_spmm(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
@@ -339,8 +339,8 @@ typedef struct {
                                5 = row blocks: the whole product, or the popular columns of
                                split rows (tasks = blocks, deltas = columns gathered, each
                                once per block), 6 = shared sums: level 1 the sets, level 2
-                               the rows made of them (tasks = sets or rows, deltas = rows of X
-                               and sums gathered)                                        */
+                               the rows made of them, level 3 rows that sum their sets in place
+                               (tasks = sets or rows, deltas = rows of X and sums gathered) */
     int32_t level;          /* round for kinds 0 and 2, launch for kind 6, else 0      */
     int64_t tasks;          /* work items in the launch                               */
     int64_t deltas;         /* delta entries gathered by the launch                   */

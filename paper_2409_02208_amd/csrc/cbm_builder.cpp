@@ -2108,7 +2108,7 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
 
     // ---- shared sums -----------------------------------------------------------------------------
     // Part of the automatic policy too: column sets that many rows hold in full (the cliques of a collaboration network) are summed
-    // once and the rows made of the sums.  The paths (or row blocks) stay: products run on them where a stream has no scratch.
+    // once and the rows made of the sums.  The paths (or row blocks) stay, for handles that cannot be given the memory.
     // (CBM_SHARED_SUMS: 0 = never, 1 = whenever there are any, 2 = as by default, on host-only handles too.)
     const long want_sums = env_clamped("CBM_SHARED_SUMS", -1, -1, 2);
     if (B.verbose && h->hub_blocks) std::fprintf(stderr, "[cbm_build] shared sums: products do without\n");

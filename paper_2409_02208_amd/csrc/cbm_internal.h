@@ -134,7 +134,7 @@ struct cbm_handle {
                                          // in row 32 s + l % 32
     int64_t blk_begin[CBM_XCD] = {}, blk_count[CBM_XCD] = {};  // each XCD's run of blocks
 
-    // ---- shared sums: where they pay, the products run on these; the work items above stand in where there is no scratch to be had ----
+    // ---- shared sums: where they pay, the products run on these ----
     std::vector<CbmSumItem> sum_items;   // the num_sums sets (set i = item i), then the m rows
     std::vector<uint32_t> sum_entries;
     int64_t num_sums = 0;                // 0: none
@@ -227,8 +227,8 @@ void cbm_launch_flat(const cbm_handle* h, bool segments, bool rows, int lanes, c
 inline double cbm_flat_us(const cbm_handle* h, int64_t k, int lanes) {
     return 4.0 + 0.25 * (double)h->levels[0].longest * lanes / 512.0 + (double)h->stats.nnz * 4.0 * (double)(k < 32 ? 32 : k) / 12.0e6;
 }
-// Products through shared sums (cbm_sums.hip): one of the two launches over k <= lds columns (sums at S, lds floats apart), and the
-// array for the sums of a stream's products (nullptr: none to be had; the caller holds h->sum_mutex).
+// Products through shared sums (cbm_sums.hip): one of the two launches over k <= lds columns (sums at S, lds floats apart; S = nullptr: the one
+// that sums each row's sets itself), and the array for the sums of a stream's products (nullptr: none to be had; the caller holds h->sum_mutex).
 void cbm_launch_sum_chunk(const cbm_handle* h, bool rows, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
                           float self_w, float* S, int64_t lds, void* stream);
 float* cbm_sum_scratch(const cbm_handle* h, void* stream);

@@ -861,16 +861,16 @@ cbm_status launch_blocked(const cbm_handle* h, const float* X, int64_t ldx, int3
 
 namespace {
 // The product through shared sums: as many columns at a time as the array of sums holds, in goes of about equal width and of whole cache
-// lines.  *taken = false: nothing was enqueued.
+// lines; one launch that needs none where there is no array.  (Never the paths: their split rows share one scratch array of the handle, and products
+// through shared sums may overlap.)  *taken = false: nothing was enqueued.
 cbm_status launch_sums(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
                        float self_w, hipStream_t stream, float* static_sums, bool* taken) {
     *taken = false;
-    if (ldx >= (int64_t)1 << 30 || ldy >= (int64_t)1 << 30) return CBM_OK;  // the kernels hold strides in 32 bits
+    if (ldx >> 32 || ldy >> 32) return CBM_OK;  // the kernels hold strides in 32 bits (512 rows, the fewest that sums are looked for in, would be 8 TB)
     std::lock_guard<std::mutex> lock(h->sum_mutex);  // both launches of a chunk follow each other on their stream
     float* sums = static_sums ? static_sums : cbm_sum_scratch(h, stream);
-    if (!sums) return CBM_OK;
     *taken = true;
-    int64_t most = cbm_sum_columns(h->num_sums);
+    int64_t most = sums ? cbm_sum_columns(h->num_sums) : 1 << 16;
     if (static_sums) {  // (32 floats a set and more: 16 columns and their sizes always fit)
         const int64_t room = CBM_STATIC_SCRATCH_FLOATS / h->num_sums;
         const bool sizes = cbm_sum_guarded(h, mode, self_w);
@@ -889,13 +889,13 @@ cbm_status launch_sums(const cbm_handle* h, const float* X, int64_t ldx, int32_t
     for (int64_t c = 0; c < k; c += width) {
         const int32_t kc = (int32_t)std::min<int64_t>(width, k - c);
         const int64_t rowb = 4 * (int64_t)kc, per_delta = rowb + 4 + (wcol ? 4 : 0);
-        for (int rows = 0; rows < 2; ++rows) {
+        for (int rows = sums ? 0 : 1; rows < 2; ++rows) {
             cbm_launch_record rec{};
             rec.kind = 6;
             rec.per_xcd = 1;
-            rec.level = rows + 1;
+            rec.level = sums ? rows + 1 : 3;
             rec.tasks = rows ? h->m : h->num_sums;
-            rec.deltas = rows ? row_entries : set_entries;
+            rec.deltas = sums ? (rows ? row_entries : set_entries) : h->stats.nnz;
             rec.algorithmic_bytes = rec.deltas * per_delta + rec.tasks * rowb;
             ProfScope ps(h, stream, rec);
             cbm_launch_sum_chunk(h, rows, X + c, ldx, kc, Y + c, ldy, mode, rw, self_w, sums, width, stream);

@@ -243,8 +243,28 @@ __device__ __forceinline__ f4 apart(const CbmSumItem* __restrict__ items, const 
     return acc;
 }
 
-// MODE as for the paths: 0 M X, 1 D^-1/2 M D^-1/2 X, 2 = 1 then max(., 0), 3 D^-1 M X, 4 M X + s X.
-template <bool RAGGED, int LANES, int MODE, bool GUARD, int U>
+// The sum over a row's entries with its sets summed here and now, in the order in which the two launches do it: the same bits without the memory.
+template <bool RAGGED, int LANES, bool WEIGHTED, bool GUARD, int U>
+__device__ __forceinline__ void in_place(f4& acc, Sizes& sizes, const CbmSumItem* __restrict__ items, const uint32_t* __restrict__ entries,
+                                         const float* __restrict__ ws, uint32_t start, uint32_t len, int sl, const Rows& r,
+                                         const Columns<RAGGED, LANES>& cols) {
+    uint32_t i = start;
+    for (; i < start + len; ++i) {  // sets come first
+        const uint32_t e = entries[i];
+        if (!(e & CBM_SUM_BIT)) break;
+        const uint32_t first = items[e & ~CBM_SUM_BIT].start, n = items[e & ~CBM_SUM_BIT].len;
+        f4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+        Sizes set;
+        walk<RAGGED, LANES, WEIGHTED, false, GUARD, false, U>(sum, set, entries + first, WEIGHTED ? ws + first : nullptr, n, sl, r, 0, cols);
+        acc += sum;
+        if (GUARD) sizes.add_to_row(sum, true, set.packed());
+    }
+    if constexpr (GUARD) walk_sized<RAGGED, LANES, U>(acc, sizes, entries + i, start + len - i, sl, r, cols);
+    else walk<RAGGED, LANES, WEIGHTED, false, false, false, U>(acc, sizes, entries + i, WEIGHTED ? ws + i : nullptr, start + len - i, sl, r, 0, cols);
+}
+
+// MODE as for the paths: 0 M X, 1 D^-1/2 M D^-1/2 X, 2 = 1 then max(., 0), 3 D^-1 M X, 4 M X + s X.  DIRECT: no sums in memory.
+template <bool RAGGED, int LANES, int MODE, bool GUARD, bool DIRECT, int U>
 __global__ __launch_bounds__(256, 4) void cbm_sum_rows_kernel(const CbmSumItem* __restrict__ items, const SumMap map,
                                                               const uint32_t* __restrict__ entries, const float* __restrict__ ws,
                                                               const float* __restrict__ X, uint32_t ldx, const float* __restrict__ S, uint32_t lds,
@@ -265,8 +285,9 @@ __global__ __launch_bounds__(256, 4) void cbm_sum_rows_kernel(const CbmSumItem* 
     if (add_own) own = cols.load(mine);
     f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     Sizes sizes;
-    const Rows from{X, ldx, S, lds, GUARD ? set_sizes + blockIdx.y * LANES + sl : nullptr, ld_sizes};
-    if constexpr (GUARD) walk_sized<RAGGED, LANES, U>(acc, sizes, entries + it.start, len, sl, from, cols);
+    const Rows from{X, ldx, S, lds, GUARD && !DIRECT ? set_sizes + blockIdx.y * LANES + sl : nullptr, ld_sizes};
+    if constexpr (DIRECT) in_place<RAGGED, LANES, WEIGHTED, GUARD, U>(acc, sizes, items, entries, ws, it.start, len, sl, from, cols);
+    else if constexpr (GUARD) walk_sized<RAGGED, LANES, U>(acc, sizes, entries + it.start, len, sl, from, cols);
     else walk<RAGGED, LANES, WEIGHTED, true, false, false, U>(acc, sizes, entries + it.start, WEIGHTED ? ws + it.start : nullptr, len, sl, from, 0, cols);
     const float times = ((float)it.own + (MODE == 4 ? self_w : 0.0f)) * (WEIGHTED ? w : 1.0f);
     if (add_own)
@@ -315,7 +336,7 @@ struct Args {
     uint32_t ldx;
     float* S;
     uint32_t lds;
-    uint32_t* sizes;  // nullptr: no guard
+    uint32_t* sizes;
     float* Y;
     uint32_t ldy;
     const float* rw;
@@ -324,43 +345,48 @@ struct Args {
     hipStream_t stream;
 };
 
+// The two launches of a product, and the one that does without memory for sums.
+enum Part { SETS, ROWS, DIRECT };
+
 template <bool RAGGED, int LANES, int MODE, bool GUARD>
-void launch(const Args& a, bool rows) {
+void launch(const Args& a, Part part) {
     constexpr int G = 64 / LANES;
     constexpr int U = 8;  // 4 waves a SIMD; 4 rows at 8 waves: 30,000 nodes, k = 64 26 us instead of 22, 235,868 nodes the same; 2 rows 31
     SumMap map;
     uint32_t most = 0;
     for (int j = 0; j < CBM_XCD; ++j) {
-        map.begin[j] = (uint32_t)a.h->sum_begin[rows][j];
-        map.count[j] = (uint32_t)a.h->sum_count[rows][j];
+        map.begin[j] = (uint32_t)a.h->sum_begin[part != SETS][j];
+        map.count[j] = (uint32_t)a.h->sum_count[part != SETS][j];
         most = std::max(most, map.count[j]);
     }
     const dim3 grid(CBM_XCD * ((most + 4 * G - 1) / (4 * G)), (a.k + 4 * LANES - 1) / (4 * LANES));
     const uint32_t ld_sizes = (uint32_t)cbm_sum_sizes(a.k);
-    if (rows)
-        hipLaunchKernelGGL((cbm_sum_rows_kernel<RAGGED, LANES, MODE, GUARD, U>), grid, dim3(256), 0, a.stream, a.h->d_sum_items, map, a.h->d_sum_entries,
-                           a.h->d_sum_w, a.X, a.ldx, a.S, a.lds, a.sizes, ld_sizes, a.Y, a.ldy, a.rw, a.self_w, a.k);
-    else
+    auto rows = [&](auto direct) {
+        hipLaunchKernelGGL((cbm_sum_rows_kernel<RAGGED, LANES, MODE, GUARD, decltype(direct)::value, U>), grid, dim3(256), 0, a.stream, a.h->d_sum_items, map,
+                           a.h->d_sum_entries, a.h->d_sum_w, a.X, a.ldx, a.S, a.lds, a.sizes, ld_sizes, a.Y, a.ldy, a.rw, a.self_w, a.k);
+    };
+    if (part == ROWS) rows(std::false_type{});
+    else if (part == DIRECT) rows(std::true_type{});
+    else if constexpr (MODE <= 1)
         hipLaunchKernelGGL((cbm_sum_sets_kernel<RAGGED, LANES, MODE == 1, GUARD, U>), grid, dim3(256), 0, a.stream, a.h->d_sum_items, map,
                            a.h->d_sum_entries, a.h->d_sum_w, a.X, a.ldx, a.S, a.lds, a.sizes, ld_sizes, a.k);
 }
 template <bool RAGGED, int LANES>
-void launch_mode(const Args& a, int mode, bool rows) {
-    const bool guard = a.sizes != nullptr;
-    if (!rows) return mode == 1 || mode == 2 ? launch<RAGGED, LANES, 1, false>(a, false) : guard ? launch<RAGGED, LANES, 0, true>(a, false) : launch<RAGGED, LANES, 0, false>(a, false);
+void launch_mode(const Args& a, int mode, bool guard, Part part) {
+    if (part == SETS) mode = mode == 1 || mode == 2 ? 1 : 0;  // (weighted or not)
     switch (mode) {
-        case 0: return guard ? launch<RAGGED, LANES, 0, true>(a, true) : launch<RAGGED, LANES, 0, false>(a, true);
-        case 1: return launch<RAGGED, LANES, 1, false>(a, true);
-        case 2: return launch<RAGGED, LANES, 2, false>(a, true);
-        case 3: return guard ? launch<RAGGED, LANES, 3, true>(a, true) : launch<RAGGED, LANES, 3, false>(a, true);
-        default: return guard ? launch<RAGGED, LANES, 4, true>(a, true) : launch<RAGGED, LANES, 4, false>(a, true);
+        case 0: return guard ? launch<RAGGED, LANES, 0, true>(a, part) : launch<RAGGED, LANES, 0, false>(a, part);
+        case 1: return launch<RAGGED, LANES, 1, false>(a, part);
+        case 2: return launch<RAGGED, LANES, 2, false>(a, part);
+        case 3: return guard ? launch<RAGGED, LANES, 3, true>(a, part) : launch<RAGGED, LANES, 3, false>(a, part);
+        default: return guard ? launch<RAGGED, LANES, 4, true>(a, part) : launch<RAGGED, LANES, 4, false>(a, part);
     }
 }
 template <bool RAGGED>
-void launch_lanes(const Args& a, int mode, bool rows) {
-    if (a.k <= 32) launch_mode<RAGGED, 8>(a, mode, rows);
-    else if (a.k <= 64) launch_mode<RAGGED, 16>(a, mode, rows);
-    else launch_mode<RAGGED, 32>(a, mode, rows);
+void launch_lanes(const Args& a, int mode, bool guard, Part part) {
+    if (a.k <= 32) launch_mode<RAGGED, 8>(a, mode, guard, part);
+    else if (a.k <= 64) launch_mode<RAGGED, 16>(a, mode, guard, part);
+    else launch_mode<RAGGED, 32>(a, mode, guard, part);
 }
 
 constexpr size_t kMostScratch = 8;  // arrays of sums a handle keeps: one each for so many streams and captures
@@ -370,11 +396,13 @@ constexpr uint64_t kNobody = ~0ull;
 
 void cbm_launch_sum_chunk(const cbm_handle* h, bool rows, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
                           float self_w, float* S, int64_t lds, void* stream) {
-    uint32_t* sizes = cbm_sum_guarded(h, mode, self_w) ? reinterpret_cast<uint32_t*>(S + h->num_sums * lds) : nullptr;
+    const bool guard = cbm_sum_guarded(h, mode, self_w);
+    uint32_t* sizes = guard && S ? reinterpret_cast<uint32_t*>(S + h->num_sums * lds) : nullptr;
     const Args a{h, X, (uint32_t)ldx, S, (uint32_t)lds, sizes, Y, (uint32_t)ldy, rw, self_w, (int)k, (hipStream_t)stream};
     const bool aligned = k % 4 == 0 && ldx % 4 == 0 && ldy % 4 == 0 && ((uintptr_t)X & 15) == 0 && ((uintptr_t)Y & 15) == 0;
-    if (aligned) launch_lanes<false>(a, mode, rows);
-    else launch_lanes<true>(a, mode, rows);
+    const Part part = !S ? DIRECT : rows ? ROWS : SETS;
+    if (aligned) launch_lanes<false>(a, mode, guard, part);
+    else launch_lanes<true>(a, mode, guard, part);
 }
 
 bool cbm_sum_guarded(const cbm_handle* h, int mode, float self_w) {  // (the sum that a GIN layer makes holds 1 + eps times the row's own value)
