@@ -210,11 +210,15 @@ cbm_status cbm_build(int64_t m, int64_t n, const int64_t* rowptr, const int32_t*
  *    any before it frees and reallocates it (the free waits for the device), which is
  *    not allowed under HIP-graph capture: call cbm_reserve(h, widest k) once beforehand;
  *    after that, products with k <= that width only launch kernels and can be captured.
- * A handle whose products take shared sums (launch records of kind 6) keeps an array of at most 32 MiB (128 columns of sums
- * where that is more; a quarter more without self-loops) for each of up to eight streams and captures, the first from cbm_build on; the others are
- * allocated when a product first needs them, also under capture.  A product for which there is none sums each row's sets in place: one
- * launch, the same bits, two to four times the time.  Neither touches the scratch of split rows, so such products may overlap freely,
- * whatever num_split_rows says; a stream may be destroyed once those it was given are done.
+ * A handle whose products take shared sums (launch records of kind 6) keeps an array of at most 32 MiB (128 columns of
+ * sums where that is more; a quarter more without self-loops) for each of up to sixteen streams and captures, of these
+ * fourteen captures at most.  The first is there from cbm_build on; the others are allocated when a product first needs
+ * them, also under capture.  Where more than four streams have one, a stream that asks is given that of another whose
+ * products are done; that of a capture comes back when the graph and all that is instantiated from it are destroyed;
+ * cbm_free frees them.  A product for which there is none sums each row's sets in place: one launch (level 3 of kind 6),
+ * the same bits, two to four times the time.  Neither way touches the scratch of split rows, so such products may overlap
+ * freely, whatever num_split_rows says (those of cbm_spmm_noalloc may not).  A stream or a captured graph may be destroyed
+ * once what it was given is done.
  * Per-launch profiling (cbm_profile_enable) records events and must be off during capture.
  */
 cbm_status cbm_spmm(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,

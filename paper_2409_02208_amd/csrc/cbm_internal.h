@@ -1,7 +1,9 @@
 // Internal layout shared by the host builder, the kernel launchers and the C ABI.
 #pragma once
 
+#include <atomic>
 #include <cstdint>
+#include <memory>
 #include <mutex>
 #include <vector>
 
@@ -87,8 +89,11 @@ inline int64_t cbm_sum_columns(int64_t num_sums) {
 // Words beside a set's sums of k columns that hold the sizes of its values (cbm_sums.hip): one for each lane, a quarter of the columns at most.
 inline int64_t cbm_sum_sizes(int64_t k) { return k <= 32 ? 8 : k <= 64 ? 16 : (k + 127) / 128 * 32; }
 struct CbmSumScratch {  // cbm_sum_bytes of the products that one stream, or one capture on it, enqueues
-    uint64_t stream, capture, thread;
-    float* sums;
+    uint64_t stream = 0, capture = 0, thread = 0;
+    float* sums = nullptr;
+    void* done = nullptr;                     // an event; `passed`: it is behind the last of these products
+    bool passed = false;
+    std::shared_ptr<std::atomic<bool>> gone;  // of a capture: its graph is
 };
 
 struct cbm_handle {
@@ -231,7 +236,8 @@ inline double cbm_flat_us(const cbm_handle* h, int64_t k, int lanes) {
 // that sums each row's sets itself), and the array for the sums of a stream's products (nullptr: none to be had; the caller holds h->sum_mutex).
 void cbm_launch_sum_chunk(const cbm_handle* h, bool rows, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
                           float self_w, float* S, int64_t lds, void* stream);
-float* cbm_sum_scratch(const cbm_handle* h, void* stream);
+CbmSumScratch* cbm_sum_scratch(const cbm_handle* h, void* stream);
+void cbm_sum_enqueued(const cbm_handle* h, CbmSumScratch* s, void* stream);
 bool cbm_sum_guarded(const cbm_handle* h, int mode, float self_w);  // whether the product keeps the sets' sizes beside their sums
 inline size_t cbm_sum_bytes(const cbm_handle* h) {
     return (size_t)h->num_sums * cbm_sum_columns(h->num_sums) * sizeof(float) / 4 * (h->sum_most_taken_off > 0 ? 5 : 4);

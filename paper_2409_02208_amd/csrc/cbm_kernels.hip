@@ -868,7 +868,8 @@ cbm_status launch_sums(const cbm_handle* h, const float* X, int64_t ldx, int32_t
     *taken = false;
     if (ldx >> 32 || ldy >> 32) return CBM_OK;  // the kernels hold strides in 32 bits (512 rows, the fewest that sums are looked for in, would be 8 TB)
     std::lock_guard<std::mutex> lock(h->sum_mutex);  // both launches of a chunk follow each other on their stream
-    float* sums = static_sums ? static_sums : cbm_sum_scratch(h, stream);
+    CbmSumScratch* own = static_sums ? nullptr : cbm_sum_scratch(h, stream);
+    float* sums = own ? own->sums : static_sums;
     *taken = true;
     int64_t most = sums ? cbm_sum_columns(h->num_sums) : 1 << 16;
     if (static_sums) {  // (32 floats a set and more: 16 columns and their sizes always fit)
@@ -902,6 +903,7 @@ cbm_status launch_sums(const cbm_handle* h, const float* X, int64_t ldx, int32_t
         }
     }
     HIP_TRY(hipGetLastError(), CBM_ERR_HIP);
+    if (own) cbm_sum_enqueued(h, own, stream);
     return CBM_OK;
 }
 }  // namespace

@@ -239,7 +239,7 @@ def test_streams_threads_and_captures_at_a_time(env, graph):
     torch, cbm = env
     g, k = graph, 64
     h = cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=True)
-    Xs = [torch.from_numpy(wl.gaussian_features(g.n, k, s)).cuda() for s in range(12)]
+    Xs = [torch.from_numpy(wl.gaussian_features(g.n, k, s)).cuda() for s in range(24)]
     want = []
     for X in Xs:
         Y = torch.empty_like(X)
@@ -327,7 +327,7 @@ def test_products_without_memory_for_sums(env, hubs, k, loops):
     n = len(rowptr) - 1
     h = cbm.cbm_build(n, n, rowptr, colidx, add_self_loops=loops)
     assert cbm.cbm_stats(h)["num_split_rows"] > 0
-    Xs = [torch.from_numpy(wl.gaussian_features(n, k, s)).cuda() for s in range(12)]
+    Xs = [torch.from_numpy(wl.gaussian_features(n, k, s)).cuda() for s in range(20)]
     Xs[1][::7] *= 1e6                                # (rows that are put together without their own value)
     ops = [cbm.cbm_spmm, cbm.cbm_spmm_mean, lambda h, X, Y: cbm.cbm_spmm_gin(h, -1.0, X, Y)] + ([cbm.cbm_spmm_normalized, cbm.cbm_spmm_normalized_relu] if loops else [])
     Ys, graphs = [torch.empty_like(X) for X in Xs], []
@@ -358,7 +358,7 @@ def test_streams_share_no_scratch_of_split_rows(env, hubs):
     rowptr, colidx = hubs
     n, k = len(rowptr) - 1, 96
     h = cbm.cbm_build(n, n, rowptr, colidx, add_self_loops=True)
-    Xs = [torch.from_numpy(wl.gaussian_features(n, k, s)).cuda() for s in range(14)]
+    Xs = [torch.from_numpy(wl.gaussian_features(n, k, s)).cuda() for s in range(24)]
     streams, Ys = [torch.cuda.Stream() for _ in Xs], [torch.full_like(X, float("nan")) for X in Xs]
     torch.cuda.synchronize()
     for _ in range(20):
@@ -368,6 +368,69 @@ def test_streams_share_no_scratch_of_split_rows(env, hubs):
     torch.cuda.synchronize()
     for X, Y in zip(Xs, Ys):
         assert _err(Y.cpu().numpy(), orc.spmm_csr_normalized(rowptr, colidx, X.cpu().numpy())) <= TOL
+
+
+def _sixes(n):
+    """Cliques of six."""
+    members = np.random.default_rng(2).permutation(n).reshape(-1, 6)
+    pairs = [(i, j) for i in range(6) for j in range(i)]
+    return wl.graphs.csr_from_edges(n, np.concatenate([members[:, i] for i, _ in pairs]), np.concatenate([members[:, j] for _, j in pairs]))
+
+
+def test_arrays_of_streams_and_graphs_that_are_done_come_back(env):
+    """One stream after the other, one graph after the other: no more than a few arrays of 29 MiB, and every product has one."""
+    torch, cbm = env
+    n, k, array = 60000, 64, 29 << 20
+    rowptr, colidx = _sixes(n)
+    h = cbm.cbm_build(n, n, rowptr, colidx, add_self_loops=True)
+    X = torch.from_numpy(wl.integer_features(n, k, 1)).cuda()
+    Y, want = torch.empty_like(X), torch.empty_like(X)
+    cbm.cbm_spmm(h, X, want)
+    torch.cuda.synchronize()
+
+    def levels():
+        cbm.cbm_profile_enable(h, True)
+        cbm.cbm_spmm(h, X, Y)
+        torch.cuda.synchronize()
+        got = [r["level"] for r in cbm.cbm_profile_read(h)]
+        cbm.cbm_profile_enable(h, False)
+        return got
+
+    free, streams = [], [torch.cuda.Stream() for _ in range(24)]
+    for s in streams:
+        with torch.cuda.stream(s):
+            cbm.cbm_spmm(h, X, Y)
+            s.synchronize()
+            assert levels() == [1, 2]
+        assert torch.equal(Y, want)
+        free.append(torch.cuda.mem_get_info()[0])
+    assert free[6] - free[-1] < array
+    free, graphs = [], []
+    for _ in range(24):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            cbm.cbm_spmm(h, X, Y)
+        Y.fill_(float("nan"))
+        for _ in range(3):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, want)
+        del graph
+        torch.cuda.synchronize()
+        free.append(torch.cuda.mem_get_info()[0])
+    assert free[2] - free[-1] < array
+    for _ in range(20):                       # more than there are arrays for, all alive: streams keep some
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            cbm.cbm_spmm(h, X, Y)
+    for s in streams[:4]:
+        with torch.cuda.stream(s):
+            assert levels() == [1, 2]
+    for graph in graphs:
+        Y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, want)
 
 
 def test_columns_in_goes(env, monkeypatch):
