@@ -238,9 +238,10 @@ cbm_status cbm_spmm(const cbm_handle* h, const float* X, int64_t ldx, int32_t k,
  *   they do where shared sums need more.
  *   CBM_ERR_STATE while per-launch profiling is on (it creates events).
  * Every GPU the library runs on holds one such array until the process ends, and every call on that GPU
- * shares it, whatever the handle: calls that overlap in time on one GPU (two streams, two host threads)
- * race on it -- run them one after the other.  Nothing in it has to be cleared between calls: a product
- * writes every scratch row it later reads.
+ * shares it, whatever the handle: calls that overlap in time on one GPU (two streams, two host threads, two
+ * replayed graphs) race on it -- run them one after the other.  That holds for a handle without split rows too: where
+ * its products take shared sums, these are written to the array.  Nothing in it has to be cleared between calls: a
+ * product writes every scratch row and every sum it later reads.
  */
 cbm_status cbm_spmm_noalloc(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
                             void* hip_stream);
