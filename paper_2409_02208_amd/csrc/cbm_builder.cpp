@@ -85,6 +85,8 @@ constexpr double kSumBlockMargin = 1.1;  // of the row blocks' (collaboration re
 // 5,000 21 and 18; shared sums of 5,000 nodes 39 and 16, of 10,000 34 and 15): the rows as they stand may take less (cbm_flat.hip)
 constexpr double kFlatBlockMargin = 0.7;
 constexpr double kFlatSumMargin = 0.45;
+constexpr size_t kSumLongRows = 16;      // looked at for what sets would leave of them (collaboration recipe, 13,000 to 235,868 nodes with one of 300 to
+                                         // 1,500 neighbours more: 0.55 to 0.99 of what the plan then leaves, never more)
 constexpr size_t kSumWindow = 256;       // items that are put in order of length among themselves
 constexpr int64_t kIndexShareMinRows = 16384;  // (below, all of X is in L2 anyway)
 constexpr double kIndexShareMost = 0.9;        // R-MAT 1.0, citation recipe 0.7
@@ -2120,8 +2122,21 @@ cbm_status cbm_build_host(int64_t m, int64_t n, const int64_t* in_rowptr, const 
             parallel_chunks(B.nthreads, m, 4096, [&](int64_t x0, int64_t x1, int) {
                 for (int64_t x = x0; x < x1; ++x) holds_own[x] = std::binary_search(B.row(x), B.row(x) + B.rlen(x), (int32_t)x);
             });
-        auto sampled = [&] { return SharedSumFinder(m, B.rowptr, B.colidx, holds_own.data()).sample(kSumSample) * (double)B.nnz; };
-        const bool worth = want_sums == 1 || (m >= kSumMinRows && B.shared_sums_cost(sampled(), 0, 0) < limit);
+        auto parallel = [&](int64_t total, auto&& fn) { parallel_chunks(B.nthreads, total, 1, [&](int64_t b, int64_t e, int) { fn(b, e); }); };
+        auto promising = [&] {  // the plan takes a while to make: the least it could cost, and what a few rows say of it, come first
+            if (m < kSumMinRows || B.shared_sums_cost(0, 0, 0) >= limit) return false;
+            SharedSumFinder finder(m, B.rowptr, B.colidx, holds_own.data());
+            const double gathers = finder.sample(kSumSample, parallel) * (double)B.nnz;
+            if (B.shared_sums_cost(gathers, 0, 0) >= limit) return false;
+            std::vector<int32_t> longest;  // those long enough to matter, which is not many of them
+            for (int64_t x = 0; x < m; ++x)
+                if (B.shared_sums_cost(0, 0, (double)B.rlen(x)) >= limit) longest.push_back((int32_t)x);
+            const size_t most = std::min(longest.size(), kSumLongRows);
+            std::partial_sort(longest.begin(), longest.begin() + most, longest.end(), [&](int32_t x, int32_t y) { return B.rlen(x) != B.rlen(y) ? B.rlen(x) > B.rlen(y) : x < y; });
+            longest.resize(most);
+            return B.shared_sums_cost(gathers, 0, (double)finder.longest_left(longest, parallel)) < limit;
+        };
+        const bool worth = want_sums == 1 || promising();
         if (worth) {
             B.shared_sums(holds_own);
             double gathers = (double)h->sum_entries.size();

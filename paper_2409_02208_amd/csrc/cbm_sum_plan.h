@@ -28,28 +28,42 @@ public:
 
     // Gathered rows of X or of a set's sum per entry of the matrix, from `count` evenly spread rows: what whole neighbourhoods
     // would give, before sets of different rows get in each other's way.  A few million steps of looking at entries have to do: where
-    // neighbourhoods are so large that they are spent early, the rows looked at by then speak for the rest.
-    double sample(int64_t count) {
-        covered.assign((size_t)rowptr[m], 0);
-        sets_of.assign((size_t)m, 0);
-        Work w;
+    // neighbourhoods are so large that they are spent early, the rows looked at by then speak for the rest.  Rows are looked at side by side, as
+    // many at a time as the steps of those before suggest: the answer does not depend on the number of threads.
+    template <class Parallel>
+    double sample(int64_t count, Parallel&& parallel) {
+        start();
         double gathers = 0, entries = 0;
-        const int64_t step = std::max<int64_t>(1, m / count);
-        for (int64_t u = 0; u < m; u += step) {
-            if (w.steps > kSampleSteps) break;
-            std::vector<Found> found;
-            propose(u, true, w, found);
-            double left = (double)(rowptr[u + 1] - rowptr[u]);
-            entries += left;
-            for (const Found& f : found) {
-                const int64_t mine = std::lower_bound(f.rows.begin(), f.rows.end(), (int32_t)u) - f.rows.begin();
-                if (mine == (int64_t)f.rows.size() || f.rows[mine] != u) continue;
-                left -= (double)(f.at[mine + 1] - f.at[mine]);
-                gathers += 1.0 + (double)(f.cols.size() + 1) / (double)f.rows.size();
+        int64_t steps = 0;
+        const int64_t step = std::max<int64_t>(1, m / count), rows = (m + step - 1) / step;
+        for (int64_t b = 0, n; b < rows && steps <= kSampleSteps; b += n) {
+            n = std::min(rows - b, b == 0 ? 8 : std::max<int64_t>(8, (kSampleSteps - steps) / (steps / b + 1)));
+            std::vector<Left> left((size_t)n);
+            parallel(n, [&](int64_t i0, int64_t i1) {
+                Work w;
+                for (int64_t i = i0; i < i1; ++i) left[i] = left_of((b + i) * step, w);
+            });
+            for (int64_t i = 0; i < n && steps <= kSampleSteps; ++i) {
+                entries += (double)(rowptr[(b + i) * step + 1] - rowptr[(b + i) * step]);
+                gathers += left[i].entries + left[i].sets;
+                steps += left[i].steps;
             }
-            gathers += left;
         }
         return entries > 0 ? gathers / entries : 1.0;
+    }
+    // What sets would leave of the longest of these rows: rows of the plan are not split, and a product waits for the longest.
+    template <class Parallel>
+    int64_t longest_left(const std::vector<int32_t>& rows, Parallel&& parallel) {
+        start();
+        std::vector<double> left(rows.size(), 0.0);
+        parallel((int64_t)rows.size(), [&](int64_t i0, int64_t i1) {
+            Work w;
+            for (int64_t i = i0; i < i1; ++i) {
+                const Left l = left_of(rows[i], w);
+                left[i] = l.entries - (double)l.missed;
+            }
+        });
+        return rows.empty() ? 0 : (int64_t)*std::max_element(left.begin(), left.end());
     }
 
     // Sets are proposed for many rows at a time from what is covered so far, side by side, and taken one after the other in row
@@ -57,8 +71,7 @@ public:
     template <class Parallel>
     SharedSums find(Parallel&& parallel) {
         constexpr int64_t kBatches = 64, kPasses = 4;
-        covered.assign((size_t)rowptr[m], 0);
-        sets_of.assign((size_t)m, 0);
+        start();
         std::vector<std::vector<int32_t>> rows_of;  // rows of each set taken
         SharedSums out;
         std::vector<int32_t> seeds((size_t)m), again;
@@ -141,6 +154,31 @@ private:
     std::vector<uint8_t> covered;
     std::vector<int32_t> sets_of;  // sets of a row that hold its own column
 
+    void start() {  // nothing is covered
+        covered.assign((size_t)rowptr[m], 0);
+        sets_of.assign((size_t)m, 0);
+    }
+    // Row u while nothing is covered: its entries that no set brings (`missed` of them were not looked at, for want of steps), its sets with its
+    // share of making them, and what looking took.
+    struct Left {
+        double entries = 0, sets = 0;
+        int64_t missed = 0, steps = 0;
+    };
+    Left left_of(int64_t u, Work& w) {
+        std::vector<Found> found;
+        w.steps = 0;
+        Left r;
+        r.entries = (double)(rowptr[u + 1] - rowptr[u]);
+        r.missed = propose(u, true, w, found);
+        for (const Found& f : found) {
+            const int64_t mine = std::lower_bound(f.rows.begin(), f.rows.end(), (int32_t)u) - f.rows.begin();
+            if (mine == (int64_t)f.rows.size() || f.rows[mine] != u) continue;
+            r.entries -= (double)(f.at[mine + 1] - f.at[mine]);
+            r.sets += 1.0 + (double)(f.cols.size() + 1) / (double)f.rows.size();
+        }
+        r.steps = w.steps;
+        return r;
+    }
     int64_t find_entry(int64_t i, int32_t j) const {
         const int32_t *b = colidx + rowptr[i], *e = colidx + rowptr[i + 1];
         const int32_t* at = std::lower_bound(b, e, j);
@@ -156,14 +194,15 @@ private:
     // For every entry (u, v), v > u, that no set brings yet and whose mirror image none brings: what is common to the rows u and v
     // is the first guess at a set.  Rows and columns that most of the others do not share are dropped, and rows that do not hold all
     // of what is left.
-    void propose(int64_t u, bool all, Work& w, std::vector<Found>& found) {
+    // `all`: the row is only looked at, and from v < u too; returns how many of its entries were left out when that had taken its steps.
+    int64_t propose(int64_t u, bool all, Work& w, std::vector<Found>& found) {
         const int64_t ub = rowptr[u], ue = rowptr[u + 1];
-        if (ue - ub > kLongestRow || ue - ub + 1 < (int64_t)kLeastSet) return;
+        if (ue - ub > kLongestRow || ue - ub + 1 < (int64_t)kLeastSet) return 0;
         w.mine.assign(covered.begin() + ub, covered.begin() + ue);
         for (int64_t p = ub; p < ue; ++p) {
             const int32_t v = colidx[p];
             if (w.mine[p - ub] || v == u || (!all && v < u)) continue;
-            if (all && w.steps > kSampleSteps) return;
+            if (all && w.steps > kSampleSteps) return std::count(w.mine.begin() + (p - ub), w.mine.end(), 0);
             const int64_t vb = rowptr[v], ve = rowptr[v + 1];
             if (ve - vb > kLongestRow) continue;
             const int64_t back = find_entry(v, (int32_t)u);
@@ -271,6 +310,7 @@ private:
                 for (uint32_t i = f.at[me - f.rows.begin()]; i < f.at[me - f.rows.begin() + 1]; ++i) w.mine[f.places[i] - ub] = 1;
             found.push_back(std::move(f));
         }
+        return 0;
     }
     // Take a set for those of its rows whose entries are all still free, if it still pays; false if rows were lost.
     bool take(Found& f, SharedSums& out, std::vector<std::vector<int32_t>>& rows_of) {

@@ -37,3 +37,21 @@ def test_who_takes_shared_sums(monkeypatch, capfd, name, kw, taken):
     cbm.cbm_build(g.n, g.n, g.rowptr, g.colidx, add_self_loops=True, host_only=True)
     said = [ln for ln in capfd.readouterr().err.splitlines() if "shared sums" in ln and "products" in ln]
     assert len(said) == 1 and ("products take them" in said[0]) == taken
+
+
+@pytest.mark.parametrize("extra,planned", [(0, True), (1500, False)])
+def test_a_row_that_no_set_shortens_is_seen_before_the_plan_is_made(monkeypatch, capfd, extra, planned):
+    """One node with neighbours all over: the rows of the plan are not split, so the handle keeps its paths, and says so without looking for all sets;
+    what a few rows say does not depend on the number of threads."""
+    for name in ("CBM_SHARED_SUMS", "CBM_ROW_BLOCKS"):
+        monkeypatch.setenv(name, "2")
+    monkeypatch.setenv("CBM_HUB_BLOCKS", "3")
+    monkeypatch.setenv("CBM_VERBOSE", "1")
+    g = wl.make_graph("collaboration", n=20000)
+    src = np.concatenate([np.repeat(np.arange(g.n), np.diff(g.rowptr)), np.full(extra, 7)])
+    dst = np.concatenate([g.colidx.astype(np.int64), np.random.default_rng(1).choice(g.n, extra, replace=False)])
+    rowptr, colidx = wl.graphs.csr_from_edges(g.n, src[src != dst], dst[src != dst])
+    for threads in (1, 3):
+        cbm.cbm_build(g.n, g.n, rowptr, colidx, add_self_loops=True, host_only=True, num_threads=threads)
+        said = [ln for ln in capfd.readouterr().err.splitlines() if "shared sums:" in ln]
+        assert any("sets of" in ln for ln in said) == planned and ("products take them" in said[-1]) == planned
