@@ -461,6 +461,8 @@ constexpr int64_t kManyWavesShort = 16384;
 constexpr double kEntryManyUs = 0.35;      // an entry in batches of 2
 constexpr double kManyBytesPerUs = 6.0e6;  // gathered rows of X
 constexpr double kManyLongest = 0.75;      // the longest work item's share of the launch
+// bytes of 64 columns of X from which on it goes through 64 at a time: two such slabs, and an odd number of them
+constexpr int64_t kSlabOfTwo = 500000000, kSlabOfOdd = 1 << 28;
 
 struct LaunchCtx {
     const cbm_handle* h;
@@ -989,10 +991,15 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
     // 18 1127 -> 915 us, 60,000 nodes of the citation recipe 80 -> 69; k = 301 1270 -> 1083 and 87 -> 83; k = 500 would lose 8 %).
     if (lanes == 64 && k > 256 && (k - 1) % 256 < 128) lanes = 32;
     // Where X is far larger than the caches, slabs of 64 columns keep twice as many of its popular rows in them again, at the price of one
-    // more walk over the entries: at two million rows k = 128 pays (R-MAT scale 21, 32 edges a node 3993 -> 3785 us, 8 edges 1627 -> 1609; citation
-    // recipe of 2.5 million nodes 1154 -> 1112; at scale 20 1681 / 1690) and k = 256 does not (8025 / 7951, 3238 / 3284); an odd multiple
-    // of 64 has a chunk half empty otherwise and pays from a million rows on (k = 192 2853 -> 2530; at scale 16 it would lose 23 %).
-    if (aligned && k > 64 && k % 64 == 0 && ((k == 128 && h->n >= (1 << 21)) || (k % 128 == 64 && h->n >= (1 << 20)))) lanes = 16;
+    // more walk over the entries.  The lines are the size of such a slab.  Odd multiples of 64, which have a chunk half empty otherwise, gain once it is
+    // larger than the 256 MB behind the L2s (k = 192, 1.05 million nodes 2853 -> 2530; citation recipe, 1.0 million 629 / 645; at scale 16 it would lose
+    // 23 %).  k = 128, one full chunk, gains on dense graphs from there on, but on none less once the slab is about twice that (us, 128 / 64 columns:
+    // R-MAT of 1.05 million nodes 1325 / 1339; 1.57 million, 8 edges a node 1249 / 1283, 32 edges 3017 / 2871, citation recipe 672 / 674; 2.0 million
+    // 897 / 867; 2.1 million, 8 edges 1606 / 1601, 16 2480 / 2455, 32 4026 / 3768; 3.0 million 1424 / 1385).  Widths whose last slab is not full lose
+    // whatever the size (2.1 million, 16 edges: k = 96 1914 / 2078, 112 2430 / 2659, 120 2825 / 3191; 32 edges: k = 124 4938 / 5500), and k = 256 has slabs
+    // of 128 already: between +1 and -8 %.
+    const int64_t slab = h->n * 64 * (int64_t)sizeof(float);
+    if (aligned && ((k == 128 && slab >= kSlabOfTwo) || (k > 64 && k % 128 == 64 && slab >= kSlabOfOdd))) lanes = 16;
     const int mode = (int)epi;
     const Variant var = aligned ? pick_lanes<false>(lanes, mode) : pick_lanes<true>(lanes, mode);
     if (h->profiling) {

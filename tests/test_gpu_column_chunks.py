@@ -30,7 +30,7 @@ def test_wide_products(env, k):
     assert np.array_equal(Y.cpu().numpy().astype(np.float64), orc.spmm_csr(g.rowptr, g.colidx, X))
 
 
-@pytest.mark.parametrize("n,ks", [((1 << 20) - 1, (192,)), (1 << 20, (192, 128, 320)), (1 << 21, (128, 192, 256))])
+@pytest.mark.parametrize("n,ks", [((1 << 20) - 1, (192,)), (1 << 20, (192, 128, 320)), (1953124, (128,)), (1953125, (128, 124)), (1 << 21, (128, 192, 256))])
 def test_slabs_of_64_columns_of_a_large_x(env, n, ks):
     """Node i and its neighbours i - 1 and i + 1 on a ring, and node 0 with 300 more (a split row): sums of three whole numbers."""
     torch, cbm = env
