@@ -589,16 +589,19 @@ inline int panel_depth(int K, int nt16) {
     return ((K + 15) / 16 + ring - 1) / ring * ring * 16;
 }
 
-// LDS bytes of the resident panel, or 0 if this product cannot take the panel kernel.
-inline size_t panel_lds_bytes(int N, int K, const float* A, int64_t lda, int* nt16) {
+// LDS bytes of the resident panel, or 0 if this product cannot take the panel kernel.  A panel that fits only because its depth is not a multiple
+// of 64 (N of 33 to 48 with K of 769 to 784, of 17 to 32 with 1089 to 1120) is for a B of odd width or alignment (us, kernel below / panel: 132,534 x 784 .
+// 784 x 47 185 / 126, 60,000 rows 78 / 59, x 1120 . 1120 x 31 218 / 157): with wide loads of B it loses (30,000 x 784 . 784 x 48 34 / 36, 40 wide 34 / 40,
+// 132,534 x 772 . 772 x 40 124 / 128, 132,534 x 1092 . 1092 x 24 138 / 162, 30,000 rows 33 / 39; 300,000 x 784 . 784 x 48 would gain, 266 / 243).
+inline size_t panel_lds_bytes(int N, int K, const float* A, int64_t lda, bool wide_b, int* nt16) {
     const bool vec = K % 4 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0 && K >= 4;
     if (!vec || N < 16) return 0;
     const int tiles = (N + 15) / 16, npanels = (tiles + 7) / 8;
     *nt16 = (tiles + npanels - 1) / npanels;  // panels of equal width, at most 128 columns
     if (K > 4096) return 0;  // (no panel of that depth fits)
-    const int64_t Kp = panel_depth(K, *nt16);
-    const size_t bytes = (size_t)Kp * (16 * *nt16 + 4) * sizeof(float);
-    return bytes <= 160 * 1024 ? bytes : 0;
+    const size_t row = (16 * *nt16 + 4) * sizeof(float);
+    const size_t bytes = (size_t)panel_depth(K, *nt16) * row;
+    return (wide_b ? (size_t)((K + 63) / 64 * 64) * row : bytes) <= 160 * 1024 ? bytes : 0;
 }
 
 template <int NT16, int RINGS>
@@ -691,8 +694,9 @@ cbm_status cbm_launch_gemm(int64_t M, int32_t N, int32_t K, const float* A, int6
         static const char* env = std::getenv("CBM_GEMM_PANEL_MIN_ROWS");
         const int64_t min_rows = env ? std::atoll(env) : 8192;
         int nt16 = 0;
-        const bool pays = M >= min_rows && (wide_loads_of_b(N, B, ldb) || cbm_panel_takes_unaligned(M, N, K));
-        const size_t smem = pays ? panel_lds_bytes(N, K, A, lda, &nt16) : 0;
+        const bool wide_b = wide_loads_of_b(N, B, ldb);
+        const bool pays = M >= min_rows && (wide_b || cbm_panel_takes_unaligned(M, N, K));
+        const size_t smem = pays ? panel_lds_bytes(N, K, A, lda, wide_b, &nt16) : 0;
         if (smem) {
             switch (nt16) {
                 case 1: return launch_panel<1>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);

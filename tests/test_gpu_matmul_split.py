@@ -207,3 +207,18 @@ def test_depths_of_the_panel_kernel(env, monkeypatch, k, n):
         C = torch.full((m, n), float("nan"), device="cuda")
         cbm.cbm_dense_matmul(A, B, C)
         assert torch.equal(C.double(), A.double() @ B.double()), (m, k, n)
+
+
+@pytest.mark.parametrize("k", [764, 768, 772, 784, 788, 1088, 1092, 1104, 1120, 1124])
+@pytest.mark.parametrize("n", [17, 24, 31, 32, 33, 40, 47, 48])
+def test_deepest_panels(env, monkeypatch, k, n):
+    """On both sides of where the panel fits: B of even widths and of odd ones end at different depths."""
+    monkeypatch.setenv("CBM_GEMM_SPLIT", "0")
+    torch, cbm = env
+    gen = torch.Generator(device="cuda").manual_seed(k * 1000 + n)
+    for m in (8192, 66000):
+        A = torch.randint(-8, 9, (m, k), device="cuda", generator=gen).float()
+        B = torch.randint(-8, 9, (k, n), device="cuda", generator=gen).float()
+        C = torch.full((m, n), float("nan"), device="cuda")
+        cbm.cbm_dense_matmul(A, B, C)
+        assert torch.equal(C.double(), A.double() @ B.double()), (m, k, n)
