@@ -197,11 +197,27 @@ def test_panel_kernel_on_any_b(env, monkeypatch, m, k, n):
 @pytest.mark.parametrize("k", [4, 16, 32, 36, 48, 64, 68, 80, 84, 96, 100, 112, 116, 128, 132, 144, 160, 176, 200, 240, 320])
 @pytest.mark.parametrize("n", [16, 32, 48, 64, 112])
 def test_depths_of_the_panel_kernel(env, monkeypatch, k, n):
-    """K of every remainder of the groups that a wave keeps in flight, with rows that leave a chunk: whole numbers, bit for bit."""
+    """K of every remainder of the groups that a wave keeps in flight, with fewer groups of rows than waves: whole numbers, bit for bit."""
     monkeypatch.setenv("CBM_GEMM_SPLIT", "0")
     torch, cbm = env
     gen = torch.Generator(device="cuda").manual_seed(k * 1000 + n)
     for m in (8192, 8209):
+        A = torch.randint(-8, 9, (m, k), device="cuda", generator=gen).float()
+        B = torch.randint(-8, 9, (k, n), device="cuda", generator=gen).float()
+        C = torch.full((m, n), float("nan"), device="cuda")
+        cbm.cbm_dense_matmul(A, B, C)
+        assert torch.equal(C.double(), A.double() @ B.double()), (m, k, n)
+
+
+@pytest.mark.parametrize("k", [48, 64, 80, 100, 112, 144, 160, 224])
+@pytest.mark.parametrize("n", [16, 32, 48, 64])
+def test_depths_of_the_panel_kernel_with_whole_groups(env, monkeypatch, k, n):
+    """Rows beyond 32 for each of its 2,048 waves, one group after the other in a wave and the next one's rows asked for by the last pass of the one before; what is
+    left over goes out in single column tiles, in pairs of them and whole (left over here: 1,000 and 1,500 groups of nothing else, then 2, 1,000, 1,500 and 1)."""
+    monkeypatch.setenv("CBM_GEMM_SPLIT", "0")
+    torch, cbm = env
+    gen = torch.Generator(device="cuda").manual_seed(k * 1000 + n)
+    for m in (31995, 47995, 65569, 97531, 113531, 131077):
         A = torch.randint(-8, 9, (m, k), device="cuda", generator=gen).float()
         B = torch.randint(-8, 9, (k, n), device="cuda", generator=gen).float()
         C = torch.full((m, n), float("nan"), device="cuda")
