@@ -1317,6 +1317,7 @@ cbm_status Builder::emit(int32_t nrounds) {
     h->flat = nrounds == 1 && !h->levels[0].by_xcd && std::all_of(h->parent.begin(), h->parent.end(), [](int32_t y) { return y < 0; });
     h->flat_long = 0;
     h->flat_rich = false;
+    h->flat_most_waves = env_clamped("CBM_FLAT_WAVES", CBM_FLAT_MOST_WAVES, 0, 1 << 30);
     if (h->flat) {
         const CbmLevel& R = h->levels[0];
         int64_t longs = h->seg_deltas;

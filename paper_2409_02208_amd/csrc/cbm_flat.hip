@@ -13,7 +13,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cstdlib>
 
 #include "cbm_internal.h"
 #include "cbm_rows.h"
@@ -200,12 +199,10 @@ constexpr int64_t kFlatNarrowWaves = 2048;
 }  // namespace
 
 int cbm_flat_lanes(const cbm_handle* h, int32_t k) {
-    const char* env = std::getenv("CBM_FLAT_WAVES");  // (read at every launch, so that a test can run both forms in one process)
-    const int64_t most = env ? std::atoll(env) : CBM_FLAT_MOST_WAVES;
     int lanes = 8;
     while (lanes < 32 && 4 * (int64_t)lanes < k) lanes *= 2;
     while (lanes > 8 && cbm_flat_waves(h, lanes / 2, k) <= kFlatNarrowWaves) lanes /= 2;
-    return cbm_flat_waves(h, lanes, k) <= most ? lanes : 0;
+    return cbm_flat_waves(h, lanes, k) <= h->flat_most_waves ? lanes : 0;
 }
 
 void cbm_launch_flat(const cbm_handle* h, bool segments, bool rows, int lanes, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,

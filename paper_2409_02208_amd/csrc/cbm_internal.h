@@ -123,6 +123,7 @@ struct cbm_handle {
     bool flat = false;             // every row is stored in full: one round of single rows, longest first, and segments
     int64_t flat_long = 0;         // how many of the rows have more than CBM_FLAT_SHORT entries
     bool flat_rich = false;        // a quarter of the entries or more are theirs or segments'
+    int64_t flat_most_waves = CBM_FLAT_MOST_WAVES;
     double other_us = 0;           // > 0: products run in row blocks or through shared sums, in about this time, unless the rows as they stand
                                    // (none of them split) take less: the device holds both
     bool bundled = false;          // some round's paths are emitted as bundles: delta columns are 26-bit in this handle

@@ -163,3 +163,17 @@ def test_which_launches_a_small_product_takes(env, name, kw, narrow, wide):
         torch.cuda.synchronize()
         assert [r["kind"] for r in cbm.cbm_profile_read(h)] == kinds, (k, kinds)
         cbm.cbm_profile_enable(h, False)
+
+
+def test_the_environment_is_read_when_the_handle_is_built(env, monkeypatch, square):
+    torch, cbm = env
+    rowptr, colidx = square
+    n = len(rowptr) - 1
+    X = torch.from_numpy(wl.gaussian_features(n, 32, 1)).cuda()
+    Y, Z, want = (torch.empty_like(X) for _ in range(3))
+    h = cbm.cbm_build(n, n, rowptr, colidx, max_depth=1)
+    cbm.cbm_spmm(h, X, want)
+    monkeypatch.setenv("CBM_FLAT_WAVES", "0")
+    cbm.cbm_spmm(h, X, Y)
+    cbm.cbm_spmm(cbm.cbm_build(n, n, rowptr, colidx, max_depth=1), X, Z)   # the kernels that larger products take: other orders of addition
+    assert torch.equal(Y, want) and not torch.equal(Z, want)
