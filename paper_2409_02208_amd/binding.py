@@ -124,8 +124,8 @@ def _stream_ptr(stream):
 
 def _dev_f32(t, name):
     """(address, leading dimension, rows, columns) of a matrix, each attribute asked for once: a small product's time is this code."""
-    strides = t.stride()
-    if not (t.is_cuda and t.dtype is _F32 and len(strides) == 2 and strides[1] == 1):
+    strides = t.stride() if t.is_cuda and t.dtype is _F32 else ()
+    if len(strides) != 2 or strides[1] != 1:
         raise ValueError(f"{name} must be a 2-D fp32 device tensor with unit column stride")
     rows, cols = t.shape
     ld = strides[0]

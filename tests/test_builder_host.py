@@ -391,3 +391,11 @@ def test_build_is_independent_of_the_thread_count():
             assert ref[1] == cur[1]
             assert np.array_equal(ref[2][0], cur[2][0]) and np.array_equal(ref[2][1], cur[2][1])
         cbm.cbm_free(h)
+
+
+@pytest.mark.parametrize("kind", ["host", "sparse", "double", "vector"])
+def test_operands_that_are_no_matrices_on_the_device_are_refused_as_such(kind):
+    torch = pytest.importorskip("torch")
+    A = {"host": torch.zeros(4, 4), "sparse": torch.eye(4).to_sparse_csr(), "double": torch.zeros(4, 4, dtype=torch.float64), "vector": torch.zeros(4)}[kind]
+    with pytest.raises(ValueError, match="A must be a 2-D fp32 device tensor"):
+        cbm.cbm_dense_matmul(A, A, A)
