@@ -52,7 +52,7 @@ L2_PEAK_GBS = 8 * 16 * 128 * 2.4
 COUNTER_GROUPS = (("fetch", ["FETCH_SIZE"]), ("write", ["WRITE_SIZE"]), ("l2", ["TCC_REQ_sum", "TCC_HIT_sum", "TCC_MISS_sum"]))
 # every kernel a product call can launch (the counter children match dispatches to the library's launch records by order)
 PRODUCT_KERNELS = ("cbm_level_kernel", "cbm_bundle_kernel", "cbm_combine_kernel", "cbm_finish_kernel", "cbm_block_sum_kernel",
-                   "cbm_block_kernel", "cbm_sum_sets_kernel", "cbm_sum_rows_kernel")
+                   "cbm_block_kernel", "cbm_sum_sets_kernel", "cbm_sum_rows_kernel", "cbm_flat_kernel")
 KIND_NAMES = {0: "rounds of paths", 1: "segments of split rows", 2: "combine of split rows", 3: "deferred finish",
               4: "sum of column blocks", 5: "row blocks", 6: "shared sums"}
 
@@ -207,13 +207,11 @@ def counter_child(args):
         X = torch.randn((g.n, k), device="cuda")
         Y = torch.empty((g.n, k), device="cuda")
         cbm.cbm_profile_enable(h, True)
-        cbm.cbm_spmm_normalized(h, X, Y)     # the library's own record of its launches (this product is counted too)
-        torch.cuda.synchronize()
-        recs = cbm.cbm_profile_read(h)
-        cbm.cbm_profile_enable(h, False)
-        for _ in range(reps - 1):
+        for _ in range(reps):                # all of them with the library's own record: segments and rows of small handles are then launched apart
             cbm.cbm_spmm_normalized(h, X, Y)
-        torch.cuda.synchronize()
+            torch.cuda.synchronize()
+            recs = cbm.cbm_profile_read(h)
+        cbm.cbm_profile_enable(h, False)
         plan.append(dict(workload=name, k=k, reps=reps, launches=[dict(kind=r["kind"], level=r["level"]) for r in recs]))
         del X, Y
     print(json.dumps({"plan": plan, "copy_bytes": 1 << 30, "copies": 3}), flush=True)
@@ -221,7 +219,7 @@ def counter_child(args):
 
 def run_counter_children(args, cache_dir):
     """One rocprofv3 --pmc child per counter group.  Returns {(workload, k): [per launch of one product:
-    {kind, level, fetch, write, req, hit, miss} in bytes / requests]} and a note; None + reason if unavailable."""
+    {kind, level, kernel, fetch, write, req, hit, miss} in bytes / requests]} and a note; None + reason if unavailable."""
     prof = shutil.which("rocprofv3") or "/opt/rocm/bin/rocprofv3"
     if not os.path.exists(prof):
         return None, "rocprofv3 not found"
@@ -268,6 +266,7 @@ def run_counter_children(args, cache_dir):
             acc = out.setdefault(key, [dict(kind=l["kind"], level=l["level"]) for l in p["launches"]])
             for li in range(nl):
                 vals = {c: np.mean([mine[at + rep * nl + li][c] for rep in range(p["reps"])]) for c in counters}
+                acc[li]["kernel"] = next(s for s in PRODUCT_KERNELS if s in mine[at + li]["name"])
                 if tag == "fetch":
                     acc[li]["fetch"] = vals["FETCH_SIZE"] * 1024.0 * calib["fetch"]
                 elif tag == "write":
@@ -406,6 +405,12 @@ def launch_table(agg, nprof, counted):
     return out
 
 
+def dominant_kernel(kind, counted):
+    """The kernel behind a product's launches of one kind: as the counters saw it (the last one: of shared sums the rows), else the usual one."""
+    seen = [l["kernel"] for l in counted or [] if l["kind"] == kind and "kernel" in l]
+    return seen[-1] if seen else {5: "cbm_block_kernel", 6: "cbm_sum_rows_kernel"}.get(kind, "cbm_level_kernel")
+
+
 def bench_product(torch, cbm, orc, g, h, hc, Xh, k, steps, warmup, workload, counted=None, ceiling=None, profile_steps=20):
     """Time cbm_spmm_normalized on handle h (and on the all-roots handle hc), with the per-launch roofline."""
     st = cbm.cbm_stats(h)
@@ -429,7 +434,7 @@ def bench_product(torch, cbm, orc, g, h, hc, Xh, k, steps, warmup, workload, cou
     if dom is not None:
         per = dom["launches_per_product"]
         avg_ms = dom["ms"] / per
-        roofline = dict(bound="hbm", kernel={5: "cbm_block_kernel", 6: "cbm_sum_rows_kernel"}.get(dom["kind"], "cbm_level_kernel"), launch=dom["launch"], peak=HBM_PEAK_GBS, unit="GB/s",
+        roofline = dict(bound="hbm", kernel=dominant_kernel(dom["kind"], counted), launch=dom["launch"], peak=HBM_PEAK_GBS, unit="GB/s",
                         avg_launch_ms=avg_ms, launches_per_step=per,
                         algorithmic_bytes_per_launch=dom["algorithmic_bytes"] / per, algorithmic_GBps=dom["algorithmic_GBps"],
                         share_of_step_ms=dom["ms"] / ms_prof if ms_prof > 0 else None)

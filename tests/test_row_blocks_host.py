@@ -74,6 +74,22 @@ def test_bench_figures_are_of_what_runs():
     assert bench.method_figures(stats, k, True, hubs, 2) == (500000, 1240, 4 * k * 200 + 640 * 24 + 600 * 8 + 100 * 8)
 
 
+def test_bench_knows_every_kernel_of_a_product():
+    """The counter children match dispatches to launch records by their order, so no kernel of a product may be missing; the roofline names what ran."""
+    import glob
+    import os
+    import re
+
+    import bench
+
+    sources = [open(p).read() for p in glob.glob(os.path.join(os.path.dirname(cbm.__file__), "csrc", "*.hip")) if "gemm" not in p and "build" not in p]
+    kernels = {k for s in sources for k in re.findall(r"__global__[^;{]*?void (cbm_\w+_kernel)\(", s)} - {"cbm_entry_weights_kernel"}  # (once per handle)
+    assert kernels == set(bench.PRODUCT_KERNELS)
+    counted = [dict(kind=6, level=1, kernel="cbm_sum_sets_kernel"), dict(kind=6, level=2, kernel="cbm_sum_rows_kernel"), dict(kind=0, level=1, kernel="cbm_flat_kernel")]
+    assert [bench.dominant_kernel(kind, counted) for kind in (0, 6)] == ["cbm_flat_kernel", "cbm_sum_rows_kernel"]
+    assert [bench.dominant_kernel(kind, None) for kind in (0, 5, 6)] == ["cbm_level_kernel", "cbm_block_kernel", "cbm_sum_rows_kernel"]
+
+
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_panel_kernel_takes_an_unaligned_b_where_that_was_measured_to_pay(tmp_path):
     """(M, N, K, staged kernel, panel kernel: microseconds, or the panel's time over the staged kernel's) on both sides of the rule's lines."""
