@@ -214,11 +214,10 @@ cbm_status cbm_build(int64_t m, int64_t n, const int64_t* rowptr, const int32_t*
  * sums where that is more; a quarter more without self-loops) for each of up to sixteen streams and captures, of these
  * fourteen captures at most.  The first is there from cbm_build on; the others are allocated when a product first needs
  * them, also under capture.  Where more than four streams have one, a stream that asks is given that of another whose
- * products are done; that of a capture comes back when the graph and all that is instantiated from it are destroyed;
- * cbm_free frees them.  A product for which there is none sums each row's sets in place: one launch (level 3 of kind 6),
- * the same bits, two to four times the time.  Neither way touches the scratch of split rows, so such products may overlap
- * freely, whatever num_split_rows says (those of cbm_spmm_noalloc may not).  A stream or a captured graph may be destroyed
- * once what it was given is done.
+ * products are done; those of captures come back by cbm_release_captures; cbm_free frees them all.  A product for which
+ * there is none sums each row's sets in place: one launch (level 3 of kind 6), the same bits, two to four times the time.
+ * Neither way touches the scratch of split rows, so such products may overlap freely, whatever num_split_rows says (those
+ * of cbm_spmm_noalloc may not).  A stream may be destroyed once what it was given is done.
  * Per-launch profiling (cbm_profile_enable) records events and must be off during capture.
  */
 cbm_status cbm_spmm(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
@@ -252,6 +251,14 @@ cbm_status cbm_spmm_noalloc(const cbm_handle* h, const float* X, int64_t ldx, in
  * current.  A handle without split rows needs no scratch: the call then does nothing.
  */
 cbm_status cbm_reserve(cbm_handle* h, int32_t max_k);
+
+/*
+ * cbm_release_captures -- the caller's word that no graph with products of this handle captured so far runs or will
+ * be launched again (nor an instance updated from one): their arrays of sums (see cbm_spmm) are there for
+ * later captures and streams.  For programs that capture anew many times in a handle's life; not while a capture with
+ * products of the handle is under way.  A handle whose products take no shared sums has none: the call then does nothing.
+ */
+cbm_status cbm_release_captures(cbm_handle* h);
 
 /*
  * cbm_spmm_normalized -- Y = D^-1/2 (A + I) D^-1/2 . X  (Eq. (1); Section 2.2,

@@ -112,6 +112,13 @@ cbm_status cbm_reserve(cbm_handle* h, int32_t max_k) {
     return cbm_reserve_scratch(h, max_k);  // (a column-blocked handle: its partial rows and the inner scratch)
 }
 
+cbm_status cbm_release_captures(cbm_handle* h) {
+    if (!h) return CBM_ERR_INVALID_ARG;
+    if (!h->on_device) return CBM_ERR_STATE;
+    cbm_sum_release_captures(h->blocks > 1 ? h->inner : h);
+    return CBM_OK;
+}
+
 cbm_status cbm_dense_matmul(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb,
                             float* C, int64_t ldc, void* hip_stream) {
     if (M < 0 || N < 0 || K < 0 || lda < K || ldb < N || ldc < N) return CBM_ERR_INVALID_ARG;

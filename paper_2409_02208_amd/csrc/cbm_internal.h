@@ -1,9 +1,7 @@
 // Internal layout shared by the host builder, the kernel launchers and the C ABI.
 #pragma once
 
-#include <atomic>
 #include <cstdint>
-#include <memory>
 #include <mutex>
 #include <vector>
 
@@ -91,9 +89,8 @@ inline int64_t cbm_sum_sizes(int64_t k) { return k <= 32 ? 8 : k <= 64 ? 16 : (k
 struct CbmSumScratch {  // cbm_sum_bytes of the products that one stream, or one capture on it, enqueues
     uint64_t stream = 0, capture = 0, thread = 0;
     float* sums = nullptr;
-    void* done = nullptr;                     // an event; `passed`: it is behind the last of these products
+    void* done = nullptr;  // an event; `passed`: it is behind the last of these products
     bool passed = false;
-    std::shared_ptr<std::atomic<bool>> gone;  // of a capture: its graph is
 };
 
 struct cbm_handle {
@@ -238,6 +235,7 @@ inline double cbm_flat_us(const cbm_handle* h, int64_t k, int lanes) {
 void cbm_launch_sum_chunk(const cbm_handle* h, bool rows, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
                           float self_w, float* S, int64_t lds, void* stream);
 CbmSumScratch* cbm_sum_scratch(const cbm_handle* h, void* stream);
+void cbm_sum_release_captures(const cbm_handle* h);
 void cbm_sum_enqueued(const cbm_handle* h, CbmSumScratch* s, void* stream);
 bool cbm_sum_guarded(const cbm_handle* h, int mode, float self_w);  // whether the product keeps the sets' sizes beside their sums
 inline size_t cbm_sum_bytes(const cbm_handle* h) {

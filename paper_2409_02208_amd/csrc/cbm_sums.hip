@@ -9,10 +9,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <functional>
-#include <memory>
 #include <thread>
 #include <type_traits>
 
@@ -396,28 +394,6 @@ constexpr size_t kForStreams = 2;    // of these, never given to captures
 constexpr size_t kQuietStreams = 4;
 constexpr uint64_t kNobody = ~0ull;
 
-// Tell `gone` when the graph of the capture under way on this stream, and all that is instantiated from it, are destroyed; nullptr if that cannot be had.
-std::shared_ptr<std::atomic<bool>> end_of_capture(hipGraph_t graph) {
-    using Flag = std::shared_ptr<std::atomic<bool>>;
-    auto* told = new Flag(std::make_shared<std::atomic<bool>>(false));
-    const Flag gone = *told;
-    hipUserObject_t object = nullptr;
-    if (hipUserObjectCreate(&object, told, [](void* p) {
-            (*static_cast<Flag*>(p))->store(true);
-            delete static_cast<Flag*>(p);
-        }, 1, hipUserObjectNoDestructorSync) != hipSuccess) {
-        (void)hipGetLastError();
-        delete told;
-        return nullptr;
-    }
-    if (hipGraphRetainUserObject(graph, object, 1, hipGraphUserObjectMove) != hipSuccess) {
-        (void)hipGetLastError();
-        (void)hipUserObjectRelease(object, 1);
-        return nullptr;
-    }
-    return gone;
-}
-
 }  // namespace
 
 void cbm_launch_sum_chunk(const cbm_handle* h, bool rows, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy, int mode, const float* rw,
@@ -436,18 +412,18 @@ bool cbm_sum_guarded(const cbm_handle* h, int mode, float self_w) {  // (the sum
 }
 
 // The array for the sums of products on this stream; nullptr if there is none and none can be had.  Products of different streams may
-// run at the same time, so each has its own; so has every capture, whose graph may be replayed beside anything.  An array comes back when the graph
-// of its capture is gone, or when another stream asks for one and the event behind the last product on its own stream, where there is one, has passed.  The caller
-// holds h->sum_mutex and calls cbm_sum_enqueued when the product is enqueued.  (The first is allocated with the handle; the allocation and the
-// questions here are ones that a capture under way does not mind.)
+// run at the same time, so each has its own; so has every capture, whose graph may be replayed beside anything.  A stream's array is another's that asks
+// for one when the event behind the last product on its own stream, where there is one, has passed.  A capture's is kept until the caller says that no graph
+// is left (cbm_release_captures): the graph's end does not say so, for hipGraphExecUpdate has an instance of another graph go on with what this one
+// used.  The caller holds h->sum_mutex and calls cbm_sum_enqueued when the product is enqueued.  (The first array is allocated with the handle; the
+// allocation and the questions here are ones that a capture under way does not mind.)
 CbmSumScratch* cbm_sum_scratch(const cbm_handle* h, void* stream_) {
     hipStream_t stream = (hipStream_t)stream_;
     const uint64_t me = (uint64_t)(uintptr_t)stream;
     uint64_t capture = 0, thread = 0;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     unsigned long long id = 0;
-    hipGraph_t graph = nullptr;
-    if (hipStreamGetCaptureInfo_v2(stream, &status, &id, &graph, nullptr, nullptr) != hipSuccess) (void)hipGetLastError();
+    if (hipStreamGetCaptureInfo(stream, &status, &id) != hipSuccess) (void)hipGetLastError();
     else if (status == hipStreamCaptureStatusActive) capture = id + 1;
     if (stream == hipStreamPerThread) thread = (uint64_t)std::hash<std::thread::id>{}(std::this_thread::get_id());
     auto& all = h->sum_scratch;
@@ -462,14 +438,7 @@ CbmSumScratch* cbm_sum_scratch(const cbm_handle* h, void* stream_) {
         return nullptr;
     }
     size_t captured = 0;
-    for (CbmSumScratch& s : all) {
-        if (s.capture != 0 && s.gone && s.gone->load()) {
-            s.stream = kNobody;
-            s.capture = 0;
-            s.gone.reset();
-        }
-        captured += s.capture != 0;
-    }
+    for (const CbmSumScratch& s : all) captured += s.capture != 0;
     CbmSumScratch* mine = nullptr;
     for (CbmSumScratch& s : all)
         if (!mine && s.stream == kNobody && (capture == 0 || captured + 1 < all.size())) mine = &s;
@@ -494,7 +463,6 @@ CbmSumScratch* cbm_sum_scratch(const cbm_handle* h, void* stream_) {
         mine->capture = capture;
         mine->thread = thread;
         mine->passed = false;
-        if (capture != 0) mine->gone = end_of_capture(graph);
     }
     (void)hipThreadExchangeStreamCaptureMode(&mode);
     return mine;
@@ -509,6 +477,15 @@ void cbm_sum_enqueued(const cbm_handle* h, CbmSumScratch* s, void* stream) {
     if (!s->done && hipEventCreateWithFlags((hipEvent_t*)&s->done, hipEventDisableTiming) != hipSuccess) s->done = nullptr;
     s->passed = s->done && hipEventRecord((hipEvent_t)s->done, (hipStream_t)stream) == hipSuccess;
     if (!s->passed) (void)hipGetLastError();
+}
+
+void cbm_sum_release_captures(const cbm_handle* h) {
+    std::lock_guard<std::mutex> lock(h->sum_mutex);
+    for (CbmSumScratch& s : h->sum_scratch)
+        if (s.capture != 0) {
+            s.stream = kNobody;
+            s.capture = 0;
+        }
 }
 
 cbm_status cbm_upload_sums(cbm_handle* h) {

@@ -378,7 +378,8 @@ def _sixes(n):
 
 
 def test_arrays_of_streams_and_graphs_that_are_done_come_back(env):
-    """One stream after the other, one graph after the other: no more than a few arrays of 29 MiB, and every product has one."""
+    """One stream after the other, one graph after the other: no more than a few arrays of 29 MiB, and every product has one.  Graphs that are not given
+    up keep theirs, also beyond their own end."""
     torch, cbm = env
     n, k, array = 60000, 64, 29 << 20
     rowptr, colidx = _sixes(n)
@@ -416,7 +417,7 @@ def test_arrays_of_streams_and_graphs_that_are_done_come_back(env):
         torch.cuda.synchronize()
         assert torch.equal(Y, want)
         del graph
-        torch.cuda.synchronize()
+        cbm.cbm_release_captures(h)
         free.append(torch.cuda.mem_get_info()[0])
     assert free[2] - free[-1] < array
     for _ in range(20):                       # more than there are arrays for, all alive: streams keep some
@@ -431,6 +432,8 @@ def test_arrays_of_streams_and_graphs_that_are_done_come_back(env):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(Y, want)
+    with pytest.raises(cbm.CbmError):
+        cbm.cbm_release_captures(cbm.cbm_build(n, n, rowptr, colidx, host_only=True))
 
 
 def test_columns_in_goes(env, monkeypatch):
