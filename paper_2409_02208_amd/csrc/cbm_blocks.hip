@@ -72,7 +72,7 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
     }
     __syncthreads();
     // The rows of the tile that this wave will store and their weights, one load after the other, are asked for here and kept for the end
-    // (k = 256 306 -> 297 us, communities of 1,024 nodes 9.8 -> 9.1).  Rows alone are asked for when the walk is over, beside the reduction: here
+    // (k = 256 292 -> 286 us, communities of 1,024 nodes 9.8 -> 9.1).  Rows alone are asked for when the walk is over, beside the reduction: here
     // they cost what they would save (40,000 nodes, k = 32, no weights 13.9 -> 14.6).
     const uint32_t my_row = WROW ? rows[(size_t)blk.row0 + 32 * wave + (lane & 31)] : 0u;
     float my_rw = 0.0f;

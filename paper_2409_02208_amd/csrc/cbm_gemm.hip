@@ -574,7 +574,7 @@ __global__ __launch_bounds__(64 * WPB) void cbm_gemm_panel_kernel(int64_t M, int
 inline bool wide_loads_of_b(int N, const float* B, int64_t ldb) { return N % 4 == 0 && ldb % 4 == 0 && ((uintptr_t)B & 15) == 0; }
 
 // Groups of 16 k that a wave of the panel kernel keeps in flight, and that its K loop is a multiple of: whichever of 4, 3, 5 and 7 pads K least
-// (132,534 x K . K x 47, us, with 4 always -> here: K = 48 18.2 -> 16.7, 80 25.4 -> 20.7, 96 26.0 -> 23.0, 100 27.1 -> 25.7, 144 33.3 -> 29.0; x 64: 80 29.9 -> 23.1,
+// (132,534 x K . K x 47, us, with 4 always -> here: K = 48 19.0 -> 16.9, 80 25.7 -> 20.8, 96 25.7 -> 22.4, 100 26.6 -> 25.7, 144 32.9 -> 27.8; x 64: 80 29.8 -> 22.8,
 // 200 47.7 -> 44.7; 7 beside one tile would lose, 100 x 16 17.7 -> 18.4).
 inline int panel_ring(int K, int nt16) {
     const int nkg = (K + 15) / 16;
