@@ -216,8 +216,9 @@ cbm_status cbm_build(int64_t m, int64_t n, const int64_t* rowptr, const int32_t*
  * them, also under capture.  Where more than four streams have one, a stream that asks is given that of another whose
  * products are done; those of captures come back by cbm_release_captures; cbm_free frees them all (bytes_cbm leaves them
  * out, as it does all scratch).  A product for which there is none sums each row's sets in place: one launch (level 3 of
- * kind 6), the same bits, two to four times the time.  Neither way touches the scratch of split rows, so such products may overlap freely, whatever num_split_rows says (those
- * of cbm_spmm_noalloc may not).  A stream may be destroyed once what it was given is done.
+ * kind 6), the same bits, two to four times the time.  Neither way touches the scratch of split rows, so such products
+ * may overlap freely, whatever num_split_rows says (those of cbm_spmm_noalloc may not).  A stream may be destroyed once
+ * what it was given is done.
  * Per-launch profiling (cbm_profile_enable) records events and must be off during capture.
  */
 cbm_status cbm_spmm(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
