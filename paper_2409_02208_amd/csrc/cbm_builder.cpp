@@ -1715,7 +1715,14 @@ void Builder::shared_sums(const std::vector<uint8_t>& holds_own) {
                 continue;
             }
             const int32_t x = rows[i - ns];
-            for (int64_t q = S.row_ptr[x]; q < S.row_ptr[x + 1]; ++q) *e++ = CBM_SUM_BIT | (uint32_t)at[S.row_sets[q]];
+            auto add_sets = [&](bool with_own) {
+                for (int64_t q = S.row_ptr[x]; q < S.row_ptr[x + 1]; ++q) {
+                    const int32_t *b = S.set_cols.data() + S.set_ptr[S.row_sets[q]], *t = S.set_cols.data() + S.set_ptr[S.row_sets[q] + 1];
+                    if (holds_own[x] ? with_own : std::binary_search(b, t, x) == with_own) *e++ = CBM_SUM_BIT | (uint32_t)at[S.row_sets[q]];
+                }
+            };
+            add_sets(true);  // (of a row that does not hold its own column: the sets that do come first, -own of them)
+            add_sets(false);
             for (int64_t p = rowptr[x]; p < rowptr[x + 1]; ++p)
                 if (colidx[p] != x && !S.covered[p]) *e++ = (uint32_t)colidx[p];
         }

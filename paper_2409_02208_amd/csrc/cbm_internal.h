@@ -72,7 +72,7 @@ constexpr float CBM_BLOCK_UP = 16777216.0f;         // 2^24: rows of X are split
 
 // Shared sums: a work item is a column set that is summed once, or a row made of such sums and of columns of its own.
 struct CbmSumItem {
-    uint32_t start, len;  // its entries: columns, or CBM_SUM_BIT | set
+    uint32_t start, len;  // its entries: CBM_SUM_BIT | set, then columns (sets with the own column of a row that does not hold it come first)
     int32_t row;          // the row it stores
     int32_t own;          // how often the row adds its own column (negative: its sets hold it more often than the row does)
 };

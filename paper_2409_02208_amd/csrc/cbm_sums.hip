@@ -27,8 +27,8 @@ typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 // often as it is taken off, is more than kGuard times the largest of the others (or half as much: the exponent is all that is known of it) is put
 // together without it.  What is let through is off by 32 x 2^-24 = 2e-6 of the row's terms at most.  Rows put together again are waited for, and
 // sets have as few as four columns: with 16 the rows' launch takes 113 us instead of 83 on Gaussian features (235,868 nodes, k = 128), with 32 and 128
-// the same (79 where no row is looked at); of features with every other value zero 89, with 128 86.  Both launches 137 us instead of 127; 30,000 nodes,
-// k = 64 26 instead of 23.  (Rows that hold their own column are off by as much of a sum that it is part of.)
+// the same (79 where no row is looked at); of features with every other value zero 92, with 128 86.  Both launches 132 us instead of 127; 30,000 nodes,
+// k = 64 25 instead of 23.  (Rows that hold their own column are off by as much of a sum that it is part of.)
 constexpr float kGuard = 32.0f;
 
 // The four columns of a lane in the block's 4 LANES.  RAGGED = false: 4 sl .. 4 sl + 3, one 128-bit access; true: sl, sl + LANES, ..., 32-bit
@@ -76,7 +76,8 @@ struct SumMap {
 };
 
 // What a row's others amount to, for rows that do not hold their own column (kGuard above): in the sets' launch the largest and the second largest value
-// of each column, in the rows' launch the largest of the single ones and, as packed exponents, of the sets' second largest.
+// of each column, in the rows' launch the largest of the single ones and of the sums without the row's own value and, as packed exponents, of the
+// sets' second largest.  (Zero is zero: a value that is alone in its set is that set's sum.)
 struct Sizes {
     f4 first = {0.0f, 0.0f, 0.0f, 0.0f}, second = {0.0f, 0.0f, 0.0f, 0.0f};
     ushort2v even = {0, 0}, odd = {0, 0};
@@ -94,10 +95,10 @@ struct Sizes {
         for (int c = 0; c < 4; ++c) r |= (second[c] != 0.0f ? max(__float_as_uint(second[c]) >> 23 & 255u, 1u) : 0u) << (8 * c);
         return r;
     }
-    __device__ __forceinline__ void add_to_row(const f4& x, bool set, uint32_t exponents) {
+    // `mine`: x is the sum of a set that holds the row's own value, of which only the others are asked for
+    __device__ __forceinline__ void add_to_row(const f4& x, bool mine, uint32_t exponents) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) first[c] = fmaxf(first[c], fabsf(set ? 0.0f : x[c]));
-        exponents = set ? exponents : 0u;
+        for (int c = 0; c < 4; ++c) first[c] = fmaxf(first[c], fabsf(mine ? 0.0f : x[c]));
         even = __builtin_elementwise_max(even, __builtin_bit_cast(ushort2v, exponents & 0x00ff00ffu));
         odd = __builtin_elementwise_max(odd, __builtin_bit_cast(ushort2v, exponents >> 8 & 0x00ff00ffu));
     }
@@ -161,9 +162,9 @@ __device__ __forceinline__ void walk(f4& acc, Sizes& sizes, const uint32_t* __re
 }
 
 // The same for a row whose others' sizes are wanted too.  These cost a batch of entries twice its instructions where sets are among them (30,000 nodes,
-// k = 64: 6 us more, waiting for the longest rows); sets come first, and batches without any do without.
+// k = 64: 6 us more, waiting for the longest rows); sets come first, and batches without any do without.  The first `mine` hold the row's own column.
 template <bool RAGGED, int LANES, int U0>
-__device__ __forceinline__ void walk_sized(f4& acc, Sizes& sizes, const uint32_t* __restrict__ es, uint32_t len, int sl, const Rows& r,
+__device__ __forceinline__ void walk_sized(f4& acc, Sizes& sizes, const uint32_t* __restrict__ es, uint32_t len, int mine, int sl, const Rows& r,
                                            const Columns<RAGGED, LANES>& cols) {
     uint32_t e = (uint32_t)sl < len ? __builtin_nontemporal_load(es + sl) : 0u;
     for (uint32_t at = 0; at < len; at += LANES) {
@@ -190,7 +191,7 @@ __device__ __forceinline__ void walk_sized(f4& acc, Sizes& sizes, const uint32_t
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 acc += x[u];
-                sizes.add_to_row(x[u], MIXED && b + u < sets, size[u]);
+                sizes.add_to_row(x[u], MIXED && (int)at + b + u < mine, b + u < sets ? size[u] : 0u);
             }
         };
         int b = 0;
@@ -246,7 +247,7 @@ __device__ __forceinline__ f4 apart(const CbmSumItem* __restrict__ items, const 
 // The sum over a row's entries with its sets summed here and now, in the order in which the two launches do it: the same bits without the memory.
 template <bool RAGGED, int LANES, bool WEIGHTED, bool GUARD, int U>
 __device__ __forceinline__ void in_place(f4& acc, Sizes& sizes, const CbmSumItem* __restrict__ items, const uint32_t* __restrict__ entries,
-                                         const float* __restrict__ ws, uint32_t start, uint32_t len, int sl, const Rows& r,
+                                         const float* __restrict__ ws, uint32_t start, uint32_t len, int mine, int sl, const Rows& r,
                                          const Columns<RAGGED, LANES>& cols) {
     uint32_t i = start;
     for (; i < start + len; ++i) {  // sets come first
@@ -257,9 +258,9 @@ __device__ __forceinline__ void in_place(f4& acc, Sizes& sizes, const CbmSumItem
         Sizes set;
         walk<RAGGED, LANES, WEIGHTED, false, GUARD, false, U>(sum, set, entries + first, WEIGHTED ? ws + first : nullptr, n, sl, r, 0, cols);
         acc += sum;
-        if (GUARD) sizes.add_to_row(sum, true, set.packed());
+        if (GUARD) sizes.add_to_row(sum, (int)(i - start) < mine, set.packed());
     }
-    if constexpr (GUARD) walk_sized<RAGGED, LANES, U>(acc, sizes, entries + i, start + len - i, sl, r, cols);
+    if constexpr (GUARD) walk_sized<RAGGED, LANES, U>(acc, sizes, entries + i, start + len - i, 0, sl, r, cols);
     else walk<RAGGED, LANES, WEIGHTED, false, false, false, U>(acc, sizes, entries + i, WEIGHTED ? ws + i : nullptr, start + len - i, sl, r, 0, cols);
 }
 
@@ -282,13 +283,14 @@ __global__ __launch_bounds__(256, 4) void cbm_sum_rows_kernel(const CbmSumItem* 
     const float* mine = X + (uint64_t)(uint32_t)it.row * ldx;
     const bool add_own = MODE == 4 || it.own != 0;
     f4 own = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (add_own) own = cols.load(mine);
+    if (add_own && !GUARD) own = cols.load(mine);
     f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     Sizes sizes;
     const Rows from{X, ldx, S, lds, GUARD && !DIRECT ? set_sizes + blockIdx.y * LANES + sl : nullptr, ld_sizes};
-    if constexpr (DIRECT) in_place<RAGGED, LANES, WEIGHTED, GUARD, U>(acc, sizes, items, entries, ws, it.start, len, sl, from, cols);
-    else if constexpr (GUARD) walk_sized<RAGGED, LANES, U>(acc, sizes, entries + it.start, len, sl, from, cols);
+    if constexpr (DIRECT) in_place<RAGGED, LANES, WEIGHTED, GUARD, U>(acc, sizes, items, entries, ws, it.start, len, -it.own, sl, from, cols);
+    else if constexpr (GUARD) walk_sized<RAGGED, LANES, U>(acc, sizes, entries + it.start, len, -it.own, sl, from, cols);
     else walk<RAGGED, LANES, WEIGHTED, true, false, false, U>(acc, sizes, entries + it.start, WEIGHTED ? ws + it.start : nullptr, len, sl, from, 0, cols);
+    if (add_own && GUARD) own = cols.load(mine);  // (here, 7 waves a SIMD; asked for before the walk, 6)
     const float times = ((float)it.own + (MODE == 4 ? self_w : 0.0f)) * (WEIGHTED ? w : 1.0f);
     if (add_own)
 #pragma unroll

@@ -1,6 +1,7 @@
 // The shared sums of small square matrices, put together again: every row's sets, single columns and own column add up to the row, every
 // index is in range, every item is in one XCD's run, and the sets do not depend on the number of threads.  Built with ASan/UBSan by
 // test_shared_sums_host.py.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -29,7 +30,7 @@ int main() {
     setenv("CBM_HUB_BLOCKS", "0", 1);
     setenv("CBM_SHARED_SUMS", "1", 1);
     std::mt19937 rng(5);
-    int trial = 0, with = 0;
+    int trial = 0, with = 0, without = 0;
     long saved = 0;
     for (int n : {1, 2, 5, 40, 300, 1500})
         for (int form = 0; form < 8; ++form, ++trial) {
@@ -101,6 +102,13 @@ int main() {
                 for (int64_t p = orp[it.row]; p < orp[it.row + 1]; ++p) want[oci[p]] = 1, holds = holds || oci[p] == it.row;
                 if (sum != want) return fail("a row's parts do not add up to it", trial);
                 if (holds != ((it.len & CBM_SUM_OWN) != 0)) return fail("own column", trial);
+                if (!holds)  // sets that hold the row's column come first, -own of them
+                    for (uint32_t p = it.start; p < it.start + len && (x.sum_entries[p] & CBM_SUM_BIT); ++p) {
+                        const CbmSumItem& s = x.sum_items[x.sum_entries[p] & ~CBM_SUM_BIT];
+                        const bool mine = std::count(x.sum_entries.begin() + s.start, x.sum_entries.begin() + s.start + s.len, (uint32_t)it.row) > 0;
+                        if (mine != ((int)(p - it.start) < -it.own)) return fail("sets with the own column come first", trial);
+                        without += !mine;
+                    }
             }
             if (entries != (int64_t)x.sum_entries.size()) return fail("entries left over", trial);
             saved += x.stats.nnz - entries;
@@ -114,7 +122,7 @@ int main() {
                 if (at != (half ? x.num_sums + n : x.num_sums)) return fail("runs do not cover the items", trial);
             }
         }
-    if (with < 15 || saved <= 0) return fail("too few plans", with);
+    if (with < 15 || saved <= 0 || without == 0) return fail("too few plans", with);
     std::printf("sums ok: %d plans, %ld entries saved\n", with, saved);
     return 0;
 }

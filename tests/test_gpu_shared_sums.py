@@ -214,6 +214,42 @@ def test_a_value_that_its_neighbours_do_not_see(env, cliques, k, op):
     assert not bad.any(), [(int(r), int(c), float(X[r, c]), float(ref[r, c]), float(Y[r, c]), int(r % 3 + 1)) for r, c in np.argwhere(bad)[:5]]
 
 
+@pytest.mark.parametrize("own", [1.0, 300.0, -1e5, LOWEST])
+@pytest.mark.parametrize("k", [16, 50, 160])
+def test_sets_that_do_not_hold_the_rows_own_column(env, k, own):
+    """Node w is in a clique of its own and points at all of another one, of which only five nodes point back: that clique is a set of the row w without
+    its column w, and what is in it counts though it is the only value there."""
+    torch, cbm = env
+    groups, big, small = 25, 20, 12
+    n = groups * (big + small)
+    nodes = np.random.default_rng(1).permutation(n).reshape(groups, big + small)
+    src, dst = [], []
+    for g in nodes:
+        K, own_clique = g[:big], g[big:]
+        w = own_clique[0]
+        for c in (K, own_clique):
+            src += [x for x in c for y in c if x != y]
+            dst += [y for x in c for y in c if x != y]
+        src += [w] * big + list(K[:5])
+        dst += list(K) + [w] * 5
+    order = np.lexsort((dst, src))
+    src, dst = np.array(src)[order], np.array(dst, dtype=np.int32)[order]
+    rowptr = np.concatenate(([0], np.cumsum(np.bincount(src, minlength=n)))).astype(np.int64)
+    h = cbm.cbm_build(n, n, rowptr, dst)
+    X = np.zeros((n, k), dtype=np.float32)
+    ws = nodes[:, big]
+    X[ws] = own                                            # beside nothing in its own clique, and one value (or none) in the other
+    for c in range(k):
+        if c % 3:
+            X[nodes[:, c % big], c] = 3.0
+    want = np.stack([X[dst[a:b]].astype(np.float64).sum(0) for a, b in zip(rowptr[:-1], rowptr[1:])])
+    Xd, Y = torch.from_numpy(X).cuda(), torch.full((n, k), float("nan"), device="cuda")
+    assert _kinds(torch, cbm, h, lambda: cbm.cbm_spmm(h, Xd, Y)) == [6, 6]
+    assert np.array_equal(Y.cpu().numpy()[ws], want[ws].astype(np.float32))
+    cbm.cbm_spmm_mean(h, Xd, Y)
+    assert np.allclose(Y.cpu().numpy()[ws], want[ws] / np.diff(rowptr)[ws, None], rtol=1e-6, atol=0)
+
+
 def test_a_mask_on_a_graph_that_row_blocks_take_too(env, monkeypatch):
     """As the library chooses by itself: with shared sums and without, a row next to nothing but ordinary values is an ordinary value."""
     torch, cbm = env
