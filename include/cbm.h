@@ -102,7 +102,7 @@ typedef enum {
  *                sums; bytes_cbm counts these lists too.  A row that does not hold its
  *                own column is then its sets' sums less its own row of X as often as
  *                they hold it, unless that is more than 32 times the largest other value
- *                of a column: what rounding leaves of it stays below 2e-6 of the row's
+ *                of a column: what rounding leaves of it stays below 1e-5 of the row's
  *                terms, whatever value the row itself has.  A host-only handle has no
  *                blocks or shared sums: num_tasks and bytes_cbm are those of the
  *                paths.  The
