@@ -6,6 +6,8 @@
 #include <cstdlib>
 #include <vector>
 
+#include "cbm_internal.h"
+
 // The rows among row s's columns that share most columns with it (counted on about 64 evenly spread ones of theirs), in
 // descending order: `wanted(y)` says which rows count, `take(y)` gets them.  `mark` holds no s.
 template <class Wanted, class Take>
@@ -107,4 +109,18 @@ inline void tiles_of_alike_rows(uint32_t* rows, int count, int tile, const int64
     std::vector<uint32_t> out((size_t)count);
     for (int i = 0; i < count; ++i) out[i] = rows[order[i]];
     std::copy(out.begin(), out.end(), rows);
+}
+
+// The blocks' columns as the device has them: bit 31 of a group's column 4 i + s says whether tile s holds any of the columns of step i (its bytes in
+// `masks`: word i of each of the group's 64 lanes), so that the kernel knows it for a whole group by one comparison of what it loads anyway.
+inline std::vector<uint32_t> flag_active_tiles(const std::vector<uint32_t>& cols, const std::vector<uint32_t>& masks) {
+    std::vector<uint32_t> flagged(cols);
+    for (size_t g = 0; g < cols.size() / 64; ++g)
+        for (int i = 0; i < 4; ++i) {
+            uint32_t any = 0;
+            for (int l = 0; l < 64; ++l) any |= masks[g * 256 + 4 * (size_t)l + i];
+            for (int s = 0; s < 4; ++s)
+                if (any >> (8 * s) & 255u) flagged[g * 64 + 4 * i + s] |= CBM_BLOCK_ACTIVE;
+        }
+    return flagged;
 }

@@ -14,10 +14,15 @@
 // 32-bit load a row: two rows of 128 bytes an instruction, 5.7 cycles; 128-bit loads take 16 and bring a lane four columns of
 // one row, which is not what a matrix-core operand is) and splits them in registers: they are the B operand of
 // v_mfma_f32_32x32x16_bf16 as they stand.  The A operand is a byte of bits through a table in LDS.  Tiles that hold none of a
-// step's 16 columns are left out.
+// step's 16 columns are left out; which ones do comes with the columns (flag_active_tiles).
 //
 // What bounds it (protein recipe, k = 256; before: 0.79 ms on the paths, now 0.32): matrix cores 36 % and vector ALU 53 % of the
 // cycles at a clock that the two bring down to 1.9 GHz; rows of X from L1 instead of L2 change 5 %, no weights or table 3 %.
+// A step's instructions add up, whichever unit they go to: with two waves a SIMD instead of three 325 us instead of 290, with twice as many matrix
+// instructions 371, with a third of them and no split 211, with rows from L1 260.  So what helps is fewer of them -- row offsets multiplied out once a
+// column and tiles known to be empty without looking at their bits 292 -> 284 us (40,000 nodes, k = 32 13.0 -> 12.2, k = 47 18.4 -> 17.7) -- and not another
+// arrangement: rows by 128-bit loads turned in LDS 339, the next step's split between the products of this one 318, a table read for active tiles
+// only 295, workgroups that walk one block after another 434.
 // Measured on the way: 64 columns a slab with scalar loads of the column numbers 0.52 ms (two waves per SIMD, waits for
 // scalar loads), blocks of 64 rows 0.46 ms, all tiles without a test 0.51 ms, rows not sorted into tiles 0.41 ms.
 #include <hip/hip_runtime.h>
@@ -93,6 +98,12 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
         return *reinterpret_cast<const float*>(base + (uint32_t)(__umul24(row, (uint32_t)ldxb) + (uint32_t)ccol * 4u));
     };
 
+    // the same of a row by what stands in LDS for it: where it begins (one multiplication a column there instead of one a load here), or, BIG, its number
+    auto x_from = [&](uint32_t at) -> float {
+        if (BIG) return x_at(at);
+        return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(X) + (at + (uint32_t)ccol * 4u));
+    };
+
     floatx16 acc[T];
 #pragma unroll
     for (int s = 0; s < T; ++s)
@@ -119,9 +130,9 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
     };
     auto load_x = [&](float (&x)[8], const Ids& i) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = x_at(i.v[j / 4][j % 4]);
+        for (int j = 0; j < 8; ++j) x[j] = x_from(i.v[j / 4][j % 4]);
     };
-    auto consume = [&](float (&x)[8], const Weights& w, uint32_t mask) {
+    auto consume = [&](float (&x)[8], const Weights& w, uint32_t mask, uint32_t active) {
         uintx4 a[T];
 #pragma unroll
         for (int s = 0; s < T; ++s) a[s] = lut[(mask >> (8 * s)) & 255u];
@@ -139,7 +150,8 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
         }
 #pragma unroll
         for (int s = 0; s < T; ++s)
-            if (__ballot(((mask >> (8 * s)) & 255u) != 0)) {
+            // (a scalar: six vector instructions a step that looked at the bits are gone; hub blocks, whose tiles are nearly all active, lose 1 % by it)
+            if (MODE == 5 ? __ballot(((mask >> (8 * s)) & 255u) != 0) != 0 : (active >> s & 1u) != 0) {
 #pragma unroll
                 for (int q = 2; q >= 0; --q)
                     acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[s]), __builtin_bit_cast(bf16x8, P[q]), acc[s], 0, 0, 0);
@@ -153,7 +165,7 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
         const float* gw = wcols + (size_t)blk.group0 * 64 + lane;
         const uintx4* gm = masks + (size_t)blk.group0 * 64 + lane;
         auto put = [&](int buf, uint32_t id, float w) {
-            reinterpret_cast<uint32_t*>(ids[wave][buf])[lane] = id;
+            reinterpret_cast<uint32_t*>(ids[wave][buf])[lane] = BIG ? id & ~CBM_BLOCK_ACTIVE : __umul24(id, (uint32_t)ldxb);
             if (WCOL) reinterpret_cast<float*>(wts[wave][buf])[lane] = w;
         };
         // (three buffers of rows in flight besides the one in use would cost a wave per SIMD; four names, three alive)
@@ -163,8 +175,10 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
         uint32_t g = wave;
         size_t at = (size_t)g * 64, next = (size_t)min(g + WAVES, last) * 64;
         uintx4 mask = gm[at];
-        put(0, gc[at], WCOL ? gw[at] : 0.0f);
-        uint32_t nid = gc[next];
+        uint32_t nid = gc[at];
+        uint32_t active = (uint32_t)__ballot(nid & CBM_BLOCK_ACTIVE), nactive = active;
+        put(0, nid, WCOL ? gw[at] : 0.0f);
+        nid = gc[next];
         float nw = WCOL ? gw[next] : 0.0f;
         uintx4 nmask = gm[next];
         ask_weight();
@@ -182,34 +196,36 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
             read_ids(i, buf, 3);
             read_weights(w1, buf, 1);
             __builtin_amdgcn_sched_barrier(0);
-            consume(x[0], w0, mask[0]);
+            consume(x[0], w0, mask[0], active);
 
             load_x(x[3], i);
             put(buf ^ 1, nid, nw);
+            nactive = (uint32_t)__ballot(nid & CBM_BLOCK_ACTIVE);
             next = (size_t)min(g + 2 * WAVES, last) * 64;
             nid = gc[next];
             if (WCOL) nw = gw[next];
             read_ids(i, buf ^ 1, 0);
             read_weights(w0, buf, 2);
             __builtin_amdgcn_sched_barrier(0);
-            consume(x[1], w1, mask[1]);
+            consume(x[1], w1, mask[1], active >> 4);
 
             load_x(x[0], i);
             read_ids(i, buf ^ 1, 1);
             read_weights(w1, buf, 3);
             __builtin_amdgcn_sched_barrier(0);
-            consume(x[2], w0, mask[2]);
+            consume(x[2], w0, mask[2], active >> 8);
 
             load_x(x[1], i);
             read_ids(i, buf ^ 1, 2);
             read_weights(w0, buf ^ 1, 0);
             __builtin_amdgcn_sched_barrier(0);
-            consume(x[3], w1, mask[3]);
+            consume(x[3], w1, mask[3], active >> 12);
 
             if (g == last) break;
             g += WAVES;
             buf ^= 1;
             mask = nmask;
+            active = nactive;
             nmask = gm[next];
         }
     } else {
@@ -304,8 +320,12 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
             }
             nheld = gm[(size_t)(i / 4) * 256 + i % 4] >> (8 * wave) & 255u;
         };
+        auto load_next = [&] {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) nx[j] = x_at(ci.v[j / 4][j % 4] & ~CBM_BLOCK_ACTIVE);
+        };
         fetch(0);
-        load_x(nx, ci);
+        load_next();
         w = nw;
         held = nheld;
         fetch(min(1, last));
@@ -314,7 +334,7 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
 #pragma unroll
             for (int j = 0; j < 8; ++j) x[j] = WCOL ? nx[j] * (w.v[j / 4][j % 4] * kDown) : nx[j];
             const uintx4 bits = lut[held];
-            load_x(nx, ci);
+            load_next();
             w = nw;
             held = nheld;
             fetch(min(i + 2, last));

@@ -68,6 +68,7 @@ struct CbmBlock {
     uint32_t ngroups;  // groups of 64 columns: four steps of 16
 };
 constexpr uint32_t CBM_BLOCK_NO_ROW = 0xffffffffu;  // an empty place
+constexpr uint32_t CBM_BLOCK_ACTIVE = 0x80000000u;  // in a column of a group, on the device (flag_active_tiles)
 constexpr float CBM_BLOCK_UP = 16777216.0f;         // 2^24: rows of X are split at this size (cbm_blocks.hip says why)
 
 // Shared sums: a work item is a column set that is summed once, or a row made of such sums and of columns of its own.

@@ -18,6 +18,7 @@
 #include <mutex>
 #include <vector>
 
+#include "cbm_block_plan.h"
 #include "cbm_internal.h"
 #include "cbm_rows.h"
 
@@ -669,7 +670,7 @@ cbm_status cbm_upload(cbm_handle* h) {
         if (h->row_blocks.empty()) return CBM_OK;
         cbm_status bs = CBM_OK;
         if ((bs = up(&h->d_blocks, h->row_blocks)) != CBM_OK || (bs = up(&h->d_block_rows, h->block_rows)) != CBM_OK ||
-            (bs = up(&h->d_block_cols, h->block_cols)) != CBM_OK || (bs = up(&h->d_block_masks, h->block_masks)) != CBM_OK)
+            (bs = up(&h->d_block_cols, flag_active_tiles(h->block_cols, h->block_masks))) != CBM_OK || (bs = up(&h->d_block_masks, h->block_masks)) != CBM_OK)
             return bs;
         if (h->square_self_loops) {
             std::vector<float> w(h->block_cols.size());
