@@ -685,8 +685,9 @@ cbm_status cbm_launch_gemm(int64_t M, int32_t N, int32_t K, const float* A, int6
             return CBM_ERR_HIP;
         return CBM_OK;
     }
-    {   // short and deep, or wide enough to be bound by the matrix cores: their bf16 side
+    {   // a B that fits in registers; short and deep, or wide enough to be bound by the matrix cores: their bf16 side
         bool taken = false;
+        if (const cbm_status st = cbm_launch_gemm_held(M, N, K, A, lda, B, ldb, C, ldc, stream_, &taken); taken || st != CBM_OK) return st;
         const cbm_status st = cbm_launch_gemm_split(M, N, K, A, lda, B, ldb, C, ldc, stream_, &taken);
         if (taken || st != CBM_OK) return st;
     }

@@ -1,0 +1,325 @@
+// Dense fp32 matmul C = A.B for up to 64 columns on the bf16 matrix cores, B held in registers.
+//
+// Operands are split into three bf16 parts and multiplied in six products as in cbm_gemm_split.hip, which says why that is as good as fp32.  What is
+// different is who holds what: B is small, so each wave keeps the parts of its piece of B -- all columns, 32 STEPS of its rows -- in registers, split once,
+// and streams 16 rows of A at a time past them: no LDS, no barrier and no second look at B in the loop.  Where K is deeper than a wave can hold,
+// SLICES waves of a workgroup share K and add their sums through LDS, one barrier for 16 rows.  Rows of A go straight from memory into operand
+// layout (lane l: row l % 16, eight k from 8 (l / 16) on); a step's registers are free when it is split, and the next rows are asked for there and then.
+// Asking two tiles of rows ahead gains nothing, nor does adding up a tile's shares beside the next one's products.
+//
+// What bounds it: reading A and writing C (us, the kernels that ran before -> here; what a large copy's 4.66 TB/s would take): 132534 x 100 . 100 x 47
+// 26.3 -> 20.0 (16.7), 132534 x 256 . 256 x 64 47 -> 35 (36), 132534 x 32 . 32 x 32 11.8 -> 8.7, 300000 x 16 . 16 x 16 12.6 -> 9.6 (8.2), 60000 x 500 . 500 x 64
+// 42 -> 31 (29), 100000 x 301 . 301 x 40 51 -> 34 (29).  Few rows: a wave's piece of B and one or two tiles of rows, one after the other: 19717 x 500 . 500 x 64
+// 23 -> 15 (9.6; 1,233 tiles are 4.8 for each compute unit), . 500 x 7 13.3 -> 8.5, 3000 x 512 . 512 x 64 10.4 -> 6.4; a call costs 5 us of host time beside it.
+// Error against 64 bits in the 2-norm, Gaussian values: K = 100 1.8e-7 (fp32 kernels) -> 0.6e-7, 256 2.9e-7 -> 0.5e-7, 500 4.0e-7 -> 0.5e-7 (through parts
+// without B held 0.76e-7).  Values that are not finite: one infinity in B 20 -> 37, NaN all over A 72 (132534 x 100 . 100 x 47), 17 -> 108, 162 (20000 x 500 . 500 x 64).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdlib>
+
+#include "cbm_internal.h"
+#include "cbm_split.h"
+
+namespace {
+
+// Operands are split at 2^24 times their size and sums come back by 2^-48: nothing small is lost (cbm_gemm_split.hip).
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;
+constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};  // the six products, the one of the large parts last
+
+struct Parts {
+    bf16x8 p[3];  // h, m, l
+};
+__device__ __forceinline__ Parts split8(const float (&x)[8], uint32_t minus_low) {
+    uintx4 q[3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t h, m, l;
+        split_pair_nearest(x[2 * i] * kUp, x[2 * i + 1] * kUp, minus_low, h, m, l);
+        q[0][i] = h;
+        q[1][i] = m;
+        q[2][i] = l;
+    }
+    Parts r;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) r.p[i] = __builtin_bit_cast(bf16x8, q[i]);
+    return r;
+}
+
+struct Shape {
+    int64_t M;
+    int N, K;
+    const float* A;
+    int64_t lda;
+    const float* B;
+    int64_t ldb;
+    float* C;
+    int64_t ldc;
+};
+
+// Rows row0 .. + 15, columns col0 .. + 15 of C on the fp32 matrix cores, for sums that the parts do not give: lane l's are rows row0 + 4 (l / 16) .. + 3 of
+// column col0 + l % 16.
+__device__ __forceinline__ floatx4 plain_tile(const Shape& s, int64_t row0, int col0) {
+    const int lane = threadIdx.x & 63, l16 = lane & 15;
+    const float* a = s.A + min(row0 + l16, s.M - 1) * s.lda;
+    const float* b = s.B + min(col0 + l16, s.N - 1);
+    floatx4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int k = lane >> 4; k - (lane >> 4) < s.K; k += 32) {  // eight products a turn, to have their loads in flight together
+        float x[8], y[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int at = min(k + 4 * j, s.K - 1);
+            x[j] = a[at];
+            y[j] = b[(int64_t)at * s.ldb];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j)  // (beyond K both are zero: what stands there may be infinite)
+            sum = __builtin_amdgcn_mfma_f32_16x16x4f32(k + 4 * j < s.K ? x[j] : 0.0f, k + 4 * j < s.K ? y[j] : 0.0f, sum, 0, 0, 0);
+    }
+    return sum;
+}
+
+constexpr int held_waves(int slices) { return slices == 8 ? 8 : 4; }
+// VEC: K is a multiple of 4 and rows of A start on 16-byte boundaries.
+template <int NT, int STEPS, int SLICES, bool VEC>
+__global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kernel(const Shape s) {
+    constexpr int WAVES = held_waves(SLICES);
+    constexpr int GROUPS = WAVES / SLICES;  // rows of 16 that a workgroup works on at a time
+    static_assert(GROUPS == 1 || SLICES == 1, "waves that share K are a whole workgroup");
+    __shared__ float red[SLICES > 1 ? 2 : 1][SLICES > 1 ? SLICES : 1][SLICES > 1 ? 8 * NT : 1][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, l16 = lane & 15;
+    const int slice = SLICES > 1 ? wave : 0;
+    const int k0 = slice * 32 * STEPS + 8 * (lane >> 4);  // this lane's k: 8 from here on, 32 further for each step
+    uint32_t minus_low = 0xbf80u;
+    asm("" : "+s"(minus_low));
+
+    const int64_t tiles = (s.M + 15) / 16, stride = (int64_t)gridDim.x * GROUPS;
+    int64_t tile = (int64_t)blockIdx.x * GROUPS + (SLICES > 1 ? 0 : wave);
+    if (tile >= tiles) return;  // (waves that share K leave together)
+    float x[STEPS][8];
+    const int whole = (s.K - slice * 32 * STEPS) / 32;  // steps that lie inside K
+    // loads stay inside the matrix: beyond K they are cut, beyond M never stored
+    auto row_of = [&](int64_t t) { return s.A + min(16 * t + l16, s.M - 1) * s.lda; };
+    auto load_a = [&](float (&r)[8], const float* row, int step) {
+        if (VEC || step < whole) {
+            const int k = k0 + 32 * step;
+            floatx4 lo, hi;
+            if constexpr (VEC) {
+                lo = *reinterpret_cast<const floatx4*>(row + min(k, s.K - 4));
+                hi = *reinterpret_cast<const floatx4*>(row + min(k + 4, s.K - 4));
+            } else {
+                __builtin_memcpy(&lo, row + k, sizeof(lo));
+                __builtin_memcpy(&hi, row + k + 4, sizeof(hi));
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                r[j] = lo[j];
+                r[4 + j] = hi[j];
+            }
+        } else {
+            int k = k0 + 32 * step;
+            asm("" : "+v"(k));  // (its eight places are not worth registers of their own outside the loop)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) r[j] = row[min(k + j, s.K - 1)];
+        }
+    };
+    {
+        const float* row = row_of(tile);
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) load_a(x[i], row, i);
+    }
+    Parts b[STEPS][NT];
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+        float y[NT][8];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const float* col = s.B + min(16 * t + l16, s.N - 1);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) y[t][j] = col[(int64_t)min(k0 + 32 * i + j, s.K - 1) * s.ldb];
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) y[t][j] = k0 + 32 * i + j < s.K ? y[t][j] : 0.0f;
+            b[i][t] = split8(y[t], minus_low);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // register v of lane l of a tile of 16 x 16: row 4 (l / 16) + v, column l % 16
+    auto put = [&](int64_t row, int t, float sum) {
+        const int c = 16 * t + l16;
+        if (c < s.N && row < s.M) s.C[row * s.ldc + c] = sum;
+    };
+    // The waves' shares of the 16 rows, a register at a time: the large sums in 64 bits, where their sum loses nothing (in 32 bits K = 320 7.1e-8
+    // instead of 5.5e-8), with the small ones added at the end.
+    auto add_up = [&](int buf) {
+        constexpr int PER = (4 * NT + SLICES - 1) / SLICES;  // registers of a wave, one after the other: few tiles
+        float sum[PER];
+        int doubtful = -1, first = -1;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int at = slice * PER + i;
+            if (at >= 4 * NT) break;
+            float few = red[buf][0][at][lane];
+            double most = (double)red[buf][0][4 * NT + at][lane];
+#pragma unroll
+            for (int w = 1; w < SLICES; ++w) {
+                few += red[buf][w][at][lane];
+                most += (double)red[buf][w][4 * NT + at][lane];
+            }
+            sum[i] = (float)(most + (double)few) * kDown;
+            if (__ballot(!(fabsf(sum[i]) < INFINITY))) {
+                doubtful = at / 4;
+                if (first < 0) first = at / 4;
+            }
+        }
+        for (int t = first; first >= 0 && t <= doubtful; ++t) {
+            const floatx4 all = plain_tile(s, 16 * tile, 16 * t);
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int v = slice * PER + i - 4 * t;
+                if (v >= 0 && v < 4) sum[i] = v == 0 ? all[0] : v == 1 ? all[1] : v == 2 ? all[2] : all[3];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int at = slice * PER + i;
+            if (at < 4 * NT) put(16 * tile + 4 * (lane >> 4) + at % 4, at / 4, sum[i]);
+        }
+    };
+    for (int buf = 0;; buf ^= 1) {
+        const float* next = row_of(min(tile + stride, tiles - 1));
+        floatx4 acc[NT], small[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = small[t] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) {
+            if (i >= whole) {
+                int k = k0 + 32 * i;
+                asm("" : "+v"(k));  // (nor are its eight conditions)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) x[i][j] = k + j < s.K ? x[i][j] : 0.0f;
+            }
+            const Parts a = split8(x[i], minus_low);
+            load_a(x[i], next, i);
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    floatx4& sum = q < 5 ? small[t] : acc[t];
+                    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[PA[q]], b[i][t].p[PB[q]], sum, 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (SLICES == 1) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                floatx4 sum;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sum[v] = (acc[t][v] + small[t][v]) * kDown;
+                bool bad = false;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) bad = bad || !(fabsf(sum[v]) < INFINITY);
+                if (__ballot(bad)) sum = plain_tile(s, 16 * tile, 16 * t);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) put(16 * tile + 4 * (lane >> 4) + v, t, sum[v]);
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    red[buf][slice][4 * t + v][lane] = small[t][v];
+                    red[buf][slice][4 * NT + 4 * t + v][lane] = acc[t][v];
+                }
+            __syncthreads();  // (the other buffer is free again when all have come here)
+            add_up(buf);
+        }
+        tile += stride;
+        if (tile >= tiles) return;
+    }
+}
+
+// Workgroups: two waves a SIMD, four where their registers leave room (300000 x 32 . 32 x 32 15.2 -> 13.8 us).
+constexpr int held_grid(int nt, int steps, int slices) { return slices == 8 ? 256 : steps * (12 * nt + 8) + 8 * nt + 60 <= 128 ? 1024 : 512; }
+
+template <int NT, int STEPS, int SLICES>
+void launch(const Shape& s, hipStream_t stream) {
+    constexpr int WAVES = held_waves(SLICES), GROUPS = WAVES / SLICES;
+    const int64_t wanted = ((s.M + 15) / 16 + GROUPS - 1) / GROUPS;
+    const dim3 grid((unsigned)std::min<int64_t>(wanted, held_grid(NT, STEPS, SLICES)));
+    const bool vec = s.K % 4 == 0 && s.lda % 4 == 0 && ((uintptr_t)s.A & 15) == 0;
+    if (vec) hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, true>), grid, dim3(64 * WAVES), 0, stream, s);
+    else hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, false>), grid, dim3(64 * WAVES), 0, stream, s);
+}
+
+// Steps of 32 k that a wave can hold beside NT tiles of 16 columns: 12 registers each.
+constexpr int most_steps(int nt) { return nt == 4 ? 3 : 4; }
+
+template <int NT, int SLICES>
+bool launch_slices(const Shape& s, int steps, hipStream_t stream) {
+    switch (steps) {
+        case 1: launch<NT, 1, SLICES>(s, stream); return true;
+        case 2: launch<NT, 2, SLICES>(s, stream); return true;
+        case 3: launch<NT, 3, SLICES>(s, stream); return true;
+        case 4:
+            if constexpr (most_steps(NT) == 4) {
+                launch<NT, 4, SLICES>(s, stream);
+                return true;
+            }
+            return false;
+        default: return false;
+    }
+}
+// How many waves share K: those that pad it least and, of these, as few as there are (132534 x 100 . 100 x 47, 4 steps: one wave 20, four 23; 20000 x 256 .
+// 256 x 47, 8 steps: four 8.1, eight 8.6) with no more than two steps each (x 16 one wave 13.7, four 11.4; 20000 x 500 . 500 x 47, 16 steps: four 13.9, eight
+// 12.1), three tiles of columns up to 50,000 rows only (50000 x 128 . 128 x 47 one wave 13.4, four 12.6; 80000 rows 15.7, 16.4).  Where there are not rows
+// enough for all waves, as many as K takes: 8192 x 128 . 128 x 47 one wave 7.1, four 5.4, 5000 x 320 . 320 x 32 four 6.7, eight 6.1 (12,000 rows: 7.2, 7.8).
+template <int NT>
+bool launch_nt(const Shape& s, hipStream_t stream) {
+    const int64_t steps = ((int64_t)s.K + 31) / 32;
+    const int64_t enough = s.M <= 8192 ? 1 : NT <= 2 || s.M <= 50000 ? 2 : most_steps(NT);
+    int64_t slices = 0, each = 0;
+    for (int64_t n : {1, 4, 8}) {
+        const int64_t e = (steps + n - 1) / n;
+        if (e > most_steps(NT) || (slices && (each <= enough || (s.M > 8192 && n * e > slices * each)))) continue;
+        slices = n;
+        each = e;
+    }
+    switch (slices) {
+        case 1: return launch_slices<NT, 1>(s, (int)each, stream);
+        case 4: return launch_slices<NT, 4>(s, (int)each, stream);
+        case 8: return launch_slices<NT, 8>(s, (int)each, stream);
+        default: return false;
+    }
+}
+
+}  // namespace
+
+// Every product of up to 64 columns whose K the waves can hold (1,024, beside more than 48 columns 768): over M from 500 to 300,000, K from 8 to
+// 1,000 and ten widths none is slower than through the other kernels by more than a call's noise, but for K just above 32 (padded to 64) and few
+// rows (20000 x 33 . 33 x 64 7.6 / 8.0).  Below K = 8 a product is a few roundings, which the fp32 kernels make no fewer of than needed: theirs.
+cbm_status cbm_launch_gemm_held(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
+                                int64_t ldc, void* stream, bool* taken) {
+    *taken = false;
+    // (for tests, which run several in one process: 5 = whatever K, 0 to 4 = never, as another kernel is asked for)
+    const char* e = std::getenv("CBM_GEMM_SPLIT");
+    const bool asked = e && e[0] >= '0' && e[0] <= '5' && !e[1];
+    if (N > 64 || (asked ? e[0] != '5' : K < 8)) return CBM_OK;
+    const Shape s{M, N, K, A, lda, B, ldb, C, ldc};
+    switch ((N + 15) / 16) {
+        case 1: *taken = launch_nt<1>(s, (hipStream_t)stream); break;
+        case 2: *taken = launch_nt<2>(s, (hipStream_t)stream); break;
+        case 3: *taken = launch_nt<3>(s, (hipStream_t)stream); break;
+        default: *taken = launch_nt<4>(s, (hipStream_t)stream); break;
+    }
+    if (!*taken) return CBM_OK;
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) {
+        cbm_set_error_detail("held matmul launch", hipGetErrorString(err));
+        return CBM_ERR_HIP;
+    }
+    return CBM_OK;
+}

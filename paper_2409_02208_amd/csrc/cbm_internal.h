@@ -250,6 +250,9 @@ inline size_t cbm_static_scratch_bytes() { return (size_t)CBM_STATIC_SCRATCH_FLO
 // the same through bf16 parts (cbm_gemm_split.hip) where its own rule says so: *taken
 cbm_status cbm_launch_gemm_split(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                  int64_t ldc, void* stream, bool* taken);
+// the same with B in registers, for up to 64 columns (cbm_gemm_held.hip), where its own rule says so
+cbm_status cbm_launch_gemm_held(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
+                                int64_t ldc, void* stream, bool* taken);
 // Whether the panel-resident fp32 kernel also takes a B that 128-bit loads cannot read (odd width or alignment): filling the panel
 // element by element has to be earned by depth and by rows.  The staged kernel has blocks of 128 rows, so it loses where M / 128 just
 // exceeds the 256 compute units, and tiles of 48 columns, which suit N from 33 to 48 (microseconds, or its share of the staged kernel's time):

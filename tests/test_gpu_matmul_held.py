@@ -1,0 +1,90 @@
+"""Dense matmul with B held in registers: every width, number of steps and number of waves that share K, at their edges."""
+import numpy as np
+import pytest
+
+import test_gpu_matmul_split as split
+from test_gpu_matmul_split import _product, env  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+WIDTHS = (1, 16, 17, 32, 33, 48, 49, 64)
+
+
+# K on both sides of every step of 32 and of what one, four and eight waves hold, for rows enough for all waves or not
+@pytest.mark.parametrize("k", [1, 3, 8, 31, 32, 33, 64, 65, 96, 97, 100, 128, 129, 200, 256, 257, 301, 320, 384, 385, 500, 512, 513, 768, 769, 1000, 1024, 1025])
+def test_whole_numbers_come_out_exactly(env, monkeypatch, k):  # noqa: F811
+    monkeypatch.setenv("CBM_GEMM_SPLIT", "5")
+    torch, cbm = env
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    for n in WIDTHS:
+        for m in (1, 15, 17, 8192, 8200) + ((17001, 33333, 51001) if n in (16, 48, 64) else ()):  # (from 32,768 on waves have several tiles of rows)
+            for pad in ((0, 0, 0), (4, 0, 1), (3, 1, 0)):
+                A, B = (torch.randint(-9, 10, s, device="cuda", generator=gen).float() for s in ((m, k + pad[0]), (k, n + pad[1])))
+                A, B, C = A[:, pad[0] // 2:][:, :k], B[:, :n], torch.full((m, n + pad[2]), float("nan"), device="cuda")
+                cbm.cbm_dense_matmul(A, B, C[:, :n])
+                assert torch.equal(C[:, :n].double(), A.double() @ B.double()), (m, n, pad)
+                assert bool(C[:, n:].isnan().all()), "wrote outside the columns"
+
+
+@pytest.mark.parametrize("m,k", [(1, 1), (31, 17), (129, 33), (300, 100), (257, 500), (9000, 300)])
+def test_within_the_componentwise_bound(env, monkeypatch, m, k):  # noqa: F811
+    monkeypatch.setenv("CBM_GEMM_SPLIT", "5")
+    rng = np.random.default_rng(m + k)
+    for n in WIDTHS:
+        A, B = (rng.standard_normal(s, dtype=np.float32) for s in ((m, k), (k, n)))
+        ref = A.astype(np.float64) @ B.astype(np.float64)
+        # a rounding of at most 2^-24 for each of K additions, and of the small sums at the end; what is left out is below 1.01 * 2^-24 of a term
+        bound = (k + 6) * 2.0 ** -24 * (np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64))
+        assert np.all(np.abs(_product(env, A, B) - ref) <= bound + 1e-37), n
+
+
+@pytest.mark.parametrize("m", [2000, 10000])
+@pytest.mark.parametrize("k,n", [(8, 16), (32, 64), (100, 47), (128, 64), (200, 33), (320, 64), (500, 64), (500, 7), (768, 40)])
+def test_error_is_no_larger_than_that_of_the_kernels_before(env, monkeypatch, m, k, n):  # noqa: F811
+    """The fp32 kernels, and the kernel of parts for short and deep products (at m = 2000: 640,000 roundings in each 2-norm for n = 64, 3 % is noise)."""
+    rng = np.random.default_rng(k + n)
+    A, B = (rng.standard_normal(s, dtype=np.float32) for s in ((m, k), (k, n)))
+    ref = A.astype(np.float64) @ B.astype(np.float64)
+    err = {}
+    for which in ("0", "2", "5"):
+        monkeypatch.setenv("CBM_GEMM_SPLIT", which)
+        err[which] = np.linalg.norm(_product(env, A, B) - ref) / np.linalg.norm(ref)
+    assert err["5"] <= err["0"] and err["5"] <= 1.03 * err["2"], err
+
+
+@pytest.fixture
+def widths(monkeypatch):
+    monkeypatch.setitem(split.WIDTHS, 5, (16, 33, 64))
+
+
+@pytest.mark.parametrize("k", [1, 2, 5, 16, 17, 32])
+def test_worst_mantissas_lose_no_more_than_a_rounding(env, monkeypatch, widths, k):  # noqa: F811
+    split.test_worst_mantissas_lose_no_more_than_a_rounding(env, monkeypatch, 5, k)
+
+
+def test_values_that_have_no_parts(env, monkeypatch, widths):  # noqa: F811
+    split.test_values_that_have_no_parts(env, monkeypatch, 5)
+
+
+@pytest.mark.parametrize("a,b", [(1e-41, 1e37), (1e-39, 1.0), (1e10, 1e-40), (1e-22, 1e-22), (2.0 ** -149, 1.0)])
+def test_values_too_small_for_the_parts_are_not_lost(env, monkeypatch, widths, a, b):  # noqa: F811
+    split.test_values_too_small_for_the_parts_are_not_lost(env, monkeypatch, 5, a, b)
+
+
+@pytest.mark.parametrize("k", [20, 200, 600])
+def test_values_that_are_not_finite(env, monkeypatch, k):  # noqa: F811
+    """They reach the outputs they reach by definition, where K is one wave's, four waves' and eight's; beyond K and N nothing is read as a value."""
+    monkeypatch.setenv("CBM_GEMM_SPLIT", "5")
+    rng = np.random.default_rng(k)
+    for n in (7, 33, 64):
+        for m in (40, 9000):
+            A, B = (rng.standard_normal(s, dtype=np.float32) for s in ((m, k), (k, n)))
+            A[7, 3], A[30, k - 1], B[k // 2, n - 2], A[m - 1, 0] = np.inf, np.nan, -np.inf, 3e37  # (times 5, more than |B| gets to: finite)
+            with np.errstate(invalid="ignore"):
+                ref = A.astype(np.float64) @ B.astype(np.float64)
+            got = _product(env, A, B, (2, 1, 0))
+            with np.errstate(over="ignore"):
+                ref32 = ref.astype(np.float32)
+            assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref32)], ref32[np.isinf(ref32)])
+            ok = np.isfinite(ref32)
+            size = np.abs(np.nan_to_num(A, posinf=0, neginf=0)).astype(np.float64) @ np.abs(np.nan_to_num(B, posinf=0, neginf=0)).astype(np.float64)
+            assert np.all(np.abs(got - ref)[ok] <= (k + 6) * 2.0 ** -24 * size[ok])
