@@ -1314,7 +1314,8 @@ cbm_status Builder::emit(int32_t nrounds) {
         h->comb.insert(h->comb.end(), rcomb[r].begin(), rcomb[r].end());
     }
     h->stats.num_split_rows = split_rows;
-    h->flat = nrounds == 1 && !h->levels[0].by_xcd && std::all_of(h->parent.begin(), h->parent.end(), [](int32_t y) { return y < 0; });
+    h->whole_rows = nrounds == 1 && !h->levels[0].bundled && std::all_of(h->parent.begin(), h->parent.end(), [](int32_t y) { return y < 0; });
+    h->flat = h->whole_rows && !h->levels[0].by_xcd;
     h->flat_long = 0;
     h->flat_rich = false;
     h->flat_most_waves = env_clamped("CBM_FLAT_WAVES", CBM_FLAT_MOST_WAVES, 0, 1 << 30);

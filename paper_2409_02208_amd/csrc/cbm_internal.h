@@ -118,7 +118,8 @@ struct cbm_handle {
     int64_t seg_begin[CBM_XCD] = {}, seg_count[CBM_XCD] = {};  // segment work items in tasks[], per column range
     int64_t seg_deltas = 0;        // delta entries gathered by the segment launch
     int64_t seg_longest = 0;       // entries of the longest segment
-    bool flat = false;             // every row is stored in full: one round of single rows, longest first, and segments
+    bool whole_rows = false;       // every row is stored in full: one round of single rows, and segments
+    bool flat = false;             // the same with all rows in one list, longest first
     int64_t flat_long = 0;         // how many of the rows have more than CBM_FLAT_SHORT entries
     bool flat_rich = false;        // a quarter of the entries or more are theirs or segments'
     int64_t flat_most_waves = CBM_FLAT_MOST_WAVES;

@@ -84,8 +84,8 @@ constexpr int level_min_waves(bool ragged, int lanes, int mode, int umax) {
 }
 
 template <bool RAGGED, int LANES, int MODE, int UMAX>
-__global__ __launch_bounds__(256, level_min_waves(RAGGED, LANES, MODE, UMAX)) void cbm_level_kernel(const CbmTask* __restrict__ tasks, int64_t ntasks,
-                                                        const CbmSegMap map,
+__global__ __launch_bounds__(256, level_min_waves(RAGGED, LANES, MODE, UMAX)) void cbm_level_kernel(const CbmTask* __restrict__ tasks, int64_t first, int64_t ntasks,
+                                                        const CbmSegMap segments, uint32_t segment_blocks, const CbmSegMap map,
                                                         const uint32_t* __restrict__ stream,
                                                         const float* __restrict__ X, int64_t ldx, float* Y,
                                                         int64_t ldy, float* scratch, int64_t ld_scratch,
@@ -99,14 +99,19 @@ __global__ __launch_bounds__(256, level_min_waves(RAGGED, LANES, MODE, UMAX)) vo
     const int sub = lane / LANES;
     const int sl = lane % LANES;
     int64_t t;
-    if (map.use) {
-        const int xcd = blockIdx.x % CBM_XCD;  // gridDim.x is a multiple of 8, so this is the linear id mod 8
-        const int64_t tl = ((int64_t)(blockIdx.x / CBM_XCD) * 4 + (threadIdx.x >> 6)) * G + sub;
-        if (tl >= map.count[xcd]) return;
-        t = map.begin[xcd] + tl;
+    // (the first workgroups may have segments, those after them the round's work items)
+    const bool on_segments = blockIdx.x < segment_blocks;
+    const uint32_t block = on_segments ? blockIdx.x : blockIdx.x - segment_blocks;  // segment_blocks is a multiple of 8
+    if (on_segments || map.use) {
+        const CbmSegMap& shares = on_segments ? segments : map;
+        const int xcd = block % CBM_XCD;  // gridDim.x is a multiple of 8, so this is the linear id mod 8
+        const int64_t tl = ((int64_t)(block / CBM_XCD) * 4 + (threadIdx.x >> 6)) * G + sub;
+        if (tl >= shares.count[xcd]) return;
+        t = shares.begin[xcd] + tl;
     } else {
-        t = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * G + sub;
+        t = ((int64_t)block * 4 + (threadIdx.x >> 6)) * G + sub;
         if (t >= ntasks) return;  // a whole group leaves together: no lane it exchanges with is gone
+        t += first;
     }
     const CbmTask tk = tasks[t];
     const uint32_t len = tk.len_flags & CBM_TASK_LEN_MASK;
@@ -478,6 +483,7 @@ struct LaunchCtx {
     const float* ws;  // per-entry weights of the stream (MODE 1/2)
     const float* rw;  // row weights (MODE 1/2/3)
     float self_w;     // MODE 4
+    bool with_segments;  // the round's launch takes the segments too
 };
 
 // launches of up to this many waves (counted with one group per work item) share every work item among four groups
@@ -525,11 +531,33 @@ void launch_bundles(const LaunchCtx& c, const CbmLevel& L) {
     launch_bundles_as<RAGGED, LANES, MODE, UMAX, 1>(c, L);
 }
 
+// The segments, a round's work items, or both in one launch.
 template <bool RAGGED, int LANES, int MODE, int UMAX>
-void launch_level(const LaunchCtx& c, const CbmLevel& L) {
+void launch_items(const LaunchCtx& c, bool segments, const CbmLevel* L) {
     constexpr int G = 64 / LANES;
     const int ychunks = (c.k + LANES * 4 - 1) / (LANES * 4);
-    CbmSegMap map{};
+    auto shares = [&](CbmSegMap& map, const int64_t (&begin)[CBM_XCD], const int64_t (&count)[CBM_XCD]) {  // one block of work items per XCD
+        int64_t most = 0;
+        for (int j = 0; j < CBM_XCD; ++j) {
+            map.begin[j] = begin[j];
+            map.count[j] = count[j];
+            most = std::max(most, map.count[j]);
+        }
+        map.use = 1;
+        return CBM_XCD * ((most + 4 * G - 1) / (4 * G));
+    };
+    CbmSegMap seg{}, map{};
+    const int64_t segment_blocks = segments ? shares(seg, c.h->seg_begin, c.h->seg_count) : 0;
+    int64_t blocks = segment_blocks;
+    if (L) blocks += L->by_xcd ? shares(map, L->xcd_begin, L->xcd_count) : (L->task_count + 4 * G - 1) / (4 * G);
+    if (segments && ychunks > 1) blocks = (blocks + CBM_XCD - 1) / CBM_XCD * CBM_XCD;  // (workgroup b on XCD b mod 8 in every chunk of columns)
+    hipLaunchKernelGGL((cbm_level_kernel<RAGGED, LANES, MODE, UMAX>), dim3((unsigned)blocks, (unsigned)ychunks), dim3(256), 0, c.stream, c.h->d_tasks,
+                       L ? L->task_begin : 0, L ? L->task_count : 0, seg, (uint32_t)segment_blocks, map, c.h->d_stream, c.X, c.ldx, c.Y, c.ldy,
+                       c.scratch, c.ld_scratch, c.ws, c.rw, c.self_w, c.k);
+}
+
+template <bool RAGGED, int LANES, int MODE, int UMAX>
+void launch_level(const LaunchCtx& c, const CbmLevel& L) {
     if (L.task_count <= 0) return;
     if (L.bundled) return launch_bundles<RAGGED, LANES, MODE, UMAX>(c, L);
     if constexpr (LANES <= 16 && UMAX >= 8) {
@@ -537,45 +565,15 @@ void launch_level(const LaunchCtx& c, const CbmLevel& L) {
         // groups of the wave; the kernel below would walk it with one (protein recipe, k = 64: that round 0.077 ms, the product
         // 0.317 -> 0.288 ms)
         const int64_t ychunks2 = (c.k + LANES * 4 - 1) / (LANES * 4);
-        if (L.long_single_rows && L.task_count / (64 / LANES) * ychunks2 <= wide_max_waves())
+        if (L.long_single_rows && !c.with_segments && L.task_count / (64 / LANES) * ychunks2 <= wide_max_waves())
             return launch_bundles_as<RAGGED, LANES, MODE, UMAX, 4>(c, L);
     }
-    if (L.by_xcd) {  // one block of the (locality-ordered) work items per XCD
-        int64_t most = 0;
-        for (int j = 0; j < CBM_XCD; ++j) {
-            map.begin[j] = L.xcd_begin[j];
-            map.count[j] = L.xcd_count[j];
-            most = std::max(most, map.count[j]);
-        }
-        map.use = 1;
-        dim3 grid((unsigned)(CBM_XCD * ((most + 4 * G - 1) / (4 * G))), (unsigned)ychunks);
-        hipLaunchKernelGGL((cbm_level_kernel<RAGGED, LANES, MODE, UMAX>), grid, dim3(256), 0, c.stream, c.h->d_tasks,
-                           (int64_t)c.h->tasks.size(), map, c.h->d_stream, c.X, c.ldx, c.Y, c.ldy, c.scratch,
-                           c.ld_scratch, c.ws, c.rw, c.self_w, c.k);
-        return;
-    }
-    dim3 grid((unsigned)((L.task_count + 4 * G - 1) / (4 * G)), (unsigned)ychunks);
-    hipLaunchKernelGGL((cbm_level_kernel<RAGGED, LANES, MODE, UMAX>), grid, dim3(256), 0, c.stream,
-                       c.h->d_tasks + L.task_begin, L.task_count, map, c.h->d_stream, c.X, c.ldx, c.Y, c.ldy,
-                       c.scratch, c.ld_scratch, c.ws, c.rw, c.self_w, c.k);
+    launch_items<RAGGED, LANES, MODE, UMAX>(c, c.with_segments, &L);
 }
 // all segments of all split rows, one block of work items per XCD
 template <bool RAGGED, int LANES, int MODE, int UMAX>
 void launch_segments(const LaunchCtx& c, const CbmLevel&) {
-    constexpr int G = 64 / LANES;
-    const int ychunks = (c.k + LANES * 4 - 1) / (LANES * 4);
-    CbmSegMap map{};
-    int64_t most = 0;
-    for (int j = 0; j < CBM_XCD; ++j) {
-        map.begin[j] = c.h->seg_begin[j];
-        map.count[j] = c.h->seg_count[j];
-        most = std::max(most, map.count[j]);
-    }
-    map.use = 1;
-    dim3 grid((unsigned)(CBM_XCD * ((most + 4 * G - 1) / (4 * G))), (unsigned)ychunks);
-    hipLaunchKernelGGL((cbm_level_kernel<RAGGED, LANES, MODE, UMAX>), grid, dim3(256), 0, c.stream, c.h->d_tasks,
-                       (int64_t)c.h->tasks.size(), map, c.h->d_stream, c.X, c.ldx, c.Y, c.ldy, c.scratch,
-                       c.ld_scratch, c.ws, c.rw, c.self_w, c.k);
+    launch_items<RAGGED, LANES, MODE, UMAX>(c, true, nullptr);
 }
 template <bool RAGGED, int LANES, int MODE>
 void launch_combine(const LaunchCtx& c, const CbmLevel& L) {
@@ -1029,7 +1027,15 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         return longest * kEntryManyUs <= kManyLongest * (double)deltas * k * 4 / kManyBytesPerUs;
     };
     const bool wcol = mode == 1 || mode == 2, wrow = wcol || mode == 3;
-    const LaunchCtx ctx{h, X, ldx, k, Y, ldy, scratch, ld_scratch, stream, h->d_wstream, mode == 3 ? h->d_rinv : h->d_dinv, self_weight};
+    int64_t segments = 0;  // (not num_slots: hub blocks write scratch rows too)
+    for (int64_t c : h->seg_count) segments += c;
+    // Segments wait for nobody and nobody but the combine launch waits for them: where all rows are stored in full they share the rows' launch, first in it
+    // because they are longest, and their tail and the rows' start fill each other's gaps (R-MAT, us apart / together: directed scale 17, k = 100, both
+    // directions 190 / 164, scale 16, k = 128 152 / 106; scale 18, mean of 47 columns 215 / 191, k = 200 636 / 638; scale 16, k = 128 98 / 86; scale 21, k = 128
+    // 3793 / 3758).  Apart for per-launch times, and where few, long rows are shared among groups (launch_level).
+    const bool together = segments > 0 && !flat_lanes && h->whole_rows && !h->profiling && h->levels[0].task_count > 0 &&
+                          !(h->levels[0].long_single_rows && lanes <= 16 && h->levels[0].task_count / (64 / lanes) * ychunks <= wide_max_waves());
+    const LaunchCtx ctx{h, X, ldx, k, Y, ldy, scratch, ld_scratch, stream, h->d_wstream, mode == 3 ? h->d_rinv : h->d_dinv, self_weight, together};
     const int64_t rowb = 4 * (int64_t)k;
     const int64_t per_delta = rowb + 4 + (wcol ? 4 : 0);
     const int64_t per_row = rowb + 4 + (wrow ? 4 : 0) + (mode == 4 ? rowb : 0);  // Y write, marker, weight, own X row
@@ -1055,9 +1061,7 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         ProfScope ps(h, stream, rec);
         cbm_launch_hub_blocks(h, X, ldx, k, scratch, ld_scratch, wcol, stream_);
     }
-    int64_t segments = 0;  // (not num_slots: hub blocks write scratch rows too)
-    for (int64_t c : h->seg_count) segments += c;
-    if (segments > 0) {
+    if (segments > 0 && !together) {
         cbm_launch_record rec{};
         rec.kind = 1;
         rec.per_xcd = 1;
@@ -1082,7 +1086,8 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
             // per work item with a parent: the parent's row
             rec.algorithmic_bytes = L.deltas * per_delta + L.rows_written * per_row + L.parent_reads * rowb;
             ProfScope ps(h, stream, rec);
-            if (!flat_lanes) (many(L.task_count, L.deltas, L.longest) ? var.level_many : var.level)(ctx, L);
+            if (together) (many(segments + L.task_count, h->seg_deltas + L.deltas, std::max(h->seg_longest, L.longest)) ? var.level_many : var.level)(ctx, L);
+            else if (!flat_lanes) (many(L.task_count, L.deltas, L.longest) ? var.level_many : var.level)(ctx, L);
             else if (segments == 0 || h->profiling)
                 cbm_launch_flat(h, false, true, flat_lanes, X, ldx, k, Y, ldy, scratch, ld_scratch, mode, ctx.rw, self_weight, aligned, stream_);
         }
