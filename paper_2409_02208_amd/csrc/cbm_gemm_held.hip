@@ -1,9 +1,10 @@
-// Dense fp32 matmul C = A.B for up to 64 columns on the bf16 matrix cores, B held in registers.
+// Dense fp32 matmul C = A.B for few columns on the bf16 matrix cores, B held in registers: a panel of up to 64 of them, or up to four such panels side by
+// side (grid dimension y).
 //
 // Operands are split into three bf16 parts and multiplied in six products as in cbm_gemm_split.hip, which says why that is as good as fp32.  What is
 // different is who holds what: B is small, so each wave keeps the parts of its piece of B -- all columns, 32 STEPS of its rows -- in registers, split once,
-// and streams 16 rows of A at a time past them: no LDS, no barrier and no second look at B in the loop.  Where K is deeper than a wave can hold,
-// SLICES waves of a workgroup share K and add their sums through LDS, one barrier for 16 rows.  Rows of A go straight from memory into operand
+// and streams 16 rows of A at a time past them (all columns: of the panel): no LDS, no barrier and no second look at B in the loop.  Where K is deeper than a wave can hold,
+// SLICES waves, a workgroup, share K and add their sums through LDS, one barrier for 16 rows.  Rows of A go straight from memory into operand
 // layout (lane l: row l % 16, eight k from 8 (l / 16) on); a step's registers are free when it is split, and the next rows are asked for there and then.
 // Asking two tiles of rows ahead gains nothing, nor does adding up a tile's shares beside the next one's products.
 //
@@ -79,10 +80,14 @@ __device__ __forceinline__ floatx4 plain_tile(const Shape& s, int64_t row0, int 
     return sum;
 }
 
-constexpr int held_waves(int slices) { return slices == 8 ? 8 : 4; }
+constexpr int held_waves(int slices) { return slices == 1 ? 4 : slices; }
 // VEC: K is a multiple of 4 and rows of A start on 16-byte boundaries.
 template <int NT, int STEPS, int SLICES, bool VEC>
-__global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kernel(const Shape s) {
+__global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kernel(const Shape all) {
+    Shape s = all;  // this panel's
+    s.B += blockIdx.y * (16 * NT);
+    s.C += blockIdx.y * (16 * NT);
+    s.N = min(s.N - (int)blockIdx.y * (16 * NT), 16 * NT);
     constexpr int WAVES = held_waves(SLICES);
     constexpr int GROUPS = WAVES / SLICES;  // rows of 16 that a workgroup works on at a time
     static_assert(GROUPS == 1 || SLICES == 1, "waves that share K are a whole workgroup");
@@ -99,11 +104,13 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
     if (tile >= tiles) return;  // (waves that share K leave together)
     float x[STEPS][8];
     const int whole = (s.K - slice * 32 * STEPS) / 32;  // steps that lie inside K
-    // loads stay inside the matrix: beyond K they are cut, beyond M never stored
+    // loads stay inside A: what they bring from beyond K is cut, from beyond M never stored
     auto row_of = [&](int64_t t) { return s.A + min(16 * t + l16, s.M - 1) * s.lda; };
-    auto load_a = [&](float (&r)[8], const float* row, int step) {
-        if (VEC || step < whole) {
-            const int k = k0 + 32 * step;
+    // whether rows of 16 can be read whole steps at a time: what a step reads beyond K is then of the next rows, and all of it inside A
+    auto inside = [&](int64_t t) { return VEC || (16 * t + 15) * s.lda + (slice + 1) * 32 * STEPS <= (s.M - 1) * s.lda + s.K; };
+    auto load_a = [&](float (&r)[8], const float* row, int step, bool whole_steps) {
+        int k = k0 + 32 * step;
+        if (whole_steps) {
             floatx4 lo, hi;
             if constexpr (VEC) {
                 lo = *reinterpret_cast<const floatx4*>(row + min(k, s.K - 4));
@@ -118,7 +125,6 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
                 r[4 + j] = hi[j];
             }
         } else {
-            int k = k0 + 32 * step;
             asm("" : "+v"(k));  // (its eight places are not worth registers of their own outside the loop)
 #pragma unroll
             for (int j = 0; j < 8; ++j) r[j] = row[min(k + j, s.K - 1)];
@@ -127,7 +133,7 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
     {
         const float* row = row_of(tile);
 #pragma unroll
-        for (int i = 0; i < STEPS; ++i) load_a(x[i], row, i);
+        for (int i = 0; i < STEPS; ++i) load_a(x[i], row, i, inside(tile));
     }
     Parts b[STEPS][NT];
 #pragma unroll
@@ -190,7 +196,9 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
         }
     };
     for (int buf = 0;; buf ^= 1) {
-        const float* next = row_of(min(tile + stride, tiles - 1));
+        const int64_t then = min(tile + stride, tiles - 1);
+        const float* next = row_of(then);
+        const bool whole_steps = inside(then);
         floatx4 acc[NT], small[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = small[t] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -203,7 +211,7 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
                 for (int j = 0; j < 8; ++j) x[i][j] = k + j < s.K ? x[i][j] : 0.0f;
             }
             const Parts a = split8(x[i], minus_low);
-            load_a(x[i], next, i);
+            load_a(x[i], next, i, whole_steps);
 #pragma unroll
             for (int q = 0; q < 6; ++q)
 #pragma unroll
@@ -242,14 +250,16 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
     }
 }
 
-// Workgroups: two waves a SIMD, four where their registers leave room (300000 x 32 . 32 x 32 15.2 -> 13.8 us).
-constexpr int held_grid(int nt, int steps, int slices) { return slices == 8 ? 256 : steps * (12 * nt + 8) + 8 * nt + 60 <= 128 ? 1024 : 512; }
+// Workgroups: two waves a SIMD (eight sharing K: always), four where their registers leave room (300000 x 32 . 32 x 32 15.2 -> 13.8 us).
+constexpr int held_grid(int nt, int steps, int slices) { return (steps * (12 * nt + 8) + 8 * nt + 60 <= 128 && slices != 8 ? 4096 : 2048) / held_waves(slices); }
 
 template <int NT, int STEPS, int SLICES>
 void launch(const Shape& s, hipStream_t stream) {
     constexpr int WAVES = held_waves(SLICES), GROUPS = WAVES / SLICES;
     const int64_t wanted = ((s.M + 15) / 16 + GROUPS - 1) / GROUPS;
-    const dim3 grid((unsigned)std::min<int64_t>(wanted, held_grid(NT, STEPS, SLICES)));
+    const int panels = (s.N + 16 * NT - 1) / (16 * NT);
+    const int64_t each = (held_grid(NT, STEPS, SLICES) / panels + 7) / 8 * 8;  // (a multiple of 8: panels that read the same rows share an XCD)
+    const dim3 grid((unsigned)std::min<int64_t>(wanted, each), (unsigned)panels);
     const bool vec = s.K % 4 == 0 && s.lda % 4 == 0 && ((uintptr_t)s.A & 15) == 0;
     if (vec) hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, true>), grid, dim3(64 * WAVES), 0, stream, s);
     else hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, false>), grid, dim3(64 * WAVES), 0, stream, s);
@@ -275,14 +285,15 @@ bool launch_slices(const Shape& s, int steps, hipStream_t stream) {
 }
 // How many waves share K: those that pad it least and, of these, as few as there are (132534 x 100 . 100 x 47, 4 steps: one wave 20, four 23; 20000 x 256 .
 // 256 x 47, 8 steps: four 8.1, eight 8.6) with no more than two steps each (x 16 one wave 13.7, four 11.4; 20000 x 500 . 500 x 47, 16 steps: four 13.9, eight
-// 12.1), three tiles of columns up to 50,000 rows only (50000 x 128 . 128 x 47 one wave 13.4, four 12.6; 80000 rows 15.7, 16.4).  Where there are not rows
-// enough for all waves, as many as K takes: 8192 x 128 . 128 x 47 one wave 7.1, four 5.4, 5000 x 320 . 320 x 32 four 6.7, eight 6.1 (12,000 rows: 7.2, 7.8).
+// 12.1), three tiles of columns up to 50,000 rows only (50000 x 128 . 128 x 47 one wave 13.4, four 12.6; 80000 rows 15.7, 16.4).  Two waves are for 5 or 6
+// steps (250000 x 150 . 150 x 24 four 61, two 41).  Where there are not rows enough for all waves, as many as K takes: 8192 x 128 . 128 x 47 one wave 7.1, four
+// 5.4, 5000 x 320 . 320 x 32 four 6.7, eight 6.1 (12,000 rows: 7.2, 7.8).
 template <int NT>
 bool launch_nt(const Shape& s, hipStream_t stream) {
     const int64_t steps = ((int64_t)s.K + 31) / 32;
     const int64_t enough = s.M <= 8192 ? 1 : NT <= 2 || s.M <= 50000 ? 2 : most_steps(NT);
     int64_t slices = 0, each = 0;
-    for (int64_t n : {1, 4, 8}) {
+    for (int64_t n : {1, 2, 4, 8}) {
         const int64_t e = (steps + n - 1) / n;
         if (e > most_steps(NT) || (slices && (each <= enough || (s.M > 8192 && n * e > slices * each)))) continue;
         slices = n;
@@ -290,6 +301,7 @@ bool launch_nt(const Shape& s, hipStream_t stream) {
     }
     switch (slices) {
         case 1: return launch_slices<NT, 1>(s, (int)each, stream);
+        case 2: return launch_slices<NT, 2>(s, (int)each, stream);
         case 4: return launch_slices<NT, 4>(s, (int)each, stream);
         case 8: return launch_slices<NT, 8>(s, (int)each, stream);
         default: return false;
@@ -298,18 +310,43 @@ bool launch_nt(const Shape& s, hipStream_t stream) {
 
 }  // namespace
 
-// Every product of up to 64 columns whose K the waves can hold (1,024, beside more than 48 columns 768): over M from 500 to 300,000, K from 8 to
-// 1,000 and ten widths none is slower than through the other kernels by more than a call's noise, but for K just above 32 (padded to 64) and few
-// rows (20000 x 33 . 33 x 64 7.6 / 8.0).  Below K = 8 a product is a few roundings, which the fp32 kernels make no fewer of than needed: theirs.
+namespace {
+// Where the lines lie (us, the other kernels -> these), measured over M from 500 to 300,000, K from 8 to 1,000 and 21 widths.  Up to 64 columns nothing is slower
+// by more than a call's noise, but for K just above 32 (padded to 64) and few rows (20000 x 33 . 33 x 64 7.6 -> 8.0).  Wider products go in panels of up to 64
+// columns side by side, each of which reads A:
+//  K <= 32, where C is most of the traffic: 300000 x 32 . 32 x 128 67 -> 36, x 256 141 -> 115, 20000 x 8 . 8 x 192 15 -> 8; with rows of A off 16-byte boundaries not
+//    just beyond one panel (170000 x 30 . 30 x 66 20 -> 24) nor four of them at their tallest (250000 x 30 . 30 x 250 85 -> 93);
+//  more than 128 columns, K > 32: three or four panels lose (132534 x 100 . 100 x 160 60 -> 109) but where there are few rows (2000 x 500 . 500 x 256 22 -> 8.7,
+//    8192 rows and 160 columns 22.5 -> 26);
+//  two panels, K <= 64: 132534 x 64 . 64 x 80 23 -> 21, 50000 rows 14.5 -> 11.8, 20000 x 64 . 64 x 112 8.9 -> 9.7, 8192 rows 6.5 -> 6.4, 2000 6.2 -> 5.5;
+//  two of more than 48 columns, K <= 192: 50000 x 100 . 100 x 112 23.3 -> 22.0, 132534 rows 45 -> 49, 28000 x 80 . 80 x 104 11.7 -> 12.4, 160 deep 15.7 -> 16.6; of up
+//    to 48: 132534 x 100 . 100 x 96 40 -> 32;
+//  deeper: 20000 x 500 . 500 x 112 34 -> 23, 132534 x 256 . 256 x 112 75 -> 67, 300000 rows and x 80 126 -> 130, 132534 x 320 . 320 x 80 66 -> 71, 50000 rows 42 -> 31,
+//    132534 x 500 . 500 x 80 122 -> 92, but 13 steps of K are padded to 16 beside four tiles (40000 x 400 . 400 x 104 41.4 -> 42.5).
+// Below K = 8 a product is a few roundings, which the fp32 kernels make no fewer of than needed: theirs.
+bool held_takes(int64_t M, int32_t N, int32_t K, bool vec) {
+    if (K < 8 || N > 256) return false;
+    if (N <= 64) return true;
+    if (K <= 32) return vec || (N > 80 && (N <= 192 || M <= 200000));
+    if (N > 128) return M <= 2048;
+    if (K <= 64) return M <= 4096 || M >= 32768;
+    if (N > 96 && K <= 192) return M <= 4096 || (M >= 32768 && M <= 65536);
+    if (N > 96 && K > 384 && K < 448) return false;
+    if (K <= 128) return true;
+    return M <= 100000 || K >= 480 || (K <= 256 && M <= 200000);
+}
+}  // namespace
+
 cbm_status cbm_launch_gemm_held(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                 int64_t ldc, void* stream, bool* taken) {
     *taken = false;
     // (for tests, which run several in one process: 5 = whatever K, 0 to 4 = never, as another kernel is asked for)
     const char* e = std::getenv("CBM_GEMM_SPLIT");
     const bool asked = e && e[0] >= '0' && e[0] <= '5' && !e[1];
-    if (N > 64 || (asked ? e[0] != '5' : K < 8)) return CBM_OK;
+    if (asked ? e[0] != '5' || N > 256 : !held_takes(M, N, K, K % 4 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0)) return CBM_OK;
     const Shape s{M, N, K, A, lda, B, ldb, C, ldc};
-    switch ((N + 15) / 16) {
+    const int panels = (N + 63) / 64;
+    switch (((N + 15) / 16 + panels - 1) / panels) {
         case 1: *taken = launch_nt<1>(s, (hipStream_t)stream); break;
         case 2: *taken = launch_nt<2>(s, (hipStream_t)stream); break;
         case 3: *taken = launch_nt<3>(s, (hipStream_t)stream); break;

@@ -251,7 +251,7 @@ inline size_t cbm_static_scratch_bytes() { return (size_t)CBM_STATIC_SCRATCH_FLO
 // the same through bf16 parts (cbm_gemm_split.hip) where its own rule says so: *taken
 cbm_status cbm_launch_gemm_split(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                  int64_t ldc, void* stream, bool* taken);
-// the same with B in registers, for up to 64 columns (cbm_gemm_held.hip), where its own rule says so
+// the same with B in registers, for few columns (cbm_gemm_held.hip), where its own rule says so
 cbm_status cbm_launch_gemm_held(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                 int64_t ldc, void* stream, bool* taken);
 // Whether the panel-resident fp32 kernel also takes a B that 128-bit loads cannot read (odd width or alignment): filling the panel

@@ -25,6 +25,21 @@ def test_whole_numbers_come_out_exactly(env, monkeypatch, k):  # noqa: F811
                 assert bool(C[:, n:].isnan().all()), "wrote outside the columns"
 
 
+# two, three and four panels of columns, the last of them narrow or not; by the rule, on both sides of its lines, and whatever it says
+@pytest.mark.parametrize("n", [65, 80, 81, 96, 97, 112, 128, 129, 160, 193, 255, 256, 257])
+def test_panels_of_columns(env, monkeypatch, n):  # noqa: F811
+    torch, cbm = env
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    for m, k in ((17, 9), (2048, 65), (2049, 65), (4097, 40), (32768, 64), (32767, 33), (65537, 100), (9000, 300), (40000, 32), (3, 800)):
+        A, B = (torch.randint(-9, 10, s, device="cuda", generator=gen).float() for s in ((m, k), (k, n + 3)))
+        for form in (None, "5"):
+            monkeypatch.delenv("CBM_GEMM_SPLIT", raising=False) if form is None else monkeypatch.setenv("CBM_GEMM_SPLIT", form)
+            C = torch.full((m, n + 1), float("nan"), device="cuda")
+            cbm.cbm_dense_matmul(A, B[:, 1:n + 1], C[:, :n])
+            assert torch.equal(C[:, :n].double(), A.double() @ B[:, 1:n + 1].double()), (m, k, form)
+            assert bool(C[:, n:].isnan().all()), "wrote outside the columns"
+
+
 @pytest.mark.parametrize("m,k", [(1, 1), (31, 17), (129, 33), (300, 100), (257, 500), (9000, 300)])
 def test_within_the_componentwise_bound(env, monkeypatch, m, k):  # noqa: F811
     monkeypatch.setenv("CBM_GEMM_SPLIT", "5")
@@ -38,17 +53,17 @@ def test_within_the_componentwise_bound(env, monkeypatch, m, k):  # noqa: F811
 
 
 @pytest.mark.parametrize("m", [2000, 10000])
-@pytest.mark.parametrize("k,n", [(8, 16), (32, 64), (100, 47), (128, 64), (200, 33), (320, 64), (500, 64), (500, 7), (768, 40)])
+@pytest.mark.parametrize("k,n", [(8, 16), (32, 64), (100, 47), (128, 64), (200, 33), (320, 64), (500, 64), (500, 7), (768, 40), (32, 200), (100, 80), (256, 112)])
 def test_error_is_no_larger_than_that_of_the_kernels_before(env, monkeypatch, m, k, n):  # noqa: F811
     """The fp32 kernels, and the kernel of parts for short and deep products (at m = 2000: 640,000 roundings in each 2-norm for n = 64, 3 % is noise)."""
     rng = np.random.default_rng(k + n)
     A, B = (rng.standard_normal(s, dtype=np.float32) for s in ((m, k), (k, n)))
     ref = A.astype(np.float64) @ B.astype(np.float64)
     err = {}
-    for which in ("0", "2", "5"):
+    for which in ("0", "2" if n <= 64 else "4", "5"):
         monkeypatch.setenv("CBM_GEMM_SPLIT", which)
         err[which] = np.linalg.norm(_product(env, A, B) - ref) / np.linalg.norm(ref)
-    assert err["5"] <= err["0"] and err["5"] <= 1.03 * err["2"], err
+    assert err["5"] <= err["0"] and err["5"] <= 1.03 * min(err.values()), err
 
 
 @pytest.fixture
