@@ -9,7 +9,8 @@
 // scale 14, k = 64 37 -> 16, scale 16 68 -> 45; R-MAT scale 14, 32 edges a node, k = 64 46 -> 24.
 // Which launches (CBM_FLAT_MOST_WAVES and the builder's flat_rich): what has more waves keeps the chip busy as it is, and sharing rows out costs it
 // (R-MAT scale 15, k = 200, 54,000 waves 85 -> 99; scale 16, k = 100, 54,000 77 -> 86; directed scale 17, k = 128, 90,000 97 -> 130;
-// below 43,000 everything gains: scale 16, k = 64 62 -> 57).  Nor do rows that are nearly all short gain (citation recipe, 19,717 nodes, k = 128 12 -> 16).
+// below 43,000 everything gained: scale 16, k = 64 62 -> 57).  Now that segments share the rows' launch (cbm_kernels.hip) some below the line would be
+// faster there (scale 16, k = 64 56 / 50, scale 14, k = 200 49 / 39), but less precise (2.3e-8 / 2.6e-8).  Nor do rows that are nearly all short gain (citation recipe, 19,717 nodes, k = 128 12 -> 16).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

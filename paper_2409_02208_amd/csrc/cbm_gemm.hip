@@ -1,6 +1,6 @@
 // Dense fp32 matmul C = A.B on the gfx950 matrix cores, for the X.W products of
 // the two-layer GCN (Eq. (1)).  A is tall (one row per graph node), B is a small
-// weight matrix.  Three kernels: tall products whose weight panel fits in LDS take
+// weight matrix.  (Narrow B of moderate depth is held in registers: cbm_gemm_held.hip.)  Three kernels: tall products whose weight panel fits in LDS take
 // the panel-resident kernel further down (cbm_gemm_panel_kernel); the rest are
 // staged through LDS slabs, on 32x32x2 tiles (first kernel) or 16x16x4 tiles.
 //

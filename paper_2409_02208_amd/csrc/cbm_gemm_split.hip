@@ -385,9 +385,9 @@ void pick(const Shape& s, int form) {
 
 }  // namespace
 
-// Where the lines lie (microseconds, fp32 kernels of cbm_gemm.hip -> these; M x K . K x N).  Measured at M from 1,000 to 132,534, K from
+// Where the lines lie (microseconds, fp32 kernels of cbm_gemm.hip -> these; M x K . K x N), for products that do not hold B in registers.  Measured at M from 1,000 to 132,534, K from
 // 32 to 1,000 and 20 widths: nowhere inside the lines are these slower by more than the launch's own noise; some outside would be faster.
-//  up to 64 columns: short and deep products, which leave the chip idle there -- 19717 x 500 . 500 x 64 26.1 -> 21.0, . 500 x 7
+//  up to 64 columns (what cbm_gemm_held.hip leaves: K beyond 768 or 1,024): short and deep products, which leave the chip idle there -- 19717 x 500 . 500 x 64 26.1 -> 21.0, . 500 x 7
 //    25.2 -> 13.4, 24000 x 128 . 128 x 64 13.0 -> 10.3, 3000 x 512 . 512 x 64 24 -> 10.  The line in M: at 28,000 rows the two are level
 //    (200 x 64: 17.2, 16.6; 500 x 64: 27.0, 27.4), at 60,000 the fp32 kernels stream A at the rate of memory (200 x 64: 25.7, 28.6; 500 x 64:
 //    42, 48; 500 x 32: 25.7, 31.1), and what lies between depends on N (40000 x 500 . 500 x 7: 40, 22).  The line in K: at 100 24,576 rows
