@@ -1,8 +1,9 @@
 // Dense fp32 matmul C = A.B for few columns on the bf16 matrix cores, B held in registers: a panel of up to 64 of them, or up to four such panels side by
 // side (grid dimension y).
 //
-// Operands are split into three bf16 parts and multiplied in six products as in cbm_gemm_split.hip, which says why that is as good as fp32.  What is
-// different is who holds what: B is small, so each wave keeps the parts of its piece of B -- all columns, 32 STEPS of its rows -- in registers, split once,
+// Operands are split into three bf16 parts as in cbm_gemm_split.hip, which says why that is as good as fp32, and multiplied in eight products instead of six: this
+// kernel takes over from the fp32 ones, where a row of a single term is rounded once, and ml and lm are up to another rounding of a term.  (ll is 2^-34 of it.)
+// Also different is who holds what: B is small, so each wave keeps the parts of its piece of B -- all columns, 32 STEPS of its rows -- in registers, split once,
 // and streams 16 rows of A at a time past them (all columns: of the panel): no LDS, no barrier and no second look at B in the loop.  Where K is deeper than a wave can hold,
 // SLICES waves, a workgroup, share K and add their sums through LDS, one barrier for 16 rows.  Rows of A go straight from memory into operand
 // layout (lane l: row l % 16, eight k from 8 (l / 16) on); a step's registers are free when it is split, and the next rows are asked for there and then.
@@ -13,7 +14,8 @@
 // 42 -> 31 (29), 100000 x 301 . 301 x 40 51 -> 34 (29).  Few rows: a wave's piece of B and one or two tiles of rows, one after the other: 19717 x 500 . 500 x 64
 // 23 -> 15 (9.6; 1,233 tiles are 4.8 for each compute unit), . 500 x 7 13.3 -> 8.5, 3000 x 512 . 512 x 64 10.4 -> 6.4; a call costs 5 us of host time beside it.
 // Error against 64 bits in the 2-norm, Gaussian values: K = 100 1.8e-7 (fp32 kernels) -> 0.6e-7, 256 2.9e-7 -> 0.5e-7, 500 4.0e-7 -> 0.5e-7 (through parts
-// without B held 0.76e-7).  Values that are not finite: one infinity in B 20 -> 37, NaN all over A 72 (132534 x 100 . 100 x 47), 17 -> 108, 162 (20000 x 500 . 500 x 64).
+// without B held 0.76e-7).  One term a row 2.53e-8, at most 1.002 times 2^-24 of it (six products: 2.60e-8 and 1.6 to 1.7 times; fp32 2.53e-8 and once).  What the two
+// products cost (us): 132534 x 100 . 100 x 47 20.0 -> 20.9, 132534 x 256 . 256 x 64 36 -> 39, 19717 x 500 . 500 x 64 14.8 -> 15.6, 132534 x 32 . 32 x 32 no time.  Values that are not finite: one infinity in B 20 -> 37, NaN all over A 72 (132534 x 100 . 100 x 47), 17 -> 108, 162 (20000 x 500 . 500 x 64).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,7 +28,7 @@ namespace {
 
 // Operands are split at 2^24 times their size and sums come back by 2^-48: nothing small is lost (cbm_gemm_split.hip).
 constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;
-constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};  // the six products, the one of the large parts last
+constexpr int PRODUCTS = 8, PA[PRODUCTS] = {2, 1, 2, 0, 1, 1, 0, 0}, PB[PRODUCTS] = {1, 2, 0, 2, 1, 0, 1, 0};  // small ones first, that of the large parts last
 
 struct Parts {
     bf16x8 p[3];  // h, m, l
@@ -213,10 +215,10 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
             const Parts a = split8(x[i], minus_low);
             load_a(x[i], next, i, whole_steps);
 #pragma unroll
-            for (int q = 0; q < 6; ++q)
+            for (int q = 0; q < PRODUCTS; ++q)
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
-                    floatx4& sum = q < 5 ? small[t] : acc[t];
+                    floatx4& sum = q < PRODUCTS - 1 ? small[t] : acc[t];
                     sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[PA[q]], b[i][t].p[PB[q]], sum, 0, 0, 0);
                 }
             __builtin_amdgcn_sched_barrier(0);

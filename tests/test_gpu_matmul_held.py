@@ -47,7 +47,7 @@ def test_within_the_componentwise_bound(env, monkeypatch, m, k):  # noqa: F811
     for n in WIDTHS:
         A, B = (rng.standard_normal(s, dtype=np.float32) for s in ((m, k), (k, n)))
         ref = A.astype(np.float64) @ B.astype(np.float64)
-        # a rounding of at most 2^-24 for each of K additions, and of the small sums at the end; what is left out is below 1.01 * 2^-24 of a term
+        # a rounding of at most 2^-24 for each of K additions, and of the small sums at the end
         bound = (k + 6) * 2.0 ** -24 * (np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64))
         assert np.all(np.abs(_product(env, A, B) - ref) <= bound + 1e-37), n
 
@@ -103,3 +103,27 @@ def test_values_that_are_not_finite(env, monkeypatch, k):  # noqa: F811
             ok = np.isfinite(ref32)
             size = np.abs(np.nan_to_num(A, posinf=0, neginf=0)).astype(np.float64) @ np.abs(np.nan_to_num(B, posinf=0, neginf=0)).astype(np.float64)
             assert np.all(np.abs(got - ref)[ok] <= (k + 6) * 2.0 ** -24 * size[ok])
+
+
+# one wave, two, four and eight, for few rows and many; panels of columns beside it
+@pytest.mark.parametrize("m", [2000, 20000])
+@pytest.mark.parametrize("k,n", [(20, 32), (128, 47), (150, 16), (300, 64), (500, 64), (700, 33), (32, 200), (256, 96)])
+def test_a_row_of_one_term_is_rounded_once(env, monkeypatch, m, k, n):  # noqa: F811
+    """As the fp32 kernels do it.  Left out is the product of the lowest parts, at most 2^-34 of the term; the small products are below 2^-6.9 of it and are added in
+    seven roundings: together below 2^-28, beside the one rounding of 2^-24 at the end."""
+    rng = np.random.default_rng(k + n)
+    A, B = np.zeros((m, k), np.float32), rng.standard_normal((k, n), dtype=np.float32)
+    A[np.arange(m), rng.integers(0, k, m)] = rng.standard_normal(m, dtype=np.float32)
+    ref = A.astype(np.float64) @ B.astype(np.float64)
+    err = {}
+    for which in ("0", "5"):
+        monkeypatch.setenv("CBM_GEMM_SPLIT", which)
+        got = _product(env, A, B)
+        assert np.all(np.abs(got - ref) <= (1 + 2.0 ** -4) * 2.0 ** -24 * np.abs(ref) + 2.0 ** -150), which
+        err[which] = np.linalg.norm(got - ref)
+    assert err["5"] <= (1 + 2.0 ** -10) * err["0"], err
+
+
+@pytest.mark.parametrize("k,nonzeros", [(128, 1), (500, 4), (500, 10), (500, 50), (96, 96), (500, 500)])
+def test_error_is_no_larger_than_that_of_the_fp32_kernels(env, monkeypatch, widths, k, nonzeros):  # noqa: F811
+    split.test_error_is_no_larger_than_that_of_the_fp32_kernels(env, monkeypatch, 5, k, nonzeros)
