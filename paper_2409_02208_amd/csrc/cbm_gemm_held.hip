@@ -15,7 +15,9 @@
 // 23 -> 15 (9.6; 1,233 tiles are 4.8 for each compute unit), . 500 x 7 13.3 -> 8.5, 3000 x 512 . 512 x 64 10.4 -> 6.4; a call costs 5 us of host time beside it.
 // Error against 64 bits in the 2-norm, Gaussian values: K = 100 1.8e-7 (fp32 kernels) -> 0.6e-7, 256 2.9e-7 -> 0.5e-7, 500 4.0e-7 -> 0.5e-7 (through parts
 // without B held 0.76e-7).  One term a row 2.53e-8, at most 1.002 times 2^-24 of it (six products: 2.60e-8 and 1.6 to 1.7 times; fp32 2.53e-8 and once).  What the two
-// products cost (us): 132534 x 100 . 100 x 47 20.0 -> 20.9, 132534 x 256 . 256 x 64 36 -> 39, 19717 x 500 . 500 x 64 14.8 -> 15.6, 132534 x 32 . 32 x 32 no time.  Values that are not finite: one infinity in B 20 -> 37, NaN all over A 72 (132534 x 100 . 100 x 47), 17 -> 108, 162 (20000 x 500 . 500 x 64).
+// products cost (us): 132534 x 100 . 100 x 47 20.0 -> 20.9, 132534 x 256 . 256 x 64 36 -> 39, 19717 x 500 . 500 x 64 14.8 -> 15.6, 132534 x 32 . 32 x 32 no time.  Values that are not finite (finite ones, one infinity in B, NaN all
+// over A): 132534 x 100 . 100 x 47 22, 36, 62, 132534 x 256 . 256 x 64 42, 80, 167, 20000 x 500 . 500 x 64 16, 27, 52, 50000 x 300 . 300 x 33 21, 40, 71 (where each wave
+// that added shares up went over all of K alone, between two barriers: 20000 x 500 . 500 x 64 110, 158, 50000 x 300 . 300 x 33 107, 216, 132534 x 256 . 256 x 64 207, 336).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -60,28 +62,6 @@ struct Shape {
     int64_t ldc;
 };
 
-// Rows row0 .. + 15, columns col0 .. + 15 of C on the fp32 matrix cores, for sums that the parts do not give: lane l's are rows row0 + 4 (l / 16) .. + 3 of
-// column col0 + l % 16.
-__device__ __forceinline__ floatx4 plain_tile(const Shape& s, int64_t row0, int col0) {
-    const int lane = threadIdx.x & 63, l16 = lane & 15;
-    const float* a = s.A + min(row0 + l16, s.M - 1) * s.lda;
-    const float* b = s.B + min(col0 + l16, s.N - 1);
-    floatx4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int k = lane >> 4; k - (lane >> 4) < s.K; k += 32) {  // eight products a turn, to have their loads in flight together
-        float x[8], y[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int at = min(k + 4 * j, s.K - 1);
-            x[j] = a[at];
-            y[j] = b[(int64_t)at * s.ldb];
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j)  // (beyond K both are zero: what stands there may be infinite)
-            sum = __builtin_amdgcn_mfma_f32_16x16x4f32(k + 4 * j < s.K ? x[j] : 0.0f, k + 4 * j < s.K ? y[j] : 0.0f, sum, 0, 0, 0);
-    }
-    return sum;
-}
-
 constexpr int held_waves(int slices) { return slices == 1 ? 4 : slices; }
 // VEC: K is a multiple of 4 and rows of A start on 16-byte boundaries.
 template <int NT, int STEPS, int SLICES, bool VEC>
@@ -94,6 +74,7 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
     constexpr int GROUPS = WAVES / SLICES;  // rows of 16 that a workgroup works on at a time
     static_assert(GROUPS == 1 || SLICES == 1, "waves that share K are a whole workgroup");
     __shared__ float red[SLICES > 1 ? 2 : 1][SLICES > 1 ? SLICES : 1][SLICES > 1 ? 8 * NT : 1][64];
+    __shared__ uint32_t doubt[2][SLICES];  // by wave that added them up: the tiles of columns that hold a sum that is not finite
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, l16 = lane & 15;
     const int slice = SLICES > 1 ? wave : 0;
@@ -115,6 +96,7 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
         if (whole_steps) {
             floatx4 lo, hi;
             if constexpr (VEC) {
+                if constexpr (NT * STEPS == 12 || (NT == 1 && STEPS == 3)) asm("" : "+v"(k));  // (its places are not worth registers of their own outside the loop where there are none to spare)
                 lo = *reinterpret_cast<const floatx4*>(row + min(k, s.K - 4));
                 hi = *reinterpret_cast<const floatx4*>(row + min(k + 4, s.K - 4));
             } else {
@@ -127,7 +109,7 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
                 r[4 + j] = hi[j];
             }
         } else {
-            asm("" : "+v"(k));  // (its eight places are not worth registers of their own outside the loop)
+            asm("" : "+v"(k));  // (nor are its eight)
 #pragma unroll
             for (int j = 0; j < 8; ++j) r[j] = row[min(k + j, s.K - 1)];
         }
@@ -160,16 +142,36 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
         const int c = 16 * t + l16;
         if (c < s.N && row < s.M) s.C[row * s.ldc + c] = sum;
     };
+    // Rows 16 at .. + 15, columns 16 t .. + 15 on the fp32 matrix cores, over this wave's k: a sum of infinite, NaN or very large values, which the parts
+    // do not give.  (A tile at a time, by a loop: its registers come beside all that the wave holds.)
+    auto plain = [&](int64_t at, int t) {
+        const float* row = row_of(at);
+        const bool whole_steps = inside(at);
+        const float* col = s.B + min(16 * t + l16, s.N - 1);
+        floatx4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+        for (int i = 0; i < STEPS; ++i) {
+            float a[8], y[8];
+            load_a(a, row, i, whole_steps);
+            int k = k0 + 32 * i;
+            asm("" : "+v"(k));
+#pragma unroll
+            for (int j = 0; j < 8; ++j) y[j] = col[(int64_t)min(k + j, s.K - 1) * s.ldb];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)  // (beyond K both are zero: what stands there may be infinite)
+                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(k + j < s.K ? a[j] : 0.0f, k + j < s.K ? y[j] : 0.0f, sum, 0, 0, 0);
+        }
+        return sum;
+    };
     // The waves' shares of the 16 rows, a register at a time: the large sums in 64 bits, where their sum loses nothing (in 32 bits K = 320 7.1e-8
-    // instead of 5.5e-8), with the small ones added at the end.
+    // instead of 5.5e-8) and does not overflow, with the small ones added at the end.
+    constexpr int PER = (4 * NT + SLICES - 1) / SLICES;  // registers of a wave, one after the other
     auto add_up = [&](int buf) {
-        constexpr int PER = (4 * NT + SLICES - 1) / SLICES;  // registers of a wave, one after the other: few tiles
+        uint32_t again = 0;
         float sum[PER];
-        int doubtful = -1, first = -1;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int at = slice * PER + i;
-            if (at >= 4 * NT) break;
+            const int at = PER * SLICES > 4 * NT ? min(slice * PER + i, 4 * NT - 1) : slice * PER + i;
             float few = red[buf][0][at][lane];
             double most = (double)red[buf][0][4 * NT + at][lane];
 #pragma unroll
@@ -177,25 +179,40 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
                 few += red[buf][w][at][lane];
                 most += (double)red[buf][w][4 * NT + at][lane];
             }
-            sum[i] = (float)(most + (double)few) * kDown;
-            if (__ballot(!(fabsf(sum[i]) < INFINITY))) {
-                doubtful = at / 4;
-                if (first < 0) first = at / 4;
-            }
+            sum[i] = (float)((most + (double)few) * (double)kDown);
+            again |= (__ballot(!(fabsf(sum[i]) < INFINITY)) != 0 ? 1u : 0u) << (at / 4);
         }
-        for (int t = first; first >= 0 && t <= doubtful; ++t) {
-            const floatx4 all = plain_tile(s, 16 * tile, 16 * t);
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const int v = slice * PER + i - 4 * t;
-                if (v >= 0 && v < 4) sum[i] = v == 0 ? all[0] : v == 1 ? all[1] : v == 2 ? all[2] : all[3];
-            }
-        }
+        doubt[buf][slice] = again;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int at = slice * PER + i;
-            if (at < 4 * NT) put(16 * tile + 4 * (lane >> 4) + at % 4, at / 4, sum[i]);
+            if (PER * SLICES == 4 * NT || at < 4 * NT) put(16 * tile + 4 * (lane >> 4) + at % 4, at / 4, sum[i]);
         }
+    };
+    // Tiles of rows 16 at .. + 15 that add_up was not sure of, stored once more by the lanes that stored them: all waves come here after the barrier that
+    // follows it, and share K as before.
+    auto settle = [&](int buf, int64_t at, uint32_t unsure) {
+        uint32_t again = 0;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) again |= (__ballot(unsure >> t & 1u) != 0 ? 1u : 0u) << t;
+        for (uint32_t left = again; left; left &= left - 1) {
+            const int t = __builtin_ctz(left);
+            const floatx4 sum = plain(at, t);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[buf][slice][4 * t + v][lane] = sum[v];
+        }
+        __syncthreads();
+        for (uint32_t left = again; left; left &= left - 1) {
+            const int t = __builtin_ctz(left);
+            for (int v = 0; v < 4; ++v) {
+                if ((4 * t + v) / PER != slice) continue;
+                double sum = 0.0;
+#pragma unroll
+                for (int w = 0; w < SLICES; ++w) sum += (double)red[buf][w][4 * t + v][lane];
+                put(16 * at + 4 * (lane >> 4) + v, t, (float)sum);
+            }
+        }
+        __syncthreads();  // (the next tile's shares go where these were)
     };
     for (int buf = 0;; buf ^= 1) {
         const int64_t then = min(tile + stride, tiles - 1);
@@ -208,7 +225,7 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
         for (int i = 0; i < STEPS; ++i) {
             if (i >= whole) {
                 int k = k0 + 32 * i;
-                asm("" : "+v"(k));  // (nor are its eight conditions)
+                asm("" : "+v"(k));  // (nor are their conditions)
 #pragma unroll
                 for (int j = 0; j < 8; ++j) x[i][j] = k + j < s.K ? x[i][j] : 0.0f;
             }
@@ -224,15 +241,21 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
             __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (SLICES == 1) {
+            uint32_t again = 0;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                floatx4 sum;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) sum[v] = (acc[t][v] + small[t][v]) * kDown;
+                for (int v = 0; v < 4; ++v) acc[t][v] = (acc[t][v] + small[t][v]) * kDown;
                 bool bad = false;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) bad = bad || !(fabsf(sum[v]) < INFINITY);
-                if (__ballot(bad)) sum = plain_tile(s, 16 * tile, 16 * t);
+                for (int v = 0; v < 4; ++v) bad = bad || !(fabsf(acc[t][v]) < INFINITY);
+                again |= (__ballot(bad) != 0 ? 1u : 0u) << t;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) put(16 * tile + 4 * (lane >> 4) + v, t, acc[t][v]);
+            }
+            for (; again; again &= again - 1) {  // (what was stored is stored once more: stores that may not be would have the next rows waited for with them)
+                const int t = __builtin_ctz(again);
+                const floatx4 sum = plain(tile, t);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) put(16 * tile + 4 * (lane >> 4) + v, t, sum[v]);
             }
@@ -245,10 +268,18 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
                     red[buf][slice][4 * NT + 4 * t + v][lane] = acc[t][v];
                 }
             __syncthreads();  // (the other buffer is free again when all have come here)
+            const uint32_t unsure = doubt[buf ^ 1][lane % SLICES];
             add_up(buf);
+            if (tile >= stride && __ballot(unsure != 0)) settle(buf ^ 1, tile - stride, unsure);
         }
         tile += stride;
-        if (tile >= tiles) return;
+        if (tile < tiles) continue;
+        if constexpr (SLICES > 1) {
+            __syncthreads();
+            const uint32_t unsure = doubt[buf][lane % SLICES];
+            if (__ballot(unsure != 0)) settle(buf, tile - stride, unsure);
+        }
+        return;
     }
 }
 

@@ -127,3 +127,55 @@ def test_a_row_of_one_term_is_rounded_once(env, monkeypatch, m, k, n):  # noqa: 
 @pytest.mark.parametrize("k,nonzeros", [(128, 1), (500, 4), (500, 10), (500, 50), (96, 96), (500, 500)])
 def test_error_is_no_larger_than_that_of_the_fp32_kernels(env, monkeypatch, widths, k, nonzeros):  # noqa: F811
     split.test_error_is_no_larger_than_that_of_the_fp32_kernels(env, monkeypatch, 5, k, nonzeros)
+
+
+# waves that share K or not, with several tiles of 16 rows one after the other; three tiles of columns, and two panels of them
+@pytest.mark.parametrize("k", [30, 100, 190, 300, 500, 760])
+@pytest.mark.parametrize("n", [5, 47, 96])
+def test_sums_that_are_not_finite_among_others(env, monkeypatch, k, n):  # noqa: F811
+    """Whole numbers with infinities, NaN and values from 2^104 on in a single row, in rows of tiles that follow each other in a workgroup, in the first rows and the
+    last: these reach what they reach by definition, and all other sums come out exactly."""
+    monkeypatch.setenv("CBM_GEMM_SPLIT", "5")
+    rng = np.random.default_rng(k + n)
+    m = 20011
+    A, B = (rng.integers(-9, 10, s).astype(np.float32) for s in ((m, k), (k, n)))
+    rows = np.unique(np.concatenate(([0, m - 1, m - 12], rng.integers(0, m, 60), np.arange(4096, 4096 + 16 * 300, 16))))  # (one each: two would cancel)
+    A[rows, rng.integers(0, k, len(rows))] = rng.choice(np.float32([np.inf, -np.inf, np.nan, 2.0 ** 104, -2.0 ** 110]), len(rows))
+    for column in (None, n - 1):
+        if column is not None:
+            B[k // 3, column] = np.inf
+        with np.errstate(invalid="ignore"):
+            ref = A.astype(np.float64) @ B.astype(np.float64)
+        got = _product(env, A, B, (1, 0, 1)).astype(np.float64)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+        small = np.abs(ref) < 2.0 ** 24
+        assert np.array_equal(got[small], ref[small])
+        large = np.isfinite(ref) & ~small  # one value of 2^104 or more decides
+        assert np.all(np.abs(got - ref)[large] <= 2.0 ** -23 * np.abs(ref[large]))
+
+
+@pytest.mark.parametrize("m,k,n", [(132534, 100, 47), (132534, 256, 64), (20000, 500, 64), (50000, 300, 33)])
+def test_values_that_are_not_finite_cost_little(env, m, k, n):  # noqa: F811
+    """An infinity in B, which reaches one tile of columns in every row: 1.6 to 1.9 times the product's time (measured), the line is at 3.  NaN everywhere: 2.8 to 4.0
+    times, the line is at 6.  (Waves that go over all of K alone: 5.2 to 7.3 and 8.4 to 10.7 times where waves share K.)"""
+    torch, cbm = env
+    A, B, C = torch.randn(m, k, device="cuda"), torch.randn(k, n, device="cuda"), torch.empty(m, n, device="cuda")
+
+    def best():
+        us = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                cbm.cbm_dense_matmul(A, B, C)
+            b.record()
+            torch.cuda.synchronize()
+            us.append(a.elapsed_time(b))
+        return min(us)
+
+    best()
+    clean = best()
+    B[3, 2] = float("inf")
+    assert best() <= 3 * clean
+    A.fill_(float("nan"))
+    assert best() <= 6 * clean
