@@ -291,8 +291,7 @@ void launch(const Shape& s, hipStream_t stream) {
     constexpr int WAVES = held_waves(SLICES), GROUPS = WAVES / SLICES;
     const int64_t wanted = ((s.M + 15) / 16 + GROUPS - 1) / GROUPS;
     const int panels = (s.N + 16 * NT - 1) / (16 * NT);
-    const int64_t each = (held_grid(NT, STEPS, SLICES) / panels + 7) / 8 * 8;  // (a multiple of 8: panels that read the same rows share an XCD)
-    const dim3 grid((unsigned)std::min<int64_t>(wanted, each), (unsigned)panels);
+    const dim3 grid((unsigned)cbm_panel_blocks(wanted, panels, held_grid(NT, STEPS, SLICES)), (unsigned)panels);
     const bool vec = s.K % 4 == 0 && s.lda % 4 == 0 && ((uintptr_t)s.A & 15) == 0;
     if (vec) hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, true>), grid, dim3(64 * WAVES), 0, stream, s);
     else hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, false>), grid, dim3(64 * WAVES), 0, stream, s);

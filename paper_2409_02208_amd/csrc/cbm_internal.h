@@ -254,6 +254,14 @@ cbm_status cbm_launch_gemm_split(int64_t M, int32_t N, int32_t K, const float* A
 // the same with B in registers, for few columns (cbm_gemm_held.hip), where its own rule says so
 cbm_status cbm_launch_gemm_held(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                 int64_t ldc, void* stream, bool* taken);
+// Workgroups for each of its panels of columns, where there is work for `wanted` and `resident` run at once: all panels' together no more than that (one that
+// waited would start on its equal share when others are done: with 3 x 344 and 3 x 88 of them for 1,024 and 256 that run 300000 x 32 . 32 x 144 took 52 us instead
+// of 45, 2000 x 500 . 500 x 160 11.7 instead of 8.8), and several panels' a multiple of 8, so that those that read the same rows share an XCD.
+inline int64_t cbm_panel_blocks(int64_t wanted, int panels, int64_t resident) {
+    if (panels == 1) return wanted < resident ? wanted : resident;
+    const int64_t rounded = (wanted + CBM_XCD - 1) / CBM_XCD * CBM_XCD, each = resident / panels / CBM_XCD * CBM_XCD;
+    return rounded < each ? rounded : each;
+}
 // Whether the panel-resident fp32 kernel also takes a B that 128-bit loads cannot read (odd width or alignment): filling the panel
 // element by element has to be earned by depth and by rows.  The staged kernel has blocks of 128 rows, so it loses where M / 128 just
 // exceeds the 256 compute units, and tiles of 48 columns, which suit N from 33 to 48 (microseconds, or its share of the staged kernel's time):
