@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <cstdlib>
 
+#include "cbm_held_rule.h"
 #include "cbm_internal.h"
 #include "cbm_split.h"
 
@@ -297,9 +298,6 @@ void launch(const Shape& s, hipStream_t stream) {
     else hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, false>), grid, dim3(64 * WAVES), 0, stream, s);
 }
 
-// Steps of 32 k that a wave can hold beside NT tiles of 16 columns: 12 registers each.
-constexpr int most_steps(int nt) { return nt == 4 ? 3 : 4; }
-
 template <int NT, int SLICES>
 bool launch_slices(const Shape& s, int steps, hipStream_t stream) {
     switch (steps) {
@@ -307,7 +305,7 @@ bool launch_slices(const Shape& s, int steps, hipStream_t stream) {
         case 2: launch<NT, 2, SLICES>(s, stream); return true;
         case 3: launch<NT, 3, SLICES>(s, stream); return true;
         case 4:
-            if constexpr (most_steps(NT) == 4) {
+            if constexpr (cbm_held_most_steps(NT) == 4) {
                 launch<NT, 4, SLICES>(s, stream);
                 return true;
             }
@@ -315,58 +313,17 @@ bool launch_slices(const Shape& s, int steps, hipStream_t stream) {
         default: return false;
     }
 }
-// How many waves share K: those that pad it least and, of these, as few as there are (132534 x 100 . 100 x 47, 4 steps: one wave 20, four 23; 20000 x 256 .
-// 256 x 47, 8 steps: four 8.1, eight 8.6) with no more than two steps each (x 16 one wave 13.7, four 11.4; 20000 x 500 . 500 x 47, 16 steps: four 13.9, eight
-// 12.1), three tiles of columns up to 50,000 rows only (50000 x 128 . 128 x 47 one wave 13.4, four 12.6; 80000 rows 15.7, 16.4).  Two waves are for 5 or 6
-// steps (250000 x 150 . 150 x 24 four 61, two 41).  Where there are not rows enough for all waves, as many as K takes: 8192 x 128 . 128 x 47 one wave 7.1, four
-// 5.4, 5000 x 320 . 320 x 32 four 6.7, eight 6.1 (12,000 rows: 7.2, 7.8).
 template <int NT>
-bool launch_nt(const Shape& s, hipStream_t stream) {
-    const int64_t steps = ((int64_t)s.K + 31) / 32;
-    const int64_t enough = s.M <= 8192 ? 1 : NT <= 2 || s.M <= 50000 ? 2 : most_steps(NT);
-    int64_t slices = 0, each = 0;
-    for (int64_t n : {1, 2, 4, 8}) {
-        const int64_t e = (steps + n - 1) / n;
-        if (e > most_steps(NT) || (slices && (each <= enough || (s.M > 8192 && n * e > slices * each)))) continue;
-        slices = n;
-        each = e;
-    }
-    switch (slices) {
-        case 1: return launch_slices<NT, 1>(s, (int)each, stream);
-        case 2: return launch_slices<NT, 2>(s, (int)each, stream);
-        case 4: return launch_slices<NT, 4>(s, (int)each, stream);
-        case 8: return launch_slices<NT, 8>(s, (int)each, stream);
+bool launch_nt(const Shape& s, const CbmHeldPlan& p, hipStream_t stream) {
+    switch (p.slices) {
+        case 1: return launch_slices<NT, 1>(s, p.each, stream);
+        case 2: return launch_slices<NT, 2>(s, p.each, stream);
+        case 4: return launch_slices<NT, 4>(s, p.each, stream);
+        case 8: return launch_slices<NT, 8>(s, p.each, stream);
         default: return false;
     }
 }
 
-}  // namespace
-
-namespace {
-// Where the lines lie (us, the other kernels -> these), measured over M from 500 to 300,000, K from 8 to 1,000 and 21 widths.  Up to 64 columns nothing is slower
-// by more than a call's noise, but for K just above 32 (padded to 64) and few rows (20000 x 33 . 33 x 64 7.6 -> 8.0).  Wider products go in panels of up to 64
-// columns side by side, each of which reads A:
-//  K <= 32, where C is most of the traffic: 300000 x 32 . 32 x 128 67 -> 36, x 256 141 -> 115, 20000 x 8 . 8 x 192 15 -> 8; with rows of A off 16-byte boundaries not
-//    just beyond one panel (170000 x 30 . 30 x 66 20 -> 24) nor four of them at their tallest (250000 x 30 . 30 x 250 85 -> 93);
-//  more than 128 columns, K > 32: three or four panels lose (132534 x 100 . 100 x 160 60 -> 109) but where there are few rows (2000 x 500 . 500 x 256 22 -> 8.7,
-//    8192 rows and 160 columns 22.5 -> 26);
-//  two panels, K <= 64: 132534 x 64 . 64 x 80 23 -> 21, 50000 rows 14.5 -> 11.8, 20000 x 64 . 64 x 112 8.9 -> 9.7, 8192 rows 6.5 -> 6.4, 2000 6.2 -> 5.5;
-//  two of more than 48 columns, K <= 192: 50000 x 100 . 100 x 112 23.3 -> 22.0, 132534 rows 45 -> 49, 28000 x 80 . 80 x 104 11.7 -> 12.4, 160 deep 15.7 -> 16.6; of up
-//    to 48: 132534 x 100 . 100 x 96 40 -> 32;
-//  deeper: 20000 x 500 . 500 x 112 34 -> 23, 132534 x 256 . 256 x 112 75 -> 67, 300000 rows and x 80 126 -> 130, 132534 x 320 . 320 x 80 66 -> 71, 50000 rows 42 -> 31,
-//    132534 x 500 . 500 x 80 122 -> 92, but 13 steps of K are padded to 16 beside four tiles (40000 x 400 . 400 x 104 41.4 -> 42.5).
-// Below K = 8 a product is a few roundings, which the fp32 kernels make no fewer of than needed: theirs.
-bool held_takes(int64_t M, int32_t N, int32_t K, bool vec) {
-    if (K < 8 || N > 256) return false;
-    if (N <= 64) return true;
-    if (K <= 32) return vec || (N > 80 && (N <= 192 || M <= 200000));
-    if (N > 128) return M <= 2048;
-    if (K <= 64) return M <= 4096 || M >= 32768;
-    if (N > 96 && K <= 192) return M <= 4096 || (M >= 32768 && M <= 65536);
-    if (N > 96 && K > 384 && K < 448) return false;
-    if (K <= 128) return true;
-    return M <= 100000 || K >= 480 || (K <= 256 && M <= 200000);
-}
 }  // namespace
 
 cbm_status cbm_launch_gemm_held(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
@@ -375,14 +332,14 @@ cbm_status cbm_launch_gemm_held(int64_t M, int32_t N, int32_t K, const float* A,
     // (for tests, which run several in one process: 5 = whatever K, 0 to 4 = never, as another kernel is asked for)
     const char* e = std::getenv("CBM_GEMM_SPLIT");
     const bool asked = e && e[0] >= '0' && e[0] <= '5' && !e[1];
-    if (asked ? e[0] != '5' || N > 256 : !held_takes(M, N, K, K % 4 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0)) return CBM_OK;
+    if (asked ? e[0] != '5' || N > 256 : !cbm_held_takes(M, N, K, K % 4 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0)) return CBM_OK;
     const Shape s{M, N, K, A, lda, B, ldb, C, ldc};
-    const int panels = (N + 63) / 64;
-    switch (((N + 15) / 16 + panels - 1) / panels) {
-        case 1: *taken = launch_nt<1>(s, (hipStream_t)stream); break;
-        case 2: *taken = launch_nt<2>(s, (hipStream_t)stream); break;
-        case 3: *taken = launch_nt<3>(s, (hipStream_t)stream); break;
-        default: *taken = launch_nt<4>(s, (hipStream_t)stream); break;
+    const CbmHeldPlan p = cbm_held_plan(M, N, K);
+    switch (p.tiles) {
+        case 1: *taken = launch_nt<1>(s, p, (hipStream_t)stream); break;
+        case 2: *taken = launch_nt<2>(s, p, (hipStream_t)stream); break;
+        case 3: *taken = launch_nt<3>(s, p, (hipStream_t)stream); break;
+        default: *taken = launch_nt<4>(s, p, (hipStream_t)stream); break;
     }
     if (!*taken) return CBM_OK;
     const hipError_t err = hipGetLastError();
