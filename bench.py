@@ -54,7 +54,7 @@ COUNTER_GROUPS = (("fetch", ["FETCH_SIZE"]), ("write", ["WRITE_SIZE"]), ("l2", [
 PRODUCT_KERNELS = ("cbm_level_kernel", "cbm_bundle_kernel", "cbm_combine_kernel", "cbm_finish_kernel", "cbm_block_sum_kernel",
                    "cbm_block_kernel", "cbm_sum_sets_kernel", "cbm_sum_rows_kernel", "cbm_flat_kernel")
 KIND_NAMES = {0: "rounds of paths", 1: "segments of split rows", 2: "combine of split rows", 3: "deferred finish",
-              4: "sum of column blocks", 5: "row blocks", 6: "shared sums"}
+              4: "sum of column blocks", 5: "row blocks", 6: "shared sums", 7: "segments and rows"}
 
 DEFAULTS = {  # workload -> k of the timed product, alpha, GCN shape or None
     "tiny": dict(k=16, alpha=0, gcn=(16, 8, 4)),
@@ -206,8 +206,8 @@ def counter_child(args):
         h = last[1]
         X = torch.randn((g.n, k), device="cuda")
         Y = torch.empty((g.n, k), device="cuda")
-        cbm.cbm_profile_enable(h, True)
-        for _ in range(reps):                # all of them with the library's own record: segments and rows of small handles are then launched apart
+        cbm.cbm_profile_enable(h, 2)
+        for _ in range(reps):                # all of them with the library's own record, which says what was launched
             cbm.cbm_spmm_normalized(h, X, Y)
             torch.cuda.synchronize()
             recs = cbm.cbm_profile_read(h)
@@ -314,7 +314,7 @@ def method_figures(stats, k, normalized, agg, nprof):
 
 def profile_product(torch, cbm, h, fn, steps):
     """Per-launch HIP-event timing inside the library (events on the stream the kernels run on), summed per kind."""
-    cbm.cbm_profile_enable(h, True)
+    cbm.cbm_profile_enable(h, 2)  # the launches as they are
     agg = {}
     t_total = 0.0
     for _ in range(steps):
@@ -428,7 +428,7 @@ def bench_product(torch, cbm, orc, g, h, hc, Xh, k, steps, warmup, workload, cou
         + (f", HBM side {hbm_total / ms / 1e6:.0f} GB/s ({hbm_total / 1e9:.2f} GB)" if hbm_total else ""))
 
     # the dominant launch = the kind that takes the most time
-    lv = [l for l in launches if l["kind"] in (0, 1, 5, 6)]
+    lv = [l for l in launches if l["kind"] in (0, 1, 5, 6, 7)]
     dom = max(lv, key=lambda l: l["ms"]) if lv else None
     roofline = None
     if dom is not None:

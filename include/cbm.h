@@ -341,6 +341,10 @@ cbm_status cbm_decompress(const cbm_handle* h, int64_t* rowptr, int32_t* colidx)
 /*
  * Per-launch timing of the product kernels.  With profiling on, every kernel a
  * product call enqueues is bracketed by HIP events on the caller's stream.
+ * on = 1 changes what is launched: segments of split rows and rows stored in full,
+ * which share a launch otherwise, are launched one after the other (kinds 1 and 0), so
+ * that each has a time.  on = 2 leaves the launches as they are (kind 7 where the two
+ * share one).  The results are the same.
  * After synchronising the stream, cbm_profile_read returns, for the most
  * recent product call, up to `cap` records and the total count in *count.
  */
@@ -353,8 +357,9 @@ typedef struct {
                                split rows (tasks = blocks, deltas = columns gathered, each
                                once per block), 6 = shared sums: level 1 the sets, level 2
                                the rows made of them, level 3 rows that sum their sets in place
-                               (tasks = sets or rows, deltas = rows of X and sums gathered) */
-    int32_t level;          /* round for kinds 0 and 2, launch for kind 6, else 0      */
+                               (tasks = sets or rows, deltas = rows of X and sums gathered),
+                               7 = segments of split rows and rows stored in full (on = 2) */
+    int32_t level;          /* round for kinds 0, 2 and 7, launch for kind 6, else 0   */
     int64_t tasks;          /* work items in the launch                               */
     int64_t deltas;         /* delta entries gathered by the launch                   */
     int64_t algorithmic_bytes; /* bytes the method itself must move in this launch    */
@@ -362,7 +367,7 @@ typedef struct {
     int32_t per_xcd;        /* 1 = the launch hands every XCD a work list of its own (segments
                                by column range; a round in graph-locality order), else 0     */
 } cbm_launch_record;
-cbm_status cbm_profile_enable(cbm_handle* h, int32_t on);
+cbm_status cbm_profile_enable(cbm_handle* h, int32_t on); /* 0 off, 1 (or any other value) apart, 2 as they are */
 cbm_status cbm_profile_read(cbm_handle* h, cbm_launch_record* records, int32_t cap, int32_t* count);
 
 void cbm_free(cbm_handle* h); /* NULL-safe; releases everything the handle owns */

@@ -274,7 +274,8 @@ def cbm_decompress(h: Handle):
     return rowptr, colidx[:s["nnz"]]
 
 
-def cbm_profile_enable(h: Handle, on: bool = True):
+def cbm_profile_enable(h: Handle, on: int = True):
+    """0 off, 1 segments of split rows and rows stored in full each a launch, 2 the launches as they are without it."""
     _check(_lib().cbm_profile_enable(h.ptr, int(on)), "cbm_profile_enable")
 
 

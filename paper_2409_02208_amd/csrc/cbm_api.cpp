@@ -195,8 +195,8 @@ cbm_status cbm_decompress(const cbm_handle* h, int64_t* rowptr, int32_t* colidx)
 cbm_status cbm_profile_enable(cbm_handle* h, int32_t on) {
     if (!h) return CBM_ERR_INVALID_ARG;
     if (!h->on_device) return CBM_ERR_STATE;
-    h->profiling = on != 0;
-    if (h->inner) h->inner->profiling = on != 0;
+    h->profiling = on == 2 ? 2 : on != 0;
+    if (h->inner) h->inner->profiling = h->profiling;
     return CBM_OK;
 }
 

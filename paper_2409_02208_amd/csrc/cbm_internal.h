@@ -177,7 +177,7 @@ struct cbm_handle {
     mutable int64_t partial_k = 0;
 
     // ---- per-launch profiling ----------------------------------------------------
-    bool profiling = false;
+    int profiling = 0;  // as cbm_profile_enable has it: 1 segments and rows apart, 2 the launches as they are
     mutable std::vector<cbm_launch_record> prof_records;
     mutable std::vector<void*> prof_events;  // hipEvent_t pairs
 

@@ -1048,8 +1048,11 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
     // Segments wait for nobody and nobody but the combine launch waits for them: where all rows are stored in full they share the rows' launch, first in it
     // because they are longest, and their tail and the rows' start fill each other's gaps (R-MAT, us apart / together: directed scale 17, k = 100, both
     // directions 190 / 164, scale 16, k = 128 152 / 106; scale 18, mean of 47 columns 215 / 191, k = 200 636 / 638; scale 16, k = 128 98 / 86; scale 21, k = 128
-    // 3793 / 3758).  Apart for per-launch times, and where few, long rows are shared among groups (launch_level).
-    const bool together = segments > 0 && !flat_lanes && h->whole_rows && !h->profiling && h->levels[0].task_count > 0 &&
+    // 3793 / 3758).  So they do where segments are few beside the rows (one node of 1,000 neighbours in the citation recipe: 19,717 nodes, k = 64 30 / 24, k = 500
+    // 54 / 45, 170,000 nodes, k = 128 94 / 73; 20 of 3,000 among 60,000 rows of 24, k = 200 202 / 187).  Apart where a caller wants a time for each, and where few,
+    // long rows are shared among groups (launch_level).
+    const bool apart = h->profiling == 1, flat_together = segments > 0 && flat_lanes && !apart;
+    const bool together = segments > 0 && !flat_lanes && h->whole_rows && !apart && h->levels[0].task_count > 0 &&
                           !(h->levels[0].long_single_rows && lanes <= 16 && h->levels[0].task_count / (64 / lanes) * ychunks <= wide_max_waves());
     const LaunchCtx ctx{h, X, ldx, k, Y, ldy, scratch, ld_scratch, stream, h->d_wstream, mode == 3 ? h->d_rinv : h->d_dinv, self_weight, together};
     const int64_t rowb = 4 * (int64_t)k;
@@ -1077,35 +1080,40 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         ProfScope ps(h, stream, rec);
         cbm_launch_hub_blocks(h, X, ldx, k, scratch, ld_scratch, wcol, stream_);
     }
-    if (segments > 0 && !together) {
+    // what a launch of segments, of a round's work items or of both does; the method's bytes only: the partial sums of split rows are this implementation's
+    // overhead.  Per delta: one X row + its entry (+ d^-1/2); per row: one Y write + its marker entry (+ d^-1/2); per work item with a parent: the parent's row
+    auto items_record = [&](bool with_segments, size_t round) {
         cbm_launch_record rec{};
         rec.kind = 1;
         rec.per_xcd = 1;
-        rec.tasks = segments;
-        rec.deltas = h->seg_deltas;
-        // the method's bytes only: the partial sums of split rows are this implementation's overhead
-        rec.algorithmic_bytes = h->seg_deltas * per_delta;
-        ProfScope ps(h, stream, rec);
-        if (flat_lanes) cbm_launch_flat(h, true, !h->profiling, flat_lanes, X, ldx, k, Y, ldy, scratch, ld_scratch, mode, ctx.rw, self_weight, aligned, stream_);
+        if (with_segments) {
+            rec.tasks = segments;
+            rec.deltas = h->seg_deltas;
+            rec.algorithmic_bytes = h->seg_deltas * per_delta;
+        }
+        if (round < h->levels.size()) {
+            const CbmLevel& L = h->levels[round];
+            rec.kind = with_segments ? 7 : 0;
+            rec.per_xcd = with_segments || L.by_xcd ? 1 : 0;
+            rec.level = (int32_t)round + 1;
+            rec.tasks += L.task_count;
+            rec.deltas += L.deltas;
+            rec.algorithmic_bytes += L.deltas * per_delta + L.rows_written * per_row + L.parent_reads * rowb;
+        }
+        return rec;
+    };
+    if (segments > 0 && !together) {
+        ProfScope ps(h, stream, items_record(true, flat_together ? 0 : h->levels.size()));
+        if (flat_lanes) cbm_launch_flat(h, true, flat_together, flat_lanes, X, ldx, k, Y, ldy, scratch, ld_scratch, mode, ctx.rw, self_weight, aligned, stream_);
         else (many(segments, h->seg_deltas, h->seg_longest) ? var.segments_many : var.segments)(ctx, CbmLevel{});
     }
     for (size_t l = 0; l < h->levels.size(); ++l) {
         const CbmLevel& L = h->levels[l];
-        if (L.task_count > 0) {
-            cbm_launch_record rec{};
-            rec.kind = 0;
-            rec.per_xcd = L.by_xcd ? 1 : 0;
-            rec.level = (int32_t)l + 1;
-            rec.tasks = L.task_count;
-            rec.deltas = L.deltas;
-            // per delta: one X row + its entry (+ d^-1/2); per row: one Y write + its marker entry (+ d^-1/2);
-            // per work item with a parent: the parent's row
-            rec.algorithmic_bytes = L.deltas * per_delta + L.rows_written * per_row + L.parent_reads * rowb;
-            ProfScope ps(h, stream, rec);
+        if (L.task_count > 0 && !flat_together) {
+            ProfScope ps(h, stream, items_record(together, l));
             if (together) (many(segments + L.task_count, h->seg_deltas + L.deltas, std::max(h->seg_longest, L.longest)) ? var.level_many : var.level)(ctx, L);
             else if (!flat_lanes) (many(L.task_count, L.deltas, L.longest) ? var.level_many : var.level)(ctx, L);
-            else if (segments == 0 || h->profiling)
-                cbm_launch_flat(h, false, true, flat_lanes, X, ldx, k, Y, ldy, scratch, ld_scratch, mode, ctx.rw, self_weight, aligned, stream_);
+            else cbm_launch_flat(h, false, true, flat_lanes, X, ldx, k, Y, ldy, scratch, ld_scratch, mode, ctx.rw, self_weight, aligned, stream_);
         }
         if (L.comb_count > 0) {
             cbm_launch_record rec{};
