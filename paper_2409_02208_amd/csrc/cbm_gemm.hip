@@ -573,15 +573,16 @@ __global__ __launch_bounds__(64 * WPB) void cbm_gemm_panel_kernel(int64_t M, int
 
 inline bool wide_loads_of_b(int N, const float* B, int64_t ldb) { return N % 4 == 0 && ldb % 4 == 0 && ((uintptr_t)B & 15) == 0; }
 
-// Groups of 16 k that a wave of the panel kernel keeps in flight, and that its K loop is a multiple of: whichever of 4, 3, 5 and 7 pads K least
-// (132,534 x K . K x 47, us, with 4 always -> here: K = 48 19.0 -> 16.9, 80 25.7 -> 20.8, 96 25.7 -> 22.4, 100 26.6 -> 25.7, 144 32.9 -> 27.8; x 64: 80 29.8 -> 22.8,
-// 200 47.7 -> 44.7; 7 beside one tile would lose, 100 x 16 17.7 -> 18.4).
+// Groups of 16 k that a wave of the panel kernel keeps in flight, and that its K loop is a multiple of.  Up to 64 columns K of 8 to 768 or more holds B in
+// registers instead (cbm_gemm_held.hip).  One or two tiles of columns, K of 148 to 160 or beyond 1,024: whichever of 4, 3 and 5 pads K least (132,534 x 144 . 144 x 47,
+// three tiles, 4 always -> 3: 32.9 -> 27.8).  Three or four tiles, K = 4: 3.
 inline int panel_ring(int K, int nt16) {
+    if (nt16 > 4) return 4;  // (registers for no more than that beside so many tiles)
+    if (nt16 > 2) return 3;
     const int nkg = (K + 15) / 16;
     int best = 4;
-    if (nt16 > 4) return best;  // (registers for no more than that beside so many tiles)
-    for (int r : {3, 5, 7})
-        if ((r < 7 || nt16 > 2) && (nkg + r - 1) / r * r < (nkg + best - 1) / best * best) best = r;
+    for (int r : {3, 5})
+        if ((nkg + r - 1) / r * r < (nkg + best - 1) / best * best) best = r;
     return best;
 }
 inline int panel_depth(int K, int nt16) {
@@ -590,9 +591,8 @@ inline int panel_depth(int K, int nt16) {
 }
 
 // LDS bytes of the resident panel, or 0 if this product cannot take the panel kernel.  A panel that fits only because its depth is not a multiple
-// of 64 (N of 33 to 48 with K of 769 to 784, of 17 to 32 with 1089 to 1120) is for a B of odd width or alignment (us, kernel below / panel: 132,534 x 784 .
-// 784 x 47 185 / 126, 60,000 rows 78 / 59, x 1120 . 1120 x 31 218 / 157): with wide loads of B it loses (30,000 x 784 . 784 x 48 34 / 36, 40 wide 34 / 40,
-// 132,534 x 772 . 772 x 40 124 / 128, 132,534 x 1092 . 1092 x 24 138 / 162, 30,000 rows 33 / 39; 300,000 x 784 . 784 x 48 would gain, 266 / 243).
+// of 64 (N of 17 to 32 with K of 1089 to 1120) is for a B of odd width or alignment (us, kernel below / panel: 132,534 x 1120 . 1120 x 31 218 / 157): with wide loads
+// of B it loses (132,534 x 1092 . 1092 x 24 138 / 162, 30,000 rows 33 / 39).
 inline size_t panel_lds_bytes(int N, int K, const float* A, int64_t lda, bool wide_b, int* nt16) {
     const bool vec = K % 4 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0 && K >= 4;
     if (!vec || N < 16) return 0;
@@ -630,14 +630,12 @@ cbm_status launch_panel_as(int64_t M, int N, int K, const float* A, int64_t lda,
 template <int NT16>
 cbm_status launch_panel(int64_t M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
                         size_t smem, hipStream_t stream) {
-    if constexpr (NT16 <= 4) {
+    if constexpr (NT16 <= 2) {
         const int ring = panel_ring(K, NT16);
         if (ring == 3) return launch_panel_as<NT16, 3>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);
         if (ring == 5) return launch_panel_as<NT16, 5>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);
-        if constexpr (NT16 > 2)
-            if (ring == 7) return launch_panel_as<NT16, 7>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);
     }
-    return launch_panel_as<NT16, 4>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);
+    return launch_panel_as<NT16, NT16 == 3 || NT16 == 4 ? 3 : 4>(M, N, K, A, lda, B, ldb, C, ldc, smem, stream);
 }
 
 template <int NT, bool VEC>
