@@ -134,16 +134,19 @@ def test_values_too_small_for_the_parts_are_not_lost(env, monkeypatch, form, a, 
     assert np.all(np.abs(_product(env, A, B) - ref) <= (k + 6) * 2.0 ** -24 * size + 2.0 ** -149)
 
 
-@pytest.mark.parametrize("value", ["5", "-1", "17", "2x", "", "yes"])
+@pytest.mark.parametrize("value", ["6", "-1", "17", "2x", "", "yes"])
 def test_the_switch_takes_no_other_value(env, monkeypatch, value):
     rng = np.random.default_rng(3)
-    A, B = rng.standard_normal((300, 90), dtype=np.float32), rng.standard_normal((90, 33), dtype=np.float32)  # the fp32 kernels' by the rule
+    A, B = rng.standard_normal((300, 30), dtype=np.float32), rng.standard_normal((30, 33), dtype=np.float32)  # the fp32 kernels' by the rule
     monkeypatch.delenv("CBM_GEMM_SPLIT", raising=False)
     want = _product(env, A, B)
     monkeypatch.setenv("CBM_GEMM_SPLIT", value)
     assert np.array_equal(_product(env, A, B), want)
-    monkeypatch.setenv("CBM_GEMM_SPLIT", "2")
-    assert not np.array_equal(_product(env, A, B), want)
+    monkeypatch.setenv("CBM_GEMM_SPLIT", "0")
+    assert np.array_equal(_product(env, A, B), want)
+    for kernel in ("2", "5"):
+        monkeypatch.setenv("CBM_GEMM_SPLIT", kernel)
+        assert not np.array_equal(_product(env, A, B), want)
 
 
 @pytest.mark.parametrize("k,n", [(500, 64), (500, 7), (256, 256), (300, 96)])

@@ -597,9 +597,13 @@ def test_gcn2_rejects_overlapping_buffers(env, graphs):
     torch.cuda.synchronize()
 
 
+KERNELS = pytest.mark.parametrize("split", [None, "0"], ids=["by the rule", "fp32 kernels"])
+
+
+@KERNELS
 @pytest.mark.parametrize("M,N,K", [(1000, 64, 500), (777, 3, 64), (513, 112, 256), (256, 256, 256), (130, 33, 7),
                                    (1, 1, 1), (300, 200, 37),
-                                   # widths served by the 16-column tiles (N mod 32 in 1..16 above 32), ragged M and K too
+                                   # of the fp32 kernels: widths served by the 16-column tiles (N mod 32 in 1..16 above 32), ragged M and K too
                                    (2000, 112, 256), (1029, 100, 61), (515, 48, 128), (640, 40, 36), (300, 80, 500),
                                    (129, 65, 33), (4100, 97, 5),
                                    # as many rows as fill the chip evenly with blocks of 128 rows (fewer rows run in blocks of 64)
@@ -612,8 +616,9 @@ def test_gcn2_rejects_overlapping_buffers(env, graphs):
                                    # overlaps its neighbour at seven tiles), three panels one after the other
                                    (78336, 128, 64), (78341, 128, 128), (91136, 128, 64), (78341, 112, 128), (91136, 112, 64),
                                    (9000, 300, 64)])
-def test_dense_matmul(env, M, N, K):
+def test_dense_matmul(env, monkeypatch, M, N, K, split):
     torch, cbm = env
+    monkeypatch.delenv("CBM_GEMM_SPLIT", raising=False) if split is None else monkeypatch.setenv("CBM_GEMM_SPLIT", split)
     rng = np.random.default_rng(M + N + K)
     A = rng.standard_normal((M, K)).astype(np.float32)
     B = rng.standard_normal((K, N)).astype(np.float32)
@@ -631,14 +636,16 @@ def test_dense_matmul(env, M, N, K):
     assert np.array_equal(Cd.cpu().numpy().astype(np.float64), Ai.astype(np.float64) @ Bi.astype(np.float64))
 
 
-@pytest.mark.parametrize("M,N,K,pad_a,pad_b,pad_c,off", [(40000, 112, 256, 8, 16, 4, 4),    # panel kernel, strided, aligned
-                                                          (40000, 256, 128, 4, 0, 12, 8),    # two panels side by side
-                                                          (40000, 112, 256, 8, 16, 4, 1),    # slices off the 16-byte grid
-                                                          (40000, 96, 64, 3, 5, 1, 0)])      # odd strides: staged kernels
-def test_dense_matmul_strided_operands(env, M, N, K, pad_a, pad_b, pad_c, off):
+@KERNELS
+@pytest.mark.parametrize("M,N,K,pad_a,pad_b,pad_c,off", [(40000, 112, 256, 8, 16, 4, 4),    # strided, aligned: the panel kernel of the fp32 ones
+                                                          (40000, 256, 128, 4, 0, 12, 8),    # its two panels side by side
+                                                          (40000, 112, 256, 8, 16, 4, 1),    # slices off the 16-byte grid: their staged kernels
+                                                          (40000, 96, 64, 3, 5, 1, 0)])      # odd strides: the same
+def test_dense_matmul_strided_operands(env, monkeypatch, M, N, K, pad_a, pad_b, pad_c, off, split):
     """A, B and C as column slices of wider buffers (leading dimensions larger than the widths), output rows poisoned:
     nothing outside C's columns may be written."""
     torch, cbm = env
+    monkeypatch.delenv("CBM_GEMM_SPLIT", raising=False) if split is None else monkeypatch.setenv("CBM_GEMM_SPLIT", split)
     rng = np.random.default_rng(M + N + K + off)
     Aw = rng.standard_normal((M, K + pad_a + off)).astype(np.float32)
     Bw = rng.standard_normal((K, N + pad_b + off)).astype(np.float32)
