@@ -1082,6 +1082,7 @@ cbm_status Builder::emit(int32_t nrounds) {
     h->comb.clear();
     h->stream.clear();
     h->num_slots = 0;
+    h->num_segments = 0;
     h->seg_deltas = 0;
     h->seg_longest = 0;
     int64_t split_rows = 0;
@@ -1263,6 +1264,7 @@ cbm_status Builder::emit(int32_t nrounds) {
             h->tasks.insert(h->tasks.end(), list.begin(), list.end());
         }
         h->seg_count[j] = (int64_t)h->tasks.size() - h->seg_begin[j];
+        h->num_segments += h->seg_count[j];
     }
     const bool by_locality = !loc.empty();
     for (int r = 1; r <= nrounds; ++r) {

@@ -175,21 +175,21 @@ __global__ __launch_bounds__(256, 3) void cbm_flat_kernel(const FlatArgs a) {
 }
 
 template <bool RAGGED, int LANES>
-void launch(const FlatArgs& a, int mode, dim3 grid, hipStream_t stream) {
+const void* kernel(int mode) {
     switch (mode) {
-        case 0: hipLaunchKernelGGL((cbm_flat_kernel<RAGGED, LANES, 0>), grid, dim3(256), 0, stream, a); return;
-        case 1: hipLaunchKernelGGL((cbm_flat_kernel<RAGGED, LANES, 1>), grid, dim3(256), 0, stream, a); return;
-        case 2: hipLaunchKernelGGL((cbm_flat_kernel<RAGGED, LANES, 2>), grid, dim3(256), 0, stream, a); return;
-        case 3: hipLaunchKernelGGL((cbm_flat_kernel<RAGGED, LANES, 3>), grid, dim3(256), 0, stream, a); return;
-        default: hipLaunchKernelGGL((cbm_flat_kernel<RAGGED, LANES, 4>), grid, dim3(256), 0, stream, a); return;
+        case 0: return (const void*)cbm_flat_kernel<RAGGED, LANES, 0>;
+        case 1: return (const void*)cbm_flat_kernel<RAGGED, LANES, 1>;
+        case 2: return (const void*)cbm_flat_kernel<RAGGED, LANES, 2>;
+        case 3: return (const void*)cbm_flat_kernel<RAGGED, LANES, 3>;
+        default: return (const void*)cbm_flat_kernel<RAGGED, LANES, 4>;
     }
 }
 template <bool RAGGED>
-void launch_lanes(const FlatArgs& a, int lanes, int mode, dim3 grid, hipStream_t stream) {
+const void* kernel_lanes(int lanes, int mode) {
     switch (lanes) {
-        case 8: return launch<RAGGED, 8>(a, mode, grid, stream);
-        case 16: return launch<RAGGED, 16>(a, mode, grid, stream);
-        default: return launch<RAGGED, 32>(a, mode, grid, stream);
+        case 8: return kernel<RAGGED, 8>(mode);
+        case 16: return kernel<RAGGED, 16>(mode);
+        default: return kernel<RAGGED, 32>(mode);
     }
 }
 
@@ -206,7 +206,7 @@ int cbm_flat_lanes(const cbm_handle* h, int32_t k) {
     return cbm_flat_waves(h, lanes, k) <= h->flat_most_waves ? lanes : 0;
 }
 
-void cbm_launch_flat(const cbm_handle* h, bool segments, bool rows, int lanes, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
+bool cbm_launch_flat(const cbm_handle* h, bool segments, bool rows, int lanes, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
                      float* scratch, int64_t ld_scratch, int mode, const float* rw, float self_w, bool aligned, void* stream) {
     FlatArgs a{h->d_tasks, {}, 0, 0, 0, 0, 0, h->d_stream, h->d_wstream, rw, X, ldx, Y, ldy, scratch, ld_scratch, self_w, (int)k};
     int64_t blocks = 0;
@@ -229,7 +229,9 @@ void cbm_launch_flat(const cbm_handle* h, bool segments, bool rows, int lanes, c
         const int64_t per = 4 * 64 / lanes;
         blocks += a.long_blocks + (a.row_end - a.row_long + per - 1) / per;
     }
-    if (blocks == 0) return;
+    if (blocks == 0) return true;
     const dim3 grid((unsigned)blocks, (unsigned)((k + 4 * lanes - 1) / (4 * lanes)));
-    aligned ? launch_lanes<false>(a, lanes, mode, grid, (hipStream_t)stream) : launch_lanes<true>(a, lanes, mode, grid, (hipStream_t)stream);
+    // (one call of the runtime, not one for the launch's shape and one for its status beside it: their time is a part of these products')
+    void* args[] = {&a};
+    return hipLaunchKernel(aligned ? kernel_lanes<false>(lanes, mode) : kernel_lanes<true>(lanes, mode), grid, dim3(256), args, 0, (hipStream_t)stream) == hipSuccess;
 }

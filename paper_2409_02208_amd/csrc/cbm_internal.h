@@ -116,6 +116,7 @@ struct cbm_handle {
     std::vector<CbmLevel> levels;  // levels[0] is round 1
     int64_t num_slots = 0;         // scratch rows needed by split rows
     int64_t seg_begin[CBM_XCD] = {}, seg_count[CBM_XCD] = {};  // segment work items in tasks[], per column range
+    int64_t num_segments = 0;      // all of them
     int64_t seg_deltas = 0;        // delta entries gathered by the segment launch
     int64_t seg_longest = 0;       // entries of the longest segment
     bool whole_rows = false;       // every row is stored in full: one round of single rows, and segments
@@ -219,13 +220,13 @@ void cbm_launch_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t
 void cbm_launch_hub_blocks(const cbm_handle* h, const float* X, int64_t ldx, int32_t k, float* scratch, int64_t ld_scratch, bool weighted,
                            void* stream);
 // Segments and / or rows of a handle whose rows are all stored in full, for products small enough to be bound by latency (cbm_flat.hip):
-// lanes per group and entry, 0 if this product is not for it.
+// lanes per group and entry, 0 if this product is not for it; the launch, false: the runtime's last error says why not.
 int cbm_flat_lanes(const cbm_handle* h, int32_t k);
 inline int64_t cbm_flat_waves(const cbm_handle* h, int lanes, int64_t k) {  // of such a launch, chunks of 4 lanes columns each their own
     const int64_t shorts = h->levels[0].task_count - h->flat_long;
     return ((int64_t)h->tasks.size() - shorts + (shorts * lanes + 63) / 64) * ((k + 4 * lanes - 1) / (4 * lanes));
 }
-void cbm_launch_flat(const cbm_handle* h, bool segments, bool rows, int lanes, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
+bool cbm_launch_flat(const cbm_handle* h, bool segments, bool rows, int lanes, const float* X, int64_t ldx, int32_t k, float* Y, int64_t ldy,
                      float* scratch, int64_t ld_scratch, int mode, const float* rw, float self_w, bool aligned, void* stream);
 // Their modelled time: a launch, the longest row's batches of eight loads in each of its groups, and the gathers at L2's rate, whole cache lines of
 // them (communities of 5,000 nodes, k = 128 8.1 us; 5,000 nodes of the collaboration recipe, k = 128 15.4; 1,200 nodes, k = 200 12.4).

@@ -994,6 +994,14 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
     // every lane holds four columns; rows that all start on 16-byte boundaries and hold a multiple of four columns
     // take the aligned variant (128-bit accesses), anything else the ragged one (32-bit accesses, strided columns)
     const bool aligned = k % 4 == 0 && ldx % 4 == 0 && ldy % 4 == 0 && ((uintptr_t)X & 15) == 0 && ((uintptr_t)Y & 15) == 0;
+    const int mode = (int)epi;
+    const bool wcol = mode == 1 || mode == 2, wrow = wcol || mode == 3;
+    const float* rw = mode == 3 ? h->d_rinv : h->d_dinv;
+    if (flat_lanes && h->num_segments == 0 && h->levels[0].comb_count == 0 && !h->hub_blocks && !h->profiling) {  // one launch is all of it
+        if (cbm_launch_flat(h, false, true, flat_lanes, X, ldx, k, Y, ldy, scratch, ld_scratch, mode, rw, self_weight, aligned, stream_)) return CBM_OK;
+        HIP_TRY(hipGetLastError(), CBM_ERR_HIP);
+        return CBM_ERR_HIP;
+    }
     // at least 8 lanes per work item, idle ones included: entries are fetched a group's width at a time, and groups
     // of 4 spend more on that than they save (k <= 16: 25-30 % slower, measured)
     int lanes = 8;
@@ -1015,7 +1023,6 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
     // of 128 already: between +1 and -8 %.
     const int64_t slab = h->n * 64 * (int64_t)sizeof(float);
     if (aligned && ((k == 128 && slab >= kSlabOfTwo) || (k > 64 && k % 128 == 64 && slab >= kSlabOfOdd))) lanes = 16;
-    const int mode = (int)epi;
     const Variant var = aligned ? pick_lanes<false>(lanes, mode) : pick_lanes<true>(lanes, mode);
     if (h->profiling) {
         for (void* e : h->prof_events) hipEventDestroy((hipEvent_t)e);
@@ -1042,9 +1049,7 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
         if (many_env || waves < kManyWavesShort || (lanes == 64 && deltas >= 16 * items)) return false;
         return longest * kEntryManyUs <= kManyLongest * (double)deltas * k * 4 / kManyBytesPerUs;
     };
-    const bool wcol = mode == 1 || mode == 2, wrow = wcol || mode == 3;
-    int64_t segments = 0;  // (not num_slots: hub blocks write scratch rows too)
-    for (int64_t c : h->seg_count) segments += c;
+    const int64_t segments = h->num_segments;  // (not num_slots: hub blocks write scratch rows too)
     // Segments wait for nobody and nobody but the combine launch waits for them: where all rows are stored in full they share the rows' launch, first in it
     // because they are longest, and their tail and the rows' start fill each other's gaps (R-MAT, us apart / together: directed scale 17, k = 100, both
     // directions 190 / 164, scale 16, k = 128 152 / 106; scale 18, mean of 47 columns 215 / 191, k = 200 636 / 638; scale 16, k = 128 98 / 86; scale 21, k = 128
@@ -1054,7 +1059,7 @@ cbm_status cbm_launch_product(const cbm_handle* h, const float* X, int64_t ldx, 
     const bool apart = h->profiling == 1, flat_together = segments > 0 && flat_lanes && !apart;
     const bool together = segments > 0 && !flat_lanes && h->whole_rows && !apart && h->levels[0].task_count > 0 &&
                           !(h->levels[0].long_single_rows && lanes <= 16 && h->levels[0].task_count / (64 / lanes) * ychunks <= wide_max_waves());
-    const LaunchCtx ctx{h, X, ldx, k, Y, ldy, scratch, ld_scratch, stream, h->d_wstream, mode == 3 ? h->d_rinv : h->d_dinv, self_weight, together};
+    const LaunchCtx ctx{h, X, ldx, k, Y, ldy, scratch, ld_scratch, stream, h->d_wstream, rw, self_weight, together};
     const int64_t rowb = 4 * (int64_t)k;
     const int64_t per_delta = rowb + 4 + (wcol ? 4 : 0);
     const int64_t per_row = rowb + 4 + (wrow ? 4 : 0) + (mode == 4 ? rowb : 0);  // Y write, marker, weight, own X row
