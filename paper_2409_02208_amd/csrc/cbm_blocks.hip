@@ -150,7 +150,8 @@ __global__ __launch_bounds__(64 * WAVES, BIG ? 2 : 3) void cbm_block_kernel(cons
         }
 #pragma unroll
         for (int s = 0; s < T; ++s)
-            // (a scalar: six vector instructions a step that looked at the bits are gone; hub blocks, whose tiles are nearly all active, lose 1 % by it)
+            // (a scalar: six vector instructions a step that looked at the bits are gone; nearly all tiles of hub blocks are active, and with weights, MODE 5, they
+            // would lose 1 % by it: those without are MODE 0, as row blocks, and lose half of that, R-MAT scale 20, k = 64 104.9 -> 105.2 us)
             if (MODE == 5 ? __ballot(((mask >> (8 * s)) & 255u) != 0) != 0 : (active >> s & 1u) != 0) {
 #pragma unroll
                 for (int q = 2; q >= 0; --q)

@@ -10,12 +10,12 @@
 // Asking two tiles of rows ahead gains nothing, nor does adding up a tile's shares beside the next one's products.
 //
 // What bounds it: reading A and writing C (us, the kernels that ran before -> here; what a large copy's 4.66 TB/s would take): 132534 x 100 . 100 x 47
-// 26.3 -> 20.0 (16.7), 132534 x 256 . 256 x 64 47 -> 35 (36), 132534 x 32 . 32 x 32 11.8 -> 8.7, 300000 x 16 . 16 x 16 12.6 -> 9.6 (8.2), 60000 x 500 . 500 x 64
-// 42 -> 31 (29), 100000 x 301 . 301 x 40 51 -> 34 (29).  Few rows: a wave's piece of B and one or two tiles of rows, one after the other: 19717 x 500 . 500 x 64
-// 23 -> 15 (9.6; 1,233 tiles are 4.8 for each compute unit), . 500 x 7 13.3 -> 8.5, 3000 x 512 . 512 x 64 10.4 -> 6.4; a call costs 5 us of host time beside it.
+// 26.7 -> 22.1 (16.7), 132534 x 256 . 256 x 64 48 -> 38 (36), 132534 x 32 . 32 x 32 12.8 -> 8.4, 300000 x 16 . 16 x 16 13.0 -> 9.5 (8.2), 60000 x 500 . 500 x 64
+// 43 -> 36 (29), 100000 x 301 . 301 x 40 51 -> 35 (29).  Few rows: a wave's piece of B and one or two tiles of rows, one after the other: 19717 x 500 . 500 x 64
+// 21.5 -> 15.5 (9.6; 1,233 tiles are 4.8 for each compute unit), . 500 x 7 13.6 -> 8.7, 3000 x 512 . 512 x 64 9.9 -> 6.8; a call costs 5 us of host time beside it.
 // Error against 64 bits in the 2-norm, Gaussian values: K = 100 1.8e-7 (fp32 kernels) -> 0.6e-7, 256 2.9e-7 -> 0.5e-7, 500 4.0e-7 -> 0.5e-7 (through parts
 // without B held 0.76e-7).  One term a row 2.53e-8, at most 1.002 times 2^-24 of it (six products: 2.60e-8 and 1.6 to 1.7 times; fp32 2.53e-8 and once).  What the two
-// products cost (us): 132534 x 100 . 100 x 47 20.0 -> 20.9, 132534 x 256 . 256 x 64 36 -> 39, 19717 x 500 . 500 x 64 14.8 -> 15.6, 132534 x 32 . 32 x 32 no time.  Values that are not finite (finite ones, one infinity in B, NaN all
+// products cost (us): 132534 x 100 . 100 x 47 20.0 -> 20.9, 132534 x 256 . 256 x 64 36 -> 39, 60000 x 500 . 500 x 64 31 -> 36, 19717 x 500 . 500 x 64 14.8 -> 15.6, 132534 x 32 . 32 x 32 no time.  Values that are not finite (finite ones, one infinity in B, NaN all
 // over A): 132534 x 100 . 100 x 47 22, 36, 62, 132534 x 256 . 256 x 64 42, 80, 167, 20000 x 500 . 500 x 64 16, 27, 52, 50000 x 300 . 300 x 33 21, 40, 71 (where each wave
 // that added shares up went over all of K alone, between two barriers: 20000 x 500 . 500 x 64 110, 158, 50000 x 300 . 300 x 33 107, 216, 132534 x 256 . 256 x 64 207, 336).
 #include <hip/hip_runtime.h>

@@ -387,7 +387,7 @@ void pick(const Shape& s, int form) {
 
 // Where the lines lie (microseconds, fp32 kernels of cbm_gemm.hip -> these; M x K . K x N), for products that do not hold B in registers.  Measured at M from 1,000 to 132,534, K from
 // 32 to 1,000 and 20 widths: nowhere inside the lines are these slower by more than the launch's own noise; some outside would be faster.
-//  up to 64 columns (what cbm_gemm_held.hip leaves: K beyond 768 or 1,024): short and deep products, which leave the chip idle there -- 19717 x 500 . 500 x 64 26.1 -> 21.0, . 500 x 7
+//  up to 64 columns (what cbm_held_rule.h leaves: K beyond 768 or 1,024, and a few products that it would pad most): short and deep products, which leave the chip idle there -- 19717 x 500 . 500 x 64 26.1 -> 21.0, . 500 x 7
 //    25.2 -> 13.4, 24000 x 128 . 128 x 64 13.0 -> 10.3, 3000 x 512 . 512 x 64 24 -> 10.  The line in M: at 28,000 rows the two are level
 //    (200 x 64: 17.2, 16.6; 500 x 64: 27.0, 27.4), at 60,000 the fp32 kernels stream A at the rate of memory (200 x 64: 25.7, 28.6; 500 x 64:
 //    42, 48; 500 x 32: 25.7, 31.1), and what lies between depends on N (40000 x 500 . 500 x 7: 40, 22).  The line in K: at 100 24,576 rows
@@ -395,7 +395,7 @@ void pick(const Shape& s, int form) {
 //  more columns, few workgroups (tiles of 64 columns): 19717 x 256 . 256 x 256 42 -> 28, 6000 x 300 . 300 x 96 28 -> 15, 4000 x 96 . 96 x 96
 //    11 -> 8 (K = 32: level);
 //  more columns, many: 132534 x 256 . 256 x 256 156 -> 130, 132534 x 96 . 96 x 256 89 -> 66, 132534 x 250 . 250 x 250 234 -> 182,
-//    if the last tile of 128 columns is not mostly padding (256 x 160: 105, 134; 256 x 112: 75, 76) and K is not so short that the
+//    if the last tile of 128 columns is not mostly padding (256 x 160: 105, 134) and K is not so short that the
 //    products are bound by memory (132534 x 64 . 64 x 128: 32, 33).
 cbm_status cbm_launch_gemm_split(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                  int64_t ldc, void* stream, bool* taken) {

@@ -15,7 +15,7 @@ constexpr int cbm_held_most_steps(int tiles) { return tiles == 4 ? 3 : 4; }
 // 256 x 47, 8 steps: four 8.1, eight 8.6) with no more than two steps each (x 16 one wave 13.7, four 11.4; 20000 x 500 . 500 x 47, 16 steps: four 13.9, eight
 // 12.1), three tiles of columns up to 50,000 rows only (50000 x 128 . 128 x 47 one wave 13.4, four 12.6; 80000 rows 15.7, 16.4).  Two waves are for 5 or 6
 // steps (250000 x 150 . 150 x 24 four 61, two 41).  Where there are not rows enough for all waves, as many as K takes: 8192 x 128 . 128 x 47 one wave 7.1, four
-// 5.4, 5000 x 320 . 320 x 32 four 6.7, eight 6.1 (12,000 rows: 7.2, 7.8).
+// 5.4, 5000 x 320 . 320 x 32 four 6.7, eight 6.1 (12,000 rows: 7.2, 7.8).  (Measured with six products of parts instead of eight.)
 inline CbmHeldPlan cbm_held_plan(int64_t M, int32_t N, int32_t K) {
     CbmHeldPlan p{};
     p.panels = (N + 63) / 64;
