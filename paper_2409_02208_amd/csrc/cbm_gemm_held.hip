@@ -1,8 +1,9 @@
 // Dense fp32 matmul C = A.B for few columns on the bf16 matrix cores, B held in registers: a panel of up to 64 of them, or up to four such panels side by
 // side (grid dimension y).
 //
-// Operands are split into three bf16 parts as in cbm_gemm_split.hip, which says why that is as good as fp32, and multiplied in eight products instead of six: this
-// kernel takes over from the fp32 ones, where a row of a single term is rounded once, and ml and lm are up to another rounding of a term.  (ll is 2^-34 of it.)
+// Operands are split into three bf16 parts as in cbm_gemm_split.hip, which says why that is as good as fp32, and multiplied in eight products instead of six where this
+// kernel takes over from the fp32 ones: there a row of a single term is rounded once, and ml and lm are up to another rounding of a term.  (ll is 2^-34 of it.)  Where
+// the kernels of six products would run otherwise (cbm_split_form) it makes six: 19717 x 500 . 500 x 64 15.5 -> 14.4, 20000 x 500 . 500 x 112 25 -> 23.
 // Also different is who holds what: B is small, so each wave keeps the parts of its piece of B -- all columns, 32 STEPS of its rows -- in registers, split once,
 // and streams 16 rows of A at a time past them (all columns: of the panel): no LDS, no barrier and no second look at B in the loop.  Where K is deeper than a wave can hold,
 // SLICES waves, a workgroup, share K and add their sums through LDS, one barrier for 16 rows.  Rows of A go straight from memory into operand
@@ -12,10 +13,10 @@
 // What bounds it: reading A and writing C (us, the kernels that ran before -> here; what a large copy's 4.66 TB/s would take): 132534 x 100 . 100 x 47
 // 26.7 -> 22.1 (16.7), 132534 x 256 . 256 x 64 48 -> 38 (36), 132534 x 32 . 32 x 32 12.8 -> 8.4, 300000 x 16 . 16 x 16 13.0 -> 9.5 (8.2), 60000 x 500 . 500 x 64
 // 43 -> 36 (29), 100000 x 301 . 301 x 40 51 -> 35 (29).  Few rows: a wave's piece of B and one or two tiles of rows, one after the other: 19717 x 500 . 500 x 64
-// 21.5 -> 15.5 (9.6; 1,233 tiles are 4.8 for each compute unit), . 500 x 7 13.6 -> 8.7, 3000 x 512 . 512 x 64 9.9 -> 6.8; a call costs 5 us of host time beside it.
+// 21.4 -> 14.4 (9.6; 1,233 tiles are 4.8 for each compute unit), . 500 x 7 13.6 -> 8.6, 3000 x 512 . 512 x 64 9.9 -> 6.5; a call costs 5 us of host time beside it.
 // Error against 64 bits in the 2-norm, Gaussian values: K = 100 1.8e-7 (fp32 kernels) -> 0.6e-7, 256 2.9e-7 -> 0.5e-7, 500 4.0e-7 -> 0.5e-7 (through parts
 // without B held 0.76e-7).  One term a row 2.53e-8, at most 1.002 times 2^-24 of it (six products: 2.60e-8 and 1.6 to 1.7 times; fp32 2.53e-8 and once).  What the two
-// products cost (us): 132534 x 100 . 100 x 47 20.0 -> 20.9, 132534 x 256 . 256 x 64 36 -> 39, 60000 x 500 . 500 x 64 31 -> 36, 19717 x 500 . 500 x 64 14.8 -> 15.6, 132534 x 32 . 32 x 32 no time.  Values that are not finite (finite ones, one infinity in B, NaN all
+// products cost (us): 132534 x 100 . 100 x 47 20.0 -> 20.9, 132534 x 256 . 256 x 64 36 -> 39, 60000 x 500 . 500 x 64 31 -> 36, 132534 x 32 . 32 x 32 no time.  Values that are not finite (finite ones, one infinity in B, NaN all
 // over A): 132534 x 100 . 100 x 47 22, 36, 62, 132534 x 256 . 256 x 64 42, 80, 167, 20000 x 500 . 500 x 64 16, 27, 52, 50000 x 300 . 300 x 33 21, 40, 71 (where each wave
 // that added shares up went over all of K alone, between two barriers: 20000 x 500 . 500 x 64 110, 158, 50000 x 300 . 300 x 33 107, 216, 132534 x 256 . 256 x 64 207, 336).
 #include <hip/hip_runtime.h>
@@ -23,7 +24,7 @@
 #include <algorithm>
 #include <cstdlib>
 
-#include "cbm_held_rule.h"
+#include "cbm_gemm_rules.h"
 #include "cbm_internal.h"
 #include "cbm_split.h"
 
@@ -31,7 +32,7 @@ namespace {
 
 // Operands are split at 2^24 times their size and sums come back by 2^-48: nothing small is lost (cbm_gemm_split.hip).
 constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;
-constexpr int PRODUCTS = 8, PA[PRODUCTS] = {2, 1, 2, 0, 1, 1, 0, 0}, PB[PRODUCTS] = {1, 2, 0, 2, 1, 0, 1, 0};  // small ones first, that of the large parts last
+constexpr int PA[8] = {2, 1, 2, 0, 1, 1, 0, 0}, PB[8] = {1, 2, 0, 2, 1, 0, 1, 0};  // small ones first, that of the large parts last
 
 struct Parts {
     bf16x8 p[3];  // h, m, l
@@ -61,11 +62,12 @@ struct Shape {
     int64_t ldb;
     float* C;
     int64_t ldc;
+    bool six;  // products of parts instead of eight: where the kernels of cbm_gemm_split.hip would run otherwise (two tiles of columns: from 128 k on)
 };
 
 constexpr int held_waves(int slices) { return slices == 1 ? 4 : slices; }
-// VEC: K is a multiple of 4 and rows of A start on 16-byte boundaries.
-template <int NT, int STEPS, int SLICES, bool VEC>
+// VEC: K is a multiple of 4 and rows of A start on 16-byte boundaries.  PRODUCTS of parts: eight, or without ml and lm six.
+template <int NT, int STEPS, int SLICES, bool VEC, int PRODUCTS>
 __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kernel(const Shape all) {
     Shape s = all;  // this panel's
     s.B += blockIdx.y * (16 * NT);
@@ -233,10 +235,10 @@ __global__ __launch_bounds__(64 * held_waves(SLICES), 2) void cbm_gemm_held_kern
             const Parts a = split8(x[i], minus_low);
             load_a(x[i], next, i, whole_steps);
 #pragma unroll
-            for (int q = 0; q < PRODUCTS; ++q)
+            for (int q = 8 - PRODUCTS; q < 8; ++q)
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
-                    floatx4& sum = q < PRODUCTS - 1 ? small[t] : acc[t];
+                    floatx4& sum = q < 7 ? small[t] : acc[t];
                     sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[PA[q]], b[i][t].p[PB[q]], sum, 0, 0, 0);
                 }
             __builtin_amdgcn_sched_barrier(0);
@@ -294,8 +296,14 @@ void launch(const Shape& s, hipStream_t stream) {
     const int panels = (s.N + 16 * NT - 1) / (16 * NT);
     const dim3 grid((unsigned)cbm_panel_blocks(wanted, panels, held_grid(NT, STEPS, SLICES)), (unsigned)panels);
     const bool vec = s.K % 4 == 0 && s.lda % 4 == 0 && ((uintptr_t)s.A & 15) == 0;
-    if (vec) hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, true>), grid, dim3(64 * WAVES), 0, stream, s);
-    else hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, false>), grid, dim3(64 * WAVES), 0, stream, s);
+    if constexpr (NT > 2 || STEPS * SLICES >= 4)
+        if (s.six) {
+            if (vec) hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, true, 6>), grid, dim3(64 * WAVES), 0, stream, s);
+            else hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, false, 6>), grid, dim3(64 * WAVES), 0, stream, s);
+            return;
+        }
+    if (vec) hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, true, 8>), grid, dim3(64 * WAVES), 0, stream, s);
+    else hipLaunchKernelGGL((cbm_gemm_held_kernel<NT, STEPS, SLICES, false, 8>), grid, dim3(64 * WAVES), 0, stream, s);
 }
 
 template <int NT, int SLICES>
@@ -329,11 +337,11 @@ bool launch_nt(const Shape& s, const CbmHeldPlan& p, hipStream_t stream) {
 cbm_status cbm_launch_gemm_held(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                 int64_t ldc, void* stream, bool* taken) {
     *taken = false;
-    // (for tests, which run several in one process: 5 = whatever K, 0 to 4 = never, as another kernel is asked for)
+    // (for tests, which run several in one process: 5 = whatever K, with eight products, 0 to 4 = never, as another kernel is asked for)
     const char* e = std::getenv("CBM_GEMM_SPLIT");
     const bool asked = e && e[0] >= '0' && e[0] <= '5' && !e[1];
     if (asked ? e[0] != '5' || N > 256 : !cbm_held_takes(M, N, K, K % 4 == 0 && lda % 4 == 0 && ((uintptr_t)A & 15) == 0)) return CBM_OK;
-    const Shape s{M, N, K, A, lda, B, ldb, C, ldc};
+    const Shape s{M, N, K, A, lda, B, ldb, C, ldc, !asked && cbm_split_form(M, N, K) != 0};
     const CbmHeldPlan p = cbm_held_plan(M, N, K);
     switch (p.tiles) {
         case 1: *taken = launch_nt<1>(s, p, (hipStream_t)stream); break;

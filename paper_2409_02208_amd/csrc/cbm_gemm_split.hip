@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "cbm_gemm_rules.h"
 #include "cbm_internal.h"
 #include "cbm_split.h"
 
@@ -385,27 +386,9 @@ void pick(const Shape& s, int form) {
 
 }  // namespace
 
-// Where the lines lie (microseconds, fp32 kernels of cbm_gemm.hip -> these; M x K . K x N), for products that do not hold B in registers.  Measured at M from 1,000 to 132,534, K from
-// 32 to 1,000 and 20 widths: nowhere inside the lines are these slower by more than the launch's own noise; some outside would be faster.
-//  up to 64 columns (what cbm_held_rule.h leaves: K beyond 768 or 1,024, and a few products that it would pad most): short and deep products, which leave the chip idle there -- 19717 x 500 . 500 x 64 26.1 -> 21.0, . 500 x 7
-//    25.2 -> 13.4, 24000 x 128 . 128 x 64 13.0 -> 10.3, 3000 x 512 . 512 x 64 24 -> 10.  The line in M: at 28,000 rows the two are level
-//    (200 x 64: 17.2, 16.6; 500 x 64: 27.0, 27.4), at 60,000 the fp32 kernels stream A at the rate of memory (200 x 64: 25.7, 28.6; 500 x 64:
-//    42, 48; 500 x 32: 25.7, 31.1), and what lies between depends on N (40000 x 500 . 500 x 7: 40, 22).  The line in K: at 100 24,576 rows
-//    gain (12.2, 10.4), at 64 they lose (9.0, 9.9);
-//  more columns, few workgroups (tiles of 64 columns): 19717 x 256 . 256 x 256 42 -> 28, 6000 x 300 . 300 x 96 28 -> 15, 4000 x 96 . 96 x 96
-//    11 -> 8 (K = 32: level);
-//  more columns, many: 132534 x 256 . 256 x 256 156 -> 130, 132534 x 96 . 96 x 256 89 -> 66, 132534 x 250 . 250 x 250 234 -> 182,
-//    if the last tile of 128 columns is not mostly padding (256 x 160: 105, 134) and K is not so short that the
-//    products are bound by memory (132534 x 64 . 64 x 128: 32, 33).
 cbm_status cbm_launch_gemm_split(int64_t M, int32_t N, int32_t K, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                  int64_t ldc, void* stream, bool* taken) {
-    int form = 0;
-    if (N <= 64)
-        form = M <= 24576 && K >= 128 ? (N <= 32 ? 1 : 2) : 0;
-    else if ((M + 127) / 128 * ((N + 63) / 64) <= 1024)
-        form = K >= 32 ? 3 : 0;
-    else if (K >= 96 && (N + 127) / 128 * 128 * 10 <= (int64_t)N * 11)
-        form = 4;
+    int form = cbm_split_form(M, N, K);
     // (for tests, which run several in one process: 0 = never, 1 to 4 = that kernel; anything else is not listened to)
     if (const char* e = std::getenv("CBM_GEMM_SPLIT"); e && e[0] >= '0' && e[0] <= '4' && !e[1]) form = e[0] - '0';
     if (form == 1 && N > 32) form = 2;

@@ -264,7 +264,7 @@ inline int64_t cbm_panel_blocks(int64_t wanted, int panels, int64_t resident) {
     return rounded < each ? rounded : each;
 }
 // Whether the panel-resident fp32 kernel also takes a B that 128-bit loads cannot read (odd width or alignment): filling the panel
-// element by element has to be earned by depth and by rows.  (Up to 64 columns K from 8 to 768 or more holds B in registers instead, cbm_held_rule.h: the lines
+// element by element has to be earned by depth and by rows.  (Up to 64 columns K from 8 to 768 or more holds B in registers instead, cbm_gemm_rules.h: the lines
 // there decide for K beyond 1,024, and where an environment variable asks for these kernels.)  The staged kernel has blocks of 128 rows, so it loses where M / 128 just
 // exceeds the 256 compute units, and tiles of 48 columns, which suit N from 33 to 48 (microseconds, or its share of the staged kernel's time):
 //  N > 64: 132534 x 64 . 64 x 130 0.61, 132534 x 32 . 32 x 65 17.8 -> 24.2, 40000 x 32 . 32 x 250 21.5 -> 25.7;

@@ -154,6 +154,29 @@ def test_sums_that_are_not_finite_among_others(env, monkeypatch, k, n):  # noqa:
         assert np.all(np.abs(got - ref)[large] <= 2.0 ** -23 * np.abs(ref[large]))
 
 
+# products of the fp32 kernels, and of the kernels of parts in each of their forms: there without the products ml and lm, as they do it
+@pytest.mark.parametrize("m,k,n,otherwise", [(24577, 128, 16, "0"), (24576, 128, 16, "1"), (8193, 300, 7, "1"), (20000, 500, 64, "2"), (24576, 700, 33, "2"), (24577, 500, 64, "0"),
+                                             (4000, 32, 65, "3"), (4000, 31, 65, "0"), (36000, 192, 112, "3"), (2000, 500, 200, "3"), (66000, 256, 128, "4"), (66000, 95, 128, "0")])
+def test_as_near_to_64_bits_as_what_would_run_otherwise(env, monkeypatch, m, k, n, otherwise):  # noqa: F811
+    rng = np.random.default_rng(k + n)
+    B = rng.standard_normal((k, n), dtype=np.float32)
+    one = np.zeros((m, k), np.float32)
+    one[np.arange(m), rng.integers(0, k, m)] = rng.standard_normal(m, dtype=np.float32)
+    for A in (rng.standard_normal((m, k), dtype=np.float32), one):
+        ref, err = A.astype(np.float64) @ B.astype(np.float64), {}
+        for which in (None, otherwise):
+            monkeypatch.delenv("CBM_GEMM_SPLIT", raising=False) if which is None else monkeypatch.setenv("CBM_GEMM_SPLIT", which)
+            err[which] = np.linalg.norm(_product(env, A, B) - ref)
+        assert err[None] <= 1.03 * err[otherwise], err  # (3 %: as many roundings in each as above)
+    monkeypatch.delenv("CBM_GEMM_SPLIT", raising=False)
+    A = rng.integers(-9, 10, (m, k)).astype(np.float32)
+    B = rng.integers(-9, 10, (k, n)).astype(np.float32)
+    A[m - 3, k - 1], A[16, 0], B[1, n - 1] = np.inf, np.nan, -np.inf
+    with np.errstate(invalid="ignore"):
+        ref = A.astype(np.float64) @ B.astype(np.float64)
+    assert np.array_equal(_product(env, A, B), ref, equal_nan=True)
+
+
 @pytest.mark.parametrize("m,k,n", [(132534, 100, 47), (132534, 256, 64), (20000, 500, 64), (50000, 300, 33)])
 def test_values_that_are_not_finite_cost_little(env, m, k, n):  # noqa: F811
     """An infinity in B, which reaches one tile of columns in every row: 1.6 to 1.9 times the product's time (measured), the line is at 3.  NaN everywhere: 2.8 to 4.0
